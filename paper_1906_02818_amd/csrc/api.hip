@@ -545,7 +545,7 @@ mc_status gbm_run(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64
                   double* kernel_ms) {
   const bool fp64 = o.prec == MC_FP64;
   const bool logs = m->scheme == MC_LOG_EULER;
-  const uint32_t mask = gbm_pick_mask(want, fp64, logs, ctx->coarsen);
+  const uint32_t mask = gbm_pick_mask(want, fp64, logs, ctx->coarsen, path_values != nullptr);
   if (!mask) return fail(ctx, MC_ERR_UNSUPPORTED, "payoff not available for this scheme/precision");
   *mask_used = mask;
   GbmParams p = gbm_params(m, f, n_paths, n_steps, seed, o, fp64, tag);
@@ -1230,7 +1230,7 @@ mc_status payoff_channel(mc_context* ctx, const mc_model* m, const mc_payoff* f,
     const uint32_t want = gbm_want_mask(f, o, &st);
     if (st != MC_OK) return fail(ctx, st, "payoff not offered for GBM");
     const uint32_t mask =
-        gbm_pick_mask(want, o.prec == MC_FP64, m->scheme == MC_LOG_EULER, coarsen);
+        gbm_pick_mask(want, o.prec == MC_FP64, m->scheme == MC_LOG_EULER, coarsen, false);
     if (!mask) return fail(ctx, MC_ERR_UNSUPPORTED, "payoff not available for this coupling");
     uint32_t bit = 0;
     switch (f->kind) {
@@ -1500,7 +1500,7 @@ uint32_t mc_path_channels(const mc_model* m, const mc_payoff* f, const mc_option
     mc_status st;
     const uint32_t want = gbm_want_mask(f, o, &st);
     if (st != MC_OK) return 0;
-    const uint32_t mask = gbm_pick_mask(want, o.prec == MC_FP64, m->scheme == MC_LOG_EULER);
+    const uint32_t mask = gbm_pick_mask(want, o.prec == MC_FP64, m->scheme == MC_LOG_EULER, 1, true);
     return mask ? (uint32_t)gbm_channels(mask) : 0;
   }
   if (m->kind == MC_HESTON) return (o.greeks || f->cv == MC_CV_LEARNED) ? 3u : 2u;
@@ -1516,7 +1516,7 @@ const char* mc_path_channel_name(const mc_model* m, const mc_payoff* f, const mc
     mc_status st;
     const uint32_t want = gbm_want_mask(f, o, &st);
     if (st != MC_OK) return nullptr;
-    const uint32_t mask = gbm_pick_mask(want, o.prec == MC_FP64, m->scheme == MC_LOG_EULER);
+    const uint32_t mask = gbm_pick_mask(want, o.prec == MC_FP64, m->scheme == MC_LOG_EULER, 1, true);
     return mask ? gbm_channel_name(mask, i) : nullptr;
   }
   if (m->kind == MC_HESTON) {

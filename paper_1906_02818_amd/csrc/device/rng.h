@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fp64.h"
+
 namespace mcp {
 
 constexpr uint32_t kPhiloxM0 = 0xD2511F53u;
@@ -92,37 +94,47 @@ __device__ __forceinline__ void box_muller_f32(uint32_t w_rad, uint32_t w_ang, f
   z1 = rad * __builtin_amdgcn_sinf(ua);
 }
 
-__device__ __forceinline__ void box_muller_f64(uint32_t w_rad, uint32_t w_ang, double& z0,
-                                               double& z1) {
-  const double ur = uniform_f64(w_rad);
-  const double ua = uniform_f64(w_ang);
-  const double rad = sqrt(-2.0 * log(ur));
-  const double ang = 6.283185307179586476925286766559 * ua;
-  z0 = rad * cos(ang);
-  z1 = rad * sin(ang);
-}
-
 template <typename R>
 struct Normals4 {
   R z[4];
 };
 
+// What a path's arithmetic in R needs beside its state: nothing in FP32 (the
+// hardware's transcendental unit), the workgroup's tables in FP64.
 template <typename R>
-__device__ __forceinline__ Normals4<R> normals4(const Words4& w);
-
+struct PathMath;
 template <>
-__device__ __forceinline__ Normals4<float> normals4<float>(const Words4& w) {
+struct PathMath<float> {
+  struct Shared {};
+  __device__ __forceinline__ explicit PathMath(Shared&) {}
+};
+template <>
+struct PathMath<double> {
+  typedef F64Tables Shared;
+  const F64Tables& t;
+  // Fills the tables (every thread of the workgroup calls it).
+  __device__ __forceinline__ explicit PathMath(Shared& s) : t(s) {
+    f64_tables_fill(s);
+    __syncthreads();
+  }
+};
+
+__device__ __forceinline__ Normals4<float> normals4(const Words4& w) {
   Normals4<float> n;
   box_muller_f32(w.w0, w.w1, n.z[0], n.z[1]);
   box_muller_f32(w.w2, w.w3, n.z[2], n.z[3]);
   return n;
 }
-
-template <>
-__device__ __forceinline__ Normals4<double> normals4<double>(const Words4& w) {
+template <bool ROUND_ANGLE = false>
+__device__ __forceinline__ Normals4<float> normals4(const Words4& w, const PathMath<float>&) {
+  return normals4(w);
+}
+template <bool ROUND_ANGLE = false>
+__device__ __forceinline__ Normals4<double> normals4(const Words4& w,
+                                                     const PathMath<double>& pm) {
   Normals4<double> n;
-  box_muller_f64(w.w0, w.w1, n.z[0], n.z[1]);
-  box_muller_f64(w.w2, w.w3, n.z[2], n.z[3]);
+  box_muller_f64<ROUND_ANGLE>(w.w0, w.w1, pm.t, n.z[0], n.z[1]);
+  box_muller_f64<ROUND_ANGLE>(w.w2, w.w3, pm.t, n.z[2], n.z[3]);
   return n;
 }
 

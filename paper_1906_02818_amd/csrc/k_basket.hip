@@ -133,8 +133,8 @@ __global__ __launch_bounds__(kThreads) void basket_kernel(const BasketParams P) 
           wa = philox(j0, pc);
           wb = philox(j0 + 1, pc);
         }
-        const Normals4<float> za = normals4<float>(wa);
-        const Normals4<float> zb = normals4<float>(wb);
+        const Normals4<float> za = normals4(wa);
+        const Normals4<float> zb = normals4(wb);
         const float z[8] = {za.z[0], za.z[1], za.z[2], za.z[3],
                             zb.z[0], zb.z[1], zb.z[2], zb.z[3]};
 #pragma unroll

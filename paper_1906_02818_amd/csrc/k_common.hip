@@ -92,11 +92,13 @@ __global__ void philox_words_kernel(uint32_t k0, uint32_t k1, uint32_t tag, uint
 template <typename R>
 __global__ void normals_kernel(uint32_t k0, uint32_t k1, uint32_t tag, uint64_t path,
                                uint64_t k_first, uint64_t count, double* __restrict__ out) {
+  __shared__ typename PathMath<R>::Shared shared;
+  const PathMath<R> pm(shared);
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   const uint64_t k = k_first + i;
   const PathCounter pc = make_counter(path, tag, k0, k1);
-  const Normals4<R> nz = normals4<R>(philox((uint32_t)(k >> 2), pc));
+  const Normals4<R> nz = normals4(philox((uint32_t)(k >> 2), pc), pm);
   out[i] = (double)nz.z[k & 3];
 }
 

@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kCvThreads) void cv_cache_kernel(const CvParams P) 
       for (int q = 0; q < 4; ++q) P.c_phi[((size_t)k * 4 + q) * S + pid] = f[q];
       st_open = Et;
     }
-    if ((i & 1) == 0) nz = normals4<float>(philox(i >> 1, pc));
+    if ((i & 1) == 0) nz = normals4(philox(i >> 1, pc));
     const float Z1 = (i & 1) ? nz.z[2] : nz.z[0];
     const float Z2 = (i & 1) ? nz.z[3] : nz.z[1];
     c.step(z, v, Z1, Z2);
@@ -854,7 +854,7 @@ __global__ __launch_bounds__(kCvThreads) void cv_eval_kernel(const CvParams P) {
       }
       st_open = Et;
     }
-    if ((i & 1) == 0) nz = normals4<float>(philox(i >> 1, pc));
+    if ((i & 1) == 0) nz = normals4(philox(i >> 1, pc));
     const float Z1 = (i & 1) ? nz.z[2] : nz.z[0];
     const float Z2 = (i & 1) ? nz.z[3] : nz.z[1];
     c.step(z, v, Z1, Z2);

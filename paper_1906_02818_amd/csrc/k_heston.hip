@@ -29,14 +29,18 @@ struct HDom;
 template <>
 struct HDom<float> {
   static constexpr double kLogScale = 1.4426950408889634;  // ln S -> log2 S
-  static __device__ __forceinline__ float exp_(float z) { return __builtin_amdgcn_exp2f(z); }
+  static __device__ __forceinline__ float exp_(float z, const PathMath<float>&) {
+    return __builtin_amdgcn_exp2f(z);
+  }
   static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
   static __device__ __forceinline__ float rsqrt_(float x) { return __builtin_amdgcn_rsqf(x); }
 };
 template <>
 struct HDom<double> {
   static constexpr double kLogScale = 1.0;
-  static __device__ __forceinline__ double exp_(double z) { return exp(z); }
+  static __device__ __forceinline__ double exp_(double z, const PathMath<double>& pm) {
+    return exp_f64(z, pm.t);
+  }
   static __device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
   static __device__ __forceinline__ double rsqrt_(double x) { return 1.0 / sqrt(x); }
 };
@@ -78,6 +82,8 @@ __device__ __forceinline__ R posv(R x) {
 template <typename R, uint32_t MASK>
 __global__ __launch_bounds__(kBlock) void heston_price_kernel(const HestonParams P) {
   constexpr int C = popcount_c(MASK);
+  __shared__ typename PathMath<R>::Shared shared;
+  const PathMath<R> pm(shared);
   ThreadSums<C> acc;
   acc.zero();
   HestonStep<R> hs;
@@ -90,17 +96,17 @@ __global__ __launch_bounds__(kBlock) void heston_price_kernel(const HestonParams
     R z = R(0), v = (R)P.v0, sumE = R(0), Zs;
     const uint32_t n = P.n_steps;
     for (uint32_t j = 0; 2 * j < n; ++j) {
-      const Normals4<R> nz = normals4<R>(philox(j, pc));
+      const Normals4<R> nz = normals4<true>(philox(j, pc), pm);
       hs.step(z, v, nz.z[0], nz.z[1], Zs);
-      if constexpr ((MASK & H_ASIAN) != 0) sumE += HDom<R>::exp_(z);
+      if constexpr ((MASK & H_ASIAN) != 0) sumE += HDom<R>::exp_(z, pm);
       if (2 * j + 1 < n) {
         hs.step(z, v, nz.z[2], nz.z[3], Zs);
-        if constexpr ((MASK & H_ASIAN) != 0) sumE += HDom<R>::exp_(z);
+        if constexpr ((MASK & H_ASIAN) != 0) sumE += HDom<R>::exp_(z, pm);
       }
     }
     const R S0 = (R)P.S0, K = (R)P.K, disc = (R)P.disc;
     int c = 0;
-    if constexpr ((MASK & H_EURO) != 0) y[c++] = (double)(disc * posv(S0 * HDom<R>::exp_(z) - K));
+    if constexpr ((MASK & H_EURO) != 0) y[c++] = (double)(disc * posv(S0 * HDom<R>::exp_(z, pm) - K));
     if constexpr ((MASK & H_ASIAN) != 0) y[c++] = (double)(disc * posv(S0 * sumE / (R)n - K));
     bool finite = true;
 #pragma unroll
@@ -123,6 +129,8 @@ __global__ __launch_bounds__(kBlock) void heston_price_kernel(const HestonParams
 // European (ASIAN = false) or arithmetic-Asian call.
 template <typename R, bool ASIAN>
 __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonParams P) {
+  __shared__ typename PathMath<R>::Shared shared;
+  const PathMath<R> pm(shared);
   ThreadSums<3> acc;
   acc.zero();
   HestonStep<R> hs;
@@ -148,13 +156,13 @@ __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonPara
       dz = dz_new;
       dv = dv_new;
       if constexpr (ASIAN) {
-        const R E = HDom<R>::exp_(z);
+        const R E = HDom<R>::exp_(z, pm);
         sumE += E;
         sumEd += E * dz;
       }
     };
     for (uint32_t j = 0; 2 * j < n; ++j) {
-      const Normals4<R> nz = normals4<R>(philox(j, pc));
+      const Normals4<R> nz = normals4<true>(philox(j, pc), pm);
       step(nz.z[0], nz.z[1]);
       if (2 * j + 1 < n) step(nz.z[2], nz.z[3]);
     }
@@ -167,7 +175,7 @@ __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonPara
       y[1] = A > K ? disc * A / S0 : 0.0;
       y[2] = A > K ? disc * S0 * inv_sc * (double)sumEd / (double)n : 0.0;
     } else {
-      const double ST = S0 * (double)HDom<R>::exp_(z);
+      const double ST = S0 * (double)HDom<R>::exp_(z, pm);
       y[0] = disc * (ST > K ? ST - K : 0.0);
       y[1] = ST > K ? disc * ST / S0 : 0.0;
       y[2] = ST > K ? disc * ST * inv_sc * (double)dz : 0.0;
@@ -203,6 +211,8 @@ struct AdjC<2> { static constexpr int C = 2; };   // delta, d/dv0
 template <typename R, int PHASE, bool ASIAN, bool LDS>
 __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointParams A) {
   constexpr int C = AdjC<PHASE>::C;
+  __shared__ typename PathMath<R>::Shared shared;
+  const PathMath<R> pm(shared);
   extern __shared__ float s_ck[];
   const HestonParams& P = A.h;
   const uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -238,16 +248,16 @@ __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointPar
         ck_store(2 * seg + 1, v);
         const uint32_t len = min(every, n - i0);
         for (uint32_t q = 0; q < len; q += 2) {
-          const Normals4<R> nz = normals4<R>(philox((i0 + q) >> 1, pc));
+          const Normals4<R> nz = normals4<true>(philox((i0 + q) >> 1, pc), pm);
           hs.step(z, v, nz.z[0], nz.z[1], Zs);
-          if (ASIAN) sumE += HDom<R>::exp_(z);
+          if (ASIAN) sumE += HDom<R>::exp_(z, pm);
           if (q + 1 < len) {
             hs.step(z, v, nz.z[2], nz.z[3], Zs);
-            if (ASIAN) sumE += HDom<R>::exp_(z);
+            if (ASIAN) sumE += HDom<R>::exp_(z, pm);
           }
         }
       }
-      term = ASIAN ? sumE * inv_n : HDom<R>::exp_(z);
+      term = ASIAN ? sumE * inv_n : HDom<R>::exp_(z, pm);
       if (PHASE == 1) A.ckpt[(size_t)(2 * A.n_ckpt) * np + pid] = (float)term;
       const R pay = disc * posv(S0 * term - K);
       if (PHASE == 0) y[0] = (double)pay;
@@ -278,16 +288,16 @@ __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointPar
 #pragma unroll
         for (int q = 0; q < kCkptMax; q += 2) {
           if ((uint32_t)q < len) {
-            const Normals4<R> nz = normals4<R>(philox((i0 + (uint32_t)q) >> 1, pc));
+            const Normals4<R> nz = normals4<true>(philox((i0 + (uint32_t)q) >> 1, pc), pm);
             vs[q] = v;
             z1s[q] = nz.z[0];
             hs.step(z, v, nz.z[0], nz.z[1], zss[q]);
-            Es[q] = HDom<R>::exp_(z);
+            Es[q] = HDom<R>::exp_(z, pm);
             if ((uint32_t)q + 1 < len) {
               vs[q + 1] = v;
               z1s[q + 1] = nz.z[2];
               hs.step(z, v, nz.z[2], nz.z[3], zss[q + 1]);
-              Es[q + 1] = HDom<R>::exp_(z);
+              Es[q + 1] = HDom<R>::exp_(z, pm);
             }
           }
         }

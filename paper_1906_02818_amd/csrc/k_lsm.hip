@@ -104,7 +104,7 @@ struct NormalCursor {
   uint32_t k = 0;
   __device__ __forceinline__ float next(const PathCounter& pc) {
     const uint32_t s = k & 3u;
-    if (s == 0u) z = normals4<float>(philox(k >> 2, pc));
+    if (s == 0u) z = normals4(philox(k >> 2, pc));
     ++k;
     return s == 0u ? z.z[0] : s == 1u ? z.z[1] : s == 2u ? z.z[2] : z.z[3];
   }
@@ -156,7 +156,7 @@ __device__ __forceinline__ void walk_dates(const LsmParams& p, const PathCounter
       float zz[4 * NB];
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const Normals4<float> q = normals4<float>(philox(blk0 + b, pc));
+        const Normals4<float> q = normals4(philox(blk0 + b, pc));
 #pragma unroll
         for (int t = 0; t < 4; ++t) zz[4 * b + t] = q.z[t];
       }

@@ -60,8 +60,9 @@ struct GbmParams {
 hipError_t launch_gbm(const GbmParams& p, uint32_t mask, bool fp64, hipStream_t s,
                       uint32_t* n_blocks);
 // Smallest instantiated mask containing `want` for this precision/scheme
-// and coupling factor, or 0 when none does.
-uint32_t gbm_pick_mask(uint32_t want, bool fp64, bool log_scheme, uint32_t coarsen = 1);
+// and coupling factor, or 0 when none does. rows: the set whose channels a
+// row of per-path values has (mc_path_channels).
+uint32_t gbm_pick_mask(uint32_t want, bool fp64, bool log_scheme, uint32_t coarsen, bool rows);
 
 // Moments of [a[ca] - b[cb], a[ca], b[cb]] over n paths of two per-path
 // tables with Ca and Cb channels (multilevel correction); returns the block
