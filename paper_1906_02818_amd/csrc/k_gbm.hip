@@ -9,6 +9,11 @@
 // on S (first-order weak error, Sec. V-B). In FP32 the log state is kept in
 // base 2, z = log2(S/S0), so that S_i/S0 = exp2(z) is one v_exp_f32; in FP64
 // it is the natural log.
+//
+// Bound: VALU issue. At 2^24 x 252 (Asian, geometric, barrier) a Philox block
+// and its four steps are 117 cycles of Philox, 100 of Box-Muller and 81 of
+// steps per wave (issue costs: device/rng.h; a transcendental 8.3, v_max3 and
+// v_alignbit 4.2), 298 in all, and the kernel runs at 299.
 #include <initializer_list>
 
 #include "device/reduce.h"
@@ -56,12 +61,22 @@ struct GbmState {
   R sumZ;    // sum of the normals       (vega)
   R dsig;    // Euler-S: d(S_i/S0)/dsigma
   R accV;    // sum of d(S_i/S0)/dsigma  (Asian vega)
+  R top;     // FP32 log scheme: running maximum of z (discrete barrier)
   bool alive, alive_bb;
 };
 
 template <typename R, uint32_t MASK, bool LOGS>
 struct GbmStepper {
-  R dz, vz, zB, cbb, sdt, sig, dt, rdt, vsdt, Brel;
+  // FP32 log paths whose functionals need no normal of their own take the
+  // step's increment straight from Box-Muller (kInc; the European payoff
+  // keeps the normals, so that its price is bit for bit the same with and
+  // without greeks), and watch the barrier through the running maximum (two
+  // dates per v_max3_f32, where a compare and a mask update per date took
+  // twice as long).
+  static constexpr bool kF32 = sizeof(R) == 4;
+  static constexpr bool kInc = kF32 && LOGS && (MASK & ~(G_ASIAN | G_GEO | G_UO)) == 0;
+  static constexpr bool kTop = kF32 && LOGS;
+  R dz, vz, zB, cbb, sdt, sig, dt, rdt, vsdt, Brel, m2;
   const PathMath<R>& pm;
 
   __device__ __forceinline__ GbmStepper(const GbmParams& P, const PathMath<R>& math) : pm(math) {
@@ -75,21 +90,48 @@ struct GbmStepper {
     rdt = (R)P.r_dt;
     vsdt = (R)P.vol_sdt;
     Brel = (R)P.barrier_rel;
+    m2 = (R)(-1.38629436111989061883 * P.vol_dom * P.vol_dom);
   }
 
-  // Step i -> i+1 with normal Z (and the bridge's uniform of word W when
-  // monitored).
+  __device__ __forceinline__ bool alive(const GbmState<R>& s) const {
+    if constexpr (kTop) return s.top < zB;
+    return s.alive;
+  }
+
+  // The four values that a Philox block gives step(): normals, or log
+  // increments.
+  __device__ __forceinline__ Normals4<R> draw(const Words4& w) const {
+    if constexpr (kInc) {
+      Normals4<R> n;
+      box_muller_inc_f32(w.w0, w.w1, m2, dz, n.z[0], n.z[1]);
+      box_muller_inc_f32(w.w2, w.w3, m2, dz, n.z[2], n.z[3]);
+      return n;
+    } else {
+      return normals4(w, pm);
+    }
+  }
+
+  // Step i -> i+1 with normal Z, or with the log increment in its place
+  // (kInc), and the bridge's uniform of word W when monitored.
   __device__ __forceinline__ void step(GbmState<R>& s, R Z, uint32_t i, uint32_t W) const {
     if constexpr (LOGS) {
       const R zp = s.z;
-      s.z = s.z + dz + vz * Z;
+      if constexpr (kInc)
+        s.z = s.z + Z;
+      else
+        s.z = s.z + dz + vz * Z;
       R E = R(0);
       if constexpr ((MASK & (G_ASIAN | G_ASIAN_G)) != 0) {
         E = Dom<R>::exp_(s.z, pm);
         s.sumE += E;
       }
       if constexpr ((MASK & G_GEO) != 0) s.sumz += s.z;
-      if constexpr ((MASK & G_UO) != 0) s.alive = s.alive && (s.z < zB);
+      if constexpr ((MASK & G_UO) != 0) {
+        if constexpr (kTop)
+          s.top = __builtin_fmaxf(s.top, s.z);
+        else
+          s.alive = s.alive && (s.z < zB);
+      }
       if constexpr ((MASK & (G_EURO_G | G_ASIAN_G)) != 0) s.sumZ += Z;
       if constexpr ((MASK & G_ASIAN_G) != 0)
         s.accV += E * (sdt * s.sumZ - sig * (dt * (R)(i + 1)));
@@ -113,26 +155,29 @@ struct GbmStepper {
 
 template <typename R, uint32_t MASK, bool LOGS, uint32_t CO>
 __device__ __forceinline__ void simulate(const GbmParams& P,
-                                         const GbmStepper<R, MASK, LOGS>& st, uint64_t path,
+                                         const GbmStepper<R, MASK, LOGS>& st,
+                                         const PhiloxKeys& keys, uint32_t lo, uint32_t hi,
                                          double (&y)[gbm_channels(MASK)]) {
   const PathMath<R>& pm = st.pm;
   GbmState<R> s;
   s.z = LOGS ? R(0) : R(1);
   s.sumE = s.sumz = s.sumZ = s.dsig = s.accV = R(0);
+  s.top = -R(__builtin_inff());
   s.alive = s.alive_bb = true;
-  const PathCounter pc = make_counter(path, P.tag, P.k0, P.k1);
-  const PathCounter pcb = make_counter(path, P.tag + 5u, P.k0, P.k1);
+  const PathRng pc = make_rng(lo, hi, P.tag, keys);
+  const PathRng pcb = make_rng(lo, hi, P.tag + 5u, keys);
   const uint32_t n = P.n_steps;
   if constexpr (CO > 1) {
     // Coupled coarse path: step i takes normals CO i .. CO i + CO - 1 of the
     // fine path, summed and scaled by 1/sqrt(CO) (same Brownian increment
     // over the coarse step). CO divides the 4 normals of a Philox block.
     static_assert(CO == 2 || CO == 4, "coupling factor");
+    static_assert(!GbmStepper<R, MASK, LOGS>::kInc, "coupled paths sum normals");
     const R rsc = CO == 2 ? R(0.70710678118654752440) : R(0.5);
     constexpr uint32_t SPB = 4 / CO;              // coarse steps per block
     const uint32_t nb = n / SPB;
     for (uint32_t j = 0; j < nb; ++j) {
-      const Normals4<R> nz = normals4(philox(j, pc), pm);
+      const Normals4<R> nz = normals4(philox(j, pc, keys), pm);
 #pragma unroll
       for (uint32_t q = 0; q < SPB; ++q) {
         R Z = nz.z[q * CO];
@@ -142,15 +187,15 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
       }
     }
     if (n % SPB) {                                 // CO = 2, odd n: one step left
-      const Normals4<R> nz = normals4(philox(nb, pc), pm);
+      const Normals4<R> nz = normals4(philox(nb, pc, keys), pm);
       st.step(s, (nz.z[0] + nz.z[1]) * rsc, n - 1, 0u);
     }
   }
   const uint32_t n_full = CO > 1 ? 0u : n >> 2;
   for (uint32_t j = 0; j < n_full; ++j) {
-    const Normals4<R> nz = normals4(philox(j, pc), pm);
+    const Normals4<R> nz = st.draw(philox(j, pc, keys));
     Words4 wb{0, 0, 0, 0};
-    if constexpr ((MASK & G_UOBB) != 0) wb = philox(j, pcb);
+    if constexpr ((MASK & G_UOBB) != 0) wb = philox(j, pcb, keys);
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q) {
       st.step(s, nz.z[q], 4 * j + q, word_at(wb, q));
@@ -158,9 +203,9 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
   }
   const uint32_t rem = CO > 1 ? 0u : n & 3u;
   if (rem) {
-    const Normals4<R> nz = normals4(philox(n_full, pc), pm);
+    const Normals4<R> nz = st.draw(philox(n_full, pc, keys));
     Words4 wb{0, 0, 0, 0};
-    if constexpr ((MASK & G_UOBB) != 0) wb = philox(n_full, pcb);
+    if constexpr ((MASK & G_UOBB) != 0) wb = philox(n_full, pcb, keys);
 #pragma unroll
     for (uint32_t q = 0; q < 3; ++q) {
       if (q >= rem) break;
@@ -182,7 +227,7 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
                      : S0 * (R)exp((double)s.sumz / (double)n);
     y[c++] = (double)(disc * pos(G - K));
   }
-  if constexpr ((MASK & G_UO) != 0) y[c++] = s.alive ? (double)(disc * call) : 0.0;
+  if constexpr ((MASK & G_UO) != 0) y[c++] = st.alive(s) ? (double)(disc * call) : 0.0;
   if constexpr ((MASK & G_UOBB) != 0) y[c++] = s.alive_bb ? (double)(disc * call) : 0.0;
   if constexpr ((MASK & G_EURO_G) != 0) {
     const bool itm = ST > K;
@@ -206,13 +251,17 @@ __global__ __launch_bounds__(kBlock) void gbm_path_kernel(const GbmParams P) {
   __shared__ typename PathMath<R>::Shared shared;
   const PathMath<R> pm(shared);
   const GbmStepper<R, MASK, LOGS> st(P, pm);
+  const PhiloxKeys keys = make_keys<sizeof(R) == 4>(P.k0, P.k1);
   ThreadSums<C> acc;
   acc.zero();
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   for (uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x; pid < P.n_paths;
        pid += stride) {
     double y[C];
-    simulate<R, MASK, LOGS, CO>(P, st, P.path_offset + pid, y);
+    const uint64_t path = P.path_offset + pid;
+    with_uniform_high(path, [&](uint32_t hi) {
+      simulate<R, MASK, LOGS, CO>(P, st, keys, (uint32_t)path, hi, y);
+    });
     bool finite = true;
 #pragma unroll
     for (int c = 0; c < C; ++c) finite = finite && isfinite(y[c]);
