@@ -1013,23 +1013,23 @@ double loss_from_moments(const double* mom) {
 }
 
 // ------------------------------------------------------------- Basket ----
-// L' = diag(sigma_a sqrt(dt) / ln 2) L, packed into the kernel's lower-
-// triangular 32x16 blocks (n block nb, k block kb <= 2 nb + 1, block id
-// nb (nb + 1) + kb, element [n][k] row-major), in the requested type.
-template <typename T, typename F>
-void pack_blocks(uint32_t d, uint32_t nd, const std::vector<double>& Ls, F&& conv,
-                 std::vector<T>* out) {
-  out->assign((size_t)nd * (nd + 1) * 512, conv(0.0));
-  for (uint32_t nb = 0; nb < nd; ++nb)
-    for (uint32_t kb = 0; kb <= 2 * nb + 1; ++kb) {
-      const size_t base = (size_t)(nb * (nb + 1) + kb) * 512;
-      for (uint32_t r = 0; r < 32; ++r)
-        for (uint32_t j = 0; j < 16; ++j) {
-          const uint32_t a = 32 * nb + r, b = 16 * kb + j;
-          const double v = (a < d && b < d && b <= a) ? Ls[(size_t)a * d + b] : 0.0;
-          (*out)[base + r * 16 + j] = conv(v);
+// L' = diag(sigma_a sqrt(dt) / ln 2) L as MFMA fragments (mc_internal.h), one
+// array per term: conv(v, t) is term t of the value v.
+template <typename F>
+void pack_fragments(uint32_t d, int terms, const std::vector<double>& Ls, F&& conv,
+                    std::vector<uint16_t>* out) {
+  const uint32_t rows = d / 16, pairs = basket_pairs(rows);
+  out->assign((size_t)terms * pairs * 512, 0);
+  for (uint32_t rb = 0; rb < rows; ++rb)
+    for (uint32_t kb = 0; 2 * kb <= rb; ++kb)
+      for (uint32_t l = 0; l < 64; ++l)
+        for (uint32_t j = 0; j < 8; ++j) {
+          const uint32_t a = 16 * rb + l % 16, b = 32 * kb + 8 * (l / 16) + j;
+          if (b > a) continue;
+          for (int t = 0; t < terms; ++t)
+            (*out)[(((size_t)t * pairs + basket_pairs(rb) + kb) * 64 + l) * 8 + j] =
+                conv(Ls[(size_t)a * d + b], t);
         }
-    }
 }
 
 uint16_t to_bf16_rne(float f) {
@@ -1052,13 +1052,23 @@ uint16_t to_f16_rne(float f) {
   return u;
 }
 
-// Workspace of a basket run: moment layout, L' blocks (twice for the split
-// BF16 form) and the per-asset table.
+int basket_prec(mc_precision prec) {
+  return prec == MC_FP32 ? BK_FP32 : prec == MC_BF16_GEMM ? BK_BF16
+       : prec == MC_FP16_GEMM ? BK_FP16 : BK_BF16X2;
+}
+
+// Moment layout of a basket run.
+RunLayout basket_layout(uint64_t n_paths, int C, bool want_path) {
+  return layout_for(n_paths, C, want_path, kBasketTile, kBasketMaxBlocks);
+}
+
+// Workspace of a basket run: moment layout, the fragments of L' and the
+// per-asset table.
+size_t basket_frag_bytes(uint32_t d, mc_precision prec) {
+  return (size_t)basket_l_terms(basket_prec(prec)) * basket_pairs(d / 16) * 512 * sizeof(uint16_t);
+}
 size_t basket_ws_bytes(size_t layout_bytes, uint32_t d, mc_precision prec) {
-  const uint32_t nd = basket_blocks_nd(d);
-  const size_t elt = prec == MC_FP32 ? 4 : 2;
-  const size_t blk = align256((size_t)nd * (nd + 1) * 512 * elt);
-  return align256(layout_bytes) + blk * (prec == MC_BF16X2_GEMM ? 2 : 1) +
+  return align256(layout_bytes) + align256(basket_frag_bytes(d, prec)) +
          align256(4 * 256 * sizeof(float));
 }
 
@@ -1085,42 +1095,32 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   std::vector<double> L;
   mc_status st = validate_basket(ctx, m, f, n_steps, o0, &L);
   if (st != MC_OK) return st;
-  const uint32_t d = m->dim, nd = basket_blocks_nd(d);
+  const uint32_t d = m->dim;
   const double dt = m->T / n_steps, inv_ln2 = 1.0 / std::log(2.0);
   std::vector<double> Ls((size_t)d * d);
   for (uint32_t a = 0; a < d; ++a)
     for (uint32_t b = 0; b < d; ++b)
       Ls[(size_t)a * d + b] = m->sigma[a] * std::sqrt(dt) * inv_ln2 * L[(size_t)a * d + b];
-  int prec = BK_FP32;
-  std::vector<float> bf32;
-  std::vector<uint16_t> b16, b16lo;
-  size_t blk_bytes = 0;
-  switch (o0.prec) {
-    case MC_FP32:
-      prec = BK_FP32;
-      pack_blocks<float>(d, nd, Ls, [](double v) { return (float)v; }, &bf32);
-      blk_bytes = bf32.size() * 4;
-      break;
-    case MC_BF16_GEMM:
-      prec = BK_BF16;
-      pack_blocks<uint16_t>(d, nd, Ls, [](double v) { return to_bf16_rne((float)v); }, &b16);
-      blk_bytes = b16.size() * 2;
-      break;
-    case MC_FP16_GEMM:
-      prec = BK_FP16;
-      pack_blocks<uint16_t>(d, nd, Ls, [](double v) { return to_f16_rne((float)v); }, &b16);
-      blk_bytes = b16.size() * 2;
-      break;
-    default:
-      prec = BK_BF16X2;
-      pack_blocks<uint16_t>(d, nd, Ls, [](double v) { return to_bf16_rne((float)v); }, &b16);
-      pack_blocks<uint16_t>(d, nd, Ls, [](double v) {
-        const float hi = from_bf16(to_bf16_rne((float)v));
-        return to_bf16_rne((float)(v - (double)hi));
-      }, &b16lo);
-      blk_bytes = b16.size() * 2;
-      break;
+  const int prec = basket_prec(o0.prec);
+  std::vector<uint16_t> frag;
+  if (prec == BK_FP16) {
+    pack_fragments(d, 1, Ls, [](double v, int) { return to_f16_rne((float)v); }, &frag);
+  } else {
+    // Terms of v in bfloat16, each the rounding of what the earlier ones
+    // leave: one, hi + lo of the double (split BF16), or the 24 bits of the
+    // float as three.
+    const bool from_float = prec != BK_BF16X2;
+    pack_fragments(d, basket_l_terms(prec), Ls, [from_float](double v, int t) {
+      double rest = from_float ? (double)(float)v : v;
+      uint16_t h = to_bf16_rne((float)v);
+      for (int q = 0; q < t; ++q) {
+        rest -= (double)from_bf16(h);
+        h = to_bf16_rne((float)rest);
+      }
+      return h;
+    }, &frag);
   }
+  const size_t blk_bytes = frag.size() * sizeof(uint16_t);
   // Per-asset constants: n mu_a in log2 units, w_a S0_a, w_a ln 2, S0_a.
   std::vector<float> asset(4 * 256, 0.f);
   double geo0 = 0.0;
@@ -1134,10 +1134,9 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     asset[768 + a] = (float)m->S0[a];
     geo0 += w * std::log(m->S0[a]);
   }
-  const RunLayout Lay = layout_for(n_paths, 3, o0.path_values != nullptr);
+  const RunLayout Lay = basket_layout(n_paths, 3, o0.path_values != nullptr);
   const size_t off_blk = align256(Lay.bytes);
-  const size_t off_lo = off_blk + align256(blk_bytes);
-  const size_t off_asset = off_lo + (prec == BK_BF16X2 ? align256(blk_bytes) : 0);
+  const size_t off_asset = off_blk + align256(blk_bytes);
   const size_t total = off_asset + align256(asset.size() * 4);
   if (total != basket_ws_bytes(Lay.bytes, d, o0.prec))
     return fail(ctx, MC_ERR_DEVICE, "basket workspace layout mismatch");
@@ -1145,10 +1144,7 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   st = get_ws(ctx, o0, total, &base);
   if (st != MC_OK) return st;
   hipStream_t s = stream_of(ctx, o0);
-  const void* hb = prec == BK_FP32 ? (const void*)bf32.data() : (const void*)b16.data();
-  HIP_TRY(ctx, hipMemcpyAsync(base + off_blk, hb, blk_bytes, hipMemcpyHostToDevice, s));
-  if (prec == BK_BF16X2)
-    HIP_TRY(ctx, hipMemcpyAsync(base + off_lo, b16lo.data(), blk_bytes, hipMemcpyHostToDevice, s));
+  HIP_TRY(ctx, hipMemcpyAsync(base + off_blk, frag.data(), blk_bytes, hipMemcpyHostToDevice, s));
   HIP_TRY(ctx, hipMemcpyAsync(base + off_asset, asset.data(), asset.size() * 4,
                               hipMemcpyHostToDevice, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));   // host vectors go out of scope
@@ -1163,8 +1159,14 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   p.k0 = (uint32_t)seed;
   p.k1 = (uint32_t)(seed >> 32);
   p.d = d;
-  p.Lblk = base + off_blk;
-  p.Lblk_lo = prec == BK_BF16X2 ? base + off_lo : nullptr;
+  p.Lfrag = base + off_blk;
+  p.z_scale = p.x_scale = 1.0f;
+  if (prec == BK_FP32) p.z_scale = (float)std::sqrt(2.0 * std::log(2.0));
+  if (prec == BK_FP16)
+    while (5.8 * (double)n_steps * p.z_scale > 32768.0) {
+      p.z_scale *= 0.5f;
+      p.x_scale *= 2.0f;
+    }
   p.asset = (const float*)(base + off_asset);
   p.disc = std::exp(-m->r * m->T);
   p.K = f->K;
@@ -1202,7 +1204,7 @@ mc_status basket_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
                      p.path_out = path_out;
                      return launch_basket(p, prec, ss, nb);
                    },
-                   &mom, &kms);
+                   &mom, &kms, kBasketTile, kBasketMaxBlocks);
   if (st != MC_OK) return st;
   mc_result r{};
   double v;
@@ -1554,7 +1556,9 @@ size_t mc_workspace_bytes(const mc_model* m, const mc_payoff* f, uint64_t n_path
   const uint32_t cap = m->kind == MC_GBM ? kGbmMaxBlocks
                        : heston_persistent ? kHestonMaxBlocks
                                            : UINT32_MAX;
-  size_t bytes = layout_for(n_paths, (int)C, o.path_values != nullptr, kBlock, cap).bytes;
+  size_t bytes = m->kind == MC_GBM_BASKET
+                     ? basket_layout(n_paths, (int)C, o.path_values != nullptr).bytes
+                     : layout_for(n_paths, (int)C, o.path_values != nullptr, kBlock, cap).bytes;
   if (m->kind == MC_HESTON && o.greeks && o.greeks_method == MC_GREEKS_PATHWISE &&
       (n_steps + mcp::kCkpt - 1) / mcp::kCkpt > (uint32_t)mcp::kLdsCkpt)
     bytes = align256(bytes) + align256(mc_adjoint_ckpt_bytes(n_paths, n_steps, mcp::kCkpt));
@@ -1928,7 +1932,7 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     mc_options orun;
     st = basket_setup(ctx, m, f, n_points, n_steps, seed, o0, nullptr, 0.0, &q0, &p, &prec, &orun);
     if (st != MC_OK) return st;
-    const RunLayout Lay = layout_for(n_points, 3, false);
+    const RunLayout Lay = basket_layout(n_points, 3, false);
     const size_t b_shift = align256((size_t)n_replicates * dims * sizeof(uint32_t));
     const size_t b_part = align256((size_t)n_replicates * Lay.n_mom * Lay.n_blocks * sizeof(double));
     const size_t b_mom = align256((size_t)n_replicates * Lay.n_mom * sizeof(double));

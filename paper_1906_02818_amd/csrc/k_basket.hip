@@ -1,24 +1,39 @@
 // Basket path kernel: d correlated GBM assets stepped by log-Euler (the
-// multivariate Euler-Maruyama scheme of Sec. II-A.2), where each time step
-// needs the correlated increment Z L^T, a (paths x d) by (d x d) matrix
-// product, on the matrix cores (the MXU product of Sec. VI-A.2 done with
-// gfx950 MFMA instead).
+// multivariate Euler-Maruyama scheme of Sec. II-A.2). A step adds the
+// correlated increment L' Z_i, L' = diag(sigma_a sqrt(dt)) L, to the vector of
+// log-prices and the payoffs read only its last value, so
+//     sum_i L' Z_i = L' (sum_i Z_i):
+// every step's normals are drawn and summed, and the product with L' (the
+// matrix-unit product of Sec. VI-A.2) is taken once per path, on the matrix
+// cores, instead of once per step. The drift n (r - sigma_a^2/2) dt is added
+// there too.
 //
-// Layout. A wave owns a tile of 32 paths x d assets. The log-prices live in
-// the MFMA accumulators (d/32 blocks of 32x32 FP32, 16 values per lane per
-// block): with L' = diag(sigma_a sqrt(dt)) L the step is
-//     X += Z_i L'^T
-// and the deterministic drift n (r - sigma_a^2/2) dt is added once after
-// the last step (the step is linear in it). Each lane draws the 8 normals
-// of its A-operand fragment (path = lane mod 32, assets 16 kb + 8 (lane/32)
-// + 0..7) straight from Philox, so Z never touches memory. L' sits in LDS
-// as the packed lower-triangular 32x16 blocks (n block nb, k block kb <=
-// 2 nb + 1), so the upper triangle costs neither MFMA issue nor LDS.
+// Sums. A lane follows one path and a wave takes four assets (one Philox
+// block) through all steps, so the block index is uniform (device/rng.h), four
+// registers hold the sums, and any number of waves can share a tile of 64
+// paths. The sums go to LDS as [asset][path]. Reduced precisions round each
+// step's normals as an operand of their products would be rounded: to
+// bfloat16 (two steps' normals per conversion, both added by one
+// v_dot2_f32_bf16) or half. The sums are FP32 in every case.
 //
-// Precisions: FP32 (v_mfma_f32_32x32x2f32, K permuted inside each 16-wide
-// k block so that a lane still consumes its 8 contiguous normals), BF16 and
-// FP16 (v_mfma_f32_32x32x16_*), and BF16 with L' split into hi + lo terms.
-// Accumulation is FP32 in every case.
+// Product. X = L' S per tile by 16x16x32 MFMAs, rows = assets, columns = 16
+// paths; wave w takes path columns w mod 4 and up to four 16-asset row blocks,
+// paired so that every wave has the same share of the triangle. The FP32 sums
+// enter as up to three terms of the 16-bit type (8 + 8 + 8 bits), and so does
+// an FP32 L', with the products of terms above 2^-24 kept: the FP32 form is
+// six bfloat16 MFMAs for the eight FP32 ones of the same block, 96 cycles
+// against 256. Its error against 64 bits is below that of a product per step
+// in FP32, whose accumulation rounds n d / 2 times (100003 paths, d = 112, 50
+// steps: largest error of a result 1.6e-7 relative against 2.3e-7).
+//
+// Bound: VALU issue of the normals, 222 cycles per block of four and wave in
+// FP32, 244 in bfloat16 (issue costs: device/rng.h; 4.3 for a conversion or a
+// v_dot2). Path kernel, product per step -> product per path: 2^18 paths x 100
+// steps x 256 assets in bfloat16 3.70 -> 2.70 ms (2.60 ms of issue), the
+// portfolio of 100003 x 50 x 112 in FP32 1.21 -> 0.26 ms (0.20 ms). A product
+// per step spent 0.2 and 0.75 of its time in MFMAs, which on gfx950 do not run
+// beside FP32 VALU work of the same SIMD: an MFMA stream and an FMA stream of
+// 0.245 and 0.219 ms in different waves take 0.434 ms.
 #include "device/reduce.h"
 #include "device/rng.h"
 #include "mc_internal.h"
@@ -27,259 +42,353 @@ namespace mcp {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 
-constexpr int kWaves = 8;                 // 8 tiles of 32 paths per workgroup
-constexpr int kThreads = 64 * kWaves;
+constexpr int kTile = kBasketTile;        // paths per tile: one per lane
+constexpr int kRow = kTile + 2;           // LDS row of an asset's sums: rows 8 apart
+                                          // fall 16 banks apart (fragment reads)
 
+// NL, NZ: terms of L' and of the sums; KEEP: a product of terms i and j is
+// taken when i + j < KEEP.
 template <int PREC>
-struct BElt;
-template <> struct BElt<BK_FP32> { typedef float T; };
-template <> struct BElt<BK_BF16> { typedef __bf16 T; };
-template <> struct BElt<BK_FP16> { typedef _Float16 T; };
-template <> struct BElt<BK_BF16X2> { typedef __bf16 T; };
+struct Form;
+template <>
+struct Form<BK_FP32> {
+  typedef bf16x8 V;
+  static constexpr int NL = 3, NZ = 3, KEEP = 3;
+};
+template <>
+struct Form<BK_BF16> {
+  typedef bf16x8 V;
+  static constexpr int NL = 1, NZ = 3, KEEP = 3;
+};
+template <>
+struct Form<BK_BF16X2> {
+  typedef bf16x8 V;
+  static constexpr int NL = 2, NZ = 3, KEEP = 3;
+};
+template <>
+struct Form<BK_FP16> {
+  typedef f16x8 V;
+  static constexpr int NL = 1, NZ = 2, KEEP = 2;
+};
 
+__device__ __forceinline__ void mma(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma(f32x4& acc, const f16x8& a, const f16x8& b) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc, 0, 0, 0);
+}
+
+// s += the normals of one or two steps (blocks a, b; two: b holds a step),
+// rounded as PREC's operands are. FP32 sums the normals over sqrt(2 ln 2), the
+// factor of every radius (P.z_scale restores it): one fma per normal.
 template <int PREC>
-__device__ __forceinline__ void mfma_block(f32x16& acc, const float (&z)[8],
-                                           const unsigned char* lds_hi,
-                                           const unsigned char* lds_lo, int off_elems) {
+__device__ __forceinline__ void add_steps(float (&s)[4], const Words4& a, const Words4& b,
+                                          bool two) {
   if constexpr (PREC == BK_FP32) {
-    const float* b = (const float*)lds_hi + off_elems;
-    const float4 b0 = *(const float4*)(b);
-    const float4 b1 = *(const float4*)(b + 4);
-    const float bb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+    auto add = [&](const Words4& w) {
+      const uint32_t wr[2] = {w.w0, w.w2}, wa[2] = {w.w1, w.w3};
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(z[kk], bb[kk], acc, 0, 0, 0);
-  } else if constexpr (PREC == BK_FP16) {
-    f16x8 a;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) a[j] = (_Float16)z[j];
-    const f16x8 b = *(const f16x8*)((const _Float16*)lds_hi + off_elems);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc, 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+        const float ua = uniform_f32(wa[h]);
+        const float rad = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(uniform_f32(wr[h])));
+        s[2 * h] = __builtin_fmaf(rad, __builtin_amdgcn_cosf(ua), s[2 * h]);
+        s[2 * h + 1] = __builtin_fmaf(rad, __builtin_amdgcn_sinf(ua), s[2 * h + 1]);
+      }
+    };
+    add(a);
+    if (two) add(b);
   } else {
-    bf16x8 a;
+    const Normals4<float> na = normals4(a);
+    Normals4<float> nb = {{0.f, 0.f, 0.f, 0.f}};
+    if (two) nb = normals4(b);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) a[j] = (__bf16)z[j];
-    const bf16x8 b = *(const bf16x8*)((const __bf16*)lds_hi + off_elems);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-    if constexpr (PREC == BK_BF16X2) {
-      const bf16x8 bl = *(const bf16x8*)((const __bf16*)lds_lo + off_elems);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bl, acc, 0, 0, 0);
+    for (int t = 0; t < 4; ++t) {
+      if constexpr (PREC == BK_FP16) {
+        s[t] += (float)(_Float16)na.z[t];
+        s[t] += (float)(_Float16)nb.z[t];
+      } else {
+        const bf16x2 p = __builtin_convertvector((f32x2){na.z[t], nb.z[t]}, bf16x2);
+        const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
+        s[t] = __builtin_amdgcn_fdot2_f32_bf16(p, one, s[t], false);
+      }
     }
   }
 }
 
-template <int ND, int PREC, bool PORT, bool QMC>
-__global__ __launch_bounds__(kThreads) void basket_kernel(const BasketParams P) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  constexpr int NBLK = ND * (ND + 1);                 // packed triangular blocks
-  constexpr int ELT = sizeof(typename BElt<PREC>::T);
-  constexpr int BLK_BYTES = NBLK * 512 * ELT;
-  // Stage L' (and its lo part) into LDS.
-  {
-    const uint4* src = (const uint4*)P.Lblk;
-    uint4* dst = (uint4*)lds;
-    for (int i = threadIdx.x; i < BLK_BYTES / 16; i += kThreads) dst[i] = src[i];
-    if constexpr (PREC == BK_BF16X2) {
-      const uint4* src2 = (const uint4*)P.Lblk_lo;
-      uint4* dst2 = (uint4*)(lds + BLK_BYTES);
-      for (int i = threadIdx.x; i < BLK_BYTES / 16; i += kThreads) dst2[i] = src2[i];
-    }
+// Words of one block of four Sobol' dimensions (dims 4j .. 4j+3) for the
+// points base + lane, each xored with its digital shift. V and shift are
+// read as scalars; the bits of the point index that are the same for all
+// lanes (above the sixth when the base is a multiple of 64) are folded on the
+// scalar unit.
+__device__ __forceinline__ Words4 sobol_words(const uint32_t* __restrict__ V,
+                                              const uint32_t* __restrict__ shift, uint32_t j,
+                                              uint32_t base, uint32_t lane) {
+  const uint32_t* v = V + (size_t)j * 128u;
+  const uint32_t last = base + 63u < base ? 0xFFFFFFFFu : base + 63u;   // points end at 2^32
+  const uint32_t bits = 32u - (uint32_t)__builtin_clz(last | 63u);
+  const uint32_t split = (base & 63u) == 0u ? 6u : bits;
+  uint32_t u[4], x[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) u[t] = shift[4u * j + t];
+  for (uint32_t b = split; b < bits; ++b) {
+    const uint32_t m = 0u - ((base >> b) & 1u);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) u[t] ^= m & v[32 * t + b];
   }
-  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) x[t] = u[t];
+  const uint32_t point = base + lane;
+  for (uint32_t b = 0; b < split; ++b) {
+    const uint32_t m = 0u - ((point >> b) & 1u);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) x[t] ^= m & v[32 * t + b];
+  }
+  return Words4{x[0], x[1], x[2], x[3]};
+}
 
+// Row block i of the wave's set of the triangle's 16-row blocks, S sets per
+// workgroup: consecutive pairs sum to a constant, so the sets have equal
+// shares of the triangle.
+template <int S>
+__device__ __forceinline__ uint32_t row_block(uint32_t set, uint32_t i) {
+  if constexpr (S == 1) return i;
+  return 2u * S * (i >> 1) + ((i & 1u) ? 2u * S - 1u - set : set);
+}
+
+// RPW: 16-row blocks per wave (d <= 4 W RPW).
+template <int PREC, bool PORT, bool QMC, int W, int RPW>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) void basket_kernel(const BasketParams P) {
+  typedef Form<PREC> F;
+  typedef typename F::V V8;
+  constexpr int SETS = W / 4, C = PORT ? 1 : 3;
+  extern __shared__ float s_sum[];         // [d][kRow]
+  __shared__ float s_part[C][SETS][kTile];
+  // Sums of the first wave's paths over the workgroup's tiles (in LDS: as
+  // registers they would be held by every wave).
+  __shared__ ThreadSums<C> s_acc[kTile];
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int row = lane & 31;          // A row / B and D column
-  const int half = lane >> 5;
-  // Block blk of the launch, or of its replicate when replicates share it.
-  uint32_t blk = blockIdx.x;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Block blk of nblk of the launch, or of its replicate when replicates
+  // share it.
+  uint32_t blk = blockIdx.x, nblk = gridDim.x;
   const uint32_t* qshift = P.qshift;
   double* partials = P.partials;
   if constexpr (QMC) {
     if (P.q_rep_blocks != 0) {
-      const uint32_t rep = blockIdx.x / P.q_rep_blocks;
-      blk = blockIdx.x - rep * P.q_rep_blocks;
+      nblk = P.q_rep_blocks;
+      const uint32_t rep = blockIdx.x / nblk;
+      blk = blockIdx.x - rep * nblk;
       qshift += (size_t)rep * P.q_dims;
-      partials += (size_t)rep * n_moments(PORT ? 1 : 3) * P.q_rep_blocks;
+      partials += (size_t)rep * n_moments(C) * nblk;
     }
   }
-  const uint64_t tile = (uint64_t)blk * kWaves + wave;
-  const uint64_t zpath = tile * 32 + row;             // path this lane draws normals for
-  const PathCounter pc = make_counter(P.path_offset + zpath, P.tag, P.k0, P.k1);
-  const uint32_t d = P.d;
-  const int nkb = (int)(d >> 4);
+  const uint32_t d = P.d, n = P.n_steps, nq = d >> 2, rows = d >> 4;
+  const PhiloxKeys keys = make_keys<true>(P.k0, P.k1);
+  if (threadIdx.x < kTile) s_acc[threadIdx.x].zero();
 
-  f32x16 acc[ND];
+  const uint64_t tiles = (P.n_paths + kTile - 1) / kTile;
+  for (uint64_t tile = blk; tile < tiles; tile += nblk) {
+    // ---- sums of the normals ----
+    const uint64_t path = P.path_offset + tile * kTile + (uint64_t)lane;
+    auto sum_block = [&](uint32_t q, auto&& words) {
+      float s[4] = {0.f, 0.f, 0.f, 0.f};
+      uint32_t i = 0;
+      for (; i + 1 < n; i += 2) {
+        const Words4 a = words(i * nq + q), b = words((i + 1) * nq + q);
+        add_steps<PREC>(s, a, b, true);
+      }
+      if (i < n) {
+        const Words4 a = words(i * nq + q);
+        add_steps<PREC>(s, a, a, false);
+      }
 #pragma unroll
-  for (int nb = 0; nb < ND; ++nb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[nb][r] = 0.f;
+      for (int t = 0; t < 4; ++t) s_sum[(4u * q + t) * kRow + lane] = s[t];
+    };
+    if constexpr (QMC) {
+      const uint32_t base = (uint32_t)(P.path_offset + tile * kTile);
+      for (uint32_t q = wave; q < nq; q += W)
+        sum_block(q, [&](uint32_t j) { return sobol_words(P.qV, qshift, j, base, (uint32_t)lane); });
+    } else {
+      with_uniform_high(path, [&](uint32_t hi) {
+        const PathRng g = make_rng((uint32_t)path, hi, P.tag, keys);
+        for (uint32_t q = wave; q < nq; q += W)
+          sum_block(q, [&](uint32_t j) { return philox(j, g, keys); });
+      });
+    }
+    __syncthreads();
 
-  for (uint32_t i = 0; i < P.n_steps; ++i) {
-    const uint64_t kbase = (uint64_t)i * d;          // first normal of step i
+    // ---- X = L' S: columns `col` (16 paths), rows of the wave's set ----
+    const uint32_t col = wave & 3u, set = wave >> 2;
+    const uint32_t c16 = (uint32_t)lane & 15u, g4 = (uint32_t)lane >> 4;
+    f32x4 x[RPW];
 #pragma unroll
-    for (int kb = 0; kb < 2 * ND; ++kb) {
-      if (kb < nkb) {
-        const uint32_t j0 = (uint32_t)((kbase + 16u * kb + 8u * half) >> 2);
-        Words4 wa, wb;
-        if constexpr (QMC) {
-          const uint32_t point = (uint32_t)(P.path_offset + zpath);
-          wa = sobol_block(P.qV, qshift, j0, point);
-          wb = sobol_block(P.qV, qshift, j0 + 1, point);
-        } else {
-          wa = philox(j0, pc);
-          wb = philox(j0 + 1, pc);
-        }
-        const Normals4<float> za = normals4(wa);
-        const Normals4<float> zb = normals4(wb);
-        const float z[8] = {za.z[0], za.z[1], za.z[2], za.z[3],
-                            zb.z[0], zb.z[1], zb.z[2], zb.z[3]};
+    for (int i = 0; i < RPW; ++i) x[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const uint32_t nz = n == 1u && PREC != BK_FP32 ? 1u : (uint32_t)F::NZ;   // one step: one term
+    const uint32_t n_pairs = (uint32_t)basket_pairs(rows);
+    for (uint32_t kb = 0; 32u * kb < d; ++kb) {
+      // The column operand: sums of assets 32 kb + 8 g4 + 0..7, path c16.
+      V8 z[F::NZ];
+      {
+        const uint32_t k0 = 32u * kb + 8u * g4;
+        float r[8];
 #pragma unroll
-        for (int nb = kb >> 1; nb < ND; ++nb) {
-          const int id = nb * (nb + 1) + kb;
-          mfma_block<PREC>(acc[nb], z, lds, lds + BLK_BYTES, (id * 32 + row) * 16 + 8 * half);
+        for (uint32_t e = 0; e < 8u; ++e)
+          r[e] = k0 < d ? s_sum[(k0 + e) * kRow + 16u * col + c16] * P.z_scale : 0.f;
+#pragma unroll
+        for (int t = 0; t < F::NZ; ++t)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            z[t][e] = r[e];
+            r[e] -= (float)z[t][e];
+          }
+      }
+#pragma unroll
+      for (uint32_t i = 0; i < (uint32_t)RPW; ++i) {
+        const uint32_t rb = row_block<SETS>(set, i);
+        if (rb < rows && 2u * kb <= rb) {
+          const V8* a = (const V8*)P.Lfrag + ((size_t)basket_pairs(rb) + kb) * 64u + lane;
+#pragma unroll
+          for (int p = 0; p < F::NL; ++p) {
+            const V8 l = a[(size_t)p * n_pairs * 64u];
+#pragma unroll
+            for (int t = 0; t < F::NZ; ++t)
+              if (p + t < F::KEEP && (uint32_t)t < nz) mma(x[i], l, z[t]);
+          }
         }
       }
     }
-  }
 
-  // Terminal values. Lane holds asset a = 32 nb + row for path rows
-  // 8 (r/4) + 4 half + (r mod 4), r = 0..15. One row r at a time: the sum
-  // over the lane's assets, then over the 32 lanes of its half (few live
-  // registers beside the accumulators).
-  float B = 0.f, G = 0.f, E0 = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
+    // ---- terminal values: the lane holds assets 16 rb + 4 g4 + 0..3 of
+    // path c16 of its column block ----
     float bs = 0.f, gs = 0.f, e0 = 0.f;
 #pragma unroll
-    for (int nb = 0; nb < ND; ++nb) {
-      const int a = 32 * nb + row;
-      const float x = acc[nb][r] + P.asset[a];          // log2(S_a / S0_a)
-      const float E = __builtin_amdgcn_exp2f(x);
-      if constexpr (PORT) {
-        // Portfolio value of asset a: S0_a sum_k q_k (E - m_k)^+ (zero-padded
-        // assets carry S0 = 0).
-        float v = 0.f;
-        for (uint32_t k = 0; k < P.n_strikes; ++k) {
-          const float itm = E - P.pm[k];
-          v = __builtin_fmaf(P.pq[k], itm > 0.f ? itm : 0.f, v);
+    for (uint32_t i = 0; i < (uint32_t)RPW; ++i) {
+      const uint32_t rb = row_block<SETS>(set, i);
+      if (rb < rows) {
+#pragma unroll
+        for (uint32_t r = 0; r < 4u; ++r) {
+          const uint32_t a = 16u * rb + 4u * g4 + r;
+          const float v = x[i][r] * P.x_scale + P.asset[a];   // log2(S_a / S0_a)
+          const float E = __builtin_amdgcn_exp2f(v);
+          if constexpr (PORT) {
+            // Portfolio value of asset a: S0_a sum_k q_k (E - m_k)^+.
+            float pv = 0.f;
+            for (uint32_t k = 0; k < P.n_strikes; ++k) {
+              const float itm = E - P.pm[k];
+              pv = __builtin_fmaf(P.pq[k], itm > 0.f ? itm : 0.f, pv);
+            }
+            bs = __builtin_fmaf(P.asset[768 + a], pv, bs);
+          } else {
+            bs += P.asset[256 + a] * E;
+            gs += P.asset[512 + a] * v;
+            if (a == 0u) e0 = E;
+          }
         }
-        bs = __builtin_fmaf(P.asset[768 + a], v, bs);
-      } else {
-        bs += P.asset[256 + a] * E;
-        gs += P.asset[512 + a] * x;
-        if (nb == 0) e0 = E;
       }
     }
 #pragma unroll
-    for (int off = 16; off > 0; off >>= 1) {
+    for (int off = 16; off < 64; off <<= 1) {
       bs += __shfl_xor(bs, off, 64);
-      if constexpr (!PORT) gs += __shfl_xor(gs, off, 64);
+      if constexpr (!PORT) {
+        gs += __shfl_xor(gs, off, 64);
+        e0 += __shfl_xor(e0, off, 64);     // one lane of the four holds it
+      }
     }
-    if constexpr (!PORT) e0 = __shfl(e0, lane & 32, 64);   // asset 0 sits in column 0
-    // Lane (half, row < 16) reports path row 8 (row/4) + 4 half + row mod 4.
-    if (r == row) {
-      B = bs;
-      G = gs;
-      E0 = e0;
+    if (g4 == 0u) {
+      s_part[0][set][16u * col + c16] = bs;
+      if constexpr (!PORT) {
+        s_part[1][set][16u * col + c16] = gs;
+        s_part[2][set][16u * col + c16] = e0;
+      }
     }
-  }
-  const int prow = 8 * (row >> 2) + 4 * half + (row & 3);
-  const uint64_t pid = tile * 32 + prow;
-  const bool active = row < 16 && pid < P.n_paths;
-  if constexpr (PORT) {
-    double y[1] = {0.0};
-    if (active) y[0] = (double)B - P.premium;
-    const bool finite = isfinite(y[0]);
-    if (active && P.path_out != nullptr) P.path_out[pid] = y[0];
-    block_moments<1, kThreads>(y, active && finite, active && !finite, partials, blk);
-  } else {
-    double y[3] = {0.0, 0.0, 0.0};
-    if (active) {
-      const double disc = P.disc, K = P.K;
-      const double basket = (double)B;
-      const double geo = exp(P.geo0 + (double)G);
-      y[0] = disc * (basket > K ? basket - K : 0.0);
-      y[1] = disc * (geo > K ? geo - K : 0.0);
-      y[2] = basket > K ? disc * P.w0 * (double)E0 : 0.0;
-    }
-    bool finite = isfinite(y[0]) && isfinite(y[1]) && isfinite(y[2]);
-    if (active && P.path_out != nullptr) {
+    __syncthreads();                       // also: every wave has read s_sum
+    const uint64_t pid = tile * kTile + (uint64_t)lane;
+    if (wave == 0u && pid < P.n_paths) {
+      float v[C];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) P.path_out[pid * 3 + c] = y[c];
+      for (int c = 0; c < C; ++c) {
+        v[c] = s_part[c][0][lane];
+#pragma unroll
+        for (int q = 1; q < SETS; ++q) v[c] += s_part[c][q][lane];
+      }
+      double y[C];
+      if constexpr (PORT) {
+        y[0] = (double)v[0] - P.premium;
+      } else {
+        const double disc = P.disc, K = P.K;
+        const double basket = (double)v[0];
+        const double geo = exp(P.geo0 + (double)v[1]);
+        y[0] = disc * (basket > K ? basket - K : 0.0);
+        y[1] = disc * (geo > K ? geo - K : 0.0);
+        y[2] = basket > K ? disc * P.w0 * (double)v[2] : 0.0;
+      }
+      bool finite = true;
+#pragma unroll
+      for (int c = 0; c < C; ++c) finite = finite && isfinite(y[c]);
+      if (P.path_out != nullptr) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) P.path_out[pid * C + c] = y[c];
+      }
+      s_acc[lane].push(y, finite, !finite);
     }
-    block_moments<3, kThreads>(y, active && finite, active && !finite, partials, blk);
+    // The next tile's terminal values are written two barriers from here.
   }
+  PartSums<C> part;
+  part.zero();
+  if (wave == 0u) part = s_acc[lane].part();
+  block_reduce<C, 64 * W>(part, partials, blk);
 }
 
-template <int ND, int PREC, bool PORT, bool QMC>
-hipError_t launch_nd_mode(const BasketParams& p, hipStream_t s, uint32_t nb) {
-  constexpr int NBLK = ND * (ND + 1);
-  constexpr int ELT = sizeof(typename BElt<PREC>::T);
-  const size_t lds = (size_t)NBLK * 512 * ELT * (PREC == BK_BF16X2 ? 2 : 1);
-  hipError_t e = hipFuncSetAttribute((const void*)basket_kernel<ND, PREC, PORT, QMC>,
+template <int PREC, bool PORT, bool QMC, int W, int RPW>
+hipError_t launch_w(const BasketParams& p, hipStream_t s, uint32_t nb) {
+  static_assert(kBasketMaxDim <= 4 * 8 * 8, "row blocks of the largest form");
+  if (p.d > (uint32_t)(4 * W * RPW)) return hipErrorInvalidValue;
+  const size_t lds = (size_t)p.d * kRow * sizeof(float);
+  hipError_t e = hipFuncSetAttribute((const void*)basket_kernel<PREC, PORT, QMC, W, RPW>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((basket_kernel<ND, PREC, PORT, QMC>), dim3(nb), dim3(kThreads), lds, s, p);
+  hipLaunchKernelGGL((basket_kernel<PREC, PORT, QMC, W, RPW>), dim3(nb), dim3(64 * W), lds, s, p);
   return hipGetLastError();
 }
 
-template <int ND, int PREC>
-hipError_t launch_nd(const BasketParams& p, hipStream_t s, uint32_t nb) {
-  if constexpr (PREC == BK_BF16X2) {   // basket call with Philox normals only
-    if (p.n_strikes != 0 || p.qV != nullptr) return hipErrorInvalidValue;
-    return launch_nd_mode<ND, PREC, false, false>(p, s, nb);
-  } else {
-    if (p.qV != nullptr) {
-      if (p.n_strikes != 0) return hipErrorInvalidValue;
-      return launch_nd_mode<ND, PREC, false, true>(p, s, nb);
-    }
-    if (p.n_strikes == 0) return launch_nd_mode<ND, PREC, false, false>(p, s, nb);
-    return launch_nd_mode<ND, PREC, true, false>(p, s, nb);
-  }
+// Waves per tile and row blocks per wave. A CU holds 16 waves at the 128 VGPRs
+// of the product phase; two or more workgroups of them should be resident so
+// that one's product runs beside the other's sums. Measured (d = 112, FP32,
+// 100003 x 50): 255 us in workgroups of 8 waves, 287 us in 4; capping the
+// registers for 20 waves spills and gains nothing.
+template <int PREC, bool PORT, bool QMC>
+hipError_t launch_mode(const BasketParams& p, hipStream_t s, uint32_t nb) {
+  if (p.d <= 64) return launch_w<PREC, PORT, QMC, 4, 4>(p, s, nb);
+  if (p.d <= 128) return launch_w<PREC, PORT, QMC, 8, 4>(p, s, nb);
+  return launch_w<PREC, PORT, QMC, 8, 8>(p, s, nb);
 }
 
 template <int PREC>
 hipError_t launch_prec(const BasketParams& p, hipStream_t s, uint32_t nb) {
-  const uint32_t nd = (p.d + 31) / 32;
-  if (nd <= 1) return launch_nd<1, PREC>(p, s, nb);
-  if (nd <= 2) return launch_nd<2, PREC>(p, s, nb);
-  if (nd <= 4) return launch_nd<4, PREC>(p, s, nb);
-  return launch_nd<8, PREC>(p, s, nb);
-}
-
-}  // namespace
-
-uint32_t basket_blocks_nd(uint32_t d) {
-  const uint32_t nd = (d + 31) / 32;
-  return nd <= 1 ? 1 : nd <= 2 ? 2 : nd <= 4 ? 4 : 8;
-}
-
-hipError_t launch_basket_qmc_batch(BasketParams p, int prec, uint32_t n_rep, hipStream_t s,
-                                   uint32_t* blocks_per_rep) {
-  const uint32_t paths_per_wg = 32 * kWaves;
-  const uint64_t nb = (p.n_paths + paths_per_wg - 1) / paths_per_wg;
-  *blocks_per_rep = (uint32_t)nb;
-  if (p.qV == nullptr || p.n_strikes != 0 || p.path_out != nullptr || n_rep == 0 || nb == 0 ||
-      nb * n_rep > 0x7fffffffull || prec == BK_BF16X2)
-    return hipErrorInvalidValue;
-  p.q_rep_blocks = (uint32_t)nb;
-  const uint32_t total = (uint32_t)(nb * n_rep);
-  switch (prec) {
-    case BK_FP32: return launch_prec<BK_FP32>(p, s, total);
-    case BK_BF16: return launch_prec<BK_BF16>(p, s, total);
-    case BK_FP16: return launch_prec<BK_FP16>(p, s, total);
+  const bool qmc = p.qV != nullptr, port = p.n_strikes != 0;
+  if (qmc && port) return hipErrorInvalidValue;
+  if constexpr (PREC == BK_FP32 || PREC == BK_FP16) {
+    if (qmc) return launch_mode<PREC, false, true>(p, s, nb);
   }
-  return hipErrorInvalidValue;
+  if constexpr (PREC != BK_BF16X2) {
+    if (port) return launch_mode<PREC, true, false>(p, s, nb);
+  }
+  if (qmc || port) return hipErrorInvalidValue;
+  return launch_mode<PREC, false, false>(p, s, nb);
 }
 
-hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks) {
-  const uint32_t paths_per_wg = 32 * kWaves;
-  const uint32_t nb = (uint32_t)((p.n_paths + paths_per_wg - 1) / paths_per_wg);
-  *n_blocks = nb;
+// Shapes the kernel assumes.
+bool shapes_ok(const BasketParams& p) {
+  return p.d >= 16 && p.d <= (uint32_t)kBasketMaxDim && p.d % 16 == 0 && p.n_steps > 0 && p.n_paths > 0;
+}
+
+hipError_t launch_any(const BasketParams& p, int prec, hipStream_t s, uint32_t nb) {
+  if (!shapes_ok(p)) return hipErrorInvalidValue;
   switch (prec) {
     case BK_FP32: return launch_prec<BK_FP32>(p, s, nb);
     case BK_BF16: return launch_prec<BK_BF16>(p, s, nb);
@@ -287,6 +396,44 @@ hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_
     case BK_BF16X2: return launch_prec<BK_BF16X2>(p, s, nb);
   }
   return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+int basket_l_terms(int prec) {
+  return prec == BK_FP32 ? Form<BK_FP32>::NL : prec == BK_BF16X2 ? Form<BK_BF16X2>::NL : 1;
+}
+
+// A workgroup ends with a reduction and a moment vector, so it takes enough
+// tiles to draw 64 Philox blocks per wave, as long as 1024 workgroups are left
+// to fill the chip.
+uint32_t basket_blocks(uint64_t n_paths, uint32_t n_steps, uint32_t d) {
+  const uint64_t tiles = (n_paths + kTile - 1) / kTile;
+  const uint64_t per_wave = (uint64_t)n_steps * (d / 4) / (d <= 64 ? 4 : 8);
+  const uint64_t per_wg = per_wave >= 64 ? 1 : (64 + per_wave - 1) / (per_wave ? per_wave : 1);
+  uint64_t nb = (tiles + per_wg - 1) / per_wg;
+  if (nb < 1024) nb = tiles < 1024 ? tiles : 1024;
+  return (uint32_t)(nb < kBasketMaxBlocks ? nb : kBasketMaxBlocks);
+}
+
+hipError_t launch_basket_qmc_batch(BasketParams p, int prec, uint32_t n_rep, hipStream_t s,
+                                   uint32_t* blocks_per_rep) {
+  if (n_rep == 0 || n_rep > kBasketMaxBlocks) return hipErrorInvalidValue;
+  uint64_t nb = basket_blocks(p.n_paths, p.n_steps, p.d);
+  const uint64_t share = kBasketMaxBlocks / 2 / n_rep;    // 2048 workgroups in all
+  if (nb > share) nb = share ? share : 1;
+  *blocks_per_rep = (uint32_t)nb;
+  if (p.qV == nullptr || p.n_strikes != 0 || p.path_out != nullptr || nb == 0)
+    return hipErrorInvalidValue;
+  p.q_rep_blocks = (uint32_t)nb;
+  return launch_any(p, prec, s, (uint32_t)(nb * n_rep));
+}
+
+hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks) {
+  const uint32_t nb = basket_blocks(p.n_paths, p.n_steps, p.d);
+  *n_blocks = nb;
+  if (nb == 0) return hipErrorInvalidValue;
+  return launch_any(p, prec, s, nb);
 }
 
 }  // namespace mcp

@@ -114,14 +114,32 @@ struct AdjointParams {
 };
 hipError_t launch_heston_adjoint(const AdjointParams& p, hipStream_t s, uint32_t* n_blocks);
 
-// ---- Basket (correlated GBM, MFMA increments) ----
+// ---- Basket (correlated GBM, MFMA product of the summed normals) ----
 enum : int { BK_FP32 = 0, BK_BF16 = 1, BK_FP16 = 2, BK_BF16X2 = 3 };
+constexpr int kBasketTile = 64;              // paths per tile, one per lane
+constexpr int kBasketMaxDim = 256;
+// Grid cap: a workgroup takes tiles blk, blk + grid, ... and writes one
+// moment vector.
+constexpr uint32_t kBasketMaxBlocks = 4096;
+uint32_t basket_blocks(uint64_t n_paths, uint32_t n_steps, uint32_t d);
+// L' in MFMA operand order: for each 16-row block rb of the lower triangle its
+// 32-column blocks kb = 0 .. rb / 2, fragment basket_pairs(rb) + kb = [64
+// lanes][8] of the 16-bit type, lane l holding row 16 rb + l mod 16 and
+// columns 32 kb + 8 (l / 16) + 0..7; one such array per term of L' (hi, mid,
+// lo).
+__host__ __device__ constexpr uint32_t basket_pairs(uint32_t rb) {   // fragments before block rb
+  return (rb / 2) * (rb / 2 + 1) + (rb % 2) * (rb / 2 + 1);
+}
+int basket_l_terms(int prec);
 struct BasketParams {
   uint64_t n_paths, path_offset;
   uint32_t n_steps, tag, k0, k1;
   uint32_t d;             // assets, multiple of 16, <= 256
-  const void* Lblk;       // packed lower-triangular 32x16 blocks of L' (device)
-  const void* Lblk_lo;    // BF16X2: the lo term, same layout
+  const void* Lfrag;      // [terms][basket_pairs(d / 16)][64][8] (device)
+  // Scale of the sums as operands, and of the product: FP32 restores the
+  // factor sqrt(2 ln 2) of the normals; half precision takes the sums times a
+  // power of two (|sum| < 5.8 n_steps stays below 2^15) and the product over it.
+  float z_scale, x_scale;
   const float* asset;     // device [4][256]: n*mu_a (log2), w_a*S0_a, w_a*ln 2, S0_a
   double disc, K, geo0, w0;
   // Call portfolio (risk mode): q_k calls of strike m_k S0_a on every asset;
@@ -141,8 +159,6 @@ struct BasketParams {
   double* path_out;       // [n_paths][3] (basket) or [n_paths] (portfolio), or nullptr
 };
 constexpr int kMaxStrikes = 8;
-// Number of 32-wide asset blocks the kernel is instantiated for (1, 2, 4, 8).
-uint32_t basket_blocks_nd(uint32_t d);
 hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks);
 // All n_rep randomised-QMC replicates of p in one launch (p.qshift holds
 // n_rep rows of p.q_dims shifts); *blocks_per_rep = one replicate's blocks.

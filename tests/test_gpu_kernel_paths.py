@@ -82,3 +82,76 @@ def test_fp64_normals_to_rounding(ctx, path, k0):
     z = mc.mc_normals(ctx, SEED, 0, path, k0, 1 << 17, mc.MC_FP64)
     ref = oracle.normals(SEED, 0, path, k0, 1 << 17)
     assert np.max(np.abs(z - ref)) < 6e-15
+
+
+# ------------------------------------------------------------- basket ----
+def _bf16(x):
+    u = np.ascontiguousarray(x, np.float32).view(np.uint32).astype(np.uint64)
+    u = (u + 0x7FFF + ((u >> 16) & 1)) & 0xFFFF0000
+    return u.astype(np.uint32).view(np.float32).astype(np.float64)
+
+
+def _rounded(x, prec):
+    """x as the operand of a product of this precision (float64 result)."""
+    if prec == mc.MC_FP32:
+        return np.asarray(x, np.float32).astype(np.float64)
+    if prec == mc.MC_FP16_GEMM:
+        return np.asarray(np.asarray(x, np.float32), np.float16).astype(np.float64)
+    return _bf16(x)
+
+
+@pytest.mark.parametrize("prec", [mc.MC_FP32, mc.MC_BF16_GEMM, mc.MC_FP16_GEMM, mc.MC_BF16X2_GEMM])
+@pytest.mark.parametrize("d,N,n,offset", [(16, 2, 1, 0), (16, 4099, 3, 5), (64, 63, 2, 0),
+                                          (80, 65, 3, (1 << 32) - 33), (128, 200, 1, 0),
+                                          (144, 129, 2, 7), (256, 64, 5, 0)])
+def test_basket_tiles_and_forms(ctx, prec, d, N, n, offset):
+    # Every wave layout, partial tiles, odd and single steps, all operand
+    # forms: the log-prices of a model that rounds each step's normals and L'
+    # as the form's operands and does everything else in 64 bits. The kernel
+    # adds FP32 rounding (1e-6 of a price); a normal within FP32 error of a
+    # rounding boundary (one in 2^14) may round to the other side.
+    print("basket tiles", prec, d, N, n, offset, flush=True)
+    sigma, corr, _ = synth.basket_market(d)
+    rng = np.random.default_rng(d + n)
+    S0 = 80.0 + 40.0 * rng.random(d)
+    w = rng.random(d) / d
+    K, r_, T = 40.0, 0.05, 1.0
+    r = mc.mc_price(ctx, mc.Model(kind=mc.MC_GBM_BASKET, S0=S0, r=r_, T=T, sigma=sigma, corr=corr),
+                    mc.Payoff(mc.MC_BASKET_CALL, K, weights=w), N, n, SEED,
+                    mc.Options(prec=prec, path_offset=offset, path_values=True))
+    L = np.linalg.cholesky(corr) * (sigma * np.sqrt(T / n) / np.log(2.0))[:, None]
+    Lr = _rounded(L, prec)
+    if prec == mc.MC_BF16X2_GEMM:
+        Lr = Lr + _bf16(L - Lr)
+    keep = np.arange(N) if N <= 300 else np.unique(np.r_[0:70, N - 70:N])
+    x = np.empty((keep.size, d))
+    for row, p in enumerate(keep):
+        z = oracle.normals(SEED, 0, offset + int(p), 0, n * d).reshape(n, d)
+        x[row] = Lr @ _rounded(z, prec).sum(0)
+    E = 2.0 ** (x + (r_ - 0.5 * sigma * sigma) * T / np.log(2.0))
+    basket = (E * S0 * w).sum(1)
+    ref = np.exp(-r_ * T) * np.maximum(basket - K, 0.0)
+    err = np.abs(r["path_values"][keep, 0] - ref)
+    tol = 4e-6 * (S0 * w).sum()
+    flips = 0.0 if prec == mc.MC_FP32 else n * d * 2.0 ** -14
+    assert np.mean(err > tol) <= 2.0 * flips + (4.0 / keep.size if flips else 0.0)
+    assert err.max() <= (tol if prec == mc.MC_FP32 else 2e-2 * (S0 * w).sum())
+    assert r["n_paths"] == N and r["n_nonfinite"] == 0
+
+
+@pytest.mark.parametrize("offset,N", [(0, 64), (0, 1), (1, 200), (61, 131), ((1 << 20) - 3, 70),
+                                      ((1 << 32) - 90, 90)])
+def test_sobol_points_at_any_offset(ctx, offset, N):
+    # Points whose tile starts at, or between, multiples of 64.
+    if N == 1:
+        N = 2
+    d, n = 16, 2
+    print("sobol offset", offset, N, flush=True)
+    sigma, corr, _ = synth.basket_market(d)
+    S0, w = np.full(d, 100.0), np.full(d, 1.0 / d)
+    model = mc.Model(kind=mc.MC_GBM_BASKET, S0=S0, r=0.05, T=1.0, sigma=sigma, corr=corr)
+    r = mc.mc_price_qmc(ctx, model, mc.Payoff(mc.MC_BASKET_CALL, 90.0), N, n, SEED, 1,
+                        mc.Options(prec=mc.MC_FP32, path_offset=offset, path_values=True))
+    o = oracle.basket_qmc(S0, sigma, oracle.cholesky(corr), w, 0.05, 1.0, 90.0, n, N, SEED,
+                          0, path0=offset)
+    np.testing.assert_allclose(r["path_values"][:, 0], o[:, 0], rtol=1e-4, atol=1e-4)
