@@ -86,10 +86,9 @@ __device__ __forceinline__ Words4 philox(uint32_t j, const PathCounter& pc) {
 // one of round 2 is a constant of the path: 15 remain.
 //
 // Measured on the Asian + geometric + barrier call of 2^24 GBM paths x 252
-// steps: 2.21 ms with SGPR keys and 18 products (16, two of them as a
-// v_mul_lo / v_mul_hi pair), 1.97 ms in this form with the increments of
-// box_muller_inc_f32. Per block and wave: 64 cycles of products, 53 of xors,
-// of about 300 for the four steps.
+// steps: 2.21 ms with SGPR keys and 18 products (two of them as v_mul_lo /
+// v_mul_hi pairs), 2.02 ms in this form. Per block and wave: 64 cycles of
+// products, 53 of xors, of about 305 for the four steps.
 struct PhiloxKeys {
   uint32_t a[10], b[10];   // round keys k0 + r W0, k1 + r W1
 };
@@ -199,18 +198,6 @@ __device__ __forceinline__ void box_muller_f32(uint32_t w_rad, uint32_t w_ang, f
   const float rad = __builtin_amdgcn_sqrtf(-1.38629436111989061883f * __builtin_amdgcn_logf(ur));
   z0 = rad * __builtin_amdgcn_cosf(ua);
   z1 = rad * __builtin_amdgcn_sinf(ua);
-}
-
-// A time step's normal as the increment of a log-price: a + b Z for both
-// normals of a pair, with b folded into the radius (m2 = -2 ln 2 b^2, so
-// b r(w) = sqrt(m2 log2 u(w))), one fma per increment.
-__device__ __forceinline__ void box_muller_inc_f32(uint32_t w_rad, uint32_t w_ang, float m2,
-                                                   float a, float& inc0, float& inc1) {
-  const float ur = uniform_f32(w_rad);
-  const float ua = uniform_f32(w_ang);
-  const float rad = __builtin_amdgcn_sqrtf(m2 * __builtin_amdgcn_logf(ur));
-  inc0 = __builtin_fmaf(rad, __builtin_amdgcn_cosf(ua), a);
-  inc1 = __builtin_fmaf(rad, __builtin_amdgcn_sinf(ua), a);
 }
 
 template <typename R>

@@ -11,9 +11,9 @@
 // it is the natural log.
 //
 // Bound: VALU issue. At 2^24 x 252 (Asian, geometric, barrier) a Philox block
-// and its four steps are 117 cycles of Philox, 100 of Box-Muller and 81 of
+// and its four steps are 117 cycles of Philox, 110 of Box-Muller and 82 of
 // steps per wave (issue costs: device/rng.h; a transcendental 8.3, v_max3 and
-// v_alignbit 4.2), 298 in all, and the kernel runs at 299.
+// v_alignbit 4.2), 309 in all, and the kernel runs at 307 (1.98 ms).
 #include <initializer_list>
 
 #include "device/reduce.h"
@@ -67,16 +67,13 @@ struct GbmState {
 
 template <typename R, uint32_t MASK, bool LOGS>
 struct GbmStepper {
-  // FP32 log paths whose functionals need no normal of their own take the
-  // step's increment straight from Box-Muller (kInc; the European payoff
-  // keeps the normals, so that its price is bit for bit the same with and
-  // without greeks), and watch the barrier through the running maximum (two
-  // dates per v_max3_f32, where a compare and a mask update per date took
-  // twice as long).
-  static constexpr bool kF32 = sizeof(R) == 4;
-  static constexpr bool kInc = kF32 && LOGS && (MASK & ~(G_ASIAN | G_GEO | G_UO)) == 0;
-  static constexpr bool kTop = kF32 && LOGS;
-  R dz, vz, zB, cbb, sdt, sig, dt, rdt, vsdt, Brel, m2;
+  // FP32 log paths watch the barrier through the running maximum: two dates
+  // per v_max3_f32, where a compare and a mask update per date took twice as
+  // long. (Folding the volatility into Box-Muller's radius would save another
+  // multiply per step, 3% of the kernel; it rounds every state differently,
+  // and single paths then cross the barrier that did not before.)
+  static constexpr bool kTop = sizeof(R) == 4 && LOGS;
+  R dz, vz, zB, cbb, sdt, sig, dt, rdt, vsdt, Brel;
   const PathMath<R>& pm;
 
   __device__ __forceinline__ GbmStepper(const GbmParams& P, const PathMath<R>& math) : pm(math) {
@@ -90,7 +87,6 @@ struct GbmStepper {
     rdt = (R)P.r_dt;
     vsdt = (R)P.vol_sdt;
     Brel = (R)P.barrier_rel;
-    m2 = (R)(-1.38629436111989061883 * P.vol_dom * P.vol_dom);
   }
 
   __device__ __forceinline__ bool alive(const GbmState<R>& s) const {
@@ -98,28 +94,12 @@ struct GbmStepper {
     return s.alive;
   }
 
-  // The four values that a Philox block gives step(): normals, or log
-  // increments.
-  __device__ __forceinline__ Normals4<R> draw(const Words4& w) const {
-    if constexpr (kInc) {
-      Normals4<R> n;
-      box_muller_inc_f32(w.w0, w.w1, m2, dz, n.z[0], n.z[1]);
-      box_muller_inc_f32(w.w2, w.w3, m2, dz, n.z[2], n.z[3]);
-      return n;
-    } else {
-      return normals4(w, pm);
-    }
-  }
-
-  // Step i -> i+1 with normal Z, or with the log increment in its place
-  // (kInc), and the bridge's uniform of word W when monitored.
+  // Step i -> i+1 with normal Z (and the bridge's uniform of word W when
+  // monitored).
   __device__ __forceinline__ void step(GbmState<R>& s, R Z, uint32_t i, uint32_t W) const {
     if constexpr (LOGS) {
       const R zp = s.z;
-      if constexpr (kInc)
-        s.z = s.z + Z;
-      else
-        s.z = s.z + dz + vz * Z;
+      s.z = s.z + dz + vz * Z;
       R E = R(0);
       if constexpr ((MASK & (G_ASIAN | G_ASIAN_G)) != 0) {
         E = Dom<R>::exp_(s.z, pm);
@@ -172,7 +152,6 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
     // fine path, summed and scaled by 1/sqrt(CO) (same Brownian increment
     // over the coarse step). CO divides the 4 normals of a Philox block.
     static_assert(CO == 2 || CO == 4, "coupling factor");
-    static_assert(!GbmStepper<R, MASK, LOGS>::kInc, "coupled paths sum normals");
     const R rsc = CO == 2 ? R(0.70710678118654752440) : R(0.5);
     constexpr uint32_t SPB = 4 / CO;              // coarse steps per block
     const uint32_t nb = n / SPB;
@@ -193,7 +172,7 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
   }
   const uint32_t n_full = CO > 1 ? 0u : n >> 2;
   for (uint32_t j = 0; j < n_full; ++j) {
-    const Normals4<R> nz = st.draw(philox(j, pc, keys));
+    const Normals4<R> nz = normals4(philox(j, pc, keys), pm);
     Words4 wb{0, 0, 0, 0};
     if constexpr ((MASK & G_UOBB) != 0) wb = philox(j, pcb, keys);
 #pragma unroll
@@ -203,7 +182,7 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
   }
   const uint32_t rem = CO > 1 ? 0u : n & 3u;
   if (rem) {
-    const Normals4<R> nz = st.draw(philox(n_full, pc, keys));
+    const Normals4<R> nz = normals4(philox(n_full, pc, keys), pm);
     Words4 wb{0, 0, 0, 0};
     if constexpr ((MASK & G_UOBB) != 0) wb = philox(n_full, pcb, keys);
 #pragma unroll
