@@ -688,8 +688,8 @@ def run_heston_adjoint(args, ctx, mc, synth, torch):
     N, n = H["n_paths"], H["n_steps"]
     model = _heston_model(mc, synth)
     f = mc.Payoff(mc.MC_ASIAN_ARITH_CALL, H["K"])
-    o = mc.Options(greeks=mc.MC_GREEK_DELTA | mc.MC_GREEK_VEGA)
-    ms, outs = _repeat(args, torch, lambda: mc.mc_price(ctx, model, f, N, n, synth.SEED, o))
+    ms, outs = _repeat(args, torch,
+                       lambda: mc.mc_greeks_adjoint(ctx, model, f, N, n, synth.SEED))
     r = outs[-1]
     k_ms = sum(x["kernel_ms"] for x in outs) / len(outs)
     per_step = 2 * SLOTS_HESTON + SLOTS_HESTON_REVERSE   # forward, recompute, reverse

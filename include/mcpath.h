@@ -116,7 +116,8 @@ typedef struct {
 
 /* How mc_price computes the requested greeks (Sec. I-A.3).
  *   MC_GREEKS_PATHWISE: derivatives of each path's payoff (forward tangents;
- *     the adjoint for Heston); refused for discontinuous payoffs (barriers).
+ *     for Heston FP32 paths with the derivatives of mc_greeks_adjoint, chained
+ *     forward in FP64); refused for discontinuous payoffs (barriers).
  *   MC_GREEKS_FD_CRN: central finite differences on common random numbers:
  *     the run is repeated with the parameter bumped up and down by the
  *     relative step fd_rel_step on the same paths (same seed, tag and path
@@ -129,9 +130,8 @@ typedef struct {
  *   MC_GREEKS_TANGENT: pathwise derivatives in forward mode. GBM and basket
  *     pathwise greeks are forward tangents already (the same as
  *     MC_GREEKS_PATHWISE); for Heston the tangents of (ln S, v) with respect
- *     to v0 ride along the forward pass instead of the checkpointed reverse
- *     sweep: no checkpoint memory and about half the cost for the two
- *     inputs, in MC_FP32 or MC_FP64 paths. Same payoff restrictions as
+ *     to v0 ride along the forward pass in the precision of the paths,
+ *     MC_FP32 or MC_FP64. Same payoff restrictions as
  *     MC_GREEKS_PATHWISE. */
 typedef enum {
     MC_GREEKS_PATHWISE = 0,

@@ -659,8 +659,13 @@ mc_status heston_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   }
   if (f->cv != MC_CV_NONE) return fail(ctx, MC_ERR_UNSUPPORTED, "control variate not available");
   const bool fp64 = o.prec == MC_FP64;
-  if (o.greeks && o.greeks_method == MC_GREEKS_TANGENT) {
-    // Forward-mode tangents: channels payoff, delta, d/dv0.
+  if (o.greeks) {
+    // Channels payoff, delta, d/dv0: forward-mode tangents in the paths'
+    // precision, or FP32 paths with FP64 derivatives (the pathwise default).
+    const bool tangent = o.greeks_method == MC_GREEKS_TANGENT;
+    if (!tangent && o.workspace && o.workspace_bytes < mc_workspace_bytes(m, f, n_paths, n_steps, &o))
+      return fail(ctx, MC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", o.workspace_bytes,
+                  mc_workspace_bytes(m, f, n_paths, n_steps, &o));
     HestonParams p = heston_params(m, f, n_paths, n_steps, seed, o, o.stream_tag);
     const bool asian = f->kind == MC_ASIAN_ARITH_CALL;
     Moments mom;
@@ -670,17 +675,18 @@ mc_status heston_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
                                    uint32_t* nb) {
                                  p.partials = partials;
                                  p.path_out = path_out;
-                                 return launch_heston_tangent(p, asian, fp64, s, nb);
+                                 return tangent ? launch_heston_tangent(p, asian, fp64, s, nb)
+                                                : launch_heston_pathwise(p, asian, s, nb);
                                },
-                               &mom, &kms, kBlock, kHestonMaxBlocks);
+                               &mom, &kms, kBlock, tangent ? kHestonMaxBlocks : UINT32_MAX);
     if (st != MC_OK) return st;
     mc_result r{};
     double v;
     fill_channel(mom, 0, &r.price, &r.variance, &r.std_err);
     r.plain_price = r.price;
     r.plain_std_err = r.std_err;
-    if (o.greeks & MC_GREEK_DELTA) fill_channel(mom, 1, &r.delta, &v, &r.delta_se);
-    if (o.greeks & MC_GREEK_VEGA) fill_channel(mom, 2, &r.vega, &v, &r.vega_se);
+    if (!tangent || (o.greeks & MC_GREEK_DELTA)) fill_channel(mom, 1, &r.delta, &v, &r.delta_se);
+    if (!tangent || (o.greeks & MC_GREEK_VEGA)) fill_channel(mom, 2, &r.vega, &v, &r.vega_se);
     r.vrf = 1.0;
     r.n_paths = (uint64_t)mom.n;
     r.n_nonfinite = (uint64_t)mom.nonfinite;
@@ -688,23 +694,23 @@ mc_status heston_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     *out = r;
     return MC_OK;
   }
-  if (o.greeks) {
-    return mc_greeks_adjoint(ctx, m, f, n_paths, n_steps, seed, &o, MC_ADJ_FULL, mcp::kCkpt,
-                             nullptr, 0, 1.0, out);
-  }
   HestonParams p = heston_params(m, f, n_paths, n_steps, seed, o, o.stream_tag);
   Moments mom;
   double kms = 0.0;
-  mc_status st = run_moments(ctx, o, n_paths, 2, o.path_values,
+  // Per-path rows (to the host or a sink) hold both payoffs; a price alone
+  // runs only its own.
+  const bool rows = o.path_values != nullptr || ctx->sink != nullptr;
+  const uint32_t mask = rows ? H_EURO | H_ASIAN : f->kind == MC_EURO_CALL ? H_EURO : H_ASIAN;
+  mc_status st = run_moments(ctx, o, n_paths, rows ? 2 : 1, o.path_values,
                              [&](double* partials, double* path_out, hipStream_t s, uint32_t* nb) {
                                p.partials = partials;
                                p.path_out = path_out;
-                               return launch_heston(p, H_EURO | H_ASIAN, fp64, s, nb);
+                               return launch_heston(p, mask, fp64, s, nb);
                              },
                              &mom, &kms, kBlock, kHestonMaxBlocks);
   if (st != MC_OK) return st;
   mc_result r{};
-  const int c = f->kind == MC_EURO_CALL ? 0 : 1;
+  const int c = rows && f->kind != MC_EURO_CALL ? 1 : 0;
   fill_channel(mom, c, &r.price, &r.variance, &r.std_err);
   r.plain_price = r.price;
   r.plain_std_err = r.std_err;

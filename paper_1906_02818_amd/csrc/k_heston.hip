@@ -6,10 +6,14 @@
 // Step i uses normals 2i (Z1, the variance driver) and 2i+1 (Z2), so one
 // Philox block feeds two steps.
 //
-// Two kernels:
+// Kernels:
 //  - heston_price_kernel: European and arithmetic-Asian payoffs fused with
 //    the block moments (Eq. 3); heston_tangent_kernel: the same with
-//    forward-mode delta and d/dv0.
+//    forward-mode delta and d/dv0 in the paths' precision;
+//    heston_pathwise_kernel: FP32 paths with the derivatives in FP64.
+//    Bound by VALU issue: 2^22 x 256 Asian price 1.30 -> 1.19 ms, tangents
+//    1.66 -> 1.45 ms with the round keys in VGPRs and 15 products per block
+//    (device/rng.h).
 //  - heston_adjoint_kernel: pathwise delta and d/dv0 by reverse-mode
 //    differentiation of the simulation (greeks by back-propagation,
 //    Sec. I-A.3). The forward sweep stores (ln S, v) every `every` steps
@@ -32,6 +36,12 @@ struct HDom<float> {
   static __device__ __forceinline__ float exp_(float z, const PathMath<float>&) {
     return __builtin_amdgcn_exp2f(z);
   }
+  // max(x, 0) in one instruction (fmaxf quiets its operand in another).
+  static __device__ __forceinline__ float pos_(float x) {
+    float r;
+    asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(x));
+    return r;
+  }
   static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
   static __device__ __forceinline__ float rsqrt_(float x) { return __builtin_amdgcn_rsqf(x); }
 };
@@ -41,6 +51,7 @@ struct HDom<double> {
   static __device__ __forceinline__ double exp_(double z, const PathMath<double>& pm) {
     return exp_f64(z, pm.t);
   }
+  static __device__ __forceinline__ double pos_(double x) { return x > 0.0 ? x : 0.0; }
   static __device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
   static __device__ __forceinline__ double rsqrt_(double x) { return 1.0 / sqrt(x); }
 };
@@ -64,7 +75,7 @@ struct HestonStep {
   }
 
   __device__ __forceinline__ void step(R& z, R& v, R Z1, R Z2, R& Zs) const {
-    const R vp = v > R(0) ? v : R(0);
+    const R vp = HDom<R>::pos_(v);
     const R sq = HDom<R>::sqrt_(vp * dt);
     Zs = rho * Z1 + rhoc * Z2;
     z = z + (a0 + a1 * vp) + a2 * (sq * Zs);
@@ -88,22 +99,30 @@ __global__ __launch_bounds__(kBlock) void heston_price_kernel(const HestonParams
   acc.zero();
   HestonStep<R> hs;
   hs.init(P);
+  const PhiloxKeys keys = make_keys<sizeof(R) == 4>(P.k0, P.k1);
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   for (uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x; pid < P.n_paths;
        pid += stride) {
     double y[C];
-    const PathCounter pc = make_counter(P.path_offset + pid, P.tag, P.k0, P.k1);
-    R z = R(0), v = (R)P.v0, sumE = R(0), Zs;
     const uint32_t n = P.n_steps;
-    for (uint32_t j = 0; 2 * j < n; ++j) {
-      const Normals4<R> nz = normals4<true>(philox(j, pc), pm);
-      hs.step(z, v, nz.z[0], nz.z[1], Zs);
-      if constexpr ((MASK & H_ASIAN) != 0) sumE += HDom<R>::exp_(z, pm);
-      if (2 * j + 1 < n) {
-        hs.step(z, v, nz.z[2], nz.z[3], Zs);
+    R z = R(0), v = (R)P.v0, sumE = R(0), Zs;
+    const uint64_t path = P.path_offset + pid;
+    with_uniform_high(path, [&](uint32_t hi) {
+      const PathRng pc = make_rng((uint32_t)path, hi, P.tag, keys);
+      auto step = [&](R Z1, R Z2) {
+        hs.step(z, v, Z1, Z2, Zs);
         if constexpr ((MASK & H_ASIAN) != 0) sumE += HDom<R>::exp_(z, pm);
+      };
+      for (uint32_t j = 0; j < n >> 1; ++j) {
+        const Normals4<R> nz = normals4<true>(philox(j, pc, keys), pm);
+        step(nz.z[0], nz.z[1]);
+        step(nz.z[2], nz.z[3]);
       }
-    }
+      if (n & 1u) {
+        const Normals4<R> nz = normals4<true>(philox(n >> 1, pc, keys), pm);
+        step(nz.z[0], nz.z[1]);
+      }
+    });
     const R S0 = (R)P.S0, K = (R)P.K, disc = (R)P.disc;
     int c = 0;
     if constexpr ((MASK & H_EURO) != 0) y[c++] = (double)(disc * posv(S0 * HDom<R>::exp_(z, pm) - K));
@@ -135,12 +154,12 @@ __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonPara
   acc.zero();
   HestonStep<R> hs;
   hs.init(P);
+  const PhiloxKeys keys = make_keys<sizeof(R) == 4>(P.k0, P.k1);
   const R half_dt = R(0.5) * hs.dt;
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   for (uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x; pid < P.n_paths;
        pid += stride) {
     double y[3];
-    const PathCounter pc = make_counter(P.path_offset + pid, P.tag, P.k0, P.k1);
     R z = R(0), v = (R)P.v0, dz = R(0), dv = R(1), sumE = R(0), sumEd = R(0);
     const uint32_t n = P.n_steps;
     auto step = [&](R Z1, R Z2) {
@@ -161,11 +180,19 @@ __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonPara
         sumEd += E * dz;
       }
     };
-    for (uint32_t j = 0; 2 * j < n; ++j) {
-      const Normals4<R> nz = normals4<true>(philox(j, pc), pm);
-      step(nz.z[0], nz.z[1]);
-      if (2 * j + 1 < n) step(nz.z[2], nz.z[3]);
-    }
+    const uint64_t path = P.path_offset + pid;
+    with_uniform_high(path, [&](uint32_t hi) {
+      const PathRng pc = make_rng((uint32_t)path, hi, P.tag, keys);
+      for (uint32_t j = 0; j < n >> 1; ++j) {
+        const Normals4<R> nz = normals4<true>(philox(j, pc, keys), pm);
+        step(nz.z[0], nz.z[1]);
+        step(nz.z[2], nz.z[3]);
+      }
+      if (n & 1u) {
+        const Normals4<R> nz = normals4<true>(philox(n >> 1, pc, keys), pm);
+        step(nz.z[0], nz.z[1]);
+      }
+    });
     // z and dz are in the kernel's log domain (log2 for FP32): d exp(x) =
     // exp(x) dz / scale.
     const double S0 = P.S0, K = P.K, disc = P.disc, inv_sc = 1.0 / HDom<R>::kLogScale;
@@ -189,6 +216,83 @@ __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonPara
   }
   PartSums<3> part = acc.part();
   block_reduce<3, kBlock>(part, P.partials, blockIdx.x);
+}
+
+// Price, delta and d/dv0 of the pathwise route: FP32 state, and per step the
+// two FP32 derivatives of (ln S_{i+1}, v_{i+1}) by v_i that the adjoint kernel
+// forms, chained forward in FP64 (under a violated Feller condition
+// dv_{i+1}/dv_i = 1 - kappa dt + xi Z1 dt / (2 sqrt(v dt)) can reach 10^3 near
+// v = 0, and products of such factors overflow FP32). For the two inputs
+// (S0, v0) the chain is one product and one sum per step, so no state is kept
+// and no step is drawn twice; the products are the reverse sweep's in another
+// association. One path per thread, as in the adjoint.
+//
+// Bound: VALU issue (170 cycles per path-step and wave for the price, 50 more
+// for the derivatives). 2^22 paths x 256 steps, Asian: 2.79 ms by the reverse
+// sweep (forward, recompute, reverse), 1.50 ms here.
+template <bool ASIAN>
+__global__ __launch_bounds__(kBlock) void heston_pathwise_kernel(const HestonParams P) {
+  PathMath<float>::Shared none;
+  const PathMath<float> pm(none);
+  const uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  const bool active = pid < P.n_paths;
+  const PhiloxKeys keys = make_keys<true>(P.k0, P.k1);
+  HestonStep<float> hs;
+  hs.init(P);
+  const float half_dt = 0.5f * hs.dt;
+  const uint32_t n = P.n_steps;
+  float z = 0.f, v = (float)P.v0, sumE = 0.f;
+  double dx = 0.0, dv = 1.0;               // d ln S_i / dv0, dv_i / dv0
+  double sE = 0.0, sEd = 0.0;              // sums of S_i/S0 and of S_i/S0 dx_i
+  const uint64_t path = P.path_offset + pid;
+  if (active)
+    with_uniform_high(path, [&](uint32_t hi) {
+      const PathRng pc = make_rng((uint32_t)path, hi, P.tag, keys);
+      auto step = [&](float Z1, float Z2) {
+        const float vq = v;
+        float Zs;
+        hs.step(z, v, Z1, Z2, Zs);
+        const float g = half_dt * __builtin_amdgcn_rsqf(vq * hs.dt);   // d sqrt(v dt) / dv
+        // The derivatives of v+ are 0 elsewhere.
+        const float a = vq > 0.f ? -half_dt + Zs * g : 0.f;
+        const float b = vq > 0.f ? (1.0f - hs.kdt) + hs.xi * Z1 * g : 1.0f;
+        dx = fma(dv, (double)a, dx);
+        dv *= (double)b;
+        if constexpr (ASIAN) {
+          const float E = __builtin_amdgcn_exp2f(z);
+          sumE += E;
+          sE += (double)E;
+          sEd = fma((double)E, dx, sEd);
+        }
+      };
+      for (uint32_t j = 0; j < n >> 1; ++j) {
+        const Normals4<float> nz = normals4(philox(j, pc, keys));
+        step(nz.z[0], nz.z[1]);
+        step(nz.z[2], nz.z[3]);
+      }
+      if (n & 1u) {
+        const Normals4<float> nz = normals4(philox(n >> 1, pc, keys));
+        step(nz.z[0], nz.z[1]);
+      }
+    });
+  double y[3] = {0.0, 0.0, 0.0};
+  if (active) {
+    const float S0 = (float)P.S0, K = (float)P.K, disc = (float)P.disc, inv_n = 1.0f / (float)n;
+    const float term = ASIAN ? sumE * inv_n : __builtin_amdgcn_exp2f(z);   // A/S0 or S_T/S0
+    y[0] = (double)(disc * posv(S0 * term - K));
+    if (S0 * term > K) {
+      // Asian: dP/d(ln S_i) = disc S_i / n.
+      const double w = ASIAN ? (double)(disc * S0 * inv_n) : (double)(disc * S0 * term);
+      y[1] = w * (ASIAN ? sE : 1.0) / P.S0;
+      y[2] = w * (ASIAN ? sEd : dx);
+    }
+  }
+  const bool finite = isfinite(y[0]) && isfinite(y[1]) && isfinite(y[2]);
+  if (active && P.path_out != nullptr) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) P.path_out[pid * 3 + c] = y[c];
+  }
+  block_moments<3, kBlock>(y, active && finite, active && !finite, P.partials);
 }
 
 // Channel sets of the adjoint phases.
@@ -215,6 +319,7 @@ __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointPar
   const PathMath<R> pm(shared);
   extern __shared__ float s_ck[];
   const HestonParams& P = A.h;
+  const PhiloxKeys keys = make_keys<true>(P.k0, P.k1);
   const uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const bool active = pid < P.n_paths;
   const uint64_t np = P.n_paths;
@@ -233,10 +338,11 @@ __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointPar
   double y[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) y[c] = 0.0;
-  if (active) {
+  const uint64_t path = P.path_offset + pid;
+  if (active) with_uniform_high(path, [&](uint32_t hi) {
     HestonStep<R> hs;
     hs.init(P);
-    const PathCounter pc = make_counter(P.path_offset + pid, P.tag, P.k0, P.k1);
+    const PathRng pc = make_rng((uint32_t)path, hi, P.tag, keys);
     const uint32_t n = P.n_steps, every = A.every;   // every: even, 2..kCkptMax
     const R S0 = (R)P.S0, K = (R)P.K, disc = (R)P.disc, inv_n = R(1) / (R)n;
     R term;  // A/S0 (Asian) or S_T/S0
@@ -248,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointPar
         ck_store(2 * seg + 1, v);
         const uint32_t len = min(every, n - i0);
         for (uint32_t q = 0; q < len; q += 2) {
-          const Normals4<R> nz = normals4<true>(philox((i0 + q) >> 1, pc), pm);
+          const Normals4<R> nz = normals4<true>(philox((i0 + q) >> 1, pc, keys), pm);
           hs.step(z, v, nz.z[0], nz.z[1], Zs);
           if (ASIAN) sumE += HDom<R>::exp_(z, pm);
           if (q + 1 < len) {
@@ -288,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointPar
 #pragma unroll
         for (int q = 0; q < kCkptMax; q += 2) {
           if ((uint32_t)q < len) {
-            const Normals4<R> nz = normals4<true>(philox((i0 + (uint32_t)q) >> 1, pc), pm);
+            const Normals4<R> nz = normals4<true>(philox((i0 + (uint32_t)q) >> 1, pc, keys), pm);
             vs[q] = v;
             z1s[q] = nz.z[0];
             hs.step(z, v, nz.z[0], nz.z[1], zss[q]);
@@ -319,7 +425,7 @@ __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointPar
       y[c0] = xb / (double)P.S0;   // d/dS0 through ln S0
       y[c0 + 1] = vb;              // d/dv0
     }
-  }
+  });
   bool finite = true;
 #pragma unroll
   for (int c = 0; c < C; ++c) finite = finite && isfinite(y[c]);
@@ -341,13 +447,20 @@ hipError_t launch_heston(const HestonParams& p, uint32_t mask, bool fp64, hipStr
                          uint32_t* n_blocks) {
   const uint32_t nb = heston_blocks(p.n_paths);
   *n_blocks = nb;
-  constexpr uint32_t EA = H_EURO | H_ASIAN;
-  if (mask != EA) return hipErrorInvalidValue;
-  if (fp64)
-    hipLaunchKernelGGL((heston_price_kernel<double, EA>), dim3(nb), dim3(kBlock), 0, s, p);
-  else
-    hipLaunchKernelGGL((heston_price_kernel<float, EA>), dim3(nb), dim3(kBlock), 0, s, p);
-  return hipGetLastError();
+#define MCP_HESTON_SET(M)                                                                       \
+  case M:                                                                                       \
+    if (fp64)                                                                                   \
+      hipLaunchKernelGGL((heston_price_kernel<double, M>), dim3(nb), dim3(kBlock), 0, s, p);    \
+    else                                                                                        \
+      hipLaunchKernelGGL((heston_price_kernel<float, M>), dim3(nb), dim3(kBlock), 0, s, p);     \
+    return hipGetLastError();
+  switch (mask) {
+    MCP_HESTON_SET(H_EURO)
+    MCP_HESTON_SET(H_ASIAN)
+    MCP_HESTON_SET(H_EURO | H_ASIAN)
+  }
+#undef MCP_HESTON_SET
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_heston_tangent(const HestonParams& p, bool asian, bool fp64, hipStream_t s,
@@ -366,6 +479,18 @@ hipError_t launch_heston_tangent(const HestonParams& p, bool asian, bool fp64, h
     else
       hipLaunchKernelGGL((heston_tangent_kernel<float, false>), dim3(nb), dim3(kBlock), 0, s, p);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_heston_pathwise(const HestonParams& p, bool asian, hipStream_t s,
+                                  uint32_t* n_blocks) {
+  const uint32_t nb = (uint32_t)((p.n_paths + kBlock - 1) / kBlock);
+  *n_blocks = nb;
+  if (nb == 0) return hipErrorInvalidValue;
+  if (asian)
+    hipLaunchKernelGGL(heston_pathwise_kernel<true>, dim3(nb), dim3(kBlock), 0, s, p);
+  else
+    hipLaunchKernelGGL(heston_pathwise_kernel<false>, dim3(nb), dim3(kBlock), 0, s, p);
   return hipGetLastError();
 }
 

@@ -95,6 +95,11 @@ hipError_t launch_heston(const HestonParams& p, uint32_t mask, bool fp64, hipStr
 hipError_t launch_heston_tangent(const HestonParams& p, bool asian, bool fp64, hipStream_t s,
                                  uint32_t* n_blocks);
 
+// The same channels in FP32 paths with the derivatives chained in FP64: one
+// path per thread.
+hipError_t launch_heston_pathwise(const HestonParams& p, bool asian, hipStream_t s,
+                                  uint32_t* n_blocks);
+
 // Pathwise adjoint (reverse sweep with checkpoints every `every` steps:
 // even, 2..kCkptMax; kCkpt by default). A full (one-launch) sweep with at
 // most kLdsCkpt checkpoints keeps them in LDS (2 kLdsCkpt floats per path,

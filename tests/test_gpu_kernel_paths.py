@@ -155,3 +155,47 @@ def test_sobol_points_at_any_offset(ctx, offset, N):
     o = oracle.basket_qmc(S0, sigma, oracle.cholesky(corr), w, 0.05, 1.0, 90.0, n, N, SEED,
                           0, path0=offset)
     np.testing.assert_allclose(r["path_values"][:, 0], o[:, 0], rtol=1e-4, atol=1e-4)
+
+
+# ------------------------------------------------------------- Heston ----
+H = synth.HESTON
+
+
+def heston():
+    return mc.Model(kind=mc.MC_HESTON, S0=H["S0"], r=H["r"], T=H["T"], v0=H["v0"],
+                    kappa=H["kappa"], theta=H["theta"], xi=H["xi"], rho=H["rho"])
+
+
+@pytest.mark.parametrize("kind", [mc.MC_ASIAN_ARITH_CALL, mc.MC_EURO_CALL])
+@pytest.mark.parametrize("N,n,offset", [(2, 1, 0), (257, 2, 3), (1000, 17, (1 << 32) - 500),
+                                        (300, 259, 0)])
+def test_pathwise_greeks_equal_the_adjoint(ctx, kind, N, n, offset):
+    # The same FP32 state and step derivatives, multiplied forward instead of
+    # backward in FP64: equal to the rounding of at most 2 n products, on the
+    # scale of the largest path (products of factors up to 1e3 near v = 0).
+    print("pathwise = adjoint", kind, N, n, offset, flush=True)
+    f = mc.Payoff(kind, H["K"])
+    a = mc.mc_greeks_adjoint(ctx, heston(), f, N, n, SEED,
+                             mc.Options(path_offset=offset, path_values=True))
+    p = mc.mc_price(ctx, heston(), f, N, n, SEED,
+                    mc.Options(greeks=3, path_offset=offset, path_values=True))
+    assert np.array_equal(p["path_values"][:, 0], a["path_values"][:, 0])
+    for c in (1, 2):
+        x, y = p["path_values"][:, c], a["path_values"][:, c]
+        tol = 4 * n * 2.0 ** -53 * (1.0 + np.abs(y).max())
+        assert np.max(np.abs(x - y)) <= tol, c
+    assert p["greeks_method"] == mc.MC_GREEKS_PATHWISE
+
+
+@pytest.mark.parametrize("prec", [mc.MC_FP32, mc.MC_FP64])
+@pytest.mark.parametrize("N,n", [(2, 1), (300, 2), (1025, 7)])
+def test_heston_payoff_of_its_own_prices_like_rows(ctx, prec, N, n):
+    # A price without rows runs its payoff alone: the same paths, so the mean
+    # of the rows to FP64 rounding.
+    for kind, name in ((mc.MC_EURO_CALL, "euro"), (mc.MC_ASIAN_ARITH_CALL, "asian")):
+        f = mc.Payoff(kind, 97.0)
+        r = mc.mc_price(ctx, heston(), f, N, n, SEED, mc.Options(prec=prec))
+        v = mc.mc_price(ctx, heston(), f, N, n, SEED, mc.Options(prec=prec, path_values=True))
+        col = v["path_values"][:, v["path_channels"].index(name)]
+        assert abs(r["price"] - col.mean()) <= 1e-13 * N * (1.0 + abs(col.mean()))
+        assert r["price"] == v["price"] and r["std_err"] == v["std_err"]
