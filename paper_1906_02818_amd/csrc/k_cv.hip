@@ -291,6 +291,35 @@ struct HestonF {
   }
 };
 
+// Takes a path through its hedge segments of m steps: open(i) at each
+// segment's first date i, step(i, Z1, Z2) for each step and close() after a
+// segment's last, with words(j) the path's Philox block j. A Philox block feeds two steps; with odd m a segment may
+// begin on a block's second half.
+template <typename Words, typename Open, typename Step, typename Close>
+__device__ __forceinline__ void walk_segments(uint32_t n, uint32_t m, Words&& words, Open&& open,
+                                              Step&& step, Close&& close) {
+  Normals4<float> nz = {{0.f, 0.f, 0.f, 0.f}};
+  for (uint32_t i0 = 0; i0 < n; i0 += m) {
+    open(i0);
+    const uint32_t end = n - i0 < m ? n : i0 + m;
+    uint32_t i = i0;
+    if (i & 1u) {
+      step(i, nz.z[2], nz.z[3]);
+      ++i;
+    }
+    for (; i + 1 < end; i += 2) {
+      nz = normals4(words(i >> 1));
+      step(i, nz.z[0], nz.z[1]);
+      step(i + 1, nz.z[2], nz.z[3]);
+    }
+    if (i < end) {
+      nz = normals4(words(i >> 1));
+      step(i, nz.z[0], nz.z[1]);
+    }
+    close();
+  }
+}
+
 // The forward pass when only Delta is needed (evaluation and the training
 // forward): layer 1's activations go straight into layer 2's B operands, so
 // they are held in the operand type (BF16 pairs) rather than as FP32 values,
@@ -350,29 +379,31 @@ __global__ __launch_bounds__(kCvThreads) void cv_cache_kernel(const CvParams P) 
   const HestonF c(Hp);
   const uint32_t n = Hp.n_steps, m = P.hedge_every;
   const uint64_t S = P.c_stride;
-  const PathCounter pc = make_counter(Hp.path_offset + pid, Hp.tag, Hp.k0, Hp.k1);
+  const PhiloxKeys keys = make_keys<true>(Hp.k0, Hp.k1);
+  const uint64_t path = Hp.path_offset + pid;
   float z = 0.f, v = (float)Hp.v0, sumE = 0.f, st_open = 0.f, Et = 1.f;
-  uint32_t k = 0;
-  Normals4<float> nz;
-  for (uint32_t i = 0; i < n; ++i) {
-    if (i % m == 0) {
-      float f[4];
-      c.features(i, z, v, sumE, f);
+  with_uniform_high(path, [&](uint32_t hi) {
+    const PathRng pc = make_rng((uint32_t)path, hi, Hp.tag, keys);
+    uint32_t k = 0;
+    walk_segments(
+        n, m, [&](uint32_t j) { return philox(j, pc, keys); },
+        [&](uint32_t i) {
+          float f[4];
+          c.features(i, z, v, sumE, f);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) P.c_phi[((size_t)k * 4 + q) * S + pid] = f[q];
-      st_open = Et;
-    }
-    if ((i & 1) == 0) nz = normals4(philox(i >> 1, pc));
-    const float Z1 = (i & 1) ? nz.z[2] : nz.z[0];
-    const float Z2 = (i & 1) ? nz.z[3] : nz.z[1];
-    c.step(z, v, Z1, Z2);
-    Et = __builtin_amdgcn_exp2f(z);
-    sumE += Et * P.dfac[i + 1];
-    if ((i + 1) % m == 0 || i + 1 == n) {
-      P.c_dst[(size_t)k * S + pid] = c.S0 * (Et - st_open);
-      ++k;
-    }
-  }
+          for (int q = 0; q < 4; ++q) P.c_phi[((size_t)k * 4 + q) * S + pid] = f[q];
+          st_open = Et;
+        },
+        [&](uint32_t i, float Z1, float Z2) {
+          c.step(z, v, Z1, Z2);
+          Et = __builtin_amdgcn_exp2f(z);
+          sumE += Et * P.dfac[i + 1];
+        },
+        [&] {
+          P.c_dst[(size_t)k * S + pid] = c.S0 * (Et - st_open);
+          ++k;
+        });
+  });
   const double A = (double)c.S0 * (double)sumE / (double)n;
   P.c_pay[pid] = Hp.disc * (A > Hp.K ? A - Hp.K : 0.0);
 }
@@ -792,6 +823,12 @@ __global__ __launch_bounds__(kCvThreads) void cv_bwd_kernel_fp32(const CvParams 
   cv_bwd_body<false>(P);
 }
 
+// Bound: VALU issue plus the MFMAs that do not overlap it (per wave and date 20
+// MFMAs of 35 cycles beside 3300 of activations; per step 170, device/rng.h).
+// 2^21 paths x 256 steps, a date every 16 steps, in bfloat16: 1.57 -> 1.45 ms
+// with the segment loops in place of a division of the step index by m on
+// every step, and the uniform Philox blocks.
+//
 // Evaluation kernel, 64 paths per wave: lane l follows its own path, and
 // at each rebalancing date the network runs twice, for the sub-tiles of
 // paths 0..31 and 32..63 of the wave. Layer 1 takes its features from half 0
@@ -828,40 +865,57 @@ __global__ __launch_bounds__(kCvThreads) void cv_eval_kernel(const CvParams P) {
   const uint32_t n = Hp.n_steps, m = P.hedge_every;
   const uint64_t pid = ((uint64_t)blockIdx.x * kCvWaves + wave) * 64 + lane;
   const bool active = pid < Hp.n_paths;
-  const PathCounter pc = make_counter(Hp.path_offset + pid, Hp.tag, Hp.k0, Hp.k1);
+  const PhiloxKeys keys = make_keys<true>(Hp.k0, Hp.k1);
 
+  // The network takes all 64 lanes at each rebalancing date, so the wave
+  // walks the dates together; only a block's words depend on the high word
+  // of the path index, which two lanes of a wave hold differently where it
+  // straddles a multiple of 2^32 (then both forms are drawn).
+  const uint64_t path = Hp.path_offset + pid;
+  const uint32_t lo = (uint32_t)path;
+  const uint32_t lo0 = (uint32_t)__builtin_amdgcn_readfirstlane(lo);
+  const uint32_t hi0 = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(path >> 32));
+  const bool wrapped = lo < lo0;
+  const bool straddle = __ballot(wrapped) != 0ull;
+  const PathRng rng0 = make_rng(lo, hi0, Hp.tag, keys), rng1 = make_rng(lo, hi0 + 1u, Hp.tag, keys);
   float z = 0.f, v = (float)Hp.v0, sumE = 0.f, H = 0.f, delta = 0.f, st_open = 0.f, Et = 1.f;
-  Normals4<float> nz;
-  for (uint32_t i = 0; i < n; ++i) {
-    if (i % m == 0) {
-      float own[4];
-      c.features(i, z, v, sumE, own);
-      float other[4];
-#pragma unroll
-      for (int f = 0; f < 4; ++f) other[f] = __shfl_xor(own[f], 32, 64);
-#pragma unroll 1
-      for (int sub = 0; sub < 2; ++sub) {
-        float phi[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) phi[j] = 0.f;
-        if (half == 0) {
-#pragma unroll
-          for (int f = 0; f < 4; ++f) phi[f] = sub == 0 ? own[f] : other[f];
-          phi[4] = 1.0f;
+  walk_segments(
+      n, m,
+      [&](uint32_t j) {
+        Words4 w = philox(j, rng0, keys);
+        if (straddle) {
+          const Words4 w1 = philox(j, rng1, keys);
+          if (wrapped) w = w1;
         }
-        const float d = mlp_delta<BF16>(phi, w1a, s_w2f, s_lanec, lane, c3);
-        if (sub == half) delta = d;
-      }
-      st_open = Et;
-    }
-    if ((i & 1) == 0) nz = normals4(philox(i >> 1, pc));
-    const float Z1 = (i & 1) ? nz.z[2] : nz.z[0];
-    const float Z2 = (i & 1) ? nz.z[3] : nz.z[1];
-    c.step(z, v, Z1, Z2);
-    Et = __builtin_amdgcn_exp2f(z);
-    sumE += Et * P.dfac[i + 1];
-    if ((i + 1) % m == 0 || i + 1 == n) H = __builtin_fmaf(delta, S0 * (Et - st_open), H);
-  }
+        return w;
+      },
+      [&](uint32_t i) {
+        float own[4];
+        c.features(i, z, v, sumE, own);
+        float other[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) other[f] = __shfl_xor(own[f], 32, 64);
+#pragma unroll 1
+        for (int sub = 0; sub < 2; ++sub) {
+          float phi[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) phi[j] = 0.f;
+          if (half == 0) {
+#pragma unroll
+            for (int f = 0; f < 4; ++f) phi[f] = sub == 0 ? own[f] : other[f];
+            phi[4] = 1.0f;
+          }
+          const float d = mlp_delta<BF16>(phi, w1a, s_w2f, s_lanec, lane, c3);
+          if (sub == half) delta = d;
+        }
+        st_open = Et;
+      },
+      [&](uint32_t i, float Z1, float Z2) {
+        c.step(z, v, Z1, Z2);
+        Et = __builtin_amdgcn_exp2f(z);
+        sumE += Et * P.dfac[i + 1];
+      },
+      [&] { H = __builtin_fmaf(delta, S0 * (Et - st_open), H); });
   double y[3] = {0.0, 0.0, 0.0};
   if (active) {
     const double A = (double)S0 * (double)sumE / (double)n;

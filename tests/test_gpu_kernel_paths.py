@@ -199,3 +199,21 @@ def test_heston_payoff_of_its_own_prices_like_rows(ctx, prec, N, n):
         col = v["path_values"][:, v["path_channels"].index(name)]
         assert abs(r["price"] - col.mean()) <= 1e-13 * N * (1.0 + abs(col.mean()))
         assert r["price"] == v["price"] and r["std_err"] == v["std_err"]
+
+
+@pytest.mark.parametrize("m_every,N,n,offset", [(1, 130, 3, (1 << 32) - 40), (3, 70, 10, 7),
+                                                (5, 65, 5, (1 << 33) - 64), (7, 129, 6, 0),
+                                                (2, 300, 9, (1 << 32) - 257)])
+def test_learned_cv_segments_and_straddles(ctx, m_every, N, n, offset):
+    # Segments that begin on either half of a Philox block, a last segment cut
+    # short, waves that straddle a multiple of 2^32; tolerances of the FP32
+    # evaluation against the oracle.
+    print("cv segments", m_every, N, n, offset, flush=True)
+    th = (synth.glorot_mlp() + np.random.default_rng(3).normal(0.0, 0.05, 4545)).astype(np.float32)
+    r = mc.mc_price(ctx, heston(), mc.Payoff(mc.MC_ASIAN_ARITH_CALL, H["K"], cv=mc.MC_CV_LEARNED),
+                    N, n, SEED, mc.Options(cv_weights=th, cv_hedge_every=m_every, cv_beta=1.0,
+                                           path_offset=offset, path_values=True))
+    o = oracle.heston_cv(H, n, th.astype(np.float64), N, SEED, path0=offset, m_every=m_every)
+    pv = r["path_values"]
+    np.testing.assert_allclose(pv[:, 0], o[:, 0], rtol=3e-4, atol=3e-4)
+    assert np.abs(pv[:, 1] - o[:, 1]).max() < 2e-3 * (1 + np.abs(o[:, 1]).max())
