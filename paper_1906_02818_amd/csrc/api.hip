@@ -24,9 +24,13 @@ struct mc_context {
   hipStream_t stream = nullptr;
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  double* pinned = nullptr;      // host staging for moments
+  double* pinned = nullptr;      // host memory the reductions write to
   size_t pinned_count = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  // Start stamps of a run's path kernel and of its reduction, on the device's
+  // constant clock (host memory the kernels write), and that clock's rate.
+  uint64_t* clock = nullptr;
+  double clock_khz = 0.0;
   std::string err;
   // Multilevel runs: when `sink` is set, run_moments writes the per-path
   // values there (device) instead of returning them to the host; `coarsen`
@@ -53,11 +57,10 @@ struct mc_context {
   std::vector<hipEvent_t> lsm_ev;
   // Allocation-free calls (mc_price_noalloc): while `noalloc` is set, every
   // device buffer of the call comes from this device's static scratch array
-  // (address from hipGetSymbolAddress at mc_create) and the reduced moments
-  // come back into host_mom instead of pinned memory.
+  // (address from hipGetSymbolAddress at mc_create); the reduced moments come
+  // back through the pinned memory of mc_create.
   void* scratch = nullptr;
   bool noalloc = false;
-  double host_mom[256] = {};
 };
 
 // Device scratch of the allocation-free entry point: the block moment
@@ -70,6 +73,8 @@ static __device__ __align__(256) unsigned char scratch[MC_NOALLOC_SCRATCH_BYTES]
 namespace {
 
 using namespace mcp;
+
+constexpr size_t kClockStamps = 256;
 
 constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
@@ -341,6 +346,11 @@ mc_status get_pinned(mc_context* ctx, size_t count) {
   return MC_OK;
 }
 
+// Milliseconds between two stamps of the last run (after its synchronisation).
+double clock_ms(const mc_context* ctx, int from, int to) {
+  return (double)(ctx->clock[to] - ctx->clock[from]) / ctx->clock_khz;
+}
+
 hipStream_t stream_of(mc_context* ctx, const mc_options& o) {
   return o.hip_stream ? (hipStream_t)o.hip_stream : ctx->stream;
 }
@@ -415,33 +425,26 @@ mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, in
   char* base = nullptr;
   mc_status st = get_ws(ctx, o, L.bytes, &base);
   if (st != MC_OK) return st;
-  double* hmom = ctx->host_mom;
-  if (!ctx->noalloc) {
-    st = get_pinned(ctx, L.n_mom);
-    if (st != MC_OK) return st;
-    hmom = ctx->pinned;
-  } else if (host_path_values || ctx->sink) {
+  if (ctx->noalloc && (host_path_values || ctx->sink))
     return fail(ctx, MC_ERR_UNSUPPORTED, "mc_price_noalloc writes no per-path values");
-  }
+  st = get_pinned(ctx, L.n_mom);           // holds any run's moments since mc_create
+  if (st != MC_OK) return st;
+  // The merge writes the moments to host memory itself: a copy after it is a
+  // launch of its own.
+  double* hmom = ctx->pinned;
   hipStream_t s = stream_of(ctx, o);
   double* partials = (double*)base;
-  double* mom = (double*)(base + L.off_mom);
   double* path_out =
       ctx->sink ? ctx->sink : (host_path_values ? (double*)(base + L.off_path) : nullptr);
-  HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
   uint32_t nb = 0;
   HIP_TRY(ctx, launch(partials, path_out, s, &nb));
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
   if (nb == 0 || nb > L.n_blocks) return fail(ctx, MC_ERR_DEVICE, "block count mismatch");
-  HIP_TRY(ctx, launch_final_merge(partials, nb, (uint32_t)C, 1, mom, s));
-  HIP_TRY(ctx, hipMemcpyAsync(hmom, mom, L.n_mom * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIP_TRY(ctx, launch_final_merge(partials, nb, (uint32_t)C, 1, hmom, s, ctx->clock + 1));
   if (host_path_values && !ctx->sink)
     HIP_TRY(ctx, hipMemcpyAsync(host_path_values, path_out, n_paths * C * sizeof(double),
                                 hipMemcpyDeviceToHost, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
-  float ms = 0.f;
-  HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
-  if (kernel_ms) *kernel_ms += ms;
+  if (kernel_ms) *kernel_ms += clock_ms(ctx, 0, 1);
   out->C = C;
   out->n = hmom[0];
   out->nonfinite = hmom[1];
@@ -554,6 +557,7 @@ mc_status gbm_run(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64
                      [&](double* partials, double* path_out, hipStream_t s, uint32_t* nb) {
                        p.partials = partials;
                        p.path_out = path_out;
+                       p.clock = ctx->clock;
                        return launch_gbm(p, mask, fp64, s, nb);
                      },
                      mom, kernel_ms, kBlock, kGbmMaxBlocks);
@@ -675,6 +679,7 @@ mc_status heston_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
                                    uint32_t* nb) {
                                  p.partials = partials;
                                  p.path_out = path_out;
+                                 p.clock = ctx->clock;
                                  return tangent ? launch_heston_tangent(p, asian, fp64, s, nb)
                                                 : launch_heston_pathwise(p, asian, s, nb);
                                },
@@ -705,6 +710,7 @@ mc_status heston_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
                              [&](double* partials, double* path_out, hipStream_t s, uint32_t* nb) {
                                p.partials = partials;
                                p.path_out = path_out;
+                               p.clock = ctx->clock;
                                return launch_heston(p, mask, fp64, s, nb);
                              },
                              &mom, &kms, kBlock, kHestonMaxBlocks);
@@ -802,6 +808,7 @@ mc_status cv_eval(mc_context* ctx, const mc_options& o, const CvParams& base, ui
                      [&](double* partials, double* path_out, hipStream_t s, uint32_t* nb) {
                        p.partials = partials;
                        p.path_out = path_out;
+                       p.h.clock = ctx->clock;
                        return launch_cv_price(p, s, nb);
                      },
                      mom, kms, kCvPathsPerBlock);
@@ -1208,6 +1215,7 @@ mc_status basket_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
                    [&](double* partials, double* path_out, hipStream_t ss, uint32_t* nb) {
                      p.partials = partials;
                      p.path_out = path_out;
+                     p.clock = ctx->clock;
                      return launch_basket(p, prec, ss, nb);
                    },
                    &mom, &kms, kBasketTile, kBasketMaxBlocks);
@@ -1366,14 +1374,13 @@ mc_status fd_greek(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint6
   const uint32_t M = (uint32_t)n_moments(3);
   const size_t bytes_p = align256((size_t)kDiffMaxBlocks * M * sizeof(double));
   char* base = nullptr;
-  st = get_mlmc_buf(ctx, 2 * bytes_a + bytes_p + align256(M * sizeof(double)), &base);
+  st = get_mlmc_buf(ctx, 2 * bytes_a + bytes_p, &base);
   if (st != MC_OK) return st;
   st = get_pinned(ctx, M);
   if (st != MC_OK) return st;
   double* A = (double*)base;
   double* B = (double*)(base + bytes_a);
   double* partials = (double*)(base + 2 * bytes_a);
-  double* mom = (double*)(base + 2 * bytes_a + bytes_p);
   double acc[n_moments(3)] = {};
   for (uint64_t p0 = 0; p0 < n_paths; p0 += chunk) {
     const uint64_t nc = n_paths - p0 < chunk ? n_paths - p0 : chunk;
@@ -1393,8 +1400,7 @@ mc_status fd_greek(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint6
     }
     uint32_t nb = 0;
     HIP_TRY(ctx, launch_diff_moments(A, C, ch, B, C, ch, nc, partials, s, &nb));
-    HIP_TRY(ctx, launch_final_merge(partials, nb, 3, 1, mom, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, mom, M * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, launch_final_merge(partials, nb, 3, 1, ctx->pinned, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
     merge_moment_vec(acc, ctx->pinned, 3);
   }
@@ -1459,10 +1465,20 @@ mc_status mc_create(mc_context** out, int device) {
   if (hipSetDevice(device) != hipSuccess || hipStreamCreate(&ctx->stream) != hipSuccess ||
       hipEventCreate(&ctx->ev0) != hipSuccess || hipEventCreate(&ctx->ev1) != hipSuccess ||
       hipEventCreate(&ctx->ev2) != hipSuccess || hipEventCreate(&ctx->ev3) != hipSuccess ||
-      scratch_address(device, &ctx->scratch) != hipSuccess) {
+      scratch_address(device, &ctx->scratch) != hipSuccess ||
+      hipHostMalloc((void**)&ctx->clock, kClockStamps * sizeof(uint64_t), hipHostMallocDefault) !=
+          hipSuccess ||
+      get_pinned(ctx, 1) != MC_OK) {
     mc_destroy(ctx);
     return MC_ERR_DEVICE;
   }
+  int khz = 0;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0) {
+    mc_destroy(ctx);
+    return MC_ERR_DEVICE;
+  }
+  ctx->clock_khz = (double)khz;
+  std::memset(ctx->clock, 0, kClockStamps * sizeof(uint64_t));
   *out = ctx;
   return MC_OK;
 }
@@ -1474,6 +1490,7 @@ mc_status mc_destroy(mc_context* ctx) {
   if (ctx->mlmc_buf) (void)hipFree(ctx->mlmc_buf);
   if (ctx->qmc_buf) (void)hipFree(ctx->qmc_buf);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->clock) (void)hipHostFree(ctx->clock);
   if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
   if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
   if (ctx->ev2) (void)hipEventDestroy(ctx->ev2);
@@ -1785,14 +1802,13 @@ mc_status mc_price_mlmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, 
     const uint32_t M = (uint32_t)n_moments(3);
     const size_t bytes_p = align256((size_t)kDiffMaxBlocks * M * sizeof(double));
     char* base = nullptr;
-    st = get_mlmc_buf(ctx, bytes_a + bytes_b + bytes_p + align256(M * sizeof(double)), &base);
+    st = get_mlmc_buf(ctx, bytes_a + bytes_b + bytes_p, &base);
     if (st != MC_OK) return st;
     st = get_pinned(ctx, M);
     if (st != MC_OK) return st;
     double* A = (double*)base;
     double* B = (double*)(base + bytes_a);
     double* partials = (double*)(base + bytes_a + bytes_b);
-    double* mom = (double*)(base + bytes_a + bytes_b + bytes_p);
     double acc[n_moments(3)] = {};
     double kms = 0.0;
     for (uint64_t p0 = 0; p0 < lv.n_paths; p0 += chunk) {
@@ -1818,9 +1834,8 @@ mc_status mc_price_mlmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, 
       uint32_t nb = 0;
       HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
       HIP_TRY(ctx, launch_diff_moments(A, Ca, ca, B, Cb, cb, nc, partials, s, &nb));
-      HIP_TRY(ctx, launch_final_merge(partials, nb, 3, 1, mom, s));
+      HIP_TRY(ctx, launch_final_merge(partials, nb, 3, 1, ctx->pinned, s));
       HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-      HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, mom, M * sizeof(double), hipMemcpyDeviceToHost, s));
       HIP_TRY(ctx, hipStreamSynchronize(s));
       float ms = 0.f;
       HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
@@ -1941,33 +1956,26 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     const RunLayout Lay = basket_layout(n_points, 3, false);
     const size_t b_shift = align256((size_t)n_replicates * dims * sizeof(uint32_t));
     const size_t b_part = align256((size_t)n_replicates * Lay.n_mom * Lay.n_blocks * sizeof(double));
-    const size_t b_mom = align256((size_t)n_replicates * Lay.n_mom * sizeof(double));
     char* base = nullptr;
-    st = get_mlmc_buf(ctx, b_shift + b_part + b_mom, &base);
+    st = get_mlmc_buf(ctx, b_shift + b_part, &base);
     if (st != MC_OK) return st;
     st = get_pinned(ctx, (size_t)n_replicates * Lay.n_mom);
     if (st != MC_OK) return st;
     uint32_t* shifts = (uint32_t*)base;
     double* parts = (double*)(base + b_shift);
-    double* moms = (double*)(base + b_shift + b_part);
-    HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
     HIP_TRY(ctx, launch_qmc_shifts((uint32_t)seed, (uint32_t)(seed >> 32), o0.stream_tag + 6u, 0,
                                    n_replicates, dims, shifts, s));
     p.qshift = shifts;
     p.q_dims = dims;
     p.partials = parts;
     p.path_out = nullptr;
+    p.clock = ctx->clock;
     uint32_t nb = 0;
     HIP_TRY(ctx, launch_basket_qmc_batch(p, prec, n_replicates, s, &nb));
     if (nb == 0 || nb > Lay.n_blocks) return fail(ctx, MC_ERR_DEVICE, "block count mismatch");
-    HIP_TRY(ctx, launch_final_merge(parts, nb, 3, n_replicates, moms, s));
-    HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, moms, (size_t)n_replicates * Lay.n_mom * 8,
-                                hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, launch_final_merge(parts, nb, 3, n_replicates, ctx->pinned, s, ctx->clock + 1));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    float ms = 0.f;
-    HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
-    r.kernel_ms = ms;
+    r.kernel_ms = clock_ms(ctx, 0, 1);
     for (uint32_t rep = 0; rep < n_replicates; ++rep) {
       // Moments: [n_valid, n_nonfinite, mean basket, mean geometric, ...].
       const double* mr = ctx->pinned + (size_t)rep * Lay.n_mom;
@@ -2160,6 +2168,7 @@ mc_status mc_greeks_adjoint(mc_context* ctx, const mc_model* m, const mc_payoff*
                    [&](double* partials, double* path_out, hipStream_t s, uint32_t* nb) {
                      a.h.partials = partials;
                      a.h.path_out = path_out;
+                     a.h.clock = ctx->clock;
                      return launch_heston_adjoint(a, s, nb);
                    },
                    &mom, &kms);

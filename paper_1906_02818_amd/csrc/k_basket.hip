@@ -163,6 +163,7 @@ __device__ __forceinline__ uint32_t row_block(uint32_t set, uint32_t i) {
 // RPW: 16-row blocks per wave (d <= 4 W RPW).
 template <int PREC, bool PORT, bool QMC, int W, int RPW>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) void basket_kernel(const BasketParams P) {
+  stamp(P.clock);
   typedef Form<PREC> F;
   typedef typename F::V V8;
   constexpr int SETS = W / 4, C = PORT ? 1 : 3;

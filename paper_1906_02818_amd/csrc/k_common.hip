@@ -44,7 +44,8 @@ constexpr int merge_threads() { return 256; }
 template <int C>
 __global__ __launch_bounds__(merge_threads<C>()) void final_merge_kernel(
     const double* __restrict__ partials, uint32_t n_blocks, uint32_t stride,
-    double* __restrict__ out) {
+    double* __restrict__ out, uint64_t* __restrict__ clock) {
+  stamp(clock);
   constexpr int M = PartSums<C>::M, NT = merge_threads<C>();
   partials += (size_t)blockIdx.x * n_blocks * M;
   PartSums<C> m;
@@ -63,7 +64,8 @@ constexpr uint32_t kMergeChunk = 2048;
 
 template <int C>
 __global__ __launch_bounds__(merge_threads<C>()) void chunk_merge_kernel(
-    double* __restrict__ partials, uint32_t n_blocks) {
+    double* __restrict__ partials, uint32_t n_blocks, uint64_t* __restrict__ clock) {
+  stamp(clock);
   constexpr int M = PartSums<C>::M, NT = merge_threads<C>();
   const uint32_t first = blockIdx.x * kMergeChunk;
   const uint32_t count = min(kMergeChunk, n_blocks - first);
@@ -163,33 +165,33 @@ hipError_t launch_diff_moments(const double* a, uint32_t Ca, uint32_t ca, const 
 // chunk heads are overwritten.
 template <int C>
 static hipError_t merge_one(double* partials, uint32_t n_blocks, uint32_t n_batch,
-                            double* out, hipStream_t s) {
+                            double* out, hipStream_t s, uint64_t* clock) {
   if (n_batch == 1 && n_blocks > 2 * kMergeChunk) {
     const uint32_t n_chunks = (n_blocks + kMergeChunk - 1) / kMergeChunk;
     hipLaunchKernelGGL(chunk_merge_kernel<C>, dim3(n_chunks), dim3(merge_threads<C>()), 0, s,
-                       partials, n_blocks);
+                       partials, n_blocks, clock);
     hipLaunchKernelGGL(final_merge_kernel<C>, dim3(1), dim3(merge_threads<C>()), 0, s, partials,
-                       n_chunks, kMergeChunk, out);
+                       n_chunks, kMergeChunk, out, nullptr);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(final_merge_kernel<C>, dim3(n_batch), dim3(merge_threads<C>()), 0, s,
-                     partials, n_blocks, 1u, out);
+                     partials, n_blocks, 1u, out, clock);
   return hipGetLastError();
 }
 
 hipError_t launch_final_merge(double* partials, uint32_t n_blocks, uint32_t C,
-                              uint32_t n_batch, double* out, hipStream_t s) {
+                              uint32_t n_batch, double* out, hipStream_t s, uint64_t* clock) {
   if (n_blocks == 0 || n_batch == 0 || n_batch > 65535) return hipErrorInvalidValue;
   switch (C) {
-    case 1: return merge_one<1>(partials, n_blocks, n_batch, out, s);
-    case 2: return merge_one<2>(partials, n_blocks, n_batch, out, s);
-    case 3: return merge_one<3>(partials, n_blocks, n_batch, out, s);
-    case 4: return merge_one<4>(partials, n_blocks, n_batch, out, s);
-    case 5: return merge_one<5>(partials, n_blocks, n_batch, out, s);
-    case 6: return merge_one<6>(partials, n_blocks, n_batch, out, s);
-    case 7: return merge_one<7>(partials, n_blocks, n_batch, out, s);
-    case 8: return merge_one<8>(partials, n_blocks, n_batch, out, s);
-    case 9: return merge_one<9>(partials, n_blocks, n_batch, out, s);
+    case 1: return merge_one<1>(partials, n_blocks, n_batch, out, s, clock);
+    case 2: return merge_one<2>(partials, n_blocks, n_batch, out, s, clock);
+    case 3: return merge_one<3>(partials, n_blocks, n_batch, out, s, clock);
+    case 4: return merge_one<4>(partials, n_blocks, n_batch, out, s, clock);
+    case 5: return merge_one<5>(partials, n_blocks, n_batch, out, s, clock);
+    case 6: return merge_one<6>(partials, n_blocks, n_batch, out, s, clock);
+    case 7: return merge_one<7>(partials, n_blocks, n_batch, out, s, clock);
+    case 8: return merge_one<8>(partials, n_blocks, n_batch, out, s, clock);
+    case 9: return merge_one<9>(partials, n_blocks, n_batch, out, s, clock);
   }
   return hipErrorInvalidValue;
 }
@@ -201,7 +203,7 @@ hipError_t launch_final_reduce(const double* partials, uint32_t n_blocks, uint32
 }
 
 hipError_t launch_final_reduce_batch(const double* partials, uint32_t n_blocks, uint32_t n_mom,
-                                     uint32_t n_batch, double* out, hipStream_t s) {
+                                     uint32_t n_batch, double* out, hipStream_t s, uint64_t* clock) {
   if (n_blocks == 0 || n_mom == 0 || n_batch == 0 || n_batch > 65535) return hipErrorInvalidValue;
   hipLaunchKernelGGL(final_reduce_kernel, dim3(n_mom, n_batch), dim3(256), 0, s, partials,
                      n_blocks, out);

@@ -838,6 +838,7 @@ __global__ __launch_bounds__(kCvThreads) void cv_bwd_kernel_fp32(const CvParams 
 // same function the training kernel evaluates.
 template <bool BF16>
 __global__ __launch_bounds__(kCvThreads) void cv_eval_kernel(const CvParams P) {
+  stamp(P.h.clock);
   using FT = FragT<BF16>;
   __shared__ __attribute__((aligned(16))) FT s_w2f[kFragFloats];
   __shared__ __attribute__((aligned(16))) float s_lanec[kLaneFloats];

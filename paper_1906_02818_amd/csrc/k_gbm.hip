@@ -226,6 +226,7 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
 // their moments in FP64 registers, so each block writes one moment vector.
 template <typename R, uint32_t MASK, bool LOGS, uint32_t CO>
 __global__ __launch_bounds__(kBlock) void gbm_path_kernel(const GbmParams P) {
+  stamp(P.clock);
   constexpr int C = gbm_channels(MASK);
   __shared__ typename PathMath<R>::Shared shared;
   const PathMath<R> pm(shared);

@@ -92,6 +92,7 @@ __device__ __forceinline__ R posv(R x) {
 // paths pid, pid + stride, ... and keeps their moments in registers.
 template <typename R, uint32_t MASK>
 __global__ __launch_bounds__(kBlock) void heston_price_kernel(const HestonParams P) {
+  stamp(P.clock);
   constexpr int C = popcount_c(MASK);
   __shared__ typename PathMath<R>::Shared shared;
   const PathMath<R> pm(shared);
@@ -148,6 +149,7 @@ __global__ __launch_bounds__(kBlock) void heston_price_kernel(const HestonParams
 // European (ASIAN = false) or arithmetic-Asian call.
 template <typename R, bool ASIAN>
 __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonParams P) {
+  stamp(P.clock);
   __shared__ typename PathMath<R>::Shared shared;
   const PathMath<R> pm(shared);
   ThreadSums<3> acc;
@@ -232,6 +234,7 @@ __global__ __launch_bounds__(kBlock) void heston_tangent_kernel(const HestonPara
 // sweep (forward, recompute, reverse), 1.50 ms here.
 template <bool ASIAN>
 __global__ __launch_bounds__(kBlock) void heston_pathwise_kernel(const HestonParams P) {
+  stamp(P.clock);
   PathMath<float>::Shared none;
   const PathMath<float> pm(none);
   const uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -314,6 +317,7 @@ struct AdjC<2> { static constexpr int C = 2; };   // delta, d/dv0
 // built: its state is FP32, so the checkpoints are exact.
 template <typename R, int PHASE, bool ASIAN, bool LDS>
 __global__ __launch_bounds__(kBlock) void heston_adjoint_kernel(const AdjointParams A) {
+  stamp(A.h.clock);
   constexpr int C = AdjC<PHASE>::C;
   __shared__ typename PathMath<R>::Shared shared;
   const PathMath<R> pm(shared);

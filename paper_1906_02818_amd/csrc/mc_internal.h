@@ -53,6 +53,7 @@ struct GbmParams {
   double r_dt, vol_sdt, barrier_rel;
   double* partials;   // [n_blocks][n_moments]
   double* path_out;   // [n_paths][C] or nullptr
+  uint64_t* clock;    // start stamp (device/reduce.h), or nullptr
 };
 
 // Launches the GBM path kernel for the instantiated mask `mask` (must be one
@@ -87,6 +88,7 @@ struct HestonParams {
   double S0, K, disc, dt, sdt, r, v0, kappa, theta, xi, rho, rho_c;
   double* partials;
   double* path_out;
+  uint64_t* clock;    // start stamp, or nullptr
 };
 hipError_t launch_heston(const HestonParams& p, uint32_t mask, bool fp64, hipStream_t s,
                          uint32_t* n_blocks);
@@ -162,6 +164,7 @@ struct BasketParams {
   uint32_t q_rep_blocks, q_dims;
   double* partials;
   double* path_out;       // [n_paths][3] (basket) or [n_paths] (portfolio), or nullptr
+  uint64_t* clock;        // start stamp, or nullptr
 };
 constexpr int kMaxStrikes = 8;
 hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks);
@@ -315,10 +318,12 @@ hipError_t launch_grad_sum(const float* partials, uint32_t n_blocks, const CvVal
 // ---- reductions and diagnostics ----
 // Moment vectors of C channels (1..kMaxMomentChannels): n_batch independent
 // merges of block-major partials [batch][n_blocks][n_moments(C)] into
-// out [batch][n_moments(C)], in a fixed order. A single batch of more than
-// 4096 vectors merges in two stages and overwrites the partials' chunk heads.
+// out [batch][n_moments(C)] (device or pinned host memory), in a fixed order.
+// A single batch of more than 4096 vectors merges in two stages and overwrites
+// the partials' chunk heads. clock: start stamp of the merge, or nullptr.
 hipError_t launch_final_merge(double* partials, uint32_t n_blocks, uint32_t C,
-                              uint32_t n_batch, double* out, hipStream_t s);
+                              uint32_t n_batch, double* out, hipStream_t s,
+                              uint64_t* clock = nullptr);
 // Plain sums: partials [n_mom][n_blocks] -> out [n_mom]; the batch form takes
 // partials [batch][n_mom][n_blocks] -> out [batch][n_mom].
 hipError_t launch_final_reduce(const double* partials, uint32_t n_blocks, uint32_t n_mom,
