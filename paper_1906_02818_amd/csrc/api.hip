@@ -1319,38 +1319,52 @@ mc_status get_lsm_buf(mc_context* ctx, size_t bytes, char** base) {
 mc_status mc_price_impl(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64_t n_paths,
                         uint32_t n_steps, uint64_t seed, const mc_options& o, mc_result* out);
 
+// The two models of a central finite difference: the greek's parameter theta
+// scaled by 1 + h and 1 - h.
+struct BumpedPair {
+  std::vector<double> S0u, S0d, sgu, sgd;
+  mc_model up, down;
+  double theta;
+
+  BumpedPair(const mc_model* m, uint32_t which, double h) : up(*m), down(*m) {
+    if (which == MC_GREEK_DELTA) {
+      S0u.assign(m->S0, m->S0 + m->dim);
+      S0d = S0u;
+      theta = m->S0[0];
+      S0u[0] = theta * (1.0 + h);
+      S0d[0] = theta * (1.0 - h);
+      up.S0 = S0u.data();
+      down.S0 = S0d.data();
+    } else if (m->kind == MC_HESTON) {
+      theta = m->v0;
+      up.v0 = theta * (1.0 + h);
+      down.v0 = theta * (1.0 - h);
+    } else {
+      sgu.assign(m->sigma, m->sigma + m->dim);
+      sgd = sgu;
+      theta = m->sigma[0];
+      sgu[0] = theta * (1.0 + h);
+      sgd[0] = theta * (1.0 - h);
+      up.sigma = sgu.data();
+      down.sigma = sgd.data();
+    }
+  }
+  BumpedPair(const BumpedPair&) = delete;
+  BumpedPair& operator=(const BumpedPair&) = delete;
+};
+
 // Central finite difference on common random numbers (Sec. I-A.3 greeks by
-// bumping): the payoff of the models with the parameter theta scaled by
-// 1 + h and 1 - h, priced on the same paths (same seed, tag and path
-// indices) into device sinks in chunks of at most 2^20 paths; the greek is
-// the mean of the per-path differences over 2 h theta, reduced in FP64.
+// bumping) of a Heston or basket payoff: the pair's models priced on the same
+// paths (same seed, tag and path indices) into device sinks in chunks of at
+// most 2^20 paths; the greek is the mean of the per-path differences over
+// 2 h theta, reduced in FP64. GBM: gbm_fd_price.
 mc_status fd_greek(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64_t n_paths,
                    uint32_t n_steps, uint64_t seed, const mc_options& o, uint32_t which,
                    double* g, double* se, double* kms) {
   const double h = o.fd_rel_step;
-  const uint32_t d = m->dim;
-  std::vector<double> s0u(m->S0, m->S0 + d), s0d = s0u, sgu, sgd;
-  mc_model mu = *m, md = *m;
-  double theta;
-  if (which == MC_GREEK_DELTA) {
-    theta = m->S0[0];
-    s0u[0] = theta * (1.0 + h);
-    s0d[0] = theta * (1.0 - h);
-    mu.S0 = s0u.data();
-    md.S0 = s0d.data();
-  } else if (m->kind == MC_HESTON) {
-    theta = m->v0;
-    mu.v0 = theta * (1.0 + h);
-    md.v0 = theta * (1.0 - h);
-  } else {
-    sgu.assign(m->sigma, m->sigma + d);
-    sgd = sgu;
-    theta = m->sigma[0];
-    sgu[0] = theta * (1.0 + h);
-    sgd[0] = theta * (1.0 - h);
-    mu.sigma = sgu.data();
-    md.sigma = sgd.data();
-  }
+  const BumpedPair pair(m, which, h);
+  const mc_model &mu = pair.up, &md = pair.down;
+  const double theta = pair.theta;
   mc_payoff fp = *f;
   fp.cv = MC_CV_NONE;
   mc_options ob = o;
@@ -1358,10 +1372,8 @@ mc_status fd_greek(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint6
   ob.greeks_method = MC_GREEKS_PATHWISE;
   ob.path_values = nullptr;
   ob.cv_beta = std::nan("");
-  // A relative bump h leaves about -log10(h) fewer significant digits in the
-  // difference: FP32 paths (about 1e-7 relative error per path) would carry
-  // errors of order 1e-7 / h into the greek, systematic ones included, so the
-  // bumped pairs run in FP64. The basket has no FP64 path; its only bump
+  // FP32 paths would carry errors of order 1e-7 / h into the greek, so the
+  // bumped pairs run in FP64 (see gbm_fd_price). The basket has no FP64 path; its only bump
   // (S0 of asset 0) scales the terminal values and loses nothing.
   if (m->kind != MC_GBM_BASKET) ob.prec = MC_FP64;
   uint32_t C = 0, ch = 0;
@@ -1429,6 +1441,81 @@ mc_status mc_price_impl(mc_context* ctx, const mc_model* m, const mc_payoff* f, 
   }
   if (m->kind == MC_GBM_BASKET) return basket_price(ctx, m, f, n_paths, n_steps, seed, o, out);
   return heston_price(ctx, m, f, n_paths, n_steps, seed, o, out);
+}
+
+// Finite differences of a GBM payoff: the price run and, queued before it, one
+// kernel for the bumped paths of every greek wanted, so that the call waits
+// once. The bumped paths run in FP64 whatever the price run's precision: a
+// relative bump h leaves about -log10(h) fewer significant digits in the
+// difference, and FP32 paths (about 1e-7 relative error per path) would carry
+// errors of order 1e-7 / h into the greek, systematic ones included.
+mc_status gbm_fd_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64_t n_paths,
+                       uint32_t n_steps, uint64_t seed, const mc_options& o,
+                       const mc_options& price_opts, mc_result* out) {
+  uint32_t bit = 0;
+  switch (f->kind) {
+    case MC_EURO_CALL: bit = G_EURO; break;
+    case MC_ASIAN_ARITH_CALL: bit = G_ASIAN; break;
+    case MC_ASIAN_GEO_CALL: bit = G_GEO; break;
+    case MC_UO_BARRIER_CALL: bit = G_UO; break;
+    case MC_UO_BRIDGE_CALL: bit = G_UOBB; break;
+    default: return fail(ctx, MC_ERR_UNSUPPORTED, "payoff not offered for GBM");
+  }
+  const uint32_t which[2] = {MC_GREEK_DELTA, MC_GREEK_VEGA};
+  const bool want[2] = {(o.greeks & MC_GREEK_DELTA) != 0, (o.greeks & MC_GREEK_VEGA) != 0};
+  const uint32_t n_greeks = (uint32_t)want[0] + (uint32_t)want[1];
+  const double h = o.fd_rel_step;
+  constexpr uint32_t M = n_moments(1);
+  // Moments: behind those of the price run (at most n_moments of ten channels).
+  constexpr size_t kFdMoments = 128;
+  static_assert(n_moments(kMaxMomentChannels) <= kFdMoments, "moment staging");
+  mc_status st = get_pinned(ctx, kFdMoments + 2 * M);
+  if (st != MC_OK) return st;
+  // The workspace a bumped run of one functional set takes.
+  const uint32_t mask = gbm_pick_mask(bit, true, m->scheme == MC_LOG_EULER, 1, false);
+  if (!mask) return fail(ctx, MC_ERR_UNSUPPORTED, "payoff not available for this scheme/precision");
+  char* base = nullptr;
+  st = get_ws(ctx, o, layout_for(n_paths < kMlmcChunk ? n_paths : kMlmcChunk, gbm_channels(mask),
+                                 false, kBlock, kGbmMaxBlocks).bytes, &base);
+  if (st != MC_OK) return st;
+  st = get_mlmc_buf(ctx, (size_t)2 * kGbmMaxBlocks * M * sizeof(double), &base);
+  if (st != MC_OK) return st;
+  double theta[2];
+  GbmFdParams p{};
+  for (int g = 0; g < 2; ++g) {
+    const BumpedPair pair(m, which[g], h);
+    theta[g] = pair.theta;
+    p.up[g] = gbm_params(&pair.up, f, n_paths, n_steps, seed, o, true, o.stream_tag);
+    p.down[g] = gbm_params(&pair.down, f, n_paths, n_steps, seed, o, true, o.stream_tag);
+  }
+  p.up[0].clock = ctx->clock + 2;
+  p.partials = (double*)base;
+  hipStream_t s = stream_of(ctx, o);
+  double* mom = ctx->pinned + kFdMoments;
+  uint32_t nb = 0;
+  HIP_TRY(ctx, launch_gbm_fd(p, bit, want[0], want[1], s, &nb));
+  mc_result r{};
+  const hipError_t merged = launch_final_merge(p.partials, nb, 1, n_greeks, mom, s, ctx->clock + 3);
+  if (merged == hipSuccess) st = mc_price_impl(ctx, m, f, n_paths, n_steps, seed, price_opts, &r);
+  if (merged != hipSuccess || st != MC_OK) {
+    HIP_TRY(ctx, hipStreamSynchronize(s));   // the queued kernels write to the context's memory
+    HIP_TRY(ctx, merged);
+    return st;
+  }
+  for (int g = 0; g < 2; ++g) {
+    if (!want[g]) continue;
+    const double n = mom[0];               // [n, non-finite, mean, sum of squares]
+    if (n < 2) return fail(ctx, MC_ERR_DEVICE, "fewer than two finite paths in a bumped run");
+    double* greek = g == 0 ? &r.delta : &r.vega;
+    double* se = g == 0 ? &r.delta_se : &r.vega_se;
+    *greek = mom[2] / (2.0 * h * theta[g]);
+    *se = std::sqrt(mom[3] / (n - 1.0) / n) / (2.0 * h * theta[g]);
+    mom += M;
+  }
+  r.kernel_ms += clock_ms(ctx, 2, 3);
+  r.greeks_method = MC_GREEKS_FD_CRN;
+  *out = r;
+  return MC_OK;
 }
 
 // Mean and standard error from (n, sum, sum of squares).
@@ -1616,11 +1703,12 @@ mc_status mc_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint6
     if (st == MC_OK && o.greeks) out->greeks_method = (int)o.greeks_method;
     return st;
   }
-  // Finite differences on common random numbers: the price run, then one
-  // pair of bumped runs per requested greek.
+  // Finite differences on common random numbers: the price run, and the
+  // bumped pair of each requested greek.
   mc_options ob = o;
   ob.greeks = 0;
   ob.greeks_method = MC_GREEKS_PATHWISE;
+  if (m->kind == MC_GBM) return gbm_fd_price(ctx, m, f, n_paths, n_steps, seed, o, ob, out);
   mc_result r{};
   st = mc_price_impl(ctx, m, f, n_paths, n_steps, seed, ob, &r);
   if (st != MC_OK) return st;

@@ -4,11 +4,7 @@
 // reduction (Eq. 3). A thread prices one path at a time, its state in
 // registers, nothing written to memory per step; over a persistent grid it
 // prices several paths and keeps their moments in FP64 registers.
-//
-// Schemes: log-Euler on ln S (exact in law for every step count) and Euler
-// on S (first-order weak error, Sec. V-B). In FP32 the log state is kept in
-// base 2, z = log2(S/S0), so that S_i/S0 = exp2(z) is one v_exp_f32; in FP64
-// it is the natural log.
+// The path itself: device/gbm.h.
 //
 // Bound: VALU issue. At 2^24 x 252 (Asian, geometric, barrier) a Philox block
 // and its four steps are 117 cycles of Philox, 110 of Box-Muller and 82 of
@@ -16,122 +12,12 @@
 // v_alignbit 4.2), 309 in all, and the kernel runs at 307 (1.98 ms).
 #include <initializer_list>
 
+#include "device/gbm.h"
 #include "device/reduce.h"
-#include "device/rng.h"
 #include "mc_internal.h"
 
 namespace mcp {
 namespace {
-
-template <typename R>
-struct Dom;
-template <>
-struct Dom<float> {
-  typedef PathMath<float> M;
-  static __device__ __forceinline__ float exp_(float z, const M&) {
-    return __builtin_amdgcn_exp2f(z);
-  }
-  // -log of the uniform of a word, in the kernel's log domain.
-  static __device__ __forceinline__ float neg_log_(uint32_t w, const M&) {
-    return -__builtin_amdgcn_logf(uniform_f32(w));
-  }
-  static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
-};
-template <>
-struct Dom<double> {
-  typedef PathMath<double> M;
-  static __device__ __forceinline__ double exp_(double z, const M& m) { return exp_f64(z, m.t); }
-  static __device__ __forceinline__ double neg_log_(uint32_t w, const M& m) {
-    return 0.5 * neg2_log_f64(w, m.t);
-  }
-  static __device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
-};
-
-template <typename R>
-__device__ __forceinline__ R pos(R x) {
-  return x > R(0) ? x : R(0);
-}
-
-// Running state of one path.
-template <typename R>
-struct GbmState {
-  R z;       // log scheme: log(S/S0) in the kernel's domain; Euler-S: S/S0
-  R sumE;    // sum of S_i/S0            (Asian)
-  R sumz;    // sum of log(S_i/S0)       (geometric Asian)
-  R sumZ;    // sum of the normals       (vega)
-  R dsig;    // Euler-S: d(S_i/S0)/dsigma
-  R accV;    // sum of d(S_i/S0)/dsigma  (Asian vega)
-  R top;     // FP32 log scheme: running maximum of z (discrete barrier)
-  bool alive, alive_bb;
-};
-
-template <typename R, uint32_t MASK, bool LOGS>
-struct GbmStepper {
-  // FP32 log paths watch the barrier through the running maximum: two dates
-  // per v_max3_f32, where a compare and a mask update per date took twice as
-  // long. (Folding the volatility into Box-Muller's radius would save another
-  // multiply per step, 3% of the kernel; it rounds every state differently,
-  // and single paths then cross the barrier that did not before.)
-  static constexpr bool kTop = sizeof(R) == 4 && LOGS;
-  R dz, vz, zB, cbb, sdt, sig, dt, rdt, vsdt, Brel;
-  const PathMath<R>& pm;
-
-  __device__ __forceinline__ GbmStepper(const GbmParams& P, const PathMath<R>& math) : pm(math) {
-    dz = (R)P.drift_dom;
-    vz = (R)P.vol_dom;
-    zB = (R)P.barrier_dom;
-    cbb = (R)P.bridge_c;
-    sdt = (R)P.sdt;
-    sig = (R)P.sigma;
-    dt = (R)P.dt;
-    rdt = (R)P.r_dt;
-    vsdt = (R)P.vol_sdt;
-    Brel = (R)P.barrier_rel;
-  }
-
-  __device__ __forceinline__ bool alive(const GbmState<R>& s) const {
-    if constexpr (kTop) return s.top < zB;
-    return s.alive;
-  }
-
-  // Step i -> i+1 with normal Z (and the bridge's uniform of word W when
-  // monitored).
-  __device__ __forceinline__ void step(GbmState<R>& s, R Z, uint32_t i, uint32_t W) const {
-    if constexpr (LOGS) {
-      const R zp = s.z;
-      s.z = s.z + dz + vz * Z;
-      R E = R(0);
-      if constexpr ((MASK & (G_ASIAN | G_ASIAN_G)) != 0) {
-        E = Dom<R>::exp_(s.z, pm);
-        s.sumE += E;
-      }
-      if constexpr ((MASK & G_GEO) != 0) s.sumz += s.z;
-      if constexpr ((MASK & G_UO) != 0) {
-        if constexpr (kTop)
-          s.top = __builtin_fmaxf(s.top, s.z);
-        else
-          s.alive = s.alive && (s.z < zB);
-      }
-      if constexpr ((MASK & (G_EURO_G | G_ASIAN_G)) != 0) s.sumZ += Z;
-      if constexpr ((MASK & G_ASIAN_G) != 0)
-        s.accV += E * (sdt * s.sumZ - sig * (dt * (R)(i + 1)));
-      if constexpr ((MASK & G_UOBB) != 0) {
-        // Maximum of the Brownian bridge between z_i and z_{i+1}.
-        const R d = zp - s.z;
-        const R twice_max = zp + s.z + Dom<R>::sqrt_(d * d + cbb * Dom<R>::neg_log_(W, pm));
-        s.alive_bb = s.alive_bb && (twice_max < R(2) * zB);
-      }
-    } else {
-      const R inc = rdt + vsdt * Z;           // S_{i+1}/S_i - 1
-      if constexpr ((MASK & (G_EURO_G | G_ASIAN_G)) != 0) s.dsig = s.dsig * (R(1) + inc) + s.z * sdt * Z;
-      s.z = s.z + s.z * inc;
-      if constexpr ((MASK & (G_ASIAN | G_ASIAN_G)) != 0) s.sumE += s.z;
-      if constexpr ((MASK & G_GEO) != 0) s.sumz += log(s.z);
-      if constexpr ((MASK & G_UO) != 0) s.alive = s.alive && (s.z < Brel);
-      if constexpr ((MASK & G_ASIAN_G) != 0) s.accV += s.dsig;
-    }
-  }
-};
 
 template <typename R, uint32_t MASK, bool LOGS, uint32_t CO>
 __device__ __forceinline__ void simulate(const GbmParams& P,
@@ -140,18 +26,14 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
                                          double (&y)[gbm_channels(MASK)]) {
   const PathMath<R>& pm = st.pm;
   GbmState<R> s;
-  s.z = LOGS ? R(0) : R(1);
-  s.sumE = s.sumz = s.sumZ = s.dsig = s.accV = R(0);
-  s.top = -R(__builtin_inff());
-  s.alive = s.alive_bb = true;
-  const PathRng pc = make_rng(lo, hi, P.tag, keys);
-  const PathRng pcb = make_rng(lo, hi, P.tag + 5u, keys);
+  s.start(LOGS);
   const uint32_t n = P.n_steps;
   if constexpr (CO > 1) {
     // Coupled coarse path: step i takes normals CO i .. CO i + CO - 1 of the
     // fine path, summed and scaled by 1/sqrt(CO) (same Brownian increment
     // over the coarse step). CO divides the 4 normals of a Philox block.
     static_assert(CO == 2 || CO == 4, "coupling factor");
+    const PathRng pc = make_rng(lo, hi, P.tag, keys);
     const R rsc = CO == 2 ? R(0.70710678118654752440) : R(0.5);
     constexpr uint32_t SPB = 4 / CO;              // coarse steps per block
     const uint32_t nb = n / SPB;
@@ -169,45 +51,22 @@ __device__ __forceinline__ void simulate(const GbmParams& P,
       const Normals4<R> nz = normals4(philox(nb, pc, keys), pm);
       st.step(s, (nz.z[0] + nz.z[1]) * rsc, n - 1, 0u);
     }
-  }
-  const uint32_t n_full = CO > 1 ? 0u : n >> 2;
-  for (uint32_t j = 0; j < n_full; ++j) {
-    const Normals4<R> nz = normals4(philox(j, pc, keys), pm);
-    Words4 wb{0, 0, 0, 0};
-    if constexpr ((MASK & G_UOBB) != 0) wb = philox(j, pcb, keys);
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      st.step(s, nz.z[q], 4 * j + q, word_at(wb, q));
-    }
-  }
-  const uint32_t rem = CO > 1 ? 0u : n & 3u;
-  if (rem) {
-    const Normals4<R> nz = normals4(philox(n_full, pc, keys), pm);
-    Words4 wb{0, 0, 0, 0};
-    if constexpr ((MASK & G_UOBB) != 0) wb = philox(n_full, pcb, keys);
-#pragma unroll
-    for (uint32_t q = 0; q < 3; ++q) {
-      if (q >= rem) break;
-      st.step(s, nz.z[q], 4 * n_full + q, word_at(wb, q));
-    }
+  } else {
+    walk_normals<R, (MASK & G_UOBB) != 0>(n, P.tag, lo, hi, keys, pm,
+                                          [&](uint32_t i, R Z, uint32_t W) { st.step(s, Z, i, W); });
   }
 
   // Terminal payoffs, discounted (e^{-rT}).
   const R S0 = (R)P.S0, K = (R)P.K, disc = (R)P.disc, inv_n = R(1) / (R)n;
   const R En = LOGS ? Dom<R>::exp_(s.z, pm) : s.z;    // S_n / S0
   const R ST = S0 * En;
-  const R call = pos(ST - K);
   const R A = S0 * s.sumE * inv_n;
   int c = 0;
-  if constexpr ((MASK & G_EURO) != 0) y[c++] = (double)(disc * call);
-  if constexpr ((MASK & G_ASIAN) != 0) y[c++] = (double)(disc * pos(A - K));
-  if constexpr ((MASK & G_GEO) != 0) {
-    const R G = LOGS ? S0 * Dom<R>::exp_(s.sumz * inv_n, pm)
-                     : S0 * (R)exp((double)s.sumz / (double)n);
-    y[c++] = (double)(disc * pos(G - K));
-  }
-  if constexpr ((MASK & G_UO) != 0) y[c++] = st.alive(s) ? (double)(disc * call) : 0.0;
-  if constexpr ((MASK & G_UOBB) != 0) y[c++] = s.alive_bb ? (double)(disc * call) : 0.0;
+  if constexpr ((MASK & G_EURO) != 0) y[c++] = payoff_of<R, G_EURO, LOGS>(P, s, En, pm);
+  if constexpr ((MASK & G_ASIAN) != 0) y[c++] = payoff_of<R, G_ASIAN, LOGS>(P, s, En, pm);
+  if constexpr ((MASK & G_GEO) != 0) y[c++] = payoff_of<R, G_GEO, LOGS>(P, s, En, pm);
+  if constexpr ((MASK & G_UO) != 0) y[c++] = payoff_of<R, G_UO, LOGS>(P, s, En, pm);
+  if constexpr ((MASK & G_UOBB) != 0) y[c++] = payoff_of<R, G_UOBB, LOGS>(P, s, En, pm);
   if constexpr ((MASK & G_EURO_G) != 0) {
     const bool itm = ST > K;
     y[c++] = itm ? (double)(disc * En) : 0.0;     // dS_T/dS0 = S_T/S0

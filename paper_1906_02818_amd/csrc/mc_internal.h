@@ -60,6 +60,16 @@ struct GbmParams {
 // returned by gbm_pick_mask). Returns the number of blocks via *n_blocks.
 hipError_t launch_gbm(const GbmParams& p, uint32_t mask, bool fp64, hipStream_t s,
                       uint32_t* n_blocks);
+
+// The bumped models of a finite-difference run, [0] for delta (S0) and [1]
+// for vega (sigma). up[0] also carries what all of them share (paths, steps,
+// key, tag, clock) and, as S0 does not enter a step, the unbumped dynamics.
+struct GbmFdParams {
+  GbmParams up[2], down[2];
+  double* partials;   // [greeks][n_blocks][n_moments(1)]
+};
+hipError_t launch_gbm_fd(const GbmFdParams& p, uint32_t bit, bool delta, bool vega, hipStream_t s,
+                         uint32_t* n_blocks);
 // Smallest instantiated mask containing `want` for this precision/scheme
 // and coupling factor, or 0 when none does. rows: the set whose channels a
 // row of per-path values has (mc_path_channels).

@@ -2,6 +2,8 @@
 remainders of a Philox block, path indices that straddle 2^32, functional sets
 of their own, the edges of tiles. Each is held to the FP64 oracle or to the
 general path."""
+import math
+
 import numpy as np
 import pytest
 
@@ -217,3 +219,42 @@ def test_learned_cv_segments_and_straddles(ctx, m_every, N, n, offset):
     pv = r["path_values"]
     np.testing.assert_allclose(pv[:, 0], o[:, 0], rtol=3e-4, atol=3e-4)
     assert np.abs(pv[:, 1] - o[:, 1]).max() < 2e-3 * (1 + np.abs(o[:, 1]).max())
+
+
+@pytest.mark.parametrize("payoff,scheme", [
+    (mc.MC_EURO_CALL, mc.MC_LOG_EULER), (mc.MC_ASIAN_ARITH_CALL, mc.MC_LOG_EULER),
+    (mc.MC_ASIAN_GEO_CALL, mc.MC_LOG_EULER), (mc.MC_UO_BARRIER_CALL, mc.MC_LOG_EULER),
+    (mc.MC_UO_BRIDGE_CALL, mc.MC_LOG_EULER), (mc.MC_EURO_CALL, mc.MC_EULER_S),
+    (mc.MC_ASIAN_ARITH_CALL, mc.MC_EULER_S), (mc.MC_UO_BARRIER_CALL, mc.MC_EULER_S)])
+@pytest.mark.parametrize("N,n,offset", [(2, 1, 0), (257, 3, 2**32 - 100), (70001, 9, 5)])
+def test_bumped_paths_in_one_pass(ctx, payoff, scheme, N, n, offset):
+    """The finite differences equal the means of explicit bumped FP64 runs,
+    for each greek alone and for both, whatever the price run's precision.
+    A payoff's last digits may differ between functional sets by a fused
+    multiply-add: 4 ulp of a price of 256, over the bump's width."""
+    h, S0, sig = 1e-3, 100.0, 0.25
+    f = mc.Payoff(payoff, 100.0, B=130.0)
+
+    def model(S=S0, s=sig):
+        return mc.Model(kind=mc.MC_GBM, S0=S, r=0.03, T=1.0, sigma=s, scheme=scheme)
+    o64 = mc.Options(prec=mc.MC_FP64, path_values=True, path_offset=offset)
+    name = {mc.MC_EURO_CALL: "euro", mc.MC_ASIAN_ARITH_CALL: "asian", mc.MC_ASIAN_GEO_CALL: "geo",
+            mc.MC_UO_BARRIER_CALL: "uo", mc.MC_UO_BRIDGE_CALL: "uo_bridge"}[payoff]
+    col = mc.mc_path_channels(model(), f, o64).index(name)
+
+    def values(m):
+        return np.asarray(mc.mc_price(ctx, m, f, N, n, SEED, o64)["path_values"])[:, col]
+    want = {"delta": (values(model(S=S0 * (1 + h))) - values(model(S=S0 * (1 - h)))) / (2 * h * S0),
+            "vega": (values(model(s=sig * (1 + h))) - values(model(s=sig * (1 - h)))) / (2 * h * sig)}
+    width = {"delta": 2 * h * S0, "vega": 2 * h * sig}
+    bits = {"delta": mc.MC_GREEK_DELTA, "vega": mc.MC_GREEK_VEGA}
+    for wanted in (("delta",), ("vega",), ("delta", "vega")):
+        for prec in (mc.MC_FP32, mc.MC_FP64):
+            r = mc.mc_price(ctx, model(), f, N, n, SEED, mc.Options(
+                prec=prec, path_offset=offset, greeks=sum(bits[g] for g in wanted),
+                greeks_method=mc.MC_GREEKS_FD_CRN, fd_rel_step=h))
+            for g in wanted:
+                tol = 4 * 256 * 2.0**-52 / width[g]
+                assert r[g] == pytest.approx(want[g].mean(), rel=1e-12, abs=tol)
+                assert r[g + "_se"] == pytest.approx(want[g].std(ddof=1) / math.sqrt(N), rel=1e-9,
+                                                     abs=tol)
