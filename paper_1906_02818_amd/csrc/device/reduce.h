@@ -40,6 +40,44 @@ __device__ __forceinline__ void stamp(uint64_t* clock) {
     *clock = (uint64_t)wall_clock64();
 }
 
+// v of the lane whose number differs in bit OFF (a power of two up to 32),
+// added to v: one stage of a butterfly whose earlier stages ran over the
+// larger offsets, so that lanes equal modulo 2 OFF hold the same v (a rotation
+// of a row by 4 or 8 then reads the partner's). The moves between lanes are on
+// the vector unit. Through LDS, whose pipe the waves of a CU share, the 132
+// moves of a wave for three channels' moments cost a full grid 2.6 us (FP64
+// European, 2^18 paths x 64: kernel 33.7 -> 31.1 us) and the merge of its
+// 1024 vectors 1 us (6.0 -> 5.0 us).
+template <int OFF>
+__device__ __forceinline__ uint32_t lane_move(uint32_t x) {
+  if constexpr (OFF == 8 || OFF == 4)        // row_ror
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x120 + OFF, 0xf, 0xf, true);
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, OFF == 2 ? 0x4E : 0xB1, 0xf, 0xf, true);
+}
+template <int OFF>
+__device__ __forceinline__ double lane_add(double v) {
+  const uint32_t hi = (uint32_t)__double2hiint(v), lo = (uint32_t)__double2loint(v);
+  if constexpr (OFF >= 16) {                 // the two halves (pairs of rows), each to all lanes
+    const auto h = OFF == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                             : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    const auto l = OFF == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                             : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  } else {
+    return v + __hiloint2double((int)lane_move<OFF>(hi), (int)lane_move<OFF>(lo));
+  }
+}
+
+// Sum over the wave, the same in every lane (every lane active).
+__device__ __forceinline__ double wave_sum(double v) {
+  v = lane_add<32>(v);
+  v = lane_add<16>(v);
+  v = lane_add<8>(v);
+  v = lane_add<4>(v);
+  v = lane_add<2>(v);
+  return lane_add<1>(v);
+}
+
 template <int C>
 struct PartSums {
   static constexpr int NC = C * (C + 1) / 2;
@@ -178,18 +216,17 @@ __device__ __forceinline__ void block_reduce(PartSums<C>& t, double* __restrict_
     const int src = __ffsll((long long)holders) - 1;
     double c[C];
 #pragma unroll
-    for (int a = 0; a < C; ++a) c[a] = __shfl(t.shift[a], src, 64);
+    for (int a = 0; a < C; ++a)
+      c[a] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(t.shift[a]), src),
+                              __builtin_amdgcn_readlane(__double2loint(t.shift[a]), src));
     t.rebase(c);
   }
+  t.n = wave_sum(t.n);
+  t.bad = wave_sum(t.bad);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    t.n += __shfl_xor(t.n, off, 64);
-    t.bad += __shfl_xor(t.bad, off, 64);
+  for (int a = 0; a < C; ++a) t.s1[a] = wave_sum(t.s1[a]);
 #pragma unroll
-    for (int a = 0; a < C; ++a) t.s1[a] += __shfl_xor(t.s1[a], off, 64);
-#pragma unroll
-    for (int k = 0; k < NC; ++k) t.s2[k] += __shfl_xor(t.s2[k], off, 64);
-  }
+  for (int k = 0; k < NC; ++k) t.s2[k] = wave_sum(t.s2[k]);
   if (lane == 0) {
     red[wave][0] = t.n;
     red[wave][1] = t.bad;
@@ -257,12 +294,6 @@ __device__ __forceinline__ void block_moments(const double (&y)[C], bool valid, 
 }
 
 // ---- Plain sums (counts, tail sums, Gram matrices): moment-major ----------
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 // Block sum of per-thread vectors, written to partials[m * n_blocks + block]
 // (fixed wave butterfly and wave order).
