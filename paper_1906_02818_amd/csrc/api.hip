@@ -47,14 +47,11 @@ struct mc_context {
   // regression workspace of the last call (device, grown on demand).
   void* lsm_buf = nullptr;
   size_t lsm_bytes = 0;
-  hipEvent_t ev2 = nullptr, ev3 = nullptr;
   // The correlation matrix of the last basket call and its Cholesky factor
   // (or that it is not positive definite): a repeated basket skips the
   // O(d^3) factorisation, which costs milliseconds on the host at d = 256.
   std::vector<double> chol_corr, chol_L;
   bool chol_pd = false;
-  // Event pairs around each date's update kernel (created on first use).
-  std::vector<hipEvent_t> lsm_ev;
   // Allocation-free calls (mc_price_noalloc): while `noalloc` is set, every
   // device buffer of the call comes from this device's static scratch array
   // (address from hipGetSymbolAddress at mc_create); the reduced moments come
@@ -74,7 +71,7 @@ namespace {
 
 using namespace mcp;
 
-constexpr size_t kClockStamps = 256;
+constexpr size_t kClockStamps = 4;
 
 constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
@@ -1551,7 +1548,6 @@ mc_status mc_create(mc_context** out, int device) {
   ctx->device = device;
   if (hipSetDevice(device) != hipSuccess || hipStreamCreate(&ctx->stream) != hipSuccess ||
       hipEventCreate(&ctx->ev0) != hipSuccess || hipEventCreate(&ctx->ev1) != hipSuccess ||
-      hipEventCreate(&ctx->ev2) != hipSuccess || hipEventCreate(&ctx->ev3) != hipSuccess ||
       scratch_address(device, &ctx->scratch) != hipSuccess ||
       hipHostMalloc((void**)&ctx->clock, kClockStamps * sizeof(uint64_t), hipHostMallocDefault) !=
           hipSuccess ||
@@ -1580,10 +1576,7 @@ mc_status mc_destroy(mc_context* ctx) {
   if (ctx->clock) (void)hipHostFree(ctx->clock);
   if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
   if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
-  if (ctx->ev2) (void)hipEventDestroy(ctx->ev2);
-  if (ctx->ev3) (void)hipEventDestroy(ctx->ev3);
   if (ctx->lsm_buf) (void)hipFree(ctx->lsm_buf);
-  for (hipEvent_t e : ctx->lsm_ev) (void)hipEventDestroy(e);
   if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
   return MC_OK;
@@ -2492,52 +2485,68 @@ mc_status mc_price_lsm(mc_context* ctx, const mc_model* m, const mc_lsm_spec* sp
   const size_t b_c = align256((size_t)p.ystride * sizeof(float));
   const size_t b_e = want_ex ? align256((size_t)n_paths) : 0;
   const size_t b_p = align256((size_t)kLsmMaxMom * kLsmMaxBlocks * sizeof(double));
-  const size_t b_s = align256((size_t)(M + 1) * kLsmMaxMom * sizeof(double));
-  const size_t b_b = align256((size_t)M * kLsmMaxFeat * sizeof(double));
-  const size_t b_v = align256((size_t)M * sizeof(int));
+  // Results: stamps (start of the simulation and of the update of stage t,
+  // start and end of the reduction of stage t), moments of the stages,
+  // coefficients and their flags.
+  auto upd_clock = [](uint32_t t) { return (size_t)t; };                    // 0: simulation
+  auto red_clock = [](uint32_t t) { return (size_t)kLsmMaxDates + 2 * t; };
+  const size_t n_clock = 3 * (size_t)kLsmMaxDates + 2;
+  const size_t n_sums = (size_t)(M + 1) * kLsmMaxMom, n_beta = (size_t)M * kLsmMaxFeat;
+  const size_t n_results = n_clock + n_sums + n_beta + M;   // then the reductions' counter
+  const size_t b_r = align256((n_results + 1) * sizeof(double));
   const size_t b_ov = want_ov ? align256((size_t)Noos * sizeof(double)) : 0;
   const size_t b_oe = want_oe ? align256((size_t)Noos) : 0;
   char* base = nullptr;
-  mc_status st = get_lsm_buf(ctx, b_y + b_c + b_e + b_p + b_s + b_b + b_v + b_ov + b_oe, &base);
+  mc_status st = get_lsm_buf(ctx, b_y + b_c + b_e + b_p + b_r + b_ov + b_oe, &base);
   if (st != MC_OK) return st;
   char* q = base;
   p.y = (float*)q;                 q += b_y;
   p.C = (float*)q;                 q += b_c;
   p.ex = want_ex ? (uint8_t*)q : nullptr;  q += b_e;
   p.partials = (double*)q;         q += b_p;
-  double* sums = (double*)q;       q += b_s;
-  double* beta = (double*)q;       q += b_b;
-  int* valid = (int*)q;            q += b_v;
+  uint64_t* clock = (uint64_t*)q;
+  double* sums = (double*)q + n_clock;
+  double* beta = sums + n_sums;
+  int* valid = (int*)(beta + n_beta);
+  q += b_r;
   double* oval = want_ov ? (double*)q : nullptr;  q += b_ov;
   uint8_t* oex = want_oe ? (uint8_t*)q : nullptr;
   p.beta = beta;
   p.valid = valid;
 
+  st = get_pinned(ctx, n_results);
+  if (st != MC_OK) return st;
+  const uint64_t* h_clock = (const uint64_t*)ctx->pinned;
+  const double *h_sums = ctx->pinned + n_clock, *h_beta = h_sums + n_sums;
+  const int* h_valid = (const int*)(h_beta + n_beta);
+  LsmReduce red{};
+  red.beta = beta;
+  red.valid = valid;
+  red.results = (const double*)clock;
+  red.n_results = (uint32_t)n_results;
+  p.arrivals = red.arrivals = (uint32_t*)(clock + n_results);
   hipStream_t s = stream_of(ctx, o);
-  while (ctx->lsm_ev.size() < 2 * (size_t)kLsmMaxDates) {
-    hipEvent_t e = nullptr;
-    HIP_TRY(ctx, hipEventCreate(&e));
-    ctx->lsm_ev.push_back(e);
-  }
   const uint32_t nmom = lsm_n_moments(nf);
+  auto reduce = [&](uint32_t stage, uint32_t blocks, uint32_t n_mom, uint32_t date) {
+    red.sums = sums + (size_t)stage * kLsmMaxMom;
+    red.clock = clock + red_clock(stage);
+    red.host = stage == (Noos ? M : M - 1) ? ctx->pinned : nullptr;
+    return launch_lsm_reduce(p.partials, blocks, n_mom, nf, date, red, s);
+  };
   uint32_t nb = 0;
-  HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
+  p.clock = clock + upd_clock(0);
   HIP_TRY(ctx, launch_lsm_sim(p, s, &nb));
   // Row 0: the simulation's moments; the Gram matrix in them is date M-1's.
-  HIP_TRY(ctx, launch_lsm_reduce_solve(p.partials, nb, nmom, sums, nf, M - 1, beta, valid, s));
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
+  HIP_TRY(ctx, reduce(0, nb, nmom, M - 1));
   // Stage t (1..M-1) updates date j = M-t with the coefficients solved at
   // stage t-1; its moments (the Gram matrix of date j-1, solved here, or the
   // price at j = 1) go to row t.
   for (uint32_t t = 1; t < M; ++t) {
     const uint32_t j = M - t;
-    HIP_TRY(ctx, hipEventRecord(ctx->lsm_ev[2 * t], s));
+    p.clock = clock + upd_clock(t);
     HIP_TRY(ctx, launch_lsm_update(p, j, s, &nb));
-    HIP_TRY(ctx, hipEventRecord(ctx->lsm_ev[2 * t + 1], s));
-    HIP_TRY(ctx, launch_lsm_reduce_solve(p.partials, nb, nmom, sums + (size_t)t * kLsmMaxMom, nf,
-                                         j - 1, beta, valid, s));
+    HIP_TRY(ctx, reduce(t, nb, nmom, j - 1));
   }
-  HIP_TRY(ctx, hipEventRecord(ctx->ev2, s));
   if (Noos) {
     LsmParams po = p;
     po.n_paths = Noos;
@@ -2546,18 +2555,9 @@ mc_status mc_price_lsm(mc_context* ctx, const mc_model* m, const mc_lsm_spec* sp
     po.C = nullptr;
     po.ex = oex;
     po.path_value = oval;
+    po.clock = nullptr;
     HIP_TRY(ctx, launch_lsm_oos(po, s, &nb));
-    HIP_TRY(ctx, launch_final_reduce(p.partials, nb, 2, sums + (size_t)M * kLsmMaxMom, s));
-  }
-  HIP_TRY(ctx, hipEventRecord(ctx->ev3, s));
-  std::vector<double> h_sums((size_t)(M + 1) * kLsmMaxMom), h_beta((size_t)M * kLsmMaxFeat);
-  std::vector<int> h_valid(M);
-  HIP_TRY(ctx, hipMemcpyAsync(h_sums.data(), sums, h_sums.size() * 8, hipMemcpyDeviceToHost, s));
-  if (M > 1) {
-    HIP_TRY(ctx, hipMemcpyAsync(h_beta.data(), beta, (size_t)(M - 1) * kLsmMaxFeat * 8,
-                                hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(h_valid.data(), valid, (size_t)(M - 1) * sizeof(int),
-                                hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, reduce(M, nb, 2, 0));
   }
   std::vector<float> h_c(want_cf ? n_paths : 0);
   std::vector<uint8_t> h_e(want_ex ? n_paths : 0), h_oe(want_oe ? Noos : 0);
@@ -2568,29 +2568,25 @@ mc_status mc_price_lsm(mc_context* ctx, const mc_model* m, const mc_lsm_spec* sp
     HIP_TRY(ctx, hipMemcpyAsync(diag->oos_value, oval, Noos * 8, hipMemcpyDeviceToHost, s));
   if (want_oe) HIP_TRY(ctx, hipMemcpyAsync(h_oe.data(), oex, Noos, hipMemcpyDeviceToHost, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
-  float ms_sim = 0.f, ms_reg = 0.f, ms_oos = 0.f;
-  HIP_TRY(ctx, hipEventElapsedTime(&ms_sim, ctx->ev0, ctx->ev1));
-  HIP_TRY(ctx, hipEventElapsedTime(&ms_reg, ctx->ev1, ctx->ev2));
-  HIP_TRY(ctx, hipEventElapsedTime(&ms_oos, ctx->ev2, ctx->ev3));
+  auto ms = [&](size_t from, size_t to) {
+    return (double)(h_clock[to] - h_clock[from]) / ctx->clock_khz;
+  };
+  const size_t sim_end = red_clock(0) + 1, reg_end = red_clock(M - 1) + 1;
   double ms_upd = 0.0;
-  for (uint32_t t = 1; t < M; ++t) {
-    float e = 0.f;
-    HIP_TRY(ctx, hipEventElapsedTime(&e, ctx->lsm_ev[2 * t], ctx->lsm_ev[2 * t + 1]));
-    ms_upd += e;
-  }
+  for (uint32_t t = 1; t < M; ++t) ms_upd += ms(upd_clock(t), red_clock(t));
 
   mc_lsm_result r{};
   const uint32_t ng = (nf + 1) * (nf + 2) / 2;
   const double n = (double)n_paths;
-  const double* row0 = h_sums.data();
+  const double* row0 = h_sums;
   moments_mean_se(n, row0[ng], row0[ng + 1], &r.european, &r.european_se);
-  const double* last = h_sums.data() + (size_t)(M - 1) * kLsmMaxMom;
+  const double* last = h_sums + (size_t)(M - 1) * kLsmMaxMom;
   if (M == 1)
     moments_mean_se(n, row0[ng], row0[ng + 1], &r.price, &r.std_err);
   else
     moments_mean_se(n, last[ng], last[ng + 1], &r.price, &r.std_err);
   if (Noos) {
-    const double* ro = h_sums.data() + (size_t)M * kLsmMaxMom;
+    const double* ro = h_sums + (size_t)M * kLsmMaxMom;
     moments_mean_se((double)Noos, ro[0], ro[1], &r.price_oos, &r.std_err_oos);
   } else {
     r.price_oos = NAN;
@@ -2609,9 +2605,9 @@ mc_status mc_price_lsm(mc_context* ctx, const mc_model* m, const mc_lsm_spec* sp
   r.n_itm[M - 1] = (uint64_t)row0[ng + 2];
   r.n_paths = n_paths;
   r.n_paths_oos = Noos;
-  r.sim_ms = ms_sim;
-  r.regress_ms = ms_reg;
-  r.oos_ms = ms_oos;
+  r.sim_ms = ms(upd_clock(0), sim_end);
+  r.regress_ms = ms(sim_end, reg_end);
+  r.oos_ms = Noos ? ms(reg_end, red_clock(M) + 1) : 0.0;
   r.update_ms = ms_upd;
   if (want_cf)
     for (uint64_t i = 0; i < n_paths; ++i) diag->cash_flow[i] = h_c[i];

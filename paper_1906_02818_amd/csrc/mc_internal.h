@@ -233,6 +233,20 @@ struct LsmParams {
   const int* valid;              // [n_dates]: 1 when date j has a regression
   double* partials;              // [n_mom][n_blocks]
   double* path_value;            // out-of-sample: [n_paths] values, or nullptr
+  uint64_t* clock;               // start stamp, or nullptr
+  uint32_t* arrivals;            // the reductions' counter, zeroed by the simulation
+};
+// Where a stage's reduction writes (device memory), and the copy of all
+// results to the host at the end of a call's last one (host: nullptr before).
+struct LsmReduce {
+  double* sums;                  // [n_mom]
+  double* beta;                  // [n_dates][kLsmMaxFeat]
+  int* valid;                    // [n_dates]
+  uint64_t* clock;               // [0] start, [1] end
+  uint32_t* arrivals;            // workgroups that have written their rows; 0 between launches
+  const double* results;         // n_results doubles: all of the above
+  double* host;
+  uint32_t n_results;
 };
 // Moments the kernels of this feature set write (see kLsmMaxMom).
 uint32_t lsm_n_moments(uint32_t nf);
@@ -240,14 +254,13 @@ uint32_t lsm_n_features(uint32_t d, uint32_t degree, uint32_t pay_feat);
 // Simulation of the stored paths (cash flows at t_M, Gram matrix of date
 // n_dates - 1 and the exercise-at-maturity moments), the update of date j
 // (exercise rule of date j, then the Gram matrix of date j - 1, or the
-// price moments when j = 1), the reduction of a stage's block partials into
-// `out` followed by the Cholesky solve of date j (none when j = 0), and the
+// price moments when j = 1), the reduction of a stage's block partials
+// followed by the Cholesky solve of date j (none when j = 0), and the
 // out-of-sample estimate on fresh paths.
 hipError_t launch_lsm_sim(const LsmParams& p, hipStream_t s, uint32_t* n_blocks);
 hipError_t launch_lsm_update(const LsmParams& p, uint32_t j, hipStream_t s, uint32_t* n_blocks);
-hipError_t launch_lsm_reduce_solve(const double* partials, uint32_t nb, uint32_t nmom,
-                                  double* out, uint32_t nf, uint32_t j, double* beta, int* valid,
-                                  hipStream_t s);
+hipError_t launch_lsm_reduce(const double* partials, uint32_t nb, uint32_t nmom, uint32_t nf,
+                             uint32_t j, const LsmReduce& r, hipStream_t s);
 hipError_t launch_lsm_oos(const LsmParams& p, hipStream_t s, uint32_t* n_blocks);
 
 // ---- Learned martingale control variate (Heston Asian) ----

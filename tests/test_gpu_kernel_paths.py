@@ -10,6 +10,7 @@ import pytest
 import oracle
 import paper_1906_02818_amd as mc
 import synth
+from lsm_basis import MAXC, PUT
 
 pytestmark = pytest.mark.gpu
 
@@ -258,3 +259,27 @@ def test_bumped_paths_in_one_pass(ctx, payoff, scheme, N, n, offset):
                 assert r[g] == pytest.approx(want[g].mean(), rel=1e-12, abs=tol)
                 assert r[g + "_se"] == pytest.approx(want[g].std(ddof=1) / math.sqrt(N), rel=1e-9,
                                                      abs=tol)
+
+
+@pytest.mark.parametrize("d,degree,M,N,n_oos,offset", [
+    (1, 1, 1, 300, 0, 0), (2, 2, 3, 1025, 5, (1 << 32) - 500), (4, 1, 2, 70000, 300, 9),
+    (3, 2, 4, (1 << 20) + 4097, 0, 1)])
+def test_lsm_sweeps_and_reductions(ctx, d, degree, M, N, n_oos, offset):
+    """Stages of one and of many rounds of quads, swept in either direction,
+    ragged path counts, a straddle of 2^32, no out-of-sample stage: prices
+    equal the oracle's up to the FP32 states (2e-6 of the strike over the
+    standard error's sqrt(N) paths), counts in the money up to the paths
+    within FP32 rounding of the strike."""
+    S0, sigma, K = np.full(d, 100.0), 0.2 + 0.03 * np.arange(d), 100.0
+    kind = PUT if d == 1 else MAXC
+    corr = np.full((d, d), 0.3) + 0.7 * np.eye(d)
+    model = mc.Model(kind=mc.MC_GBM if d == 1 else mc.MC_GBM_BASKET, S0=S0, r=0.05, T=1.0,
+                     sigma=sigma, corr=corr if d > 1 else None)
+    spec = mc.LsmSpec(payoff=kind, K=K, dividend=0.1, n_dates=M, steps_per_date=1, degree=degree,
+                      n_paths_oos=n_oos)
+    g = mc.mc_price_lsm(ctx, model, spec, N, SEED, mc.Options(path_offset=offset))
+    o = oracle.lsm(S0, sigma, np.linalg.cholesky(corr), 0.05, 0.1, 1.0, kind, K, M, 1, degree, N,
+                   SEED, path0=offset)
+    assert abs(g["price"] - o["price"]) < 2e-6 * K
+    n_itm = np.asarray(g["n_itm"], dtype=float)[:M]
+    assert np.abs(n_itm - o["n_itm"][:M]).max() <= 1 + 1e-6 * N
