@@ -48,10 +48,14 @@ struct mc_context {
   void* lsm_buf = nullptr;
   size_t lsm_bytes = 0;
   // The correlation matrix of the last basket call and its Cholesky factor
-  // (or that it is not positive definite): a repeated basket skips the
-  // O(d^3) factorisation, which costs milliseconds on the host at d = 256.
+  // (or that it is not positive definite), on the host and in device memory: a
+  // repeated basket, compared by its contents, skips the checks of the matrix
+  // and the O(d^3) factorisation, which costs milliseconds at d = 256.
   std::vector<double> chol_corr, chol_L;
   bool chol_pd = false;
+  double* dev_L = nullptr;       // chol_L while dev_L_valid
+  size_t dev_L_count = 0;
+  bool dev_L_valid = false;
   // Allocation-free calls (mc_price_noalloc): while `noalloc` is set, every
   // device buffer of the call comes from this device's static scratch array
   // (address from hipGetSymbolAddress at mc_create); the reduced moments come
@@ -165,16 +169,20 @@ mc_status validate_heston(mc_context* ctx, const mc_model* m, const mc_options& 
 
 uint32_t gbm_want_mask(const mc_payoff* f, const mc_options& o, mc_status* st);
 
-// Basket checks; on success fills L (d*d, lower Cholesky factor) if given.
+// Basket checks; on success the context holds the Cholesky factor.
 mc_status validate_basket(mc_context* ctx, const mc_model* m, const mc_payoff* f,
-                          uint32_t n_steps, const mc_options& o, std::vector<double>* L) {
+                          uint32_t n_steps, const mc_options& o) {
   const uint32_t d = m->dim;
   if (d == 0 || d > 256 || d % 16 != 0)
     return fail(ctx, MC_ERR_UNSUPPORTED, "basket dim must be a multiple of 16 up to 256");
   if (!m->sigma || !m->corr) return fail(ctx, MC_ERR_INVALID_ARG, "basket needs sigma and corr");
   for (uint32_t a = 0; a < d; ++a)
     if (!finite_nonneg(m->sigma[a])) return fail(ctx, MC_ERR_INVALID_ARG, "sigma[%u] invalid", a);
-  for (uint32_t i = 0; i < d; ++i)
+  const size_t dd = (size_t)d * d;
+  // The same matrix as last time is finite and symmetric.
+  const bool known = ctx && ctx->chol_corr.size() == dd &&
+                     std::memcmp(ctx->chol_corr.data(), m->corr, dd * sizeof(double)) == 0;
+  for (uint32_t i = 0; i < d && !known; ++i)
     for (uint32_t j = 0; j < d; ++j) {
       const double c = m->corr[(size_t)i * d + j];
       if (!std::isfinite(c)) return fail(ctx, MC_ERR_INVALID_ARG, "corr not finite");
@@ -192,27 +200,22 @@ mc_status validate_basket(mc_context* ctx, const mc_model* m, const mc_payoff* f
   if (o.greeks & MC_GREEK_VEGA) return fail(ctx, MC_ERR_UNSUPPORTED, "basket greeks: delta only");
   if ((uint64_t)n_steps * d / 4 >= (1ull << 32))
     return fail(ctx, MC_ERR_INVALID_ARG, "n_steps * dim above 2^34 normals per path");
-  // The factor is cached in the context (validation without a context
+  // The factor is kept in the context (validation without a context
   // factorises every time).
-  const size_t dd = (size_t)d * d;
-  std::vector<double> local;
-  const std::vector<double>* Lf = &local;
   bool pd = false;
   if (ctx) {
-    if (ctx->chol_corr.size() != dd ||
-        std::memcmp(ctx->chol_corr.data(), m->corr, dd * sizeof(double)) != 0) {
+    if (!known) {
       ctx->chol_corr.assign(m->corr, m->corr + dd);
       ctx->chol_L.assign(dd, 0.0);
+      ctx->dev_L_valid = false;
       ctx->chol_pd = host::cholesky((int)d, m->corr, ctx->chol_L.data());
     }
-    Lf = &ctx->chol_L;
     pd = ctx->chol_pd;
   } else {
-    local.assign(dd, 0.0);
-    pd = host::cholesky((int)d, m->corr, local.data());
+    std::vector<double> L(dd, 0.0);
+    pd = host::cholesky((int)d, m->corr, L.data());
   }
   if (!pd) return fail(ctx, MC_ERR_NOT_PD, "correlation matrix is not positive definite");
-  if (L) *L = *Lf;
   return MC_OK;
 }
 
@@ -296,7 +299,7 @@ mc_status validate_model_payoff(mc_context* ctx, const mc_model* m, const mc_pay
       return fail(ctx, MC_ERR_UNSUPPORTED, "adjoint greeks run in MC_FP32");
     return MC_OK;
   }
-  if (m->kind == MC_GBM_BASKET) return validate_basket(ctx, m, f, n_steps, o, nullptr);
+  if (m->kind == MC_GBM_BASKET) return validate_basket(ctx, m, f, n_steps, o);
   return fail(ctx, MC_ERR_INVALID_ARG, "unknown model kind");
 }
 
@@ -1023,45 +1026,6 @@ double loss_from_moments(const double* mom) {
 }
 
 // ------------------------------------------------------------- Basket ----
-// L' = diag(sigma_a sqrt(dt) / ln 2) L as MFMA fragments (mc_internal.h), one
-// array per term: conv(v, t) is term t of the value v.
-template <typename F>
-void pack_fragments(uint32_t d, int terms, const std::vector<double>& Ls, F&& conv,
-                    std::vector<uint16_t>* out) {
-  const uint32_t rows = d / 16, pairs = basket_pairs(rows);
-  out->assign((size_t)terms * pairs * 512, 0);
-  for (uint32_t rb = 0; rb < rows; ++rb)
-    for (uint32_t kb = 0; 2 * kb <= rb; ++kb)
-      for (uint32_t l = 0; l < 64; ++l)
-        for (uint32_t j = 0; j < 8; ++j) {
-          const uint32_t a = 16 * rb + l % 16, b = 32 * kb + 8 * (l / 16) + j;
-          if (b > a) continue;
-          for (int t = 0; t < terms; ++t)
-            (*out)[(((size_t)t * pairs + basket_pairs(rb) + kb) * 64 + l) * 8 + j] =
-                conv(Ls[(size_t)a * d + b], t);
-        }
-}
-
-uint16_t to_bf16_rne(float f) {
-  uint32_t u;
-  std::memcpy(&u, &f, 4);
-  const uint32_t lsb = (u >> 16) & 1u;
-  u += 0x7FFFu + lsb;
-  return (uint16_t)(u >> 16);
-}
-float from_bf16(uint16_t h) {
-  uint32_t u = (uint32_t)h << 16;
-  float f;
-  std::memcpy(&f, &u, 4);
-  return f;
-}
-uint16_t to_f16_rne(float f) {
-  _Float16 h = (_Float16)f;   // host conversion rounds to nearest even
-  uint16_t u;
-  std::memcpy(&u, &h, 2);
-  return u;
-}
-
 int basket_prec(mc_precision prec) {
   return prec == MC_FP32 ? BK_FP32 : prec == MC_BF16_GEMM ? BK_BF16
        : prec == MC_FP16_GEMM ? BK_FP16 : BK_BF16X2;
@@ -1082,10 +1046,12 @@ size_t basket_ws_bytes(size_t layout_bytes, uint32_t d, mc_precision prec) {
          align256(4 * 256 * sizeof(float));
 }
 
-// Basket run. With `port` set it prices the call portfolio of the risk
-// metrics instead: drifts port->mu (or r) and one per-path channel, the
-// horizon P&L (value of the holdings at T minus their Black-Scholes value
-// `premium` at 0); out->price / variance / std_err describe that P&L.
+// A basket run with `port` set prices the call portfolio of the risk metrics
+// instead: drifts port->mu (or r) and one per-path channel, the horizon P&L
+// (value of the holdings at T minus their Black-Scholes value
+// BasketParams::premium at 0); the price, variance and std_err of its result
+// describe that P&L.
+//
 // Quasi-Monte Carlo inputs of a basket run (device direction words and
 // shifts) and the run's geometric-basket mean, returned to the caller.
 struct BasketQmc {
@@ -1094,70 +1060,73 @@ struct BasketQmc {
   double geo_mean;
 };
 
-// Host part of a basket run: checks, Cholesky factor, packed L' and the
-// per-asset constants uploaded to the workspace (after the moment area of
-// run_moments), and the kernel parameters. *o_run is o0 with the workspace
-// narrowed to the moment area.
+// Set-up of a basket run whose arguments validate_basket has accepted: the
+// factor in device memory, the launch that packs L' and the per-asset
+// constants into the workspace (after the moment area of run_moments), and
+// the kernel parameters. *o_run is o0 with the workspace narrowed to the
+// moment area. The constants pass through the context's pinned memory, behind
+// the moments of any run, and nothing here waits for the device: the checks
+// twice, L' packed on the host, two copies and a wait took 120 us of a risk
+// call at d = 112 and 260 us of a basket at d = 256.
+constexpr size_t kBasketStage = 1024;                 // doubles: after the moments
 mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64_t n_paths,
                        uint32_t n_steps, uint64_t seed, const mc_options& o0,
-                       const mc_portfolio* port, double premium, const BasketQmc* qmc,
+                       const mc_portfolio* port, const BasketQmc* qmc, const BasketZero& zero,
                        BasketParams* p_out, int* prec_out, mc_options* o_run) {
-  std::vector<double> L;
-  mc_status st = validate_basket(ctx, m, f, n_steps, o0, &L);
-  if (st != MC_OK) return st;
+  static_assert((size_t)MC_QMC_MAX_REPLICATES * n_moments(3) <= kBasketStage, "moments");
   const uint32_t d = m->dim;
+  const size_t dd = (size_t)d * d;
+  if (ctx->chol_L.size() != dd) return fail(ctx, MC_ERR_DEVICE, "no factor for this basket");
   const double dt = m->T / n_steps, inv_ln2 = 1.0 / std::log(2.0);
-  std::vector<double> Ls((size_t)d * d);
-  for (uint32_t a = 0; a < d; ++a)
-    for (uint32_t b = 0; b < d; ++b)
-      Ls[(size_t)a * d + b] = m->sigma[a] * std::sqrt(dt) * inv_ln2 * L[(size_t)a * d + b];
   const int prec = basket_prec(o0.prec);
-  std::vector<uint16_t> frag;
-  if (prec == BK_FP16) {
-    pack_fragments(d, 1, Ls, [](double v, int) { return to_f16_rne((float)v); }, &frag);
-  } else {
-    // Terms of v in bfloat16, each the rounding of what the earlier ones
-    // leave: one, hi + lo of the double (split BF16), or the 24 bits of the
-    // float as three.
-    const bool from_float = prec != BK_BF16X2;
-    pack_fragments(d, basket_l_terms(prec), Ls, [from_float](double v, int t) {
-      double rest = from_float ? (double)(float)v : v;
-      uint16_t h = to_bf16_rne((float)v);
-      for (int q = 0; q < t; ++q) {
-        rest -= (double)from_bf16(h);
-        h = to_bf16_rne((float)rest);
-      }
-      return h;
-    }, &frag);
+  const RunLayout Lay = basket_layout(n_paths, 3, o0.path_values != nullptr);
+  const size_t off_blk = align256(Lay.bytes);
+  const size_t off_asset = off_blk + align256(basket_frag_bytes(d, o0.prec));
+  char* base = nullptr;
+  mc_status st = get_ws(ctx, o0, basket_ws_bytes(Lay.bytes, d, o0.prec), &base);
+  if (st != MC_OK) return st;
+  hipStream_t s = stream_of(ctx, o0);
+  if (!ctx->dev_L_valid) {
+    if (ctx->dev_L_count < dd) {
+      if (ctx->dev_L) HIP_TRY(ctx, hipFree(ctx->dev_L));
+      ctx->dev_L = nullptr;
+      ctx->dev_L_count = 0;
+      HIP_TRY(ctx, hipMalloc((void**)&ctx->dev_L, dd * sizeof(double)));
+      ctx->dev_L_count = dd;
+    }
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->dev_L, ctx->chol_L.data(), dd * sizeof(double),
+                                hipMemcpyHostToDevice, s));
+    HIP_TRY(ctx, hipStreamSynchronize(s));
+    ctx->dev_L_valid = true;
   }
-  const size_t blk_bytes = frag.size() * sizeof(uint16_t);
-  // Per-asset constants: n mu_a in log2 units, w_a S0_a, w_a ln 2, S0_a.
-  std::vector<float> asset(4 * 256, 0.f);
+  // Staged: sigma, then per asset n mu_a in log2 units, w_a S0_a, w_a ln 2, S0_a.
+  st = get_pinned(ctx, kBasketStage + 256 + 4 * 256 / 2);
+  if (st != MC_OK) return st;
+  double* sigma = ctx->pinned + kBasketStage;
+  float* asset = (float*)(sigma + 256);
   double geo0 = 0.0;
   for (uint32_t a = 0; a < d; ++a) {
     const double w = f->weights ? f->weights[a] : 1.0 / d;
     const double drift = (port && port->mu) ? port->mu[a] : m->r;
     const double mu = (drift - 0.5 * m->sigma[a] * m->sigma[a]) * dt * inv_ln2;
+    sigma[a] = m->sigma[a];
     asset[a] = (float)(n_steps * mu);
     asset[256 + a] = (float)(w * m->S0[a]);
     asset[512 + a] = (float)(w * std::log(2.0));
     asset[768 + a] = (float)m->S0[a];
     geo0 += w * std::log(m->S0[a]);
   }
-  const RunLayout Lay = basket_layout(n_paths, 3, o0.path_values != nullptr);
-  const size_t off_blk = align256(Lay.bytes);
-  const size_t off_asset = off_blk + align256(blk_bytes);
-  const size_t total = off_asset + align256(asset.size() * 4);
-  if (total != basket_ws_bytes(Lay.bytes, d, o0.prec))
-    return fail(ctx, MC_ERR_DEVICE, "basket workspace layout mismatch");
-  char* base = nullptr;
-  st = get_ws(ctx, o0, total, &base);
-  if (st != MC_OK) return st;
-  hipStream_t s = stream_of(ctx, o0);
-  HIP_TRY(ctx, hipMemcpyAsync(base + off_blk, frag.data(), blk_bytes, hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, hipMemcpyAsync(base + off_asset, asset.data(), asset.size() * 4,
-                              hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, hipStreamSynchronize(s));   // host vectors go out of scope
+  BasketPack k{};
+  k.L = ctx->dev_L;
+  k.sigma = sigma;
+  k.asset = asset;
+  k.sdt = std::sqrt(dt);
+  k.inv_ln2 = inv_ln2;
+  k.d = d;
+  k.frag = (uint16_t*)(base + off_blk);
+  k.asset_out = (float*)(base + off_asset);
+  k.zero = zero;
+  HIP_TRY(ctx, launch_basket_pack(k, prec, s));
   mc_options o = o0;
   o.workspace = base;
   o.workspace_bytes = Lay.bytes;
@@ -1187,7 +1156,6 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     p.pm[k] = (float)port->strike_mult[k];
     p.pq[k] = (float)port->quantity[k];
   }
-  p.premium = premium;
   p.qV = qmc ? qmc->V : nullptr;
   p.qshift = qmc ? qmc->shift : nullptr;
   *p_out = p;
@@ -1196,19 +1164,13 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   return MC_OK;
 }
 
-mc_status basket_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64_t n_paths,
-                       uint32_t n_steps, uint64_t seed, const mc_options& o0, mc_result* out,
-                       const mc_portfolio* port = nullptr, double premium = 0.0,
-                       BasketQmc* qmc = nullptr) {
-  BasketParams p{};
-  int prec = BK_FP32;
-  mc_options o;
-  mc_status st = basket_setup(ctx, m, f, n_paths, n_steps, seed, o0, port, premium, qmc, &p, &prec,
-                              &o);
-  if (st != MC_OK) return st;
+// Runs what basket_setup has prepared (o: its narrowed options).
+mc_status basket_run(mc_context* ctx, BasketParams& p, int prec, const mc_options& o,
+                     mc_result* out, double* geo_mean = nullptr) {
+  const bool port = p.n_strikes != 0;
   Moments mom;
   double kms = 0.0;
-  st = run_moments(ctx, o, n_paths, port ? 1 : 3, o0.path_values,
+  mc_status st = run_moments(ctx, o, p.n_paths, port ? 1 : 3, o.path_values,
                    [&](double* partials, double* path_out, hipStream_t ss, uint32_t* nb) {
                      p.partials = partials;
                      p.path_out = path_out;
@@ -1222,14 +1184,26 @@ mc_status basket_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   fill_channel(mom, 0, &r.price, &r.variance, &r.std_err);
   r.plain_price = r.price;
   r.plain_std_err = r.std_err;
-  if (!port && (o0.greeks & MC_GREEK_DELTA)) fill_channel(mom, 2, &r.delta, &v, &r.delta_se);
-  if (qmc) qmc->geo_mean = mom.mean(1);
+  if (!port && (o.greeks & MC_GREEK_DELTA)) fill_channel(mom, 2, &r.delta, &v, &r.delta_se);
+  if (geo_mean) *geo_mean = mom.mean(1);
   r.vrf = 1.0;
   r.n_paths = (uint64_t)mom.n;
   r.n_nonfinite = (uint64_t)mom.nonfinite;
   r.kernel_ms = kms;
   *out = r;
   return MC_OK;
+}
+
+mc_status basket_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64_t n_paths,
+                       uint32_t n_steps, uint64_t seed, const mc_options& o, mc_result* out,
+                       BasketQmc* qmc = nullptr) {
+  BasketParams p{};
+  int prec = BK_FP32;
+  mc_options orun;
+  mc_status st =
+      basket_setup(ctx, m, f, n_paths, n_steps, seed, o, nullptr, qmc, {}, &p, &prec, &orun);
+  if (st != MC_OK) return st;
+  return basket_run(ctx, p, prec, orun, out, qmc ? &qmc->geo_mean : nullptr);
 }
 
 // ---- multilevel helpers ----
@@ -1574,6 +1548,7 @@ mc_status mc_destroy(mc_context* ctx) {
   if (ctx->qmc_buf) (void)hipFree(ctx->qmc_buf);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->clock) (void)hipHostFree(ctx->clock);
+  if (ctx->dev_L) (void)hipFree(ctx->dev_L);
   if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
   if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
   if (ctx->lsm_buf) (void)hipFree(ctx->lsm_buf);
@@ -2020,7 +1995,7 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     HIP_TRY(ctx, launch_qmc_shifts((uint32_t)seed, (uint32_t)(seed >> 32), o0.stream_tag + 6u, 0,
                                    1, dims, (uint32_t*)q.shift, s));
     mc_result pr{};
-    st = basket_price(ctx, m, f, n_points, n_steps, seed, o0, &pr, nullptr, 0.0, &q);
+    st = basket_price(ctx, m, f, n_points, n_steps, seed, o0, &pr, &q);
     if (st != MC_OK) return st;
     r.replicate_price[0] = pr.price;
     r.replicate_geo[0] = q.geo_mean;
@@ -2032,7 +2007,7 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     BasketParams p{};
     int prec = BK_FP32;
     mc_options orun;
-    st = basket_setup(ctx, m, f, n_points, n_steps, seed, o0, nullptr, 0.0, &q0, &p, &prec, &orun);
+    st = basket_setup(ctx, m, f, n_points, n_steps, seed, o0, nullptr, &q0, {}, &p, &prec, &orun);
     if (st != MC_OK) return st;
     const RunLayout Lay = basket_layout(n_points, 3, false);
     const size_t b_shift = align256((size_t)n_replicates * dims * sizeof(uint32_t));
@@ -2121,11 +2096,6 @@ mc_status mc_risk(mc_context* ctx, const mc_model* m, const mc_portfolio* pf, ui
   if (k < 2 || k > n_paths)
     return fail(ctx, MC_ERR_INVALID_ARG, "n_paths (1 - alpha) must be at least 1");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, MC_ERR_DEVICE, "hipSetDevice");
-  double V0 = 0.0;
-  for (uint32_t a = 0; a < m->dim; ++a)
-    for (uint32_t j = 0; j < pf->n_strikes; ++j)
-      V0 += pf->quantity[j] *
-            host::bs_call(m->S0[a], pf->strike_mult[j] * m->S0[a], m->r, m->sigma[a], m->T);
   // Device scratch: per-path P&L, selection state and histogram, tail partials.
   const size_t bytes_x = align256((size_t)n_paths * sizeof(double));
   const size_t bytes_st = align256(kSelectStateBytes);
@@ -2140,11 +2110,22 @@ mc_status mc_risk(mc_context* ctx, const mc_model* m, const mc_portfolio* pf, ui
   uint32_t* hist = (uint32_t*)(base + bytes_x + bytes_st);
   double* partials = (double*)(base + bytes_x + bytes_st + bytes_h);
   double* tail = (double*)(base + bytes_x + bytes_st + bytes_h + bytes_p);
+  BasketParams p{};
+  int prec = BK_FP32;
+  mc_options orun;
+  st = basket_setup(ctx, m, &f, n_paths, n_steps, seed, ov, pf, nullptr, {}, &p, &prec, &orun);
+  if (st != MC_OK) return st;
+  double V0 = 0.0;
+  for (uint32_t a = 0; a < m->dim; ++a)
+    for (uint32_t j = 0; j < pf->n_strikes; ++j)
+      V0 += pf->quantity[j] *
+            host::bs_call(m->S0[a], pf->strike_mult[j] * m->S0[a], m->r, m->sigma[a], m->T);
+  p.premium = V0;
   mc_result pr{};
   {
     SinkGuard guard{ctx};
     ctx->sink = x;
-    st = basket_price(ctx, m, &f, n_paths, n_steps, seed, ov, &pr, pf, V0);
+    st = basket_run(ctx, p, prec, orun, &pr);
     if (st != MC_OK) return st;
   }
   if (pr.n_nonfinite != 0) return fail(ctx, MC_ERR_DEVICE, "non-finite P&L on %llu paths",

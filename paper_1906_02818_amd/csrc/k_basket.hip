@@ -151,6 +151,63 @@ __device__ __forceinline__ Words4 sobol_words(const uint32_t* __restrict__ V,
   return Words4{x[0], x[1], x[2], x[3]};
 }
 
+// Term t of v in the 16-bit type: bfloat16 terms are each the rounding of what
+// the earlier ones leave of the double (split BF16) or of its float (the
+// float's 24 bits as three); half has one.
+__device__ __forceinline__ uint16_t to_bf16(float f) {
+  const uint32_t u = __float_as_uint(f);
+  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+}
+template <int PREC>
+__device__ __forceinline__ void split_terms(double v, uint16_t (&h)[Form<PREC>::NL]) {
+  if constexpr (PREC == BK_FP16) {
+    const _Float16 x = (_Float16)(float)v;
+    __builtin_memcpy(&h[0], &x, 2);
+  } else {
+    double rest = PREC == BK_BF16X2 ? v : (double)(float)v;
+#pragma unroll
+    for (int t = 0; t < Form<PREC>::NL; ++t) {
+      h[t] = to_bf16((float)rest);
+      rest -= (double)__uint_as_float((uint32_t)h[t] << 16);
+    }
+  }
+}
+
+// One workgroup per four fragments of L' (a lane writes its eight entries of
+// each term), one for the asset table, and the words to clear. Latency of a
+// launch and of reads over PCIe; 4 us.
+template <int PREC>
+__global__ __launch_bounds__(256) void basket_pack_kernel(const BasketPack K) {
+  constexpr int NL = Form<PREC>::NL;
+  const uint32_t n_pairs = basket_pairs(K.d >> 4);
+  const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+  for (uint32_t i = gid; i < K.zero.n; i += gridDim.x * 256u) K.zero.words[i] = 0u;
+  if (blockIdx.x == gridDim.x - 1u) {
+    for (uint32_t i = threadIdx.x; i < 4u * 256u; i += 256u)
+      if ((i & 255u) < K.d) K.asset_out[i] = K.asset[i];
+    return;
+  }
+  const uint32_t pair = gid >> 6, lane = gid & 63u;
+  if (pair >= n_pairs) return;
+  uint32_t rb = 0;
+  while (basket_pairs(rb + 1u) <= pair) ++rb;
+  const uint32_t kb = pair - basket_pairs(rb);
+  const uint32_t a = 16u * rb + (lane & 15u), b0 = 32u * kb + 8u * (lane >> 4);
+  const double scale = K.sigma[a] * K.sdt * K.inv_ln2;
+  uint16_t h[8][NL];
+#pragma unroll
+  for (uint32_t e = 0; e < 8u; ++e) {
+    const uint32_t b = b0 + e;
+    split_terms<PREC>(b <= a ? scale * K.L[(size_t)a * K.d + b] : 0.0, h[e]);
+  }
+#pragma unroll
+  for (int t = 0; t < NL; ++t) {
+    uint16_t* out = K.frag + (((size_t)t * n_pairs + pair) * 64u + lane) * 8u;
+#pragma unroll
+    for (uint32_t e = 0; e < 8u; ++e) out[e] = h[e][t];
+  }
+}
+
 // Row block i of the wave's set of the triangle's 16-row blocks, S sets per
 // workgroup: consecutive pairs sum to a constant, so the sets have equal
 // shares of the triangle.
@@ -350,9 +407,11 @@ hipError_t launch_w(const BasketParams& p, hipStream_t s, uint32_t nb) {
   static_assert(kBasketMaxDim <= 4 * 8 * 8, "row blocks of the largest form");
   if (p.d > (uint32_t)(4 * W * RPW)) return hipErrorInvalidValue;
   const size_t lds = (size_t)p.d * kRow * sizeof(float);
-  hipError_t e = hipFuncSetAttribute((const void*)basket_kernel<PREC, PORT, QMC, W, RPW>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
+  if (lds > 32768) {                       // above it: the default limit is 64 KB with the static part
+    const hipError_t e = hipFuncSetAttribute((const void*)basket_kernel<PREC, PORT, QMC, W, RPW>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((basket_kernel<PREC, PORT, QMC, W, RPW>), dim3(nb), dim3(64 * W), lds, s, p);
   return hipGetLastError();
 }
@@ -403,6 +462,19 @@ hipError_t launch_any(const BasketParams& p, int prec, hipStream_t s, uint32_t n
 
 int basket_l_terms(int prec) {
   return prec == BK_FP32 ? Form<BK_FP32>::NL : prec == BK_BF16X2 ? Form<BK_BF16X2>::NL : 1;
+}
+
+hipError_t launch_basket_pack(const BasketPack& k, int prec, hipStream_t s) {
+  if (k.d < 16 || k.d > (uint32_t)kBasketMaxDim || k.d % 16 != 0) return hipErrorInvalidValue;
+  const dim3 grid((basket_pairs(k.d / 16) + 3) / 4 + 1);
+  switch (prec) {
+#define MCP_PACK(P) \
+  case P: hipLaunchKernelGGL(basket_pack_kernel<P>, grid, dim3(256), 0, s, k); break;
+    MCP_PACK(BK_FP32) MCP_PACK(BK_BF16) MCP_PACK(BK_FP16) MCP_PACK(BK_BF16X2)
+#undef MCP_PACK
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 // A workgroup ends with a reduction and a moment vector, so it takes enough

@@ -177,6 +177,24 @@ struct BasketParams {
   uint64_t* clock;        // start stamp, or nullptr
 };
 constexpr int kMaxStrikes = 8;
+// Words a run's set-up launch clears for later kernels of the call (n <= 2^20).
+struct BasketZero {
+  uint32_t* words = nullptr;
+  uint32_t n = 0;
+};
+// Packs L' = diag(sigma_a sdt inv_ln2) L into Lfrag form and copies the asset
+// table from pinned memory.
+struct BasketPack {
+  const double* L;        // [d][d] lower factor (device)
+  const double* sigma;    // [d] (pinned)
+  const float* asset;     // [4][256] (pinned)
+  double sdt, inv_ln2;
+  uint32_t d;
+  uint16_t* frag;
+  float* asset_out;
+  BasketZero zero;
+};
+hipError_t launch_basket_pack(const BasketPack& k, int prec, hipStream_t s);
 hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks);
 // All n_rep randomised-QMC replicates of p in one launch (p.qshift holds
 // n_rep rows of p.q_dims shifts); *blocks_per_rep = one replicate's blocks.

@@ -283,3 +283,33 @@ def test_lsm_sweeps_and_reductions(ctx, d, degree, M, N, n_oos, offset):
     assert abs(g["price"] - o["price"]) < 2e-6 * K
     n_itm = np.asarray(g["n_itm"], dtype=float)[:M]
     assert np.abs(n_itm - o["n_itm"][:M]).max() <= 1 + 1e-6 * N
+
+
+@pytest.mark.parametrize("prec", [mc.MC_FP32, mc.MC_BF16_GEMM])
+def test_basket_factor_follows_the_matrix(ctx, prec):
+    """The factor kept from the last call is used for equal contents only:
+    changed in place, of another dimension and back again, each call equals a
+    fresh context's, bit for bit."""
+    corr = {d: np.full((d, d), 0.3) + 0.7 * np.eye(d) for d in (16, 64)}
+
+    def price(c, d):
+        m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.03, T=1.0,
+                     sigma=np.linspace(0.1, 0.4, d), corr=corr[d])
+        r = mc.mc_price(c, m, mc.Payoff(mc.MC_BASKET_CALL, 100.0), 5000, 3, SEED,
+                        mc.Options(prec=prec))
+        return r["price"], r["std_err"]
+
+    def fresh(d):
+        c = mc.mc_create(0)
+        out = price(c, d)
+        c.close()
+        return out
+    for d in (64, 16, 16, 64):
+        assert price(ctx, d) == fresh(d)
+        corr[d][2, 1] = corr[d][1, 2] = corr[d][1, 2] + 0.1
+        assert price(ctx, d) == fresh(d)
+    corr[64][0, 1] = 0.2                     # no longer symmetric
+    with pytest.raises(Exception, match="symmetric"):
+        price(ctx, 64)
+    corr[64][0, 1] = corr[64][1, 0]
+    assert price(ctx, 64) == fresh(64)
