@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <functional>
 #include <vector>
 
 #include "../../include/mcpath.h"
@@ -414,11 +415,13 @@ void merge_moment_vec(double* acc, const double* b, int C) {
 }
 
 // Launch wrapper: runs `launch` (which enqueues the path kernel), then the
-// final reduction, and brings the moments to the host.
+// final reduction and what `queued` adds behind it, and brings the moments to
+// the host.
 template <typename F>
 mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, int C,
                       double* host_path_values, F&& launch, Moments* out, double* kernel_ms,
-                      uint32_t paths_per_block = kBlock, uint32_t max_blocks = UINT32_MAX) {
+                      uint32_t paths_per_block = kBlock, uint32_t max_blocks = UINT32_MAX,
+                      const std::function<hipError_t(hipStream_t)>& queued = nullptr) {
   if (C < 1 || C > kMaxChannels) return fail(ctx, MC_ERR_DEVICE, "channel count %d", C);
   const RunLayout L =
       layout_for(n_paths, C, host_path_values != nullptr, paths_per_block, max_blocks);
@@ -440,6 +443,7 @@ mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, in
   HIP_TRY(ctx, launch(partials, path_out, s, &nb));
   if (nb == 0 || nb > L.n_blocks) return fail(ctx, MC_ERR_DEVICE, "block count mismatch");
   HIP_TRY(ctx, launch_final_merge(partials, nb, (uint32_t)C, 1, hmom, s, ctx->clock + 1));
+  if (queued) HIP_TRY(ctx, queued(s));
   if (host_path_values && !ctx->sink)
     HIP_TRY(ctx, hipMemcpyAsync(host_path_values, path_out, n_paths * C * sizeof(double),
                                 hipMemcpyDeviceToHost, s));
@@ -1166,7 +1170,8 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
 
 // Runs what basket_setup has prepared (o: its narrowed options).
 mc_status basket_run(mc_context* ctx, BasketParams& p, int prec, const mc_options& o,
-                     mc_result* out, double* geo_mean = nullptr) {
+                     mc_result* out, double* geo_mean = nullptr,
+                     const std::function<hipError_t(hipStream_t)>& queued = nullptr) {
   const bool port = p.n_strikes != 0;
   Moments mom;
   double kms = 0.0;
@@ -1177,7 +1182,7 @@ mc_status basket_run(mc_context* ctx, BasketParams& p, int prec, const mc_option
                      p.clock = ctx->clock;
                      return launch_basket(p, prec, ss, nb);
                    },
-                   &mom, &kms, kBasketTile, kBasketMaxBlocks);
+                   &mom, &kms, kBasketTile, kBasketMaxBlocks, queued);
   if (st != MC_OK) return st;
   mc_result r{};
   double v;
@@ -2096,24 +2101,27 @@ mc_status mc_risk(mc_context* ctx, const mc_model* m, const mc_portfolio* pf, ui
   if (k < 2 || k > n_paths)
     return fail(ctx, MC_ERR_INVALID_ARG, "n_paths (1 - alpha) must be at least 1");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, MC_ERR_DEVICE, "hipSetDevice");
-  // Device scratch: per-path P&L, selection state and histogram, tail partials.
+  // Device scratch: per-path P&L, selection state, its list and partials.
   const size_t bytes_x = align256((size_t)n_paths * sizeof(double));
-  const size_t bytes_st = align256(kSelectStateBytes);
-  const size_t bytes_h = align256(256 * sizeof(uint32_t));
-  const size_t bytes_p = align256((size_t)2 * 1024 * sizeof(double));
+  const size_t bytes_st = align256(sizeof(SelectState));
+  const size_t bytes_l = align256(kSelectList * sizeof(uint64_t));
   char* base = nullptr;
-  st = get_mlmc_buf(ctx, bytes_x + bytes_st + bytes_h + bytes_p + align256(2 * sizeof(double)),
-                    &base);
+  st = get_mlmc_buf(ctx, bytes_x + bytes_st + bytes_l + kSelectPartialBytes, &base);
   if (st != MC_OK) return st;
   double* x = (double*)base;
-  void* state = base + bytes_x;
-  uint32_t* hist = (uint32_t*)(base + bytes_x + bytes_st);
-  double* partials = (double*)(base + bytes_x + bytes_st + bytes_h);
-  double* tail = (double*)(base + bytes_x + bytes_st + bytes_h + bytes_p);
+  SelectState* state = (SelectState*)(base + bytes_x);
+  uint64_t* list = (uint64_t*)(base + bytes_x + bytes_st);
+  double* partials = (double*)(base + bytes_x + bytes_st + bytes_l);
+  // The selection's result: pinned memory behind the moments.
+  constexpr size_t kRiskResult = kBasketStage - 16;
+  static_assert(sizeof(SelectResult) <= 16 * sizeof(double) && n_moments(1) <= kRiskResult, "staging");
   BasketParams p{};
   int prec = BK_FP32;
   mc_options orun;
-  st = basket_setup(ctx, m, &f, n_paths, n_steps, seed, ov, pf, nullptr, {}, &p, &prec, &orun);
+  static_assert(offsetof(SelectState, hist) == 0 &&
+                offsetof(SelectState, arrivals) == (kSelectZeroWords - 1) * sizeof(uint32_t), "zeroed words");
+  st = basket_setup(ctx, m, &f, n_paths, n_steps, seed, ov, pf, nullptr,
+                    {(uint32_t*)state, kSelectZeroWords}, &p, &prec, &orun);
   if (st != MC_OK) return st;
   double V0 = 0.0;
   for (uint32_t a = 0; a < m->dim; ++a)
@@ -2121,46 +2129,36 @@ mc_status mc_risk(mc_context* ctx, const mc_model* m, const mc_portfolio* pf, ui
       V0 += pf->quantity[j] *
             host::bs_call(m->S0[a], pf->strike_mult[j] * m->S0[a], m->r, m->sigma[a], m->T);
   p.premium = V0;
+  SelectResult* sel = (SelectResult*)(ctx->pinned + kRiskResult);
   mc_result pr{};
   {
     SinkGuard guard{ctx};
     ctx->sink = x;
-    st = basket_run(ctx, p, prec, orun, &pr);
+    st = basket_run(ctx, p, prec, orun, &pr, nullptr, [&](hipStream_t ss) {
+      return launch_select(x, n_paths, k, state, list, partials, sel, ss, ctx->clock + 2);
+    });
     if (st != MC_OK) return st;
   }
   if (pr.n_nonfinite != 0) return fail(ctx, MC_ERR_DEVICE, "non-finite P&L on %llu paths",
                                        (unsigned long long)pr.n_nonfinite);
   hipStream_t s = stream_of(ctx, o0);
-  st = get_pinned(ctx, 4);
-  if (st != MC_OK) return st;
-  uint32_t nb = 0;
-  HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
-  HIP_TRY(ctx, launch_select_kth(x, n_paths, k, state, hist, s));
-  HIP_TRY(ctx, launch_tail_sum(x, n_paths, state, partials, s, &nb));
-  HIP_TRY(ctx, launch_final_reduce(partials, nb, 2, tail, s));
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-  HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned, state, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-  HIP_TRY(ctx, hipMemcpyAsync(ctx->pinned + 1, tail, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+  if (!sel->done) HIP_TRY(ctx, launch_select_rest(x, n_paths, state, list, partials, sel, s));
   if (o0.path_values)
     HIP_TRY(ctx, hipMemcpyAsync(o0.path_values, x, n_paths * sizeof(double),
                                 hipMemcpyDeviceToHost, s));
-  HIP_TRY(ctx, hipStreamSynchronize(s));
-  float ms = 0.f;
-  HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
-  uint64_t key;
-  std::memcpy(&key, ctx->pinned, sizeof(key));
+  if (!sel->done || o0.path_values) HIP_TRY(ctx, hipStreamSynchronize(s));
   mc_risk_result r{};
-  r.quantile_pnl = select_key_to_value(key);
+  r.quantile_pnl = select_key_to_value(sel->key);
   r.var = -r.quantile_pnl;
-  r.n_tail = (uint64_t)ctx->pinned[1];
-  r.cvar = r.n_tail ? -ctx->pinned[2] / ctx->pinned[1] : NAN;
+  r.n_tail = (uint64_t)sel->n_tail;
+  r.cvar = r.n_tail ? -sel->tail_sum / sel->n_tail : NAN;
   r.pnl_mean = pr.price;
   r.pnl_std_err = pr.std_err;
   r.premium = V0;
   r.k = k;
   r.n_paths = pr.n_paths;
   r.kernel_ms = pr.kernel_ms;
-  r.select_ms = ms;
+  r.select_ms = (double)(sel->end - ctx->clock[2]) / ctx->clock_khz;
   *out = r;
   return MC_OK;
 }

@@ -31,13 +31,41 @@
 
 namespace mcp {
 
+// What one workgroup hands to another of the same launch goes through loads
+// and stores of device scope, past the dies' own L2 caches. (Plain stores and
+// a fence per wave, which writes a whole L2 back, took a launch of 196
+// workgroups from 5 to 30 us.)
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void store_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The start of a launch on the device's constant clock, written by its first
 // workgroup (clock: host memory, or nullptr). Two event records around a
 // kernel cost a call 7.5 us (22.9 -> 15.3 us for a short kernel, a merge and
 // the wait); a stamp costs nothing that shows.
 __device__ __forceinline__ void stamp(uint64_t* clock) {
   if (clock != nullptr && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0)
-    *clock = (uint64_t)wall_clock64();
+    store_agent(clock, (uint64_t)wall_clock64());
+}
+
+// True in the workgroup of the launch that arrives last: every store_agent and
+// device-scope atomic of the others is then visible to its load_agent. The
+// counter, zero before the launch, is left at zero.
+__device__ __forceinline__ bool arrives_last(uint32_t* arrivals) {
+  __shared__ uint32_t order;
+  __builtin_amdgcn_s_waitcnt(0);           // this wave's stores have arrived
+  __syncthreads();
+  if (threadIdx.x == 0u) {
+    order = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (order == gridDim.x - 1u) *arrivals = 0u;
+  }
+  __syncthreads();
+  return order == gridDim.x - 1u;
 }
 
 // v of the lane whose number differs in bit OFF (a power of two up to 32),

@@ -1,37 +1,13 @@
 // Second stage of the averaging reduction (Eq. 3) and its variance term
 // (Sec. V-B), the reduction of a multilevel correction (difference of two
-// runs on the same paths), plain sums, and the
-// diagnostic kernels that expose the device random numbers for bit-exact
-// checks.
+// runs on the same paths), and the diagnostic kernels that expose the device
+// random numbers for bit-exact checks.
 #include "device/reduce.h"
 #include "device/rng.h"
 #include "mc_internal.h"
 
 namespace mcp {
 namespace {
-
-// Plain sums (counts, tail sums, gradients): one workgroup per entry m of
-// batch b = blockIdx.y; thread t adds blocks t, t+256, ... in order, then a
-// fixed-shape tree adds the 256 partial sums. Deterministic. partials
-// [b][m][n_blocks], out [b][n_mom].
-__global__ __launch_bounds__(256) void final_reduce_kernel(const double* __restrict__ partials,
-                                                           uint32_t n_blocks,
-                                                           double* __restrict__ out) {
-  __shared__ double sh[256];
-  const uint32_t m = blockIdx.x;
-  partials += (size_t)blockIdx.y * gridDim.x * n_blocks;
-  out += (size_t)blockIdx.y * gridDim.x;
-  const double* row = partials + (size_t)m * n_blocks;
-  double s = 0.0;
-  for (uint32_t i = threadIdx.x; i < n_blocks; i += 256) s += row[i];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[m] = sh[0];
-}
 
 // Moment vectors of C channels (count, means, co-moments): one workgroup of
 // NT threads per batch b = blockIdx.x merges the block-major partials
@@ -194,20 +170,6 @@ hipError_t launch_final_merge(double* partials, uint32_t n_blocks, uint32_t C,
     case 9: return merge_one<9>(partials, n_blocks, n_batch, out, s, clock);
   }
   return hipErrorInvalidValue;
-}
-
-hipError_t launch_final_reduce(const double* partials, uint32_t n_blocks, uint32_t n_mom,
-                               double* out, hipStream_t s) {
-  hipLaunchKernelGGL(final_reduce_kernel, dim3(n_mom), dim3(256), 0, s, partials, n_blocks, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_final_reduce_batch(const double* partials, uint32_t n_blocks, uint32_t n_mom,
-                                     uint32_t n_batch, double* out, hipStream_t s, uint64_t* clock) {
-  if (n_blocks == 0 || n_mom == 0 || n_batch == 0 || n_batch > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(final_reduce_kernel, dim3(n_mom, n_batch), dim3(256), 0, s, partials,
-                     n_blocks, out);
-  return hipGetLastError();
 }
 
 hipError_t launch_philox_words(uint32_t k0, uint32_t k1, uint32_t tag, uint64_t n,

@@ -23,8 +23,8 @@
 // hold up the next kernel).
 //
 // Measured, max call on 2 assets, degree 2, 9 dates, 2^22 paths and as many
-// out of sample: simulation 79 us, the 8 dates 229 (updates 176), out of
-// sample 88, the call 441 us; 575 with events around each stage, the solve as
+// out of sample: simulation 79 us, the 8 dates 218 (updates 176), out of
+// sample 88, the call 431 us; 575 with events around each stage, the solve as
 // a launch of its own and per-lane Philox keys. The simulation writes 268 MB
 // (56 us at the rate of a copy) next to 50 us of issue; the out-of-sample
 // kernel is VALU issue, 70 us of Philox, Box-Muller and the FP64 rule.
@@ -368,8 +368,8 @@ __device__ __forceinline__ void solve_date(const double* sh, uint32_t j, const L
   for (int a = 0; a < NU; ++a)
 #pragma unroll
     for (int c = a; c < NU; ++c, ++m) {
-      if (c < NF) G[c][a] = sh[m];
-      else if (a < NF) b[a] = sh[m];
+      if (c < NF) G[c][a] = load_agent(&sh[m]);
+      else if (a < NF) b[a] = load_agent(&sh[m]);
     }
   bool ok = G[0][0] >= (double)NF;  // G[0][0] counts the in-the-money paths
 #pragma unroll
@@ -416,7 +416,7 @@ __device__ __forceinline__ void solve_date(const double* sh, uint32_t j, const L
 // the host.
 //
 // Bound: latency, of a launch, of loads from the other dies' memory, and of a
-// chain of square roots and divisions in one thread: 6.5 us for 39 moments of
+// chain of square roots and divisions in one thread: 5.4 us for 39 moments of
 // 1024 blocks (8.7 us by one workgroup, whose loads its own CU limits; 8 us
 // and a gap as two launches).
 constexpr int kLsmReduceThreads = 256;
@@ -439,21 +439,10 @@ __global__ __launch_bounds__(kLsmReduceThreads) void lsm_reduce_kernel(
       }
     }
     const double v = wave_sum((a[0] + a[2]) + (a[1] + a[3]));
-    if (lane == 0u) r.sums[m] = v;
+    if (lane == 0u) store_agent(&r.sums[m], v);
   }
-  // The last workgroup to arrive sees every row: each wave makes its row
-  // visible to the device before its workgroup arrives, and the last one
-  // drops what it may have cached. It leaves the counter at zero.
-  __shared__ uint32_t arrived;
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0u)
-    arrived = __hip_atomic_fetch_add(r.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  if (arrived != gridDim.x - 1u) return;
-  __threadfence();
+  if (!arrives_last(r.arrivals)) return;
   if (threadIdx.x == 0u) {
-    *r.arrivals = 0u;
     if constexpr (NF > 0) {
       if (j != 0u) solve_date<NF>(r.sums, j, r);
     }
@@ -461,7 +450,7 @@ __global__ __launch_bounds__(kLsmReduceThreads) void lsm_reduce_kernel(
   }
   if (r.host == nullptr) return;
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < r.n_results; i += kLsmReduceThreads) r.host[i] = r.results[i];
+  for (uint32_t i = threadIdx.x; i < r.n_results; i += kLsmReduceThreads) r.host[i] = load_agent(&r.results[i]);
 }
 
 template <int D, int DEG, int PF>

@@ -209,18 +209,31 @@ hipError_t launch_qmc_shifts(uint32_t k0, uint32_t k1, uint32_t tag, uint64_t re
                              uint32_t n_rep, uint32_t n_dims, uint32_t* shift, hipStream_t s);
 
 // ---- Order statistic and tail mean of per-path values (risk metrics) ----
-// Exact k-th smallest (1-based) of x[0..n) by an 8-pass radix select on the
-// order-preserving 64-bit keys of the doubles, then the count and sum of the
-// values strictly below it. `state` and `hist` are small device scratch
-// areas (kSelectStateBytes, 256 uint32); partials holds kDiffMaxBlocks x 2
-// doubles. Everything is enqueued on s without host synchronisation.
-constexpr size_t kSelectStateBytes = 64;
-hipError_t launch_select_kth(const double* x, uint64_t n, uint64_t k, void* state, uint32_t* hist,
-                             hipStream_t s);
-hipError_t launch_tail_sum(const double* x, uint64_t n, const void* state, double* partials,
-                           hipStream_t s, uint32_t* n_blocks);
-// Host view of the selection state after the passes: the key of the k-th
-// smallest value and the value itself.
+// Exact k-th smallest (1-based) of x[0..n) and the count and sum of the values
+// below it (k_risk.hip). The state is zero in hist and arrivals before the
+// first launch of a call and again after the last.
+constexpr uint32_t kSelectDigit = 12;
+constexpr uint32_t kSelectList = 2048;       // matches sorted in LDS
+struct SelectState {
+  uint32_t hist[1u << kSelectDigit];
+  uint32_t arrivals, n_match;
+  uint64_t prefix, mask;                     // digits fixed so far, and their bits
+  uint64_t k;                                // 1-based rank still sought among the matches
+  uint64_t key_min, key_max;                 // of the matches
+};
+constexpr uint32_t kSelectZeroWords = (1u << kSelectDigit) + 1;
+constexpr size_t kSelectPartialBytes = 2 * 256 * sizeof(double);
+struct SelectResult {                        // host memory
+  uint64_t key;                              // of the k-th smallest
+  double n_tail, tail_sum;                   // values strictly below it
+  uint64_t end;                              // stamp
+  uint32_t done;                             // 0: queue launch_select_rest
+};
+hipError_t launch_select(const double* x, uint64_t n, uint64_t k, SelectState* st, uint64_t* list,
+                         double* partials, SelectResult* out, hipStream_t s, uint64_t* clock);
+hipError_t launch_select_rest(const double* x, uint64_t n, SelectState* st, uint64_t* list,
+                              double* partials, SelectResult* out, hipStream_t s);
+// Value of a key.
 double select_key_to_value(uint64_t key);
 
 // ---- Longstaff-Schwartz regression (Bermudan options) ----
@@ -365,12 +378,6 @@ hipError_t launch_grad_sum(const float* partials, uint32_t n_blocks, const CvVal
 hipError_t launch_final_merge(double* partials, uint32_t n_blocks, uint32_t C,
                               uint32_t n_batch, double* out, hipStream_t s,
                               uint64_t* clock = nullptr);
-// Plain sums: partials [n_mom][n_blocks] -> out [n_mom]; the batch form takes
-// partials [batch][n_mom][n_blocks] -> out [batch][n_mom].
-hipError_t launch_final_reduce(const double* partials, uint32_t n_blocks, uint32_t n_mom,
-                               double* out, hipStream_t s);
-hipError_t launch_final_reduce_batch(const double* partials, uint32_t n_blocks, uint32_t n_mom,
-                                     uint32_t n_batch, double* out, hipStream_t s);
 hipError_t launch_philox_words(uint32_t k0, uint32_t k1, uint32_t tag, uint64_t n,
                                const uint64_t* paths, const uint64_t* blocks, uint32_t* out,
                                hipStream_t s);

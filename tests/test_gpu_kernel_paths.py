@@ -313,3 +313,30 @@ def test_basket_factor_follows_the_matrix(ctx, prec):
         price(ctx, 64)
     corr[64][0, 1] = corr[64][1, 0]
     assert price(ctx, 64) == fresh(64)
+
+
+@pytest.mark.parametrize("N,alpha,sigma,mu,strike", [
+    (2, 0.5, 0.2, 0.05, 1.0), (513, 0.9, 0.2, 0.05, 1.0), (70001, 0.99, 0.3, 0.05, 1.0),
+    ((1 << 19) + 3, 0.95, 0.3, 0.05, 0.9),   # three digits before the list
+    (5000, 0.5, 0.2, 0.05, 50.0),            # every value equal: more than the list holds
+    (20011, 0.7, 0.4, 0.05, 2.5),            # ties at one value, and others
+    (9001, 0.95, 1e-6, 3.0, 0.0)])           # distinct values that share 24 bits
+def test_risk_selection(ctx, N, alpha, sigma, mu, strike):
+    """Order statistic and tail count exactly, the tail's mean to the rounding
+    of its sum (N values: below N 2^-53, in practice sqrt(N) of it)."""
+    d = 16
+    corr = np.full((d, d), 0.2) + 0.8 * np.eye(d)
+    m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.03, T=1.0,
+                 sigma=np.full(d, sigma), corr=corr)
+    r = mc.mc_risk(ctx, m, [strike], [1.0], alpha, N, 1, SEED, mu=np.full(d, mu),
+                   opts=mc.Options(path_values=True))
+    x = np.sort(r["pnl"])
+    k = int(math.floor(N * (1.0 - alpha))) + 1
+    assert r["k"] == k and r["quantile_pnl"] == x[k - 1]
+    tail = x[x < x[k - 1]]
+    assert r["n_tail"] == tail.size
+    if tail.size:
+        assert r["cvar"] == pytest.approx(-tail.mean(), rel=1e-12)
+    again = mc.mc_risk(ctx, m, [strike], [1.0], alpha, N, 1, SEED, mu=np.full(d, mu))
+    assert again["var"] == r["var"] and again["n_tail"] == r["n_tail"]
+    assert again["cvar"] == r["cvar"] or not tail.size
