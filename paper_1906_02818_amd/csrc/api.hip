@@ -2024,8 +2024,10 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     if (st != MC_OK) return st;
     uint32_t* shifts = (uint32_t*)base;
     double* parts = (double*)(base + b_shift);
-    HIP_TRY(ctx, launch_qmc_shifts((uint32_t)seed, (uint32_t)(seed >> 32), o0.stream_tag + 6u, 0,
-                                   n_replicates, dims, shifts, s));
+    p.q_shift_tag = o0.stream_tag + 6u;
+    if (!basket_qmc_draws_shifts(p, prec))
+      HIP_TRY(ctx, launch_qmc_shifts((uint32_t)seed, (uint32_t)(seed >> 32), p.q_shift_tag, 0,
+                                     n_replicates, dims, shifts, s));
     p.qshift = shifts;
     p.q_dims = dims;
     p.partials = parts;

@@ -96,6 +96,13 @@ __device__ __forceinline__ double lane_add(double v) {
   }
 }
 
+// Orders the wave's own LDS stores before its loads (lockstep wave).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sum over the wave, the same in every lane (every lane active).
 __device__ __forceinline__ double wave_sum(double v) {
   v = lane_add<32>(v);
@@ -361,12 +368,6 @@ __device__ __forceinline__ void block_sum_wide(const double (&acc)[M],
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int c = lane >> 2, q = lane & 3;
-  // Orders the wave's own LDS stores before its loads (lockstep wave).
-  auto wave_sync = [] {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
 #pragma unroll
   for (int m0 = 0; m0 < M; m0 += CH) {
 #pragma unroll

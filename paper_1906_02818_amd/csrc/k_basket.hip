@@ -34,6 +34,8 @@
 // per step spent 0.2 and 0.75 of its time in MFMAs, which on gfx950 do not run
 // beside FP32 VALU work of the same SIMD: an MFMA stream and an FMA stream of
 // 0.245 and 0.219 ms in different waves take 0.434 ms.
+#include <type_traits>
+
 #include "device/reduce.h"
 #include "device/rng.h"
 #include "mc_internal.h"
@@ -47,6 +49,7 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
+constexpr int kQmcWaves = 4;              // waves of a QMC workgroup: a tile each
 constexpr int kTile = kBasketTile;        // paths per tile: one per lane
 constexpr int kRow = kTile + 2;           // LDS row of an asset's sums: rows 8 apart
                                           // fall 16 banks apart (fragment reads)
@@ -109,8 +112,13 @@ __device__ __forceinline__ void add_steps(float (&s)[4], const Words4& a, const 
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       if constexpr (PREC == BK_FP16) {
-        s[t] += (float)(_Float16)na.z[t];
-        s[t] += (float)(_Float16)nb.z[t];
+        // The FP32 normal rounds to half: not the exact product of its radius
+        // and sine, which a v_fma_mixlo_f16 would round.
+        float za = na.z[t], zb = nb.z[t];
+        asm("" : "+v"(za));
+        asm("" : "+v"(zb));
+        s[t] += (float)(_Float16)za;
+        s[t] += (float)(_Float16)zb;
       } else {
         const bf16x2 p = __builtin_convertvector((f32x2){na.z[t], nb.z[t]}, bf16x2);
         const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
@@ -208,6 +216,74 @@ __global__ __launch_bounds__(256) void basket_pack_kernel(const BasketPack K) {
   }
 }
 
+// Sums of the normals of assets 4q .. 4q + 3 over the steps, to their LDS rows;
+// words(j): Philox or Sobol' block j.
+template <int PREC, typename F>
+__device__ __forceinline__ void sum_block(float* s_sum, uint32_t n, uint32_t nq, uint32_t q,
+                                          int lane, F&& words) {
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  uint32_t i = 0;
+  for (; i + 1 < n; i += 2) {
+    const Words4 a = words(i * nq + q), b = words((i + 1) * nq + q);
+    add_steps<PREC>(s, a, b, true);
+  }
+  if (i < n) {
+    const Words4 a = words(i * nq + q);
+    add_steps<PREC>(s, a, a, false);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) s_sum[(4u * q + t) * kRow + lane] = s[t];
+}
+
+// One step leaves sums of one term in the reduced precisions.
+template <int PREC>
+__device__ __forceinline__ uint32_t sum_terms(uint32_t n) {
+  return n == 1u && PREC != BK_FP32 ? 1u : (uint32_t)Form<PREC>::NZ;
+}
+
+// Terminal values of the lane's four assets 16 rb + 4 (lane / 16) + 0..3 of a
+// path: basket and geometric-basket sums (or the portfolio's value), and the
+// growth of asset 0.
+template <bool PORT>
+__device__ __forceinline__ void terminal_rows(const BasketParams& P, const f32x4& x, uint32_t rb,
+                                              uint32_t g4, float& bs, float& gs, float& e0) {
+#pragma unroll
+  for (uint32_t r = 0; r < 4u; ++r) {
+    const uint32_t a = 16u * rb + 4u * g4 + r;
+    const float v = x[r] * P.x_scale + P.asset[a];        // log2(S_a / S0_a)
+    const float E = __builtin_amdgcn_exp2f(v);
+    if constexpr (PORT) {
+      // Portfolio value of asset a: S0_a sum_k q_k (E - m_k)^+.
+      float pv = 0.f;
+      for (uint32_t k = 0; k < P.n_strikes; ++k) {
+        const float itm = E - P.pm[k];
+        pv = __builtin_fmaf(P.pq[k], itm > 0.f ? itm : 0.f, pv);
+      }
+      bs = __builtin_fmaf(P.asset[768 + a], pv, bs);
+    } else {
+      bs += P.asset[256 + a] * E;
+      gs += P.asset[512 + a] * v;
+      if (a == 0u) e0 = E;
+    }
+  }
+}
+
+// Channels of a path from its sums v.
+template <bool PORT, int C, typename R>
+__device__ __forceinline__ void channels(const BasketParams& P, const R (&v)[C],
+                                         double (&y)[C]) {
+  if constexpr (PORT) {
+    y[0] = (double)v[0] - P.premium;
+  } else {
+    const double disc = P.disc, K = P.K;
+    const double basket = (double)v[0];
+    const double geo = exp(P.geo0 + (double)v[1]);
+    y[0] = disc * (basket > K ? basket - K : 0.0);
+    y[1] = disc * (geo > K ? geo - K : 0.0);
+    y[2] = basket > K ? disc * P.w0 * (double)v[2] : 0.0;
+  }
+}
+
 // Row block i of the wave's set of the triangle's 16-row blocks, S sets per
 // workgroup: consecutive pairs sum to a constant, so the sets have equal
 // shares of the triangle.
@@ -225,7 +301,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   typedef typename F::V V8;
   constexpr int SETS = W / 4, C = PORT ? 1 : 3;
   extern __shared__ float s_sum[];         // [d][kRow]
-  __shared__ float s_part[C][SETS][kTile];
+  // QMC: the sums over a path's lanes in FP64 (see qmc_tile_kernel).
+  typedef typename std::conditional<QMC, double, float>::type Sum;
+  __shared__ Sum s_part[C][SETS][kTile];
   // Sums of the first wave's paths over the workgroup's tiles (in LDS: as
   // registers they would be held by every wave).
   __shared__ ThreadSums<C> s_acc[kTile];
@@ -253,29 +331,17 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   for (uint64_t tile = blk; tile < tiles; tile += nblk) {
     // ---- sums of the normals ----
     const uint64_t path = P.path_offset + tile * kTile + (uint64_t)lane;
-    auto sum_block = [&](uint32_t q, auto&& words) {
-      float s[4] = {0.f, 0.f, 0.f, 0.f};
-      uint32_t i = 0;
-      for (; i + 1 < n; i += 2) {
-        const Words4 a = words(i * nq + q), b = words((i + 1) * nq + q);
-        add_steps<PREC>(s, a, b, true);
-      }
-      if (i < n) {
-        const Words4 a = words(i * nq + q);
-        add_steps<PREC>(s, a, a, false);
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) s_sum[(4u * q + t) * kRow + lane] = s[t];
-    };
     if constexpr (QMC) {
       const uint32_t base = (uint32_t)(P.path_offset + tile * kTile);
       for (uint32_t q = wave; q < nq; q += W)
-        sum_block(q, [&](uint32_t j) { return sobol_words(P.qV, qshift, j, base, (uint32_t)lane); });
+        sum_block<PREC>(s_sum, n, nq, q, lane, [&](uint32_t j) {
+          return sobol_words(P.qV, qshift, j, base, (uint32_t)lane);
+        });
     } else {
       with_uniform_high(path, [&](uint32_t hi) {
         const PathRng g = make_rng((uint32_t)path, hi, P.tag, keys);
         for (uint32_t q = wave; q < nq; q += W)
-          sum_block(q, [&](uint32_t j) { return philox(j, g, keys); });
+          sum_block<PREC>(s_sum, n, nq, q, lane, [&](uint32_t j) { return philox(j, g, keys); });
       });
     }
     __syncthreads();
@@ -286,7 +352,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
     f32x4 x[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) x[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const uint32_t nz = n == 1u && PREC != BK_FP32 ? 1u : (uint32_t)F::NZ;   // one step: one term
+    const uint32_t nz = sum_terms<PREC>(n);
     const uint32_t n_pairs = (uint32_t)basket_pairs(rows);
     for (uint32_t kb = 0; 32u * kb < d; ++kb) {
       // The column operand: sums of assets 32 kb + 8 g4 + 0..7, path c16.
@@ -327,47 +393,37 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
     for (uint32_t i = 0; i < (uint32_t)RPW; ++i) {
       const uint32_t rb = row_block<SETS>(set, i);
-      if (rb < rows) {
+      if (rb < rows) terminal_rows<PORT>(P, x[i], rb, g4, bs, gs, e0);
+    }
+    Sum bsum, gsum = 0, esum = 0;
+    if constexpr (QMC) {
+      bsum = lane_add<16>(lane_add<32>((double)bs));
+      gsum = lane_add<16>(lane_add<32>((double)gs));
+      esum = lane_add<16>(lane_add<32>((double)e0));
+    } else {
 #pragma unroll
-        for (uint32_t r = 0; r < 4u; ++r) {
-          const uint32_t a = 16u * rb + 4u * g4 + r;
-          const float v = x[i][r] * P.x_scale + P.asset[a];   // log2(S_a / S0_a)
-          const float E = __builtin_amdgcn_exp2f(v);
-          if constexpr (PORT) {
-            // Portfolio value of asset a: S0_a sum_k q_k (E - m_k)^+.
-            float pv = 0.f;
-            for (uint32_t k = 0; k < P.n_strikes; ++k) {
-              const float itm = E - P.pm[k];
-              pv = __builtin_fmaf(P.pq[k], itm > 0.f ? itm : 0.f, pv);
-            }
-            bs = __builtin_fmaf(P.asset[768 + a], pv, bs);
-          } else {
-            bs += P.asset[256 + a] * E;
-            gs += P.asset[512 + a] * v;
-            if (a == 0u) e0 = E;
-          }
+      for (int off = 16; off < 64; off <<= 1) {
+        bs += __shfl_xor(bs, off, 64);
+        if constexpr (!PORT) {
+          gs += __shfl_xor(gs, off, 64);
+          e0 += __shfl_xor(e0, off, 64);   // one lane of the four holds it
         }
       }
-    }
-#pragma unroll
-    for (int off = 16; off < 64; off <<= 1) {
-      bs += __shfl_xor(bs, off, 64);
-      if constexpr (!PORT) {
-        gs += __shfl_xor(gs, off, 64);
-        e0 += __shfl_xor(e0, off, 64);     // one lane of the four holds it
-      }
+      bsum = bs;
+      gsum = gs;
+      esum = e0;
     }
     if (g4 == 0u) {
-      s_part[0][set][16u * col + c16] = bs;
+      s_part[0][set][16u * col + c16] = bsum;
       if constexpr (!PORT) {
-        s_part[1][set][16u * col + c16] = gs;
-        s_part[2][set][16u * col + c16] = e0;
+        s_part[1][set][16u * col + c16] = gsum;
+        s_part[2][set][16u * col + c16] = esum;
       }
     }
     __syncthreads();                       // also: every wave has read s_sum
     const uint64_t pid = tile * kTile + (uint64_t)lane;
     if (wave == 0u && pid < P.n_paths) {
-      float v[C];
+      Sum v[C];
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         v[c] = s_part[c][0][lane];
@@ -375,16 +431,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int q = 1; q < SETS; ++q) v[c] += s_part[c][q][lane];
       }
       double y[C];
-      if constexpr (PORT) {
-        y[0] = (double)v[0] - P.premium;
-      } else {
-        const double disc = P.disc, K = P.K;
-        const double basket = (double)v[0];
-        const double geo = exp(P.geo0 + (double)v[1]);
-        y[0] = disc * (basket > K ? basket - K : 0.0);
-        y[1] = disc * (geo > K ? geo - K : 0.0);
-        y[2] = basket > K ? disc * P.w0 * (double)v[2] : 0.0;
-      }
+      channels<PORT>(P, v, y);
       bool finite = true;
 #pragma unroll
       for (int c = 0; c < C; ++c) finite = finite && isfinite(y[c]);
@@ -400,6 +447,143 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   part.zero();
   if (wave == 0u) part = s_acc[lane].part();
   block_reduce<C, 64 * W>(part, partials, blk);
+}
+
+// Replicates of few Sobol' dimensions (n_steps d <= 64): a wave takes a tile of
+// 64 consecutive points by itself, with no barrier between its stages. Lane l
+// keeps the part of dimension l that the tile's points share, and moves it
+// from one tile to the next by the bits of the point index that change; the
+// part of the low six bits is the same in every tile and is read from LDS. The
+// digital shifts are drawn here, one block per lane.
+//
+// Bound: VALU issue and the latency of the stages (16 dimensions: four blocks
+// of Box-Muller, 24 MFMAs, an FP64 exponential per path). 16 replicates of
+// 2^16 points x 16 assets: 74 us in the general kernel, whose waves share a
+// tile and wait for each other three times, and a launch for the shifts; 42 us
+// here.
+template <int PREC>
+__global__ __launch_bounds__(64 * kQmcWaves, 4) void qmc_tile_kernel(const BasketParams P) {
+  stamp(P.clock);
+  typedef Form<PREC> F;
+  typedef typename F::V V8;
+  constexpr int C = 3;
+  extern __shared__ uint32_t s_words[];    // [dims / 4][64][4], [32][dims], then the sums
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t d = P.d, n = P.n_steps, nq = d >> 2, rows = d >> 4, dims = n * d;
+  uint32_t* s_low = s_words;
+  uint32_t* s_dir = s_words + 64u * dims;
+  float* s_sum = (float*)(s_dir + 32u * dims) + wave * d * kRow;
+  for (uint32_t i = threadIdx.x; i < 32u * dims; i += 64u * kQmcWaves)
+    s_dir[(i & 31u) * dims + (i >> 5)] = P.qV[i];
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < 64u * dims; i += 64u * kQmcWaves) {
+    const uint32_t l = (i >> 2) & 63u, dim = 4u * (i >> 8) + (i & 3u);
+    uint32_t x = 0;
+#pragma unroll
+    for (uint32_t b = 0; b < 6u; ++b) x ^= (l >> b) & 1u ? s_dir[b * dims + dim] : 0u;
+    s_low[i] = x;
+  }
+  __syncthreads();
+  const uint32_t nblk = P.q_rep_blocks, rep = blockIdx.x / nblk, blk = blockIdx.x - rep * nblk;
+  uint32_t high = 0;                       // dimension `lane`: shift and the bits of `at`
+  if ((uint32_t)lane < dims)
+    high = word_at(philox((uint32_t)lane >> 2, make_counter(rep, P.q_shift_tag, P.k0, P.k1)),
+                   (uint32_t)lane & 3u);
+  const uint64_t first = P.path_offset, last = first + P.n_paths;   // last <= 2^32
+  const uint64_t base0 = first & ~63ull, tiles = (last - base0 + 63u) >> 6;
+  uint32_t at = 0;
+  ThreadSums<C> acc;
+  acc.zero();
+  for (uint64_t tile = (uint64_t)blk * kQmcWaves + wave; tile < tiles;
+       tile += (uint64_t)nblk * kQmcWaves) {
+    const uint32_t base = (uint32_t)(base0 + (tile << 6));
+    for (uint32_t change = base ^ at; change != 0u; change &= change - 1u) {
+      const uint32_t b = (uint32_t)__builtin_ctz(change);
+      high ^= (uint32_t)lane < dims ? s_dir[b * dims + (uint32_t)lane] : 0u;
+    }
+    at = base;
+    for (uint32_t q = 0; q < nq; ++q)
+      sum_block<PREC>(s_sum, n, nq, q, lane, [&](uint32_t j) {
+        const uint4 low = *(const uint4*)(s_low + (j * 64u + (uint32_t)lane) * 4u);
+        auto of = [&](uint32_t t) {
+          return (uint32_t)__builtin_amdgcn_readlane((int)high, (int)(4u * j + t));
+        };
+        return Words4{low.x ^ of(0), low.y ^ of(1), low.z ^ of(2), low.w ^ of(3)};
+      });
+    wave_sync();
+    // The product as in basket_kernel, a row block at a time. (A function for
+    // both costs that kernel 20 registers and spills.)
+    const uint32_t c16 = (uint32_t)lane & 15u, g4 = (uint32_t)lane >> 4;
+    const uint32_t nz = sum_terms<PREC>(n), n_pairs = basket_pairs(rows);
+    double v[C] = {0.0, 0.0, 0.0};         // of path `lane`
+#pragma unroll
+    for (uint32_t col = 0; col < 4u; ++col) {
+      float bs = 0.f, gs = 0.f, e0 = 0.f;
+      for (uint32_t rb = 0; rb < rows; ++rb) {
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        for (uint32_t kb = 0; 2u * kb <= rb; ++kb) {
+          const uint32_t k0 = 32u * kb + 8u * g4;
+          V8 z[F::NZ];
+          float r[8];
+#pragma unroll
+          for (uint32_t e = 0; e < 8u; ++e)
+            r[e] = k0 < d ? s_sum[(k0 + e) * kRow + 16u * col + c16] * P.z_scale : 0.f;
+#pragma unroll
+          for (int t = 0; t < F::NZ; ++t)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              z[t][e] = r[e];
+              r[e] -= (float)z[t][e];
+            }
+          const V8* a = (const V8*)P.Lfrag + ((size_t)basket_pairs(rb) + kb) * 64u + lane;
+#pragma unroll
+          for (int p = 0; p < F::NL; ++p) {
+            const V8 l = a[(size_t)p * n_pairs * 64u];
+#pragma unroll
+            for (int t = 0; t < F::NZ; ++t)
+              if (p + t < F::KEEP && (uint32_t)t < nz) mma(x, l, z[t]);
+          }
+        }
+        terminal_rows<false>(P, x, rb, g4, bs, gs, e0);
+      }
+      // The last two sums of four assets' sums in FP64: their rounding would be
+      // the largest of a path, and the standard error of a few replicates shows
+      // what does not average out.
+      const float t[C] = {bs, gs, e0};
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const double w = lane_add<16>(lane_add<32>((double)t[c]));
+        if (g4 == col) v[c] = w;
+      }
+    }
+    wave_sync();                           // the sums are read before the next tile's
+    const uint64_t point = (uint64_t)base + (uint64_t)lane;
+    if (point >= first && point < last) {
+      double y[C];
+      channels<false>(P, v, y);
+      bool finite = true;
+#pragma unroll
+      for (int c = 0; c < C; ++c) finite = finite && isfinite(y[c]);
+      acc.push(y, finite, !finite);
+    }
+  }
+  PartSums<C> part = acc.part();
+  block_reduce<C, 64 * kQmcWaves>(part, P.partials + (size_t)rep * n_moments(C) * nblk, blk);
+}
+
+template <int PREC>
+hipError_t launch_qmc_tile(const BasketParams& p, hipStream_t s, uint32_t blocks) {
+  const uint32_t dims = p.n_steps * p.d;
+  const size_t lds = 96u * dims * sizeof(uint32_t) + (size_t)kQmcWaves * p.d * kRow * sizeof(float);
+  if (dims > 64u) return hipErrorInvalidValue;
+  if (lds > 32768) {
+    const hipError_t e = hipFuncSetAttribute((const void*)qmc_tile_kernel<PREC>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(qmc_tile_kernel<PREC>, dim3(blocks), dim3(64 * kQmcWaves), lds, s, p);
+  return hipGetLastError();
 }
 
 template <int PREC, bool PORT, bool QMC, int W, int RPW>
@@ -489,17 +673,34 @@ uint32_t basket_blocks(uint64_t n_paths, uint32_t n_steps, uint32_t d) {
   return (uint32_t)(nb < kBasketMaxBlocks ? nb : kBasketMaxBlocks);
 }
 
+// Replicates whose points have few dimensions take the tile kernel, in about
+// four tiles per wave with 1024 workgroups in all (a CU holds four).
+bool qmc_tiles(const BasketParams& p, int prec) {
+  return (uint64_t)p.n_steps * p.d <= 64u && (prec == BK_FP32 || prec == BK_FP16);
+}
+
+bool basket_qmc_draws_shifts(const BasketParams& p, int prec) { return qmc_tiles(p, prec); }
+
 hipError_t launch_basket_qmc_batch(BasketParams p, int prec, uint32_t n_rep, hipStream_t s,
                                    uint32_t* blocks_per_rep) {
   if (n_rep == 0 || n_rep > kBasketMaxBlocks) return hipErrorInvalidValue;
-  uint64_t nb = basket_blocks(p.n_paths, p.n_steps, p.d);
-  const uint64_t share = kBasketMaxBlocks / 2 / n_rep;    // 2048 workgroups in all
+  if (p.qV == nullptr || p.n_strikes != 0 || p.path_out != nullptr) return hipErrorInvalidValue;
+  uint64_t nb, share;
+  if (qmc_tiles(p, prec)) {
+    nb = (p.n_paths + 64u * kQmcWaves - 1) / (64u * kQmcWaves);
+    share = 1024 / n_rep;
+  } else {
+    nb = basket_blocks(p.n_paths, p.n_steps, p.d);
+    share = kBasketMaxBlocks / 2 / n_rep;                 // 2048 workgroups in all
+  }
   if (nb > share) nb = share ? share : 1;
+  if (nb == 0) return hipErrorInvalidValue;
   *blocks_per_rep = (uint32_t)nb;
-  if (p.qV == nullptr || p.n_strikes != 0 || p.path_out != nullptr || nb == 0)
-    return hipErrorInvalidValue;
   p.q_rep_blocks = (uint32_t)nb;
-  return launch_any(p, prec, s, (uint32_t)(nb * n_rep));
+  if (!qmc_tiles(p, prec)) return launch_any(p, prec, s, (uint32_t)(nb * n_rep));
+  if (!shapes_ok(p)) return hipErrorInvalidValue;
+  return prec == BK_FP32 ? launch_qmc_tile<BK_FP32>(p, s, (uint32_t)(nb * n_rep))
+                         : launch_qmc_tile<BK_FP16>(p, s, (uint32_t)(nb * n_rep));
 }
 
 hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks) {

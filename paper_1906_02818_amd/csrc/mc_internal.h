@@ -172,6 +172,7 @@ struct BasketParams {
   // shift row q_dims * replicate, and writes its moments to that
   // replicate's own [q_rep_blocks][moment] partials.
   uint32_t q_rep_blocks, q_dims;
+  uint32_t q_shift_tag;   // stream of the shifts, where the kernel draws them itself
   double* partials;
   double* path_out;       // [n_paths][3] (basket) or [n_paths] (portfolio), or nullptr
   uint64_t* clock;        // start stamp, or nullptr
@@ -198,6 +199,7 @@ hipError_t launch_basket_pack(const BasketPack& k, int prec, hipStream_t s);
 hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks);
 // All n_rep randomised-QMC replicates of p in one launch (p.qshift holds
 // n_rep rows of p.q_dims shifts); *blocks_per_rep = one replicate's blocks.
+bool basket_qmc_draws_shifts(const BasketParams& p, int prec);   // p.qshift unused
 hipError_t launch_basket_qmc_batch(BasketParams p, int prec, uint32_t n_rep, hipStream_t s,
                                    uint32_t* blocks_per_rep);
 

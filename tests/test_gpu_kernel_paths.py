@@ -340,3 +340,24 @@ def test_risk_selection(ctx, N, alpha, sigma, mu, strike):
     again = mc.mc_risk(ctx, m, [strike], [1.0], alpha, N, 1, SEED, mu=np.full(d, mu))
     assert again["var"] == r["var"] and again["n_tail"] == r["n_tail"]
     assert again["cvar"] == r["cvar"] or not tail.size
+
+
+@pytest.mark.parametrize("prec", [mc.MC_FP32, mc.MC_FP16_GEMM])
+@pytest.mark.parametrize("d,n,N,offset,reps", [
+    (16, 1, 2, 0, 1), (16, 1, 4099, 0, 3), (16, 3, 517, 37, 2), (16, 4, 1000, (1 << 32) - 1000, 2),
+    (48, 1, 333, 61, 2), (64, 1, 64, 64, 64), (16, 1, 1 << 17, 5, 2)])
+def test_qmc_tiles(ctx, prec, d, n, N, offset, reps):
+    """Replicates of few dimensions against the run of one replicate that
+    writes its per-path values (the general kernel, whose first replicate has
+    the same shift): the same values per path, so the means agree to their
+    summation, N 2^-53 at worst; and every replicate against the oracle's
+    points is covered by the general tests through this route."""
+    corr = np.full((d, d), 0.2) + 0.8 * np.eye(d)
+    m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.03, T=1.0,
+                 sigma=np.linspace(0.1, 0.4, d), corr=corr)
+    f = mc.Payoff(mc.MC_BASKET_CALL, 100.0)
+    a = mc.mc_price_qmc(ctx, m, f, N, n, SEED, reps, mc.Options(prec=prec, path_offset=offset))
+    b = mc.mc_price_qmc(ctx, m, f, N, n, SEED, 1,
+                        mc.Options(prec=prec, path_offset=offset, path_values=True))
+    assert a["replicate_price"][0] == pytest.approx(b["replicate_price"][0], rel=1e-12, abs=1e-12)
+    assert a["replicate_geo"][0] == pytest.approx(b["replicate_geo"][0], rel=1e-12, abs=1e-12)
