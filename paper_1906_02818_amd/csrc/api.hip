@@ -736,12 +736,16 @@ mc_status heston_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
 // Device buffers of one learned-CV run: weights, their fragments and the
 // undiscounting table, after the moment layout in the workspace.
 struct CvBuffers {
-  float *theta, *w1f, *w2f, *w2tf, *lanec, *dfac;
+  float *theta, *w1f, *lanec, *dfac;
+  void *w2f, *w2tf;          // in the operand type, room for FP32
 };
+// Room for the per-lane constants: the size callers' workspaces are checked
+// against.
+constexpr size_t kLanecRoom = 2 * 64 * 32 * sizeof(float);
 
 size_t cv_extra_bytes(uint32_t n_steps) {
   return align256(kMlpNParam * 4) + align256(kW1fFloats * 4) + 2 * align256(kW2fFloats * 4) +
-         align256(kLanecFloats * 4) + align256((size_t)(n_steps + 1) * 4);
+         align256(kLanecRoom) + align256((size_t)(n_steps + 1) * 4);
 }
 
 CvBuffers cv_carve(char* p) {
@@ -750,12 +754,12 @@ CvBuffers cv_carve(char* p) {
   p += align256(kMlpNParam * 4);
   b.w1f = (float*)p;
   p += align256(kW1fFloats * 4);
-  b.w2f = (float*)p;
+  b.w2f = p;
   p += align256(kW2fFloats * 4);
-  b.w2tf = (float*)p;
+  b.w2tf = p;
   p += align256(kW2fFloats * 4);
   b.lanec = (float*)p;
-  p += align256(kLanecFloats * 4);
+  p += align256(kLanecRoom);
   b.dfac = (float*)p;
   return b;
 }
@@ -783,12 +787,12 @@ CvParams cv_params(const mc_model* m, const mc_payoff* f, uint64_t n_paths, uint
 }
 
 // Uploads weights and the discount table, builds the fragments.
-mc_status cv_upload(mc_context* ctx, hipStream_t s, const CvBuffers& b, const float* theta_host,
-                    const std::vector<float>& dfac) {
+mc_status cv_upload(mc_context* ctx, hipStream_t s, const CvBuffers& b, bool bf16,
+                    const float* theta_host, const std::vector<float>& dfac) {
   if (theta_host)
     HIP_TRY(ctx, hipMemcpyAsync(b.theta, theta_host, kMlpNParam * 4, hipMemcpyHostToDevice, s));
   HIP_TRY(ctx, hipMemcpyAsync(b.dfac, dfac.data(), dfac.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, launch_cv_pack(b.theta, b.w1f, b.w2f, b.w2tf, b.lanec, s));
+  HIP_TRY(ctx, launch_cv_pack(b.theta, bf16, b.w1f, b.w2f, b.w2tf, b.lanec, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
   return MC_OK;
 }
@@ -839,7 +843,7 @@ mc_status heston_cv_price(mc_context* ctx, const mc_model* m, const mc_payoff* f
   if (st != MC_OK) return st;
   const CvBuffers b = cv_carve(base + off);
   hipStream_t s = stream_of(ctx, o0);
-  st = cv_upload(ctx, s, b, o0.cv_weights, dfac_table(m, n_steps));
+  st = cv_upload(ctx, s, b, o0.prec == MC_BF16_GEMM, o0.cv_weights, dfac_table(m, n_steps));
   if (st != MC_OK) return st;
   mc_options o = o0;
   o.workspace = base;
@@ -2297,7 +2301,7 @@ mc_status mc_cv_loss_grad(mc_context* ctx, const mc_model* m, const mc_payoff* f
   CvTrainWs w;
   cv_train_bytes(batch, n_steps, 1, batch, n_seg, &w, base);
   hipStream_t s = ctx->stream;
-  st = cv_upload(ctx, s, w.b, weights, dfac_table(m, n_steps));
+  st = cv_upload(ctx, s, w.b, cfg->prec == MC_BF16_GEMM, weights, dfac_table(m, n_steps));
   if (st != MC_OK) return st;
   const bool bf16 = cfg->prec == MC_BF16_GEMM;
   st = cv_fill_cache(ctx, s, m, f, n_steps, seed, tag, path0, batch, cfg->hedge_every, bf16, w);
@@ -2339,7 +2343,7 @@ mc_status mc_cv_train(mc_context* ctx, const mc_model* m, const mc_payoff* f, ui
   CvTrainWs w;
   cv_train_bytes(B, n_steps, cfg->steps, n_train, n_seg, &w, base);
   hipStream_t s = ctx->stream;
-  st = cv_upload(ctx, s, w.b, weights_inout, dfac_table(m, n_steps));
+  st = cv_upload(ctx, s, w.b, cfg->prec == MC_BF16_GEMM, weights_inout, dfac_table(m, n_steps));
   if (st != MC_OK) return st;
   HIP_TRY(ctx, hipMemsetAsync(w.m, 0, kMlpNParam * 4, s));
   HIP_TRY(ctx, hipMemsetAsync(w.v, 0, kMlpNParam * 4, s));
@@ -2362,8 +2366,8 @@ mc_status mc_cv_train(mc_context* ctx, const mc_model* m, const mc_payoff* f, ui
         cfg->decay_every > 0 ? cfg->lr * std::pow(cfg->decay, (double)(t / cfg->decay_every))
                              : cfg->lr;
     HIP_TRY(ctx, launch_adam_pack(w.grad_partials, nb, vm, w.grad, w.b.theta, w.m, w.v,
-                                  (int)t + 1, lr, cfg->beta1, cfg->beta2, cfg->eps, w.b.w1f,
-                                  w.b.w2f, w.b.w2tf, w.b.lanec, s));
+                                  (int)t + 1, lr, cfg->beta1, cfg->beta2, cfg->eps, bf16,
+                                  w.b.w1f, w.b.w2f, w.b.w2tf, w.b.lanec, s));
   }
   std::vector<double> log((size_t)cfg->steps * n_mom);
   HIP_TRY(ctx, hipMemcpyAsync(weights_inout, w.b.theta, kMlpNParam * 4, hipMemcpyDeviceToHost, s));

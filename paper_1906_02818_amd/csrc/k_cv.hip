@@ -49,6 +49,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float float2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kCvWaves = 4;
 constexpr int kCvThreads = 64 * kCvWaves;
@@ -119,6 +120,19 @@ __device__ __forceinline__ void mma16(f32x16& acc, const Op8<BF16>& a, const Op8
   }
 }
 
+// acc += A x B for 16 rows, 16 columns and 32 k-slots: lane l holds row (column)
+// l mod 16, slots 8 (l / 16) .. + 7.
+template <bool BF16>
+__device__ __forceinline__ void mma16x16(f32x4& acc, const Op8<BF16>& a, const Op8<BF16>& b) {
+  if constexpr (BF16) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc, 0, 0, 0);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j], b.v[j], acc, 0, 0, 0);
+  }
+}
+
 // 1 / (1 + e^{-2(x + b)}) = (1 + tanh(x + b)) / 2, with cb = -2 b / ln 2
 // folded into the exponent.
 __device__ __forceinline__ float sigm2_b(float x, float cb) {
@@ -160,46 +174,46 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 constexpr int kFragFloats = 2 * 4 * 64 * 8;   // one set of layer-2 fragments
-constexpr int kLaneFloats = 2 * 64 * 32;      // per-lane b2 (scaled) and 2 W3
 
-// Per-lane constants (b2 scaled, then 2 W3): 32 values per lane, one per unit
-// slot q = 16 mb + r, stored as [q / 4][lane][q mod 4] so that the four
-// consecutive slots a lane reads at once sit beside those of its neighbours
-// (a wave's 16-byte reads cover 1 KB contiguously, free of bank conflicts).
-__device__ __forceinline__ int lanec_index(int lane, int q) {
-  return (q >> 2) * 256 + lane * 4 + (q & 3);
-}
+// Per-lane constants (b2 scaled, then 2 W3): the 32 unit slots q = 16 mb + r of
+// each half. The lanes of a half read the same four at a time.
+__device__ __forceinline__ int lanec_index(int half, int q) { return half * 32 + q; }
+constexpr int kLaneW3 = 64;                   // where 2 W3 begins
 
-// The layer-2 fragments (optionally also their transposes) and the per-lane
-// constants, global -> registers -> LDS: every thread issues all of its
-// loads before the first store, so a workgroup waits for one memory
-// latency rather than one per element.
-constexpr int kFillPer = kFragFloats / kCvThreads;
-static_assert(kFragFloats % kCvThreads == 0 && kLaneFloats == kFragFloats, "fragment split");
+// The layer-2 fragments (optionally also their transposes), in the operand
+// type as the pack or Adam launch left them, and the per-lane constants,
+// global -> registers -> LDS: every thread issues all of its loads before the
+// first store, so a workgroup waits for one memory latency. (As FP32, with
+// the constants repeated for each lane, the backward's workgroups loaded 48 KB
+// instead of 16.5.)
+template <bool BF16, int THREADS>
 struct WeightRegs {
-  float a[kFillPer], b[kFillPer], c[kFillPer];
+  static constexpr int kPer = kFragFloats * (int)sizeof(FragT<BF16>) / 16 / THREADS;   // 16-byte words
+  static_assert(kPer * 16 * THREADS == kFragFloats * (int)sizeof(FragT<BF16>), "fragment split");
+  uint4 a[kPer], b[kPer];
+  float c;
 };
-template <bool WITH_T>
-__device__ __forceinline__ void weights_load(const float* w2f, const float* w2tf,
-                                             const float* lanec, WeightRegs& r) {
+template <bool WITH_T, bool BF16, int THREADS>
+__device__ __forceinline__ void weights_load(const void* w2f, const void* w2tf,
+                                             const float* lanec, WeightRegs<BF16, THREADS>& r) {
 #pragma unroll
-  for (int j = 0; j < kFillPer; ++j) {
-    const int i = threadIdx.x + j * kCvThreads;
-    r.a[j] = w2f[i];
-    if constexpr (WITH_T) r.b[j] = w2tf[i];
-    r.c[j] = lanec[i];
+  for (int j = 0; j < WeightRegs<BF16, THREADS>::kPer; ++j) {
+    const int i = threadIdx.x + j * THREADS;
+    r.a[j] = ((const uint4*)w2f)[i];
+    if constexpr (WITH_T) r.b[j] = ((const uint4*)w2tf)[i];
   }
+  r.c = threadIdx.x < kLanecFloats ? lanec[threadIdx.x] : 0.f;
 }
-template <bool WITH_T, typename FT>
-__device__ __forceinline__ void weights_store(const WeightRegs& r, FT* s_w2f, FT* s_w2tf,
-                                              float* s_lanec) {
+template <bool WITH_T, bool BF16, int THREADS>
+__device__ __forceinline__ void weights_store(const WeightRegs<BF16, THREADS>& r, void* s_w2f,
+                                              void* s_w2tf, float* s_lanec) {
 #pragma unroll
-  for (int j = 0; j < kFillPer; ++j) {
-    const int i = threadIdx.x + j * kCvThreads;
-    s_w2f[i] = (FT)r.a[j];
-    if constexpr (WITH_T) s_w2tf[i] = (FT)r.b[j];
-    s_lanec[i] = r.c[j];
+  for (int j = 0; j < WeightRegs<BF16, THREADS>::kPer; ++j) {
+    const int i = threadIdx.x + j * THREADS;
+    ((uint4*)s_w2f)[i] = r.a[j];
+    if constexpr (WITH_T) ((uint4*)s_w2tf)[i] = r.b[j];
   }
+  if (threadIdx.x < kLanecFloats) s_lanec[threadIdx.x] = r.c;
 }
 
 // Forward pass of the hedge network for the wave's 32 paths, keeping the
@@ -209,6 +223,7 @@ template <bool BF16>
 __device__ __forceinline__ void mlp_forward(const float (&phi)[8], const Op8<BF16> (&w1a)[2],
                                             const FragT<BF16>* w2f, const float* lanec, int lane,
                                             float (&h1)[32], float (&h2)[32]) {
+  const int half = lane >> 5;
   f32x16 d1[2];
   const Op8<BF16> phio = op_from<BF16>(phi);
 #pragma unroll
@@ -245,7 +260,7 @@ __device__ __forceinline__ void mlp_forward(const float (&phi)[8], const Op8<BF1
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int idx = mb * 16 + r;
-      h2[idx] = tanh_b(d2[mb][r], lanec[lanec_index(lane, idx)]);
+      h2[idx] = tanh_b(d2[mb][r], lanec[lanec_index(half, idx)]);
     }
 }
 
@@ -357,13 +372,14 @@ __device__ __forceinline__ float mlp_delta(const float (&phi)[8], const Op8<BF16
     for (int mb = 0; mb < 2; ++mb)
       mma16<BF16>(d2[mb], op_lds<BF16>(&w2f[((mb * 4 + kb) * 64 + lane) * 8]), b[kb]);
   float part = 0.f;
+  const int half = lane >> 5;
 #pragma unroll
   for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int idx = mb * 16 + r;
-      const float v = sigm2_b(d2[mb][r], lanec[lanec_index(lane, idx)]);
-      part = __builtin_fmaf(lanec[64 * 32 + lanec_index(lane, idx)], v, part);
+      const float v = sigm2_b(d2[mb][r], lanec[lanec_index(half, idx)]);
+      part = __builtin_fmaf(lanec[kLaneW3 + lanec_index(half, idx)], v, part);
     }
   return part + __shfl_xor(part, 32, 64) + c3;
 }
@@ -423,13 +439,13 @@ template <bool BF16>
 __global__ __launch_bounds__(kCvThreads) void cv_values_kernel(const CvParams P) {
   using FT = FragT<BF16>;
   __shared__ __attribute__((aligned(16))) FT s_w2f[kFragFloats];
-  __shared__ __attribute__((aligned(16))) float s_lanec[kLaneFloats];
+  __shared__ __attribute__((aligned(16))) float s_lanec[kLanecFloats];
   // (Delta, dSt) of each segment a wave of a split tile takes.
   __shared__ float2 s_dd[kCvWaves][kCvValSlab][32];
   {
-    WeightRegs wr;
+    WeightRegs<BF16, kCvThreads> wr;
     weights_load<false>(P.w2f, nullptr, P.lanec, wr);
-    weights_store<false>(wr, s_w2f, (FT*)nullptr, s_lanec);
+    weights_store<false>(wr, s_w2f, nullptr, s_lanec);
   }
   __syncthreads();
 
@@ -518,44 +534,52 @@ __global__ __launch_bounds__(kCvThreads) void cv_values_kernel(const CvParams P)
 // Every weight gradient is a product over the wave's 32 paths on the
 // matrix cores, accumulated in two register sets:
 //   gw2 = delta2^T H1 (64 x 64);
-//   gx  = 64 units x 32 columns holding, by column, db2 = delta2^T 1,
+//   gx  = 64 units x 16 columns holding, by column, db2 = delta2^T 1,
 //         dW3 = H2^T gD, dW1 = delta1^T phi (4 columns) and db1 = delta1^T 1,
-//         each product with a B operand that is zero outside its columns.
+//         each product with a B operand that is zero outside its columns, as
+//         16x16 products (seven columns in 32 wide ones cost twice the matrix
+//         cycles and 16 registers more).
 // A path-major operand (delta2, H2, H1, delta1) passes through one of the
 // wave's two LDS regions to become unit-major, two operands per store ->
 // load round trip, with e1 = W2^T delta2 and delta1 computed while the
 // stores land; the column operands (gD, phi, 1) are one row each of a small
 // part of a region.
-template <bool BF16>
+template <bool BF16, int WAVES>
 __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
   using FT = FragT<BF16>;
   // One LDS area: the weight fragments and the waves' transpose regions,
   // reused after the segment loop for the block's gradient sum.
-  // Rows of kTs elements (32 paths plus padding, so that neither the
-  // lanes' 2-byte stores of a unit nor the 16-byte fragment reads of
-  // consecutive units fall on one bank group).
+  // A region is [32 paths][72] in BF16: a lane stores its units four at a time
+  // (8 bytes) and ds_read_b64_tr_b16 turns them, 4 paths x 16 units per 16
+  // lanes; with rows of 36 words neither side meets a bank twice. (Stored as
+  // [unit][path] the operands took 32 2-byte stores each, and the LDS pipe,
+  // 1000 cycles per segment and wave, was 0.7 of the loop's time.) FP32:
+  // [64 units][36], 32 paths plus padding. Behind it [8 columns][kTs paths].
   constexpr int kTs = BF16 ? 40 : 36;
-  constexpr int kTr = 64 * kTs + 8 * kTs;
-  constexpr size_t kLds =
-      2 * kFragFloats * sizeof(FT) + kLaneFloats * 4 + kCvWaves * 2 * kTr * sizeof(FT);
-  static_assert(kLds >= kCvWaves * kMlpNParam * sizeof(float), "LDS too small for the gradient sum");
+  constexpr int kPs = 72;                  // BF16: elements of a path's row
+  constexpr int kTu = BF16 ? 32 * kPs : 64 * kTs;
+  constexpr int kTr = kTu + 8 * kTs;
+  constexpr size_t kLoop =
+      2 * kFragFloats * sizeof(FT) + kLanecFloats * 4 + WAVES * 2 * kTr * sizeof(FT);
+  constexpr size_t kRed = WAVES * kMlpNParam * sizeof(float);
+  constexpr size_t kLds = kLoop > kRed ? kLoop : kRed;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
   FT* s_w2f = (FT*)lds;
   FT* s_w2tf = s_w2f + kFragFloats;
   float* s_lanec = (float*)(lds + 2 * kFragFloats * sizeof(FT));
-  FT* tr = (FT*)(lds + 2 * kFragFloats * sizeof(FT) + kLaneFloats * 4);
+  FT* tr = (FT*)(lds + 2 * kFragFloats * sizeof(FT) + kLanecFloats * 4);
   // The weight fragments and per-lane constants are loaded into registers
   // first, so that their latency overlaps the sum below.
-  WeightRegs wr;
+  WeightRegs<BF16, 64 * WAVES> wr;
   weights_load<true>(P.w2f, P.w2tf, P.lanec, wr);
   // Ybar = sum n_b mean_b / sum n_b over the hedged-value kernel's block
   // moment vectors, summed in the same fixed order by every block (the full
   // merge of those vectors, the minibatch's loss, runs in the gradient
   // reduction's launch).
-  __shared__ double s_ys[kCvWaves][2];
+  __shared__ double s_ys[WAVES][2];
   {
     double sn = 0.0, sy = 0.0;
-    for (uint32_t i = threadIdx.x; i < P.val_blocks; i += kCvThreads) {
+    for (uint32_t i = threadIdx.x; i < P.val_blocks; i += 64 * WAVES) {
       const double* v = P.partials + (size_t)i * PartSums<3>::M;
       sn += v[0];
       sy += v[0] * v[2 + 2];             // n and mean of channel 2 (Y)
@@ -582,7 +606,7 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
   // gradient is a sum over (path, segment) items, so any split of the
   // segments gives the same sum up to rounding.
   const uint32_t split = P.seg_split, part = (uint32_t)wave % split;
-  const uint64_t tile = (uint64_t)blockIdx.x * (kCvWaves / split) + (uint32_t)wave / split;
+  const uint64_t tile = (uint64_t)blockIdx.x * (WAVES / split) + (uint32_t)wave / split;
   const uint32_t k0 = (uint32_t)((uint64_t)P.n_seg * part / split);
   const uint32_t k1 = (uint32_t)((uint64_t)P.n_seg * (part + 1) / split);
   const uint64_t pid = tile * 32 + row;
@@ -591,7 +615,7 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
   if (active) {
     double n = 0.0, sy = 0.0;
 #pragma unroll
-    for (int w = 0; w < kCvWaves; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
       n += s_ys[w][0];
       sy += s_ys[w][1];
     }
@@ -605,46 +629,71 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
     load8(&P.w1f[(mb * 64 + lane) * 8], w);
     w1a[mb] = op_from<BF16>(w);
   }
-  const float col0 = row == 0 ? 1.0f : 0.0f;   // B operand entry: ones in column 0
+  const int c16 = lane & 15, q4 = lane >> 4;   // 16x16 products: row or column, k-slot group
+  const float col0 = c16 == 0 ? 1.0f : 0.0f;   // B operand entry: ones in column 0
 
-  f32x16 gw2[2][2], gx[2];
+  f32x16 gw2[2][2];
+  f32x4 gx[4];
   float gb3 = 0.f;
 #pragma unroll
-  for (int a = 0; a < 2; ++a) {
+  for (int a = 0; a < 4; ++a) gx[a] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < 16; ++r) gx[a][r] = 0.f;
+  for (int a = 0; a < 2; ++a) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) gw2[a][b][r] = 0.f;
   }
-  // Two regions per wave, each [64 units][32 paths] plus [8 columns][32
-  // paths], row stride kTs: two transposes share one store -> load round trip.
+  // Two regions per wave: two transposes share one store -> load round trip.
   FT* const T0 = tr + wave * 2 * kTr;
   FT* const T1 = T0 + kTr;
-  FT* const TP0 = T0 + 64 * kTs;
-  FT* const TP1 = T1 + 64 * kTs;
-  // Unit-major A fragments of a region (32 units of block mb x 8 paths).
+  FT* const TP0 = T0 + kTu;
+  FT* const TP1 = T1 + kTu;
+  // Unit-major fragments of a region: units 32 mb + row (16 mb + c16), eight
+  // paths from 16 pk + 8 half (8 q4). Turning read of a 16-lane group: lane i
+  // addresses path i / 4, units 4 (i mod 4) .. + 3, and receives unit i, paths
+  // 0 .. 3.
+  const int turn = (c16 >> 2) * kPs + 4 * (c16 & 3);
+  const int t32 = 8 * half * kPs + 16 * ((lane >> 4) & 1) + turn, t16 = 8 * q4 * kPs + turn;
+  auto turned = [&](const FT* T, int at) {
+    Op8<BF16> o;
+    if constexpr (BF16) {
+      typedef __attribute__((ext_vector_type(4))) short s16x4;
+      typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+      union {
+        s16x4 h[2];
+        bf16x8 v;
+      } u;
+      u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(T + at));
+      u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(T + at + 4 * kPs));
+      o.v = u.v;
+    }
+    return o;
+  };
   auto a_frag = [&](const FT* T, int pk, int mb) {
+    if constexpr (BF16) return turned(T, t32 + 16 * pk * kPs + 32 * mb);
     return op_lds<BF16>(&T[(32 * mb + row) * kTs + 16 * pk + 8 * half]);
   };
-  // Units u(mb, r) and u(mb, r + 1), r even, are consecutive rows: in the
-  // BF16 form one packed conversion makes both, stored as its low and high
-  // halves.
+  auto a_frag16 = [&](const FT* T, int mb) {
+    if constexpr (BF16) return turned(T, t16 + 16 * mb);
+    return op_lds<BF16>(&T[(16 * mb + c16) * kTs + 8 * q4]);
+  };
+  // Units u(mb, r) .. u(mb, r + 3), r a multiple of 4, are consecutive.
   auto to_T = [&](FT* T, const float (&x)[32]) {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        FT* t = &T[unit_of(mb, r, half) * kTs + row];
+      for (int r = 0; r < 16; r += 4) {
+        const float* v = &x[mb * 16 + r];
         if constexpr (BF16) {
-          const bf16x2 p = __builtin_convertvector((float2_t){x[mb * 16 + r], x[mb * 16 + r + 1]},
-                                                   bf16x2);
-          t[0] = p[0];
-          t[kTs] = p[1];
+          typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+          bf16x4 h;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) h[e] = (__bf16)v[e];
+          *(bf16x4*)&T[row * kPs + unit_of(mb, r, half)] = h;
         } else {
-          t[0] = x[mb * 16 + r];
-          t[kTs] = x[mb * 16 + r + 1];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) T[(unit_of(mb, r, half) + e) * kTs + row] = v[e];
         }
       }
   };
@@ -680,7 +729,7 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
     float d2v[32];
 #pragma unroll
     for (int q = 0; q < 32; ++q)
-      d2v[q] = gDh * s_lanec[64 * 32 + lanec_index(lane, q)] * (1.0f - h2[q] * h2[q]);
+      d2v[q] = gDh * s_lanec[kLaneW3 + lanec_index(half, q)] * (1.0f - h2[q] * h2[q]);
     // Round trip 1: H2 (with gD in column row 1) and delta2 become unit-major.
     to_T(T0, h2);
     if (half == 0) TP0[1 * kTs + row] = (FT)gD;
@@ -703,28 +752,26 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
         mma16<BF16>(e1[mb], op_lds<BF16>(&s_w2tf[((mb * 4 + kb) * 64 + lane) * 8]), b);
     }
     // dW3 (column 1 of gx) += H2^T gD.
+    {
+      const Op8<BF16> b = c16 == 1 ? op_lds<BF16>(&TP0[1 * kTs + 8 * q4]) : op_zero<BF16>();
 #pragma unroll
-    for (int pk = 0; pk < 2; ++pk) {
-      const Op8<BF16> b = row == 1 ? op_lds<BF16>(&TP0[1 * kTs + 16 * pk + 8 * half])
-                                   : op_zero<BF16>();
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) mma16<BF16>(gx[mb], a_frag(T0, pk, mb), b);
+      for (int mb = 0; mb < 4; ++mb) mma16x16<BF16>(gx[mb], a_frag16(T0, mb), b);
     }
-    // db2 (column 0 of gx) += delta2^T 1; delta2's fragments stay for dW2.
-    Op8<BF16> A2[2][2];
+    // db2 (column 0 of gx) += delta2^T 1.
     {
       float ones[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) ones[j] = col0;
       const Op8<BF16> b = op_from<BF16>(ones);
 #pragma unroll
-      for (int pk = 0; pk < 2; ++pk)
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-          A2[pk][mb] = a_frag(T1, pk, mb);
-          mma16<BF16>(gx[mb], A2[pk][mb], b);
-        }
+      for (int mb = 0; mb < 4; ++mb) mma16x16<BF16>(gx[mb], a_frag16(T1, mb), b);
     }
+    // delta2's fragments for dW2.
+    Op8<BF16> A2[2][2];
+#pragma unroll
+    for (int pk = 0; pk < 2; ++pk)
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb) A2[pk][mb] = a_frag(T1, pk, mb);
     wave_lds_sync();
     // Round trip 2: H1 and delta1 = e1 (1 - h1^2) (with phi and the ones in
     // column rows 2..6) become unit-major.
@@ -751,18 +798,16 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
     for (int pk = 0; pk < 2; ++pk)
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) {
-        const Op8<BF16> b = op_lds<BF16>(&T0[(32 * nb + row) * kTs + 16 * pk + 8 * half]);
+        const Op8<BF16> b = a_frag(T0, pk, nb);
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) mma16<BF16>(gw2[mb][nb], A2[pk][mb], b);
       }
     // dW1 and db1 (columns 2..6 of gx) += delta1^T [phi, 1].
+    {
+      const Op8<BF16> b = (c16 >= 2 && c16 <= 6) ? op_lds<BF16>(&TP1[c16 * kTs + 8 * q4])
+                                                 : op_zero<BF16>();
 #pragma unroll
-    for (int pk = 0; pk < 2; ++pk) {
-      const Op8<BF16> b = (row >= 2 && row <= 6)
-                              ? op_lds<BF16>(&TP1[row * kTs + 16 * pk + 8 * half])
-                              : op_zero<BF16>();
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) mma16<BF16>(gx[mb], a_frag(T1, pk, mb), b);
+      for (int mb = 0; mb < 4; ++mb) mma16x16<BF16>(gx[mb], a_frag16(T1, mb), b);
     }
     wave_lds_sync();
   }
@@ -775,8 +820,8 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
   // conversions are exact), so no wave waits on another's read-modify-write
   // of LDS. The block writes one partial per parameter, rounded to FP32 (the
   // precision of the accumulators it sums; the cross-block sum is FP64).
-  float* red = (float*)lds;            // [kCvWaves][kMlpNParam]
-  __shared__ double s3w[kCvWaves];
+  float* red = (float*)lds;            // [WAVES][kMlpNParam]
+  __shared__ double s3w[WAVES];
   __syncthreads();                     // every wave has left the segment loop
   {
     float* mine = red + wave * kMlpNParam;
@@ -787,15 +832,15 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           mine[320 + unit_of(mb, r, half) * 64 + 32 * nb + row] = gw2[mb][nb][r];
-    // gx: lane column `row`, unit u(mb, r, half), at slot base + u * step:
+    // gx: lane column c16, unit 16 mb + 4 q4 + r, at slot base + u * step:
     // b2 (column 0), W3 (1), W1 (2..5, one input each), b1 (6).
-    if (row <= 6) {
-      const int base = row == 0 ? 4416 : row == 1 ? 4480 : row <= 5 ? row - 2 : 256;
-      const int step = (row >= 2 && row <= 5) ? 4 : 1;
+    if (c16 <= 6) {
+      const int base = c16 == 0 ? 4416 : c16 == 1 ? 4480 : c16 <= 5 ? c16 - 2 : 256;
+      const int step = (c16 >= 2 && c16 <= 5) ? 4 : 1;
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[base + unit_of(mb, r, half) * step] = gx[mb][r];
+        for (int r = 0; r < 4; ++r) mine[base + (16 * mb + 4 * q4 + r) * step] = gx[mb][r];
     }
     const double s3 = wave_sum((double)gb3);
     if (lane == 0) s3w[wave] = s3;
@@ -803,24 +848,28 @@ __device__ __forceinline__ void cv_bwd_body(const CvParams& P) {
   __syncthreads();
   // Block-major: the block's 4545 partials are one row (padded to whole
   // 128-byte lines).
-  for (int i = threadIdx.x; i < kMlpNParam; i += kCvThreads) {
+  for (int i = threadIdx.x; i < kMlpNParam; i += 64 * WAVES) {
     double acc = i == kMlpNParam - 1 ? s3w[0] : (double)red[i];
 #pragma unroll
-    for (int w = 1; w < kCvWaves; ++w)
+    for (int w = 1; w < WAVES; ++w)
       acc += i == kMlpNParam - 1 ? s3w[w] : (double)red[w * kMlpNParam + i];
     P.grad_partials[(uint64_t)blockIdx.x * kGradStride + i] = (float)acc;
   }
 }
 
-// The BF16 form fits two waves per SIMD (256 VGPRs; 77 KB of LDS, two
-// workgroups per CU); the FP32 form's 130 KB allow one workgroup per CU.
-__global__ __launch_bounds__(kCvThreads) __attribute__((amdgpu_waves_per_eu(2))) void
+// The BF16 form fits two waves per SIMD (256 VGPRs). Eight waves to a workgroup
+// (145 KB of LDS for the gradient sum) fill a CU as two workgroups of four do,
+// with half the prologues and half the gradient rows to write and to reduce;
+// a minibatch that leaves CUs without one takes workgroups of four. The FP32
+// form's 130 KB allow four waves.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2))) void
 cv_bwd_kernel_bf16(const CvParams P) {
-  cv_bwd_body<true>(P);
+  cv_bwd_body<true, WAVES>(P);
 }
 
 __global__ __launch_bounds__(kCvThreads) void cv_bwd_kernel_fp32(const CvParams P) {
-  cv_bwd_body<false>(P);
+  cv_bwd_body<false, kCvWaves>(P);
 }
 
 // Bound: VALU issue plus the MFMAs that do not overlap it (per wave and date 20
@@ -841,12 +890,12 @@ __global__ __launch_bounds__(kCvThreads) void cv_eval_kernel(const CvParams P) {
   stamp(P.h.clock);
   using FT = FragT<BF16>;
   __shared__ __attribute__((aligned(16))) FT s_w2f[kFragFloats];
-  __shared__ __attribute__((aligned(16))) float s_lanec[kLaneFloats];
+  __shared__ __attribute__((aligned(16))) float s_lanec[kLanecFloats];
   const HestonParams& Hp = P.h;
   {
-    WeightRegs wr;
+    WeightRegs<BF16, kCvThreads> wr;
     weights_load<false>(P.w2f, nullptr, P.lanec, wr);
-    weights_store<false>(wr, s_w2f, (FT*)nullptr, s_lanec);
+    weights_store<false>(wr, s_w2f, nullptr, s_lanec);
   }
   __syncthreads();
 
@@ -936,8 +985,9 @@ __global__ __launch_bounds__(kCvThreads) void cv_eval_kernel(const CvParams P) {
 // Builds the per-lane fragments from the flat weights (one thread per
 // output float). Units: u(mb, r, h) as above; layer-2 k-slot (kb, h, j) is
 // the layer-1 unit u(kb/2, 8 (kb mod 2) + j, h).
+template <bool BF16>
 __global__ void cv_pack_kernel(const float* __restrict__ th, float* __restrict__ w1f,
-                               float* __restrict__ w2f, float* __restrict__ w2tf,
+                               FragT<BF16>* __restrict__ w2f, FragT<BF16>* __restrict__ w2tf,
                                float* __restrict__ lanec) {
   const float* W1 = th;
   const float* b1 = th + 256;
@@ -954,15 +1004,13 @@ __global__ void cv_pack_kernel(const float* __restrict__ th, float* __restrict__
     const int j = t & 7, lane = (t >> 3) & 63, kb = (t >> 9) & 3, mb = t >> 11;
     const int row = lane & 31, h = lane >> 5;
     const int k_unit = unit_of(kb >> 1, 8 * (kb & 1) + j, h);
-    w2f[t] = W2[(32 * mb + row) * 64 + k_unit];
-    w2tf[t] = W2[k_unit * 64 + (32 * mb + row)];
+    w2f[t] = (FragT<BF16>)W2[(32 * mb + row) * 64 + k_unit];
+    w2tf[t] = (FragT<BF16>)W2[k_unit * 64 + (32 * mb + row)];
   }
-  if (t < kLanecFloats / 2) {
-    const int q = ((t >> 8) << 2) | (t & 3), lane = (t >> 2) & 63;   // t = lanec_index(lane, q)
-    const int h = lane >> 5, mb = q >> 4, r = q & 15;
-    const int u = unit_of(mb, r, h);
+  if (t < kLaneW3) {                       // t = lanec_index(h, q)
+    const int u = unit_of((t >> 4) & 1, t & 15, t >> 5);
     lanec[t] = b2[u] * kNeg2Log2e;
-    lanec[kLanecFloats / 2 + t] = 2.0f * W3[u];
+    lanec[kLaneW3 + t] = 2.0f * W3[u];
   }
 }
 
@@ -981,18 +1029,18 @@ __device__ __forceinline__ void slot_of(int u, int& mb, int& r, int& h) {
 // slice 0 adds the slices in order. With ADAM, the same thread then takes
 // one Adam step on (theta, m, v) with the bias corrections c1 = 1 - b1^t,
 // c2 = 1 - b2^t, and the block writes the new values into each fragment
-// slot that cv_pack_kernel gives the parameter (W1, b1: one; W2: one in
-// each of the two layouts; b2, W3: the 32 lanes of a half-wave). Padding
+// slot that cv_pack_kernel gives the parameter (W2: one in each of the two
+// layouts; the others one). Padding
 // slots keep the zeros of the first pack; b3 lives in theta only.
 constexpr int kGradThreads = 512, kGradCols = 32, kGradSlices = kGradThreads / kGradCols;
 constexpr int kGradBlocks = (kMlpNParam + kGradCols - 1) / kGradCols;
 
-template <bool ADAM>
+template <bool ADAM, bool BF16>
 __global__ __launch_bounds__(kGradThreads) void grad_adam_kernel(
     const float* __restrict__ partials, uint32_t n_blocks, double* __restrict__ grad,
     float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float lr, float b1,
-    float b2, float eps, float c1, float c2, float* __restrict__ w1f, float* __restrict__ w2f,
-    float* __restrict__ w2tf, float* __restrict__ lanec, const double* __restrict__ vpart,
+    float b2, float eps, float c1, float c2, float* __restrict__ w1f,
+    FragT<BF16>* __restrict__ w2f, FragT<BF16>* __restrict__ w2tf, float* __restrict__ lanec, const double* __restrict__ vpart,
     uint32_t vblocks, double* __restrict__ vmom) {
   if (blockIdx.x == kGradBlocks) {
     // The extra workgroup: the fixed-order merge of the hedged values'
@@ -1035,9 +1083,9 @@ __global__ __launch_bounds__(kGradThreads) void grad_adam_kernel(
   }
   if constexpr (!ADAM) return;
   __syncthreads();
-  // Fragment slots: up to 32 per parameter (b2, W3), kGradCols parameters.
-  for (int e = threadIdx.x; e < kGradCols * 32; e += kGradThreads) {
-    const int c = e >> 5, L = e & 31, ip = p0 + c;
+  // Fragment slots: two per parameter of W2, one of the others.
+  for (int e = threadIdx.x; e < kGradCols * 2; e += kGradThreads) {
+    const int c = e >> 1, L = e & 1, ip = p0 + c;
     if (ip >= kMlpNParam) continue;
     const float t = th_new[c];
     if (ip < 320) {                       // W1 [64][4] and b1 [64]: lane = unit row, h = 0
@@ -1046,35 +1094,34 @@ __global__ __launch_bounds__(kGradThreads) void grad_adam_kernel(
         w1f[(u >> 5) * 512 + (u & 31) * 8 + j] = t;
       }
     } else if (ip < 4416) {               // W2 [64 out][64 in]
-      if (L < 2) {
-        const int q = ip - 320;
-        const int a = L == 0 ? q >> 6 : q & 63;   // fragment row
-        const int k = L == 0 ? q & 63 : q >> 6;   // k-slot unit
-        int mb, r, h;
-        slot_of(k, mb, r, h);
-        const int dst = (a >> 5) * 2048 + (2 * mb + (r >> 3)) * 512 + ((a & 31) + 32 * h) * 8 + (r & 7);
-        (L == 0 ? w2f : w2tf)[dst] = t;
-      }
+      const int q = ip - 320;
+      const int a = L == 0 ? q >> 6 : q & 63;     // fragment row
+      const int k = L == 0 ? q & 63 : q >> 6;     // k-slot unit
+      int mb, r, h;
+      slot_of(k, mb, r, h);
+      const int dst = (a >> 5) * 2048 + (2 * mb + (r >> 3)) * 512 + ((a & 31) + 32 * h) * 8 + (r & 7);
+      (L == 0 ? w2f : w2tf)[dst] = (FragT<BF16>)t;
     } else if (ip < 4544) {               // b2 [64] (scaled) and W3 [64]
       const bool is_b2 = ip < 4480;
       const int u = is_b2 ? ip - 4416 : ip - 4480;
       int mb, r, h;
       slot_of(u, mb, r, h);
-      const int dst = lanec_index(32 * h + L, 16 * mb + r);
-      if (is_b2)
-        lanec[dst] = t * kNeg2Log2e;
-      else
-        lanec[kLanecFloats / 2 + dst] = 2.0f * t;
+      const int dst = lanec_index(h, 16 * mb + r);
+      if (L == 0) lanec[is_b2 ? dst : kLaneW3 + dst] = is_b2 ? t * kNeg2Log2e : 2.0f * t;
     }
   }
 }
 
 }  // namespace
 
-hipError_t launch_cv_pack(const float* theta, float* w1f, float* w2f, float* w2tf, float* lanec,
-                          hipStream_t s) {
-  hipLaunchKernelGGL(cv_pack_kernel, dim3(kW2fFloats / 256), dim3(256), 0, s, theta, w1f, w2f,
-                     w2tf, lanec);
+hipError_t launch_cv_pack(const float* theta, bool bf16, float* w1f, void* w2f, void* w2tf,
+                          float* lanec, hipStream_t s) {
+  if (bf16)
+    hipLaunchKernelGGL(cv_pack_kernel<true>, dim3(kW2fFloats / 256), dim3(256), 0, s, theta, w1f,
+                       (__bf16*)w2f, (__bf16*)w2tf, lanec);
+  else
+    hipLaunchKernelGGL(cv_pack_kernel<false>, dim3(kW2fFloats / 256), dim3(256), 0, s, theta, w1f,
+                       (float*)w2f, (float*)w2tf, lanec);
   return hipGetLastError();
 }
 
@@ -1142,13 +1189,17 @@ uint32_t cv_values_blocks(uint64_t n_paths, uint32_t n_seg, uint32_t* split) {
 
 hipError_t launch_cv_backward(const CvParams& p, hipStream_t s, uint32_t* n_blocks) {
   CvParams q = p;
-  const uint32_t nb = cv_bwd_blocks(p.h.n_paths, p.n_seg, &q.seg_split);
-  *n_blocks = nb;
+  uint32_t nb = cv_bwd_blocks(p.h.n_paths, p.n_seg, &q.seg_split);
   if (nb == 0 || p.n_seg == 0 || p.c_first + p.h.n_paths > p.c_stride ||
       p.h.n_paths >= (1ull << 30))
     return hipErrorInvalidValue;
-  if (p.bf16)
-    hipLaunchKernelGGL(cv_bwd_kernel_bf16, dim3(nb), dim3(kCvThreads), 0, s, q);
+  const bool wide = p.bf16 && nb >= 512;
+  if (wide) nb = (nb + 1) / 2;
+  *n_blocks = nb;
+  if (wide)
+    hipLaunchKernelGGL(cv_bwd_kernel_bf16<8>, dim3(nb), dim3(512), 0, s, q);
+  else if (p.bf16)
+    hipLaunchKernelGGL(cv_bwd_kernel_bf16<4>, dim3(nb), dim3(256), 0, s, q);
   else
     hipLaunchKernelGGL(cv_bwd_kernel_fp32, dim3(nb), dim3(kCvThreads), 0, s, q);
   return hipGetLastError();
@@ -1156,14 +1207,20 @@ hipError_t launch_cv_backward(const CvParams& p, hipStream_t s, uint32_t* n_bloc
 
 hipError_t launch_adam_pack(const float* partials, uint32_t n_blocks, const CvValMoments& vm,
                             double* grad, float* theta, float* m, float* v, int t, double lr,
-                            double b1, double b2, double eps, float* w1f, float* w2f, float* w2tf,
-                            float* lanec, hipStream_t s) {
+                            double b1, double b2, double eps, bool bf16, float* w1f, void* w2f,
+                            void* w2tf, float* lanec, hipStream_t s) {
   if (n_blocks == 0 || vm.n_blocks == 0 || vm.partials == nullptr || vm.out == nullptr)
     return hipErrorInvalidValue;
   const float c1 = (float)(1.0 - std::pow(b1, t)), c2 = (float)(1.0 - std::pow(b2, t));
-  hipLaunchKernelGGL(grad_adam_kernel<true>, dim3(kGradBlocks + 1), dim3(kGradThreads), 0, s, partials,
-                     n_blocks, grad, theta, m, v, (float)lr, (float)b1, (float)b2, (float)eps, c1,
-                     c2, w1f, w2f, w2tf, lanec, vm.partials, vm.n_blocks, vm.out);
+  const dim3 grid(kGradBlocks + 1), block(kGradThreads);
+  if (bf16)
+    hipLaunchKernelGGL((grad_adam_kernel<true, true>), grid, block, 0, s, partials, n_blocks, grad,
+                       theta, m, v, (float)lr, (float)b1, (float)b2, (float)eps, c1, c2, w1f,
+                       (__bf16*)w2f, (__bf16*)w2tf, lanec, vm.partials, vm.n_blocks, vm.out);
+  else
+    hipLaunchKernelGGL((grad_adam_kernel<true, false>), grid, block, 0, s, partials, n_blocks, grad,
+                       theta, m, v, (float)lr, (float)b1, (float)b2, (float)eps, c1, c2, w1f,
+                       (float*)w2f, (float*)w2tf, lanec, vm.partials, vm.n_blocks, vm.out);
   return hipGetLastError();
 }
 
@@ -1171,7 +1228,7 @@ hipError_t launch_grad_sum(const float* partials, uint32_t n_blocks, const CvVal
                            double* grad, hipStream_t s) {
   if (n_blocks == 0 || vm.n_blocks == 0 || vm.partials == nullptr || vm.out == nullptr)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(grad_adam_kernel<false>, dim3(kGradBlocks + 1), dim3(kGradThreads), 0, s, partials,
+  hipLaunchKernelGGL((grad_adam_kernel<false, false>), dim3(kGradBlocks + 1), dim3(kGradThreads), 0, s, partials,
                      n_blocks, grad, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                      nullptr, nullptr, nullptr, nullptr, vm.partials, vm.n_blocks, vm.out);
   return hipGetLastError();

@@ -309,9 +309,10 @@ struct CvParams {
   int bf16;                  // 1: BF16 MFMA operands, 0: FP32 MFMA
   const float* theta;        // [4545] flat weights (b3 is read from here)
   const float* w1f;          // [2 mb][64 lane][8]   layer-1 A fragments (W1 | b1 | 0)
-  const float* w2f;          // [2 mb][4 kb][64][8]  layer-2 A fragments (permuted W2)
-  const float* w2tf;         // [2 mb][4 kb][64][8]  W2^T fragments for the backward pass
-  const float* lanec;        // [2][8][64][4]: per-lane b2 * (-2 / ln 2), 2 W3 of the lane's units
+  const void* w2f;           // [2 mb][4 kb][64][8]  layer-2 A fragments (permuted W2), in the
+                             // operand type (BF16 or FP32)
+  const void* w2tf;          // [2 mb][4 kb][64][8]  W2^T fragments for the backward pass
+  const float* lanec;        // [2][2 halves][32]: b2 * (-2 / ln 2), then 2 W3, of a half's units
   const float* dfac;         // [n_steps + 1]: e^{r t_i}
   // training
   uint32_t val_blocks;       // blocks of the hedged-value kernel whose moment vectors
@@ -336,9 +337,9 @@ struct CvParams {
 constexpr int kCvPathsPerBlock = 256;       // evaluation: 4 waves of 64 paths
 constexpr int kCvTrainPathsPerBlock = 128;  // training: 4 waves of 32 paths (/ split)
 // Fragment layout of the weights, built on the device from theta.
-constexpr int kW1fFloats = 2 * 64 * 8, kW2fFloats = 2 * 4 * 64 * 8, kLanecFloats = 2 * 64 * 32;
-hipError_t launch_cv_pack(const float* theta, float* w1f, float* w2f, float* w2tf, float* lanec,
-                          hipStream_t s);
+constexpr int kW1fFloats = 2 * 64 * 8, kW2fFloats = 2 * 4 * 64 * 8, kLanecFloats = 2 * 2 * 32;
+hipError_t launch_cv_pack(const float* theta, bool bf16, float* w1f, void* w2f, void* w2tf,
+                          float* lanec, hipStream_t s);
 hipError_t launch_cv_price(const CvParams& p, hipStream_t s, uint32_t* n_blocks);
 // Training on the feature cache: fill it (h.n_paths paths from h.path_offset),
 // the network along every 32-path tile of the minibatch with the per-path
@@ -366,8 +367,8 @@ struct CvValMoments {
 // the same launch merges the hedged values' moments into vm.out.
 hipError_t launch_adam_pack(const float* partials, uint32_t n_blocks, const CvValMoments& vm,
                             double* grad, float* theta, float* m, float* v, int t, double lr,
-                            double b1, double b2, double eps, float* w1f, float* w2f, float* w2tf,
-                            float* lanec, hipStream_t s);
+                            double b1, double b2, double eps, bool bf16, float* w1f, void* w2f,
+                            void* w2tf, float* lanec, hipStream_t s);
 hipError_t launch_grad_sum(const float* partials, uint32_t n_blocks, const CvValMoments& vm,
                            double* grad, hipStream_t s);
 

@@ -361,3 +361,26 @@ def test_qmc_tiles(ctx, prec, d, n, N, offset, reps):
                         mc.Options(prec=prec, path_offset=offset, path_values=True))
     assert a["replicate_price"][0] == pytest.approx(b["replicate_price"][0], rel=1e-12, abs=1e-12)
     assert a["replicate_geo"][0] == pytest.approx(b["replicate_geo"][0], rel=1e-12, abs=1e-12)
+
+
+@pytest.mark.parametrize("wide,narrow,n,m_every", [(32768, 32512, 4, 1), (65536, 65280, 3, 2)])
+def test_cv_gradient_of_wide_workgroups(ctx, wide, narrow, n, m_every):
+    """Minibatches on either side of the line between workgroups of four and
+    of eight waves (1016 and 1024 tiles over two waves; 2040 and 2048 over
+    one). The paths they share cancel in the
+    difference of their gradients, up to the BF16 rounding of dL/dDelta that
+    the moved mean changes (2^-9 of each of N segments, at random: 1e-5 of
+    the gradient); the rest is the new paths' part, to BF16's 2e-2. A lost
+    or doubled tile would show as 1e-3 or 5e-4."""
+    hp = {k: synth.HESTON[k] for k in ("S0", "v0", "kappa", "theta", "xi", "rho", "r", "T", "K")}
+    model = mc.Model(kind=mc.MC_HESTON, **{k: v for k, v in hp.items() if k != "K"})
+    pay = mc.Payoff(mc.MC_ASIAN_ARITH_CALL, hp["K"], cv=mc.MC_CV_LEARNED)
+    th = (synth.glorot_mlp() + np.random.default_rng(5).normal(0.0, 0.2, 4545)).astype(np.float32)
+    th = th.astype(np.float64)
+    g, o = [], []
+    for B in (wide, narrow):
+        g.append(mc.mc_cv_loss_grad(ctx, model, pay, n, SEED, 2, 64, B, th, hedge_every=m_every,
+                                    prec=mc.MC_BF16_GEMM)[1].astype(np.float64))
+        o.append(oracle.cv_loss_grad(hp, n, th, B, SEED, tag=2, path0=64, m_every=m_every)[1])
+    err = np.linalg.norm((g[0] - g[1]) - (o[0] - o[1]))
+    assert err < 0.05 * np.linalg.norm(o[0] - o[1]) + 1e-4 * np.linalg.norm(o[0])
