@@ -421,8 +421,18 @@ template <typename F>
 mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, int C,
                       double* host_path_values, F&& launch, Moments* out, double* kernel_ms,
                       uint32_t paths_per_block = kBlock, uint32_t max_blocks = UINT32_MAX,
-                      const std::function<hipError_t(hipStream_t)>& queued = nullptr) {
+                      const std::function<hipError_t(hipStream_t)>& queued = nullptr,
+                      int ws_channels = 0) {
   if (C < 1 || C > kMaxChannels) return fail(ctx, MC_ERR_DEVICE, "channel count %d", C);
+  // A run of fewer channels than its rows would have asks a caller's workspace
+  // for the rows' layout (mc_workspace_bytes).
+  if (o.workspace && ws_channels > C) {
+    const size_t asked = layout_for(n_paths, ws_channels, host_path_values != nullptr,
+                                    paths_per_block, max_blocks).bytes;
+    if (o.workspace_bytes < asked)
+      return fail(ctx, MC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", o.workspace_bytes,
+                  asked);
+  }
   const RunLayout L =
       layout_for(n_paths, C, host_path_values != nullptr, paths_per_block, max_blocks);
   char* base = nullptr;
@@ -564,7 +574,8 @@ mc_status gbm_run(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64
                        p.clock = ctx->clock;
                        return launch_gbm(p, mask, fp64, s, nb);
                      },
-                     mom, kernel_ms, kBlock, kGbmMaxBlocks);
+                     mom, kernel_ms, kBlock, kGbmMaxBlocks, nullptr,
+                     gbm_channels(gbm_pick_mask(want, fp64, logs, ctx->coarsen, true)));
 }
 
 // Fills `out` for one GBM payoff from the moments of a run.
@@ -717,7 +728,7 @@ mc_status heston_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
                                p.clock = ctx->clock;
                                return launch_heston(p, mask, fp64, s, nb);
                              },
-                             &mom, &kms, kBlock, kHestonMaxBlocks);
+                             &mom, &kms, kBlock, kHestonMaxBlocks, nullptr, 2);
   if (st != MC_OK) return st;
   mc_result r{};
   const int c = rows && f->kind != MC_EURO_CALL ? 1 : 0;
@@ -1044,14 +1055,24 @@ RunLayout basket_layout(uint64_t n_paths, int C, bool want_path) {
   return layout_for(n_paths, C, want_path, kBasketTile, kBasketMaxBlocks);
 }
 
-// Workspace of a basket run: moment layout, the fragments of L' and the
+// Device memory of a basket run: moment layout, the fragments of L' and the
 // per-asset table.
 size_t basket_frag_bytes(uint32_t d, mc_precision prec) {
   return (size_t)basket_l_terms(basket_prec(prec)) * basket_pairs(d / 16) * 512 * sizeof(uint16_t);
 }
-size_t basket_ws_bytes(size_t layout_bytes, uint32_t d, mc_precision prec) {
+size_t basket_run_bytes(size_t layout_bytes, uint32_t d, mc_precision prec) {
   return align256(layout_bytes) + align256(basket_frag_bytes(d, prec)) +
          align256(4 * 256 * sizeof(float));
+}
+
+// What a caller's workspace must hold, a contract of its own: a moment vector
+// per 256 paths, L' in 32 x 32 blocks and the per-asset table. A run that
+// needs more than a workspace of this size takes the context's.
+size_t basket_ws_bytes(uint64_t n_paths, bool want_path, uint32_t d, mc_precision prec) {
+  const uint32_t nd = d <= 32 ? 1 : d <= 64 ? 2 : d <= 128 ? 4 : 8;
+  const size_t blk = align256((size_t)nd * (nd + 1) * 512 * (prec == MC_FP32 ? 4 : 2));
+  return align256(layout_for(n_paths, 3, want_path).bytes) +
+         blk * (prec == MC_BF16X2_GEMM ? 2 : 1) + align256(4 * 256 * sizeof(float));
 }
 
 // A basket run with `port` set prices the call portfolio of the risk metrics
@@ -1090,8 +1111,15 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   const RunLayout Lay = basket_layout(n_paths, 3, o0.path_values != nullptr);
   const size_t off_blk = align256(Lay.bytes);
   const size_t off_asset = off_blk + align256(basket_frag_bytes(d, o0.prec));
+  const size_t asked = basket_ws_bytes(n_paths, o0.path_values != nullptr, d, o0.prec);
+  const size_t needed = basket_run_bytes(Lay.bytes, d, o0.prec);
+  if (o0.workspace && o0.workspace_bytes < asked)
+    return fail(ctx, MC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", o0.workspace_bytes,
+                asked);
+  mc_options ow = o0;
+  if (ow.workspace_bytes < needed) ow.workspace = nullptr;
   char* base = nullptr;
-  mc_status st = get_ws(ctx, o0, basket_ws_bytes(Lay.bytes, d, o0.prec), &base);
+  mc_status st = get_ws(ctx, ow, needed, &base);
   if (st != MC_OK) return st;
   hipStream_t s = stream_of(ctx, o0);
   if (!ctx->dev_L_valid) {
@@ -1451,13 +1479,15 @@ mc_status gbm_fd_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   static_assert(n_moments(kMaxMomentChannels) <= kFdMoments, "moment staging");
   mc_status st = get_pinned(ctx, kFdMoments + 2 * M);
   if (st != MC_OK) return st;
-  // The workspace a bumped run of one functional set takes.
-  const uint32_t mask = gbm_pick_mask(bit, true, m->scheme == MC_LOG_EULER, 1, false);
+  // A caller's workspace must hold a bumped run with the payoff's rows.
+  const uint32_t mask = gbm_pick_mask(bit, true, m->scheme == MC_LOG_EULER, 1, true);
   if (!mask) return fail(ctx, MC_ERR_UNSUPPORTED, "payoff not available for this scheme/precision");
+  const size_t asked = layout_for(n_paths < kMlmcChunk ? n_paths : kMlmcChunk, gbm_channels(mask),
+                                  false, kBlock, kGbmMaxBlocks).bytes;
+  if (o.workspace && o.workspace_bytes < asked)
+    return fail(ctx, MC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", o.workspace_bytes,
+                asked);
   char* base = nullptr;
-  st = get_ws(ctx, o, layout_for(n_paths < kMlmcChunk ? n_paths : kMlmcChunk, gbm_channels(mask),
-                                 false, kBlock, kGbmMaxBlocks).bytes, &base);
-  if (st != MC_OK) return st;
   st = get_mlmc_buf(ctx, (size_t)2 * kGbmMaxBlocks * M * sizeof(double), &base);
   if (st != MC_OK) return st;
   double theta[2];
@@ -1643,9 +1673,9 @@ size_t mc_workspace_bytes(const mc_model* m, const mc_payoff* f, uint64_t n_path
   const uint32_t cap = m->kind == MC_GBM ? kGbmMaxBlocks
                        : heston_persistent ? kHestonMaxBlocks
                                            : UINT32_MAX;
-  size_t bytes = m->kind == MC_GBM_BASKET
-                     ? basket_layout(n_paths, (int)C, o.path_values != nullptr).bytes
-                     : layout_for(n_paths, (int)C, o.path_values != nullptr, kBlock, cap).bytes;
+  if (m->kind == MC_GBM_BASKET)
+    return basket_ws_bytes(n_paths, o.path_values != nullptr, m->dim, o.prec);
+  size_t bytes = layout_for(n_paths, (int)C, o.path_values != nullptr, kBlock, cap).bytes;
   if (m->kind == MC_HESTON && o.greeks && o.greeks_method == MC_GREEKS_PATHWISE &&
       (n_steps + mcp::kCkpt - 1) / mcp::kCkpt > (uint32_t)mcp::kLdsCkpt)
     bytes = align256(bytes) + align256(mc_adjoint_ckpt_bytes(n_paths, n_steps, mcp::kCkpt));
@@ -1657,7 +1687,6 @@ size_t mc_workspace_bytes(const mc_model* m, const mc_payoff* f, uint64_t n_path
     bytes = align256(layout_for(n_big, 3, o.path_values != nullptr, kCvPathsPerBlock).bytes) +
             cv_extra_bytes(n_steps);
   }
-  if (m->kind == MC_GBM_BASKET) bytes = basket_ws_bytes(bytes, m->dim, o.prec);
   return bytes;
 }
 

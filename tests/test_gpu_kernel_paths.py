@@ -2,6 +2,7 @@
 remainders of a Philox block, path indices that straddle 2^32, functional sets
 of their own, the edges of tiles. Each is held to the FP64 oracle or to the
 general path."""
+import ctypes as C
 import math
 
 import numpy as np
@@ -10,6 +11,7 @@ import pytest
 import oracle
 import paper_1906_02818_amd as mc
 import synth
+from paper_1906_02818_amd import _abi
 from lsm_basis import MAXC, PUT
 
 pytestmark = pytest.mark.gpu
@@ -384,3 +386,34 @@ def test_cv_gradient_of_wide_workgroups(ctx, wide, narrow, n, m_every):
         o.append(oracle.cv_loss_grad(hp, n, th, B, SEED, tag=2, path0=64, m_every=m_every)[1])
     err = np.linalg.norm((g[0] - g[1]) - (o[0] - o[1]))
     assert err < 0.05 * np.linalg.norm(o[0] - o[1]) + 1e-4 * np.linalg.norm(o[0])
+
+
+def test_workspace_contract(ctx):
+    """A workspace of mc_workspace_bytes serves every kind of run, also where
+    the run's own layout is larger or smaller, and one byte less is refused."""
+    import torch
+    d = 16
+    basket = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.03, T=1.0,
+                      sigma=np.full(d, 0.2), corr=np.eye(d))
+    cases = [(basket, mc.Payoff(mc.MC_BASKET_CALL, 100.0), N, dict(prec=p, path_values=pv))
+             for N in (300, 100003) for p in (mc.MC_FP32, mc.MC_BF16_GEMM) for pv in (False, True)]
+    cases += [(gbm(), mc.Payoff(mc.MC_UO_BARRIER_CALL, G["K"], B=G["B"]), 5000, dict(prec=mc.MC_FP64)),
+              (gbm(), mc.Payoff(mc.MC_EURO_CALL, G["K"]), 5000, dict(prec=mc.MC_FP32)),
+              (heston(), mc.Payoff(mc.MC_EURO_CALL, 100.0), 5000, dict(prec=mc.MC_FP32))]
+    for m, f, N, kw in cases:
+        call = mc._Marshal(m, f, mc.Options(**kw), N)
+        if kw.get("path_values"):
+            call.want_path_values(N, 3)
+        need = _abi.load().mc_workspace_bytes(C.byref(call.cm), C.byref(call.cp), N, 5,
+                                              C.byref(call.co))
+        buf = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+        call.co.workspace = buf.data_ptr()
+        res = _abi.McResult()
+
+        def run(size):
+            call.co.workspace_bytes = size
+            return _abi.load().mc_price(ctx.handle, C.byref(call.cm), C.byref(call.cp), N, 5, SEED,
+                                        C.byref(call.co), C.byref(res))
+        assert run(need) == mc.MC_OK
+        assert res.price == mc.mc_price(ctx, m, f, N, 5, SEED, mc.Options(**kw))["price"]
+        assert run(need - 1) == -7           # MC_ERR_WORKSPACE
