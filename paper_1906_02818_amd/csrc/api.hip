@@ -54,6 +54,8 @@ struct mc_context {
   // and the O(d^3) factorisation, which costs milliseconds at d = 256.
   std::vector<double> chol_corr, chol_L;
   bool chol_pd = false;
+  void* split_buf = nullptr;     // sums of split basket tiles (at most 15 MB)
+  size_t split_bytes = 0;
   double* dev_L = nullptr;       // chol_L while dev_L_valid
   size_t dev_L_count = 0;
   bool dev_L_valid = false;
@@ -1089,6 +1091,21 @@ struct BasketQmc {
   double geo_mean;
 };
 
+mc_status get_split_buf(mc_context* ctx, size_t bytes, char** base) {
+  if (ctx->split_bytes < bytes) {
+    if (ctx->split_buf) {
+      HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+      HIP_TRY(ctx, hipFree(ctx->split_buf));
+      ctx->split_buf = nullptr;
+      ctx->split_bytes = 0;
+    }
+    HIP_TRY(ctx, hipMalloc(&ctx->split_buf, bytes));
+    ctx->split_bytes = bytes;
+  }
+  *base = (char*)ctx->split_buf;
+  return MC_OK;
+}
+
 // Set-up of a basket run whose arguments validate_basket has accepted: the
 // factor in device memory, the launch that packs L' and the per-asset
 // constants into the workspace (after the moment area of run_moments), and
@@ -1161,7 +1178,15 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   k.d = d;
   k.frag = (uint16_t*)(base + off_blk);
   k.asset_out = (float*)(base + off_asset);
-  k.zero = zero;
+  k.zero[0] = zero;
+  BasketSplit split;
+  if (!qmc) split = basket_split(n_paths, n_steps, d);
+  if (split.parts > 1) {
+    char* sb = nullptr;
+    st = get_split_buf(ctx, split.sums * sizeof(float) + split.arrivals * sizeof(uint32_t), &sb);
+    if (st != MC_OK) return st;
+    k.zero[1] = {(uint32_t*)(sb + split.sums * sizeof(float)), split.arrivals};
+  }
   HIP_TRY(ctx, launch_basket_pack(k, prec, s));
   mc_options o = o0;
   o.workspace = base;
@@ -1175,6 +1200,10 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   p.k1 = (uint32_t)(seed >> 32);
   p.d = d;
   p.Lfrag = base + off_blk;
+  p.split_from = split.from;
+  p.split_parts = split.parts;
+  p.split_sums = split.parts > 1 ? (float*)ctx->split_buf : nullptr;
+  p.split_arrivals = k.zero[1].words;
   p.z_scale = p.x_scale = 1.0f;
   if (prec == BK_FP32) p.z_scale = (float)std::sqrt(2.0 * std::log(2.0));
   if (prec == BK_FP16)
@@ -1588,6 +1617,7 @@ mc_status mc_destroy(mc_context* ctx) {
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->clock) (void)hipHostFree(ctx->clock);
   if (ctx->dev_L) (void)hipFree(ctx->dev_L);
+  if (ctx->split_buf) (void)hipFree(ctx->split_buf);
   if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
   if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
   if (ctx->lsm_buf) (void)hipFree(ctx->lsm_buf);

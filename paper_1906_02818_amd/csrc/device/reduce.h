@@ -53,19 +53,19 @@ __device__ __forceinline__ void stamp(uint64_t* clock) {
     store_agent(clock, (uint64_t)wall_clock64());
 }
 
-// True in the workgroup of the launch that arrives last: every store_agent and
+// True in the last of n workgroups to arrive: every store_agent and
 // device-scope atomic of the others is then visible to its load_agent. The
 // counter, zero before the launch, is left at zero.
-__device__ __forceinline__ bool arrives_last(uint32_t* arrivals) {
+__device__ __forceinline__ bool arrives_last(uint32_t* arrivals, uint32_t n) {
   __shared__ uint32_t order;
   __builtin_amdgcn_s_waitcnt(0);           // this wave's stores have arrived
   __syncthreads();
   if (threadIdx.x == 0u) {
     order = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (order == gridDim.x - 1u) *arrivals = 0u;
+    if (order == n - 1u) *arrivals = 0u;
   }
   __syncthreads();
-  return order == gridDim.x - 1u;
+  return order == n - 1u;
 }
 
 // v of the lane whose number differs in bit OFF (a power of two up to 32),

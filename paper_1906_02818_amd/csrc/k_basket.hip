@@ -189,7 +189,8 @@ __global__ __launch_bounds__(256) void basket_pack_kernel(const BasketPack K) {
   constexpr int NL = Form<PREC>::NL;
   const uint32_t n_pairs = basket_pairs(K.d >> 4);
   const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
-  for (uint32_t i = gid; i < K.zero.n; i += gridDim.x * 256u) K.zero.words[i] = 0u;
+  for (int z = 0; z < 2; ++z)
+    for (uint32_t i = gid; i < K.zero[z].n; i += gridDim.x * 256u) K.zero[z].words[i] = 0u;
   if (blockIdx.x == gridDim.x - 1u) {
     for (uint32_t i = threadIdx.x; i < 4u * 256u; i += 256u)
       if ((i & 255u) < K.d) K.asset_out[i] = K.asset[i];
@@ -293,8 +294,11 @@ __device__ __forceinline__ uint32_t row_block(uint32_t set, uint32_t i) {
   return 2u * S * (i >> 1) + ((i & 1u) ? 2u * S - 1u - set : set);
 }
 
-// RPW: 16-row blocks per wave (d <= 4 W RPW).
-template <int PREC, bool PORT, bool QMC, int W, int RPW>
+// RPW: 16-row blocks per wave (d <= 4 W RPW). SPLIT: the tiles from
+// P.split_from on have P.split_parts workgroups each, of one Philox block of
+// assets per wave; they put their sums in P.split_sums and the last to arrive
+// takes the product.
+template <int PREC, bool PORT, bool QMC, int W, int RPW, bool SPLIT = false>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) void basket_kernel(const BasketParams P) {
   stamp(P.clock);
   typedef Form<PREC> F;
@@ -328,6 +332,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   if (threadIdx.x < kTile) s_acc[threadIdx.x].zero();
 
   const uint64_t tiles = (P.n_paths + kTile - 1) / kTile;
+  uint32_t piece = ~0u;                    // SPLIT: the workgroup's part of its tile
+  if constexpr (SPLIT) {
+    nblk = (uint32_t)tiles;                // one tile, or part of one, per workgroup
+    if (blk >= P.split_from) {
+      const uint32_t i = blk - P.split_from;
+      blk = P.split_from + i / P.split_parts;
+      piece = i % P.split_parts;
+    }
+  }
   for (uint64_t tile = blk; tile < tiles; tile += nblk) {
     // ---- sums of the normals ----
     const uint64_t path = P.path_offset + tile * kTile + (uint64_t)lane;
@@ -340,9 +353,30 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
     } else {
       with_uniform_high(path, [&](uint32_t hi) {
         const PathRng g = make_rng((uint32_t)path, hi, P.tag, keys);
-        for (uint32_t q = wave; q < nq; q += W)
-          sum_block<PREC>(s_sum, n, nq, q, lane, [&](uint32_t j) { return philox(j, g, keys); });
+        if constexpr (SPLIT) {
+          const bool whole = piece == ~0u;
+          const uint32_t q0 = whole ? wave : piece * W + wave, q1 = whole ? nq : q0 + 1u;
+          for (uint32_t q = q0; q < q1 && q < nq; q += W)
+            sum_block<PREC>(s_sum, n, nq, q, lane, [&](uint32_t j) { return philox(j, g, keys); });
+        } else {
+          for (uint32_t q = wave; q < nq; q += W)
+            sum_block<PREC>(s_sum, n, nq, q, lane, [&](uint32_t j) { return philox(j, g, keys); });
+        }
       });
+    }
+    if constexpr (SPLIT) {
+      if (piece != ~0u) {
+        const uint32_t i = blk - P.split_from, q = piece * W + wave;
+        float* rows_of = P.split_sums + (size_t)i * d * kTile;
+        if (q < nq) {
+#pragma unroll
+          for (uint32_t t = 0; t < 4u; ++t)
+            store_agent(&rows_of[(4u * q + t) * kTile + lane], s_sum[(4u * q + t) * kRow + lane]);
+        }
+        if (!arrives_last(&P.split_arrivals[i], P.split_parts)) return;
+        for (uint32_t e = threadIdx.x; e < d * kTile; e += 64u * W)
+          s_sum[(e / kTile) * kRow + e % kTile] = load_agent(&rows_of[e]);
+      }
     }
     __syncthreads();
 
@@ -586,18 +620,32 @@ hipError_t launch_qmc_tile(const BasketParams& p, hipStream_t s, uint32_t blocks
   return hipGetLastError();
 }
 
-template <int PREC, bool PORT, bool QMC, int W, int RPW>
-hipError_t launch_w(const BasketParams& p, hipStream_t s, uint32_t nb) {
+template <int PREC, bool PORT, bool QMC, int W, int RPW, bool SPLIT>
+hipError_t launch_form(const BasketParams& p, hipStream_t s, uint32_t nb) {
   static_assert(kBasketMaxDim <= 4 * 8 * 8, "row blocks of the largest form");
   if (p.d > (uint32_t)(4 * W * RPW)) return hipErrorInvalidValue;
   const size_t lds = (size_t)p.d * kRow * sizeof(float);
   if (lds > 32768) {                       // above it: the default limit is 64 KB with the static part
-    const hipError_t e = hipFuncSetAttribute((const void*)basket_kernel<PREC, PORT, QMC, W, RPW>,
+    const hipError_t e = hipFuncSetAttribute((const void*)basket_kernel<PREC, PORT, QMC, W, RPW, SPLIT>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((basket_kernel<PREC, PORT, QMC, W, RPW>), dim3(nb), dim3(64 * W), lds, s, p);
+  hipLaunchKernelGGL((basket_kernel<PREC, PORT, QMC, W, RPW, SPLIT>), dim3(nb), dim3(64 * W), lds, s, p);
   return hipGetLastError();
+}
+
+template <int PREC, bool PORT, bool QMC, int W, int RPW>
+hipError_t launch_w(const BasketParams& p, hipStream_t s, uint32_t nb) {
+  if constexpr (!QMC) {
+    if (p.split_parts > 1u) {
+      if (p.split_parts != (p.d / 4u + W - 1u) / W || p.split_from > nb ||
+          p.split_sums == nullptr || p.split_arrivals == nullptr)
+        return hipErrorInvalidValue;
+      return launch_form<PREC, PORT, QMC, W, RPW, true>(
+          p, s, p.split_from + (nb - p.split_from) * p.split_parts);
+    }
+  }
+  return launch_form<PREC, PORT, QMC, W, RPW, false>(p, s, nb);
 }
 
 // Waves per tile and row blocks per wave. A CU holds 16 waves at the 128 VGPRs
@@ -646,6 +694,28 @@ hipError_t launch_any(const BasketParams& p, int prec, hipStream_t s, uint32_t n
 
 int basket_l_terms(int prec) {
   return prec == BK_FP32 ? Form<BK_FP32>::NL : prec == BK_BF16X2 ? Form<BK_BF16X2>::NL : 1;
+}
+
+// The last workgroups of a launch with one tile each leave most CUs idle: 1563
+// tiles are six on each of 256 CUs and 27 on 27 of them. Those past the last
+// multiple of 256 are split, by asset blocks so that the sums keep their
+// order, into parts of one block per wave. Portfolio kernel in FP32: 100003
+// paths x 50 steps x 112 assets 266 -> 260 us, 5000 such paths (79 tiles)
+// 56 -> 43 us, 20000 x 30 x 64 40 -> 34 us. Above 16 tiles a CU the tail is
+// lost in the rest, a last round more than 7/8 full is left whole, and a tile
+// of few asset blocks (d <= 16) has nothing to split.
+BasketSplit basket_split(uint64_t n_paths, uint32_t n_steps, uint32_t d) {
+  BasketSplit x;
+  const uint64_t tiles = (n_paths + kTile - 1) / kTile;
+  const uint32_t nb = basket_blocks(n_paths, n_steps, d);
+  const uint32_t W = d <= 64 ? 4 : 8, parts = (d / 4 + W - 1) / W, tail = (uint32_t)(tiles % 256u);
+  x.from = nb;
+  if (nb != tiles || tiles > 16u * 256u || tail == 0 || tail > 224 || parts < 2) return x;
+  x.parts = parts;
+  x.from = nb - tail;
+  x.sums = (size_t)tail * d * kTile;
+  x.arrivals = tail;
+  return x;
 }
 
 hipError_t launch_basket_pack(const BasketPack& k, int prec, hipStream_t s) {

@@ -441,7 +441,7 @@ __global__ __launch_bounds__(kLsmReduceThreads) void lsm_reduce_kernel(
     const double v = wave_sum((a[0] + a[2]) + (a[1] + a[3]));
     if (lane == 0u) store_agent(&r.sums[m], v);
   }
-  if (!arrives_last(r.arrivals)) return;
+  if (!arrives_last(r.arrivals, gridDim.x)) return;
   if (threadIdx.x == 0u) {
     if constexpr (NF > 0) {
       if (j != 0u) solve_date<NF>(r.sums, j, r);

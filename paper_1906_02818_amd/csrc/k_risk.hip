@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kSelThreads) void select_digit_kernel(
     const uint32_t c = h[b];
     if (c) __hip_atomic_fetch_add(&st->hist[b], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (!arrives_last(&st->arrivals)) return;
+  if (!arrives_last(&st->arrivals, gridDim.x)) return;
   // Eight neighbouring bins per thread; the scan of the threads' counts by
   // waves, then over the waves.
   constexpr uint32_t PER = kBins / kSelThreads;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kSelThreads) void select_finish_kernel(
     store_agent(&partials[blockIdx.x], acc[0]);
     store_agent(&partials[gridDim.x + blockIdx.x], acc[1]);
   }
-  if (!arrives_last(&st->arrivals)) return;
+  if (!arrives_last(&st->arrivals, gridDim.x)) return;
 
   __shared__ uint64_t keys[kSelectList];
   const uint32_t m = load_agent(&st->n_match);

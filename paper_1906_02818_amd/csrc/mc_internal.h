@@ -139,6 +139,14 @@ constexpr int kBasketMaxDim = 256;
 // moment vector.
 constexpr uint32_t kBasketMaxBlocks = 4096;
 uint32_t basket_blocks(uint64_t n_paths, uint32_t n_steps, uint32_t d);
+// Tiles of a run that are split: from tile `from`, into `parts` workgroups, and
+// the scratch they take (floats, counters).
+struct BasketSplit {
+  uint32_t from = 0, parts = 1;
+  size_t sums = 0;
+  uint32_t arrivals = 0;
+};
+BasketSplit basket_split(uint64_t n_paths, uint32_t n_steps, uint32_t d);
 // L' in MFMA operand order: for each 16-row block rb of the lower triangle its
 // 32-column blocks kb = 0 .. rb / 2, fragment basket_pairs(rb) + kb = [64
 // lanes][8] of the 16-bit type, lane l holding row 16 rb + l mod 16 and
@@ -172,6 +180,10 @@ struct BasketParams {
   // shift row q_dims * replicate, and writes its moments to that
   // replicate's own [q_rep_blocks][moment] partials.
   uint32_t q_rep_blocks, q_dims;
+  // Tiles split over workgroups (basket_split), or parts <= 1.
+  uint32_t split_from, split_parts;
+  float* split_sums;      // [tiles from split_from][d][kBasketTile]
+  uint32_t* split_arrivals;   // [tiles from split_from], zero
   uint32_t q_shift_tag;   // stream of the shifts, where the kernel draws them itself
   double* partials;
   double* path_out;       // [n_paths][3] (basket) or [n_paths] (portfolio), or nullptr
@@ -193,7 +205,7 @@ struct BasketPack {
   uint32_t d;
   uint16_t* frag;
   float* asset_out;
-  BasketZero zero;
+  BasketZero zero[2];
 };
 hipError_t launch_basket_pack(const BasketPack& k, int prec, hipStream_t s);
 hipError_t launch_basket(const BasketParams& p, int prec, hipStream_t s, uint32_t* n_blocks);

@@ -417,3 +417,29 @@ def test_workspace_contract(ctx):
         assert run(need) == mc.MC_OK
         assert res.price == mc.mc_price(ctx, m, f, N, 5, SEED, mc.Options(**kw))["price"]
         assert run(need - 1) == -7           # MC_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("d", [32, 112, 256])
+@pytest.mark.parametrize("N", [64, 5000, 64 * 224 - 1, 64 * 263 + 5])
+def test_split_basket_tiles(ctx, d, N):
+    """Runs with split tiles give the same values per path as runs where the
+    same paths lie in whole tiles (another path offset and count: 225 tiles
+    are not split), bit for bit; the portfolio's against its own pnl."""
+    n, corr = 2, np.full((d, d), 0.2) + 0.8 * np.eye(d)
+    m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.03, T=1.0,
+                 sigma=np.linspace(0.1, 0.4, d), corr=corr)
+    f = mc.Payoff(mc.MC_BASKET_CALL, 100.0)
+    whole = 64 * 225
+    for prec in (mc.MC_FP32, mc.MC_BF16_GEMM):
+        a = np.asarray(mc.mc_price(ctx, m, f, N, n, SEED, mc.Options(prec=prec, path_values=True))
+                       ["path_values"])
+        for first in range(0, N, whole):
+            b = np.asarray(mc.mc_price(ctx, m, f, whole, n, SEED, mc.Options(
+                prec=prec, path_values=True, path_offset=first))["path_values"])
+            k = min(whole, N - first)
+            assert np.array_equal(a[first:first + k], b[:k])
+    pa = mc.mc_risk(ctx, m, [1.0], [1.0], 0.9, N, n, SEED, opts=mc.Options(path_values=True))["pnl"]
+    pb = mc.mc_risk(ctx, m, [1.0], [1.0], 0.9, whole, n, SEED,
+                    opts=mc.Options(path_values=True))["pnl"]
+    k = min(N, whole)
+    assert np.array_equal(pa[:k], pb[:k])
