@@ -374,9 +374,15 @@ __device__ __forceinline__ void block_sum_wide(const double (&acc)[M],
     for (int j = 0; j < CH; ++j)
       if (m0 + j < M) buf[wave][j][lane] = acc[m0 + j];
     wave_sync();
+    // Quarters 2 and 3 start with their upper half: with the same t in all
+    // four, quarters 32 doubles apart met on one bank.
+    const double* lower = &buf[wave][c][16 * q + 8 * (q >> 1)];
+    const double* upper = &buf[wave][c][16 * q + 8 - 8 * (q >> 1)];
     double s = 0.0;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) s += buf[wave][c][16 * q + t];
+    for (int t = 0; t < 8; ++t) s += lower[t];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) s += upper[t];
     s += __shfl_xor(s, 1, 64);
     s += __shfl_xor(s, 2, 64);
     if (q == 0 && m0 + c < M) red[m0 + c][wave] = s;

@@ -23,8 +23,8 @@
 // hold up the next kernel).
 //
 // Measured, max call on 2 assets, degree 2, 9 dates, 2^22 paths and as many
-// out of sample: simulation 79 us, the 8 dates 218 (updates 176), out of
-// sample 88, the call 431 us; 575 with events around each stage, the solve as
+// out of sample: simulation 76 us, the 8 dates 202 (updates 162), out of
+// sample 87, the call 420 us; 575 with events around each stage, the solve as
 // a launch of its own and per-lane Philox keys. The simulation writes 268 MB
 // (56 us at the rate of a copy) next to 50 us of issue; the out-of-sample
 // kernel is VALU issue, 70 us of Philox, Box-Muller and the FP64 rule.
@@ -270,12 +270,13 @@ typedef float F4 __attribute__((ext_vector_type(4)));
 // 2^22 paths took 28 us instead of 23.
 //
 // Bound: memory, 5 floats of a path read and one written: 92 MB per update of
-// 2^22 paths on 2 assets, 22 us (4.2 TB/s; a large copy reaches 4.8). Date
+// 2^22 paths on 2 assets, 20 us (4.6 TB/s; a large copy reaches 4.8). Date
 // j - 1's state and C are read again by the next update, date j's state never
 // again: the former find room in the caches because the latter bypasses them
 // (non-temporal), and consecutive dates sweep the paths in opposite
 // directions, so that what was touched last is touched first. 24.4 -> 23.5
-// (non-temporal) -> 22.0 us.
+// (non-temporal) -> 22.0 us; 20.3 with the reduction of the moments free of bank
+// conflicts (device/reduce.h).
 template <int D, int DEG, int PF>
 __global__ __launch_bounds__(256, (Feat<D, DEG, PF>::NMOM <= 39 ? 4 : 1)) void lsm_update_kernel(LsmParams p, uint32_t j) {
   stamp(p.clock);
