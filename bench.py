@@ -37,12 +37,12 @@ sys.path.insert(0, ROOT)
 # FMA lanes per clock per CU, the unit ("slot") of the ALU roofline.
 N_CU, CLOCK_HZ, FMA_LANES_PER_CLK = 256, 2.4e9, 128
 ALU_PEAK_SLOTS = N_CU * CLOCK_HZ * FMA_LANES_PER_CLK      # 7.86e13 slots/s
-MFMA_PEAK = {"fp32": 157.3e12, "bf16": 2.5e15, "fp16": 2.5e15, "bf16x2": 2.5e15}
 HBM_PEAK = 8.0e12                                           # bytes/s
 # One v_mfma_f32_32x32x16 (BF16/FP16) occupies a SIMD for about 35.5 cycles
-# (isa_rates.hip, matrix core alone; nominal 8 passes = 32), and on one SIMD
-# the matrix core overlaps vector issue by only ~12 % (same probe), so the
-# bound of a kernel issuing both is VALU issue time + MFMA time.
+# (isa_rates.hip, matrix core alone; nominal 8 passes = 32), a 16x16x32 for
+# half of that, and on one SIMD the matrix core overlaps vector issue by only
+# ~12 % (same probe), so the bound of a kernel issuing both is VALU issue time
+# + MFMA time.
 MFMA_CYCLES_32X32X16 = 35.5
 N_SIMD = 4 * N_CU
 
@@ -51,8 +51,9 @@ def _mfma_share(n_mfma, kernel_ms):
     """Fraction of the kernel time the SIMDs spend in n_mfma 32x32x16 MFMAs."""
     return n_mfma * MFMA_CYCLES_32X32X16 / N_SIMD / CLOCK_HZ / (kernel_ms * 1e-3)
 
-# Issue cost of each instruction class on gfx950 in "slots": wave64 FMA
-# issues at the FP32 vector peak (2 per clock per CU). Costs are 2 divided
+# A common charge per instruction class, in "slots" (a wave64 FMA at the FP32
+# vector peak, 2 cycles of a SIMD), for the method's arithmetic as stated:
+# what a line's work would cost whatever the kernel does. Costs are 2 divided
 # by the wave64 issue rate per clock per CU that
 # paper_1906_02818_amd/isa_rates.hip measures in isolation
 # (profiles/isa_rates.txt). An FP32 FMA issues at 1.77 per clock, so it
@@ -75,17 +76,30 @@ def slots(mul64=0.0, trans=0.0, log=0.0, intops=0.0, fp32=0.0, fp64=0.0, bitop3=
             + fp32 * COST_FP32 + fp64 * COST_FP64 + bitop3 * COST_BITOP3)
 
 
-# One FP32 normal: a quarter of a Philox4x32-10 block (10 rounds of 2 mul64
-# and 2 three-input xors), the uniform (one alignbit, one sub) and half of a
-# Box-Muller pair (log, sqrt, sin, cos and 3 mul). Where every lane of a wave
-# draws the same block index at a step (one path per lane), round 1's two
-# products (block index; the path's high word, the same for every path below
-# 2^32) and round 2's second (fed only by round 1's uniform results) do not
-# depend on the path: 17 of the 20 products are per-path work, the count the
-# compiled kernels issue. The basket's lanes draw two block indices per step,
-# so all 20 are.
+# What the classes cost as the kernels issue them, in cycles of a SIMD per
+# wave64 instruction. FP32 add / mul / fma, a xor and a v_bitop3 take 2.4 with
+# VGPR, inline or literal operands and 4.2 as soon as one operand is an SGPR;
+# the 64-bit product, alignbit, compares, max, conversions and dot operations
+# 4.1 to 4.3; transcendentals 8.2; an FP64 fma 5.3. Streams of different
+# classes add up. The rooflines count these.
+ISSUE_CYCLES = dict(mul64=4.2, trans=8.2, log=8.2, intops=4.1, fp32=2.4, fp64=5.3, bitop3=2.4)
+
+
+def issued(**counts):
+    """Issue time of the counted instructions, in slots of 2 cycles."""
+    return sum(n * ISSUE_CYCLES[k] for k, n in counts.items()) / 2
+
+
+# One FP32 normal as the method states it: a quarter of a Philox4x32-10 block
+# (10 rounds of 2 products and 2 three-input xors), the uniform (one alignbit,
+# one sub) and half of a Box-Muller pair (log, sqrt, sin, cos and 3 mul). With
+# a wave-uniform block index 3 of a block's 20 products do not depend on the
+# path; with an index per lane all 20 do.
 NORMAL = dict(mul64=17 / 4, log=0.5, trans=1.5, bitop3=5.0, intops=1.0, fp32=1.0 + 1.5)
 NORMAL_BASKET = dict(NORMAL, mul64=20 / 4)
+# The same normal as the kernels issue it, which the rooflines count: 15
+# products, 13 three-input xors with keys in VGPRs, 4 xors with a scalar.
+NORMAL_ISSUED = dict(NORMAL, mul64=15 / 4, bitop3=13 / 4, intops=1.0 + 1.0)
 
 
 def _add(*ds):
@@ -99,16 +113,22 @@ def _add(*ds):
 # Algorithmic work per path-step (asset-path-step for the basket).
 SLOTS_ASIAN_BARRIER = slots(**_add(NORMAL, dict(trans=1.0, intops=1.0, fp32=4.0)))
 #   normal; step fma + add; Asian exp2 + add; geometric add; barrier compare
-SLOTS_HESTON = slots(**_add(NORMAL, NORMAL, dict(trans=2.0, fp32=11.0)))
+ISSUED_ASIAN_BARRIER = issued(**_add(NORMAL_ISSUED, dict(trans=1.0, intops=0.5, fp32=4.0)))
+#   as issued: half a v_max3 for the barrier
+SLOTS_HESTON = issued(**_add(NORMAL_ISSUED, NORMAL_ISSUED, dict(trans=2.0, fp32=11.0)))
 #   2 normals; v+ max, sqrt(v+ dt), Zs (mul, fma), ln S (fma, add, fma),
 #   v (fma, fma, mul), Asian exp2 + add
-SLOTS_HESTON_REVERSE = slots(trans=2.0, fp32=6.0, fp64=3.0)
+SLOTS_HESTON_REVERSE = issued(trans=2.0, fp32=6.0, fp64=3.0)
 #   per step of the reverse sweep: sqrt, rcp, 6 FP32 ops, 3 FP64 ops
-SLOTS_ASSET_STEP = slots(**_add(NORMAL_BASKET, dict(intops=0.5)))
-#   per asset-path-step of the basket: one normal and half a 16-bit pack
-SLOTS_TANH = slots(trans=2.0, fp32=3.0)
+SLOTS_ASSET_STEP = issued(**_add(NORMAL_ISSUED, dict(intops=1.0)))
+#   per asset-path-step of the basket: one normal, half a 16-bit pack, half a
+#   dot product that sums two steps
+SLOTS_ASSET_STEP_FP32 = issued(**_add(NORMAL_ISSUED, dict(fp32=-0.5)))
+#   the sum's fma takes the place of the multiply by the radius, and the
+#   radius' constant is left to the product
+SLOTS_TANH = issued(trans=2.0, fp32=3.0)
 #   tanh(x + b): fma, exp2, add, rcp, fma
-SLOTS_SIGM = slots(trans=2.0, fp32=2.0)
+SLOTS_SIGM = issued(trans=2.0, fp32=2.0)
 #   (1 + tanh(x + b)) / 2, the form layer 3 takes where only Delta is needed
 
 
@@ -311,7 +331,6 @@ def _line(args, metric, value, unit, ms, dtype, config, roofline, higher_is_bett
 # has no such measurement.
 TRAFFIC_BYTES = {
     "gbm_path_kernel<float, asian|geo|uo, log-Euler>": 1.054e6,   # 2^24 paths x 252 steps
-    "basket_kernel<8, bf16>": 2.595e6,                          # 2^20 paths x 100 steps
     "heston_adjoint_kernel<float, full, asian>": 2.261e6,       # 2^22 paths x 256 steps
     "lsm_update_kernel<2, 2, 1>": 3.660e8,                      # 2^24 paths, mean of 8 dates
 }
@@ -323,6 +342,11 @@ def _alu_roofline(slots_per_unit, units, kernel_ms, kernel):
             "unit": "Tslot/s", "frac": achieved / ALU_PEAK_SLOTS,
             "traffic": TRAFFIC_BYTES.get(kernel), "slots_per_unit": slots_per_unit,
             "kernel": kernel}
+
+
+def _asset_roofline(prec, units, kernel_ms, kernel):
+    return _alu_roofline(SLOTS_ASSET_STEP_FP32 if prec == "fp32" else SLOTS_ASSET_STEP, units,
+                         kernel_ms, f"{kernel}<{prec}>")
 
 
 def _repeat(args, torch, fn):
@@ -405,7 +429,7 @@ def run_asian_barrier(args, ctx, mc, synth, torch):
                               "+ geometric Asian on the same paths, 2^24 paths x 252 log-Euler "
                               "steps, FP32 state, FP64 reduction, Philox4x32-10",
                   "n_paths": N, "n_steps": n},
-                 _alu_roofline(SLOTS_ASIAN_BARRIER, N * n, k_ms,
+                 _alu_roofline(ISSUED_ASIAN_BARRIER, N * n, k_ms,
                                "gbm_path_kernel<float, asian|geo|uo, log-Euler>"),
                  kernel_ms=k_ms,
                  prices={"asian_cv": res[0]["price"], "asian_cv_se": res[0]["std_err"],
@@ -502,19 +526,13 @@ def run_basket(args, ctx, mc, synth, torch):
     ms, outs = _repeat(args, torch, lambda: mc.mc_price(ctx, model, f, N, n, synth.SEED, o))
     r = outs[-1]
     k_ms = sum(x["kernel_ms"] for x in outs) / len(outs)
-    # MFMA work issued: lower-triangular 32x16 blocks per 32-path tile.
-    nd = (d + 31) // 32
-    blocks = sum(2 * nb + 2 for nb in range(nd))
-    flops = (N // 32) * n * blocks * 32 * 32 * 16 * 2 * (2 if args.prec == "bf16x2" else 1)
-    roof = _alu_roofline(SLOTS_ASSET_STEP, N * n * d, k_ms, f"basket_kernel<8, {args.prec}>")
-    roof["mfma_tflops"] = flops / (k_ms * 1e-3) / 1e12
-    roof["mfma_frac"] = flops / (k_ms * 1e-3) / MFMA_PEAK[args.prec]
-    if args.prec != "fp32":
-        # VALU issue and matrix-core time add up on a SIMD: the kernel against
-        # their sum.
-        n_mfma = (N // 32) * n * blocks * (2 if args.prec == "bf16x2" else 1)
-        roof["mfma_share"] = _mfma_share(n_mfma, k_ms)
-        roof["valu_plus_mfma_frac"] = roof["frac"] + roof["mfma_share"]
+    roof = _asset_roofline(args.prec, N * n * d, k_ms, "basket_kernel")
+    # One triangular product per path: 16x16x32 MFMAs of the terms' products.
+    rows = d // 16
+    pairs = (rows // 2) * (rows // 2 + 1) + (rows % 2) * (rows // 2 + 1)
+    n_mfma = -(-N // 64) * 4 * pairs * {"fp32": 6, "bf16": 3, "fp16": 2, "bf16x2": 5}[args.prec]
+    roof["mfma_share"] = _mfma_share(n_mfma / 2, k_ms)
+    roof["valu_plus_mfma_frac"] = roof["frac"] + roof["mfma_share"]
     extra = {}
     if prec != mc.MC_FP32:
         # The rounding of the reduced-precision product at the full size: the
@@ -530,7 +548,7 @@ def run_basket(args, ctx, mc, synth, torch):
     return _line(args, "asset-path-steps/s", N * n * d / (ms * 1e-3), "asset-path-steps/s", ms,
                  args.prec,
                  {"workload": f"basket call, d = {d} correlated GBM, {n} steps, 2^20 paths, "
-                              f"per-step Z L^T on MFMA ({args.prec})", "n_paths": N,
+                              f"Z L^T on MFMA ({args.prec})", "n_paths": N,
                   "n_steps": n, "d": d},
                  roof, kernel_ms=k_ms,
                  prices={"price": r["price"], "se": r["std_err"], "delta0": r["delta"],
@@ -575,7 +593,7 @@ def run_mlmc_basket(args, ctx, mc, synth, torch):
             "bf16_bias": l1["mean"], "bf16_bias_se": math.sqrt(l1["variance"] / l1["n_paths"]),
             "level0_price": l0["mean"]}
     k_ms = l0["kernel_ms"]
-    roof = _alu_roofline(SLOTS_ASSET_STEP, N[0] * n * d, k_ms, "basket_kernel<8, bf16>")
+    roof = _asset_roofline("bf16", N[0] * n * d, k_ms, "basket_kernel")
     return _line(args, "time to 1bp SE", mlmc["total_s"], "s", mlmc["total_s"] * 1e3, "bf16",
                  {"workload": f"basket call, d = {d} correlated GBM, {n} steps; target SE = "
                               "1e-4 x price; BF16 level + FP32 correction level vs plain FP32",
@@ -606,7 +624,7 @@ def run_qmc_basket(args, ctx, mc, synth, torch):
     mcr = mc.mc_price(ctx, model, f, R * NQ, 1, synth.SEED, mc.Options(prec=prec))
     gain = (mcr["std_err"] ** 2 * mcr["kernel_ms"]) / (q["std_err"] ** 2 * q["kernel_ms"])
     k_ms = q["kernel_ms"] / R
-    roof = _alu_roofline(SLOTS_ASSET_STEP, NQ * d, k_ms, f"basket_kernel<1, {args.prec}, qmc>")
+    roof = _asset_roofline(args.prec, NQ * d, k_ms, "qmc_tile_kernel")
 
     # The paper's only printed timing (Sec. VI-D): median wall time of 100
     # calls pricing this basket call on 8192 samples, for pseudo-random MC
@@ -667,7 +685,7 @@ def run_risk(args, ctx, mc, synth, torch):
     ref = go(mc.MC_FP32)
     k_ms = sum(x["kernel_ms"] for x in outs) / len(outs)
     s_ms = sum(x["select_ms"] for x in outs) / len(outs)
-    roof = _alu_roofline(SLOTS_ASSET_STEP, N * n * d, k_ms, f"basket_kernel<8, {args.prec}, port>")
+    roof = _asset_roofline(args.prec, N * n * d, k_ms, "basket_kernel, portfolio")
     return _line(args, "scenario-asset-steps/s", N * n * d / (ms * 1e-3), "asset-path-steps/s",
                  ms, args.prec,
                  {"workload": f"VaR/CVaR 0.95 of 5 calls on each of {d} correlated GBM assets "
@@ -769,7 +787,7 @@ def run_learned_cv(args, ctx, mc, synth, torch):
     # Per date and path (two 32-path network passes per wave of 64 paths):
     # 64 tanh of layer 1, 64 sigmoid-form activations of layer 2, 64 FMAs of
     # layer 3 and 8 feature operations.
-    per_step = SLOTS_HESTON + (64 * SLOTS_TANH + 64 * SLOTS_SIGM + slots(fp32=64 + 8)) / m
+    per_step = SLOTS_HESTON + (64 * SLOTS_TANH + 64 * SLOTS_SIGM + issued(fp32=64 + 8)) / m
     roof = _alu_roofline(per_step, cv["n_paths"] * n, cv["kernel_ms"], "cv_eval_kernel<bf16>")
     # Two network passes (2 + 8 MFMAs each) per wave of 64 paths per date.
     n_mfma = -(-cv["n_paths"] // 64) * -(-n // m) * 20

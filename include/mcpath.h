@@ -222,12 +222,13 @@ mc_status mc_price(mc_context *ctx, const mc_model *model, const mc_payoff *payo
  * to what fits a fixed device scratch: models MC_GBM and MC_HESTON, payoffs
  * without the learned control variate (the geometric-Asian control variate
  * and its pilot are allowed), pathwise greeks only (GBM tangents; Heston
- * forward tangents, or the adjoint while its checkpoints fit on chip, i.e.
- * n_steps <= 256), no path_values; opts->workspace is ignored. The call performs no device or pinned-host allocation and no
- * free: the block moments and the reduced moments live in a static device
- * array of MC_NOALLOC_SCRATCH_BYTES, one per GPU, held until the process
- * ends, whose address the library looks up once per device in mc_create.
- * The moments come back through a fixed host array of the context.
+ * forward tangents, or its MC_GREEKS_PATHWISE greeks up to n_steps = 256),
+ * no path_values; opts->workspace is ignored. The call
+ * performs no device or pinned-host allocation and no free: the block
+ * moments live in a static device array of MC_NOALLOC_SCRATCH_BYTES, one per
+ * GPU, held until the process ends, whose address the library looks up once
+ * per device in mc_create. The reduced moments come back through a pinned
+ * host array of the context.
  * Every call on one GPU shares that GPU's scratch and leaves its contents
  * there; each run overwrites all of it that it reads, so nothing needs
  * clearing. Calls that overlap on one GPU (two host threads, or two
@@ -235,8 +236,8 @@ mc_status mc_price(mc_context *ctx, const mc_model *model, const mc_payoff *payo
  * The GBM kernel and the Heston price and tangent kernels run on
  * persistent grids (at most 8192 workgroups), so those runs need at most
  * 8192 moment vectors of at most 9 channels (3.7 MB) whatever n_paths is.
- * The Heston adjoint takes one path per thread: one 88-byte vector per 256
- * paths, so it fits up to about 1.2e7 paths.
+ * The Heston pathwise kernel takes one path per thread: one 88-byte vector
+ * per 256 paths, so it fits up to about 1.2e7 paths.
  * Errors: those of mc_price; a model, payoff or option outside the list
  * above -> MC_ERR_UNSUPPORTED; a run whose moments would not fit the
  * scratch -> MC_ERR_WORKSPACE, before any launch. */
