@@ -25,8 +25,12 @@ struct mc_context {
   hipStream_t stream = nullptr;
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  double* pinned = nullptr;      // host memory the reductions write to
+  // Host memory the reductions write to: behind the stamps below, or for runs
+  // with more results an allocation of its own (`grown`). Each pinned
+  // allocation costs mc_create 12 us.
+  double* pinned = nullptr;
   size_t pinned_count = 0;
+  double* grown = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // Start stamps of a run's path kernel and of its reduction, on the device's
   // constant clock (host memory the kernels write), and that clock's rate.
@@ -78,7 +82,8 @@ namespace {
 
 using namespace mcp;
 
-constexpr size_t kClockStamps = 4;
+constexpr size_t kClockStamps = 16;                  // 4 in use, a line in all
+constexpr size_t kPinnedMin = 4096;                  // doubles behind them
 
 constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
@@ -340,12 +345,13 @@ mc_status get_ws(mc_context* ctx, const mc_options& o, size_t bytes, char** base
 
 mc_status get_pinned(mc_context* ctx, size_t count) {
   if (ctx->pinned_count >= count) return MC_OK;
-  if (ctx->pinned) HIP_TRY(ctx, hipHostFree(ctx->pinned));
-  ctx->pinned = nullptr;
-  ctx->pinned_count = 0;
-  size_t want = count < 4096 ? 4096 : count;
-  HIP_TRY(ctx, hipHostMalloc((void**)&ctx->pinned, want * sizeof(double), hipHostMallocDefault));
-  ctx->pinned_count = want;
+  if (ctx->grown) HIP_TRY(ctx, hipHostFree(ctx->grown));
+  ctx->grown = nullptr;
+  ctx->pinned = (double*)(ctx->clock + kClockStamps);
+  ctx->pinned_count = kPinnedMin;
+  HIP_TRY(ctx, hipHostMalloc((void**)&ctx->grown, count * sizeof(double), hipHostMallocDefault));
+  ctx->pinned = ctx->grown;
+  ctx->pinned_count = count;
   return MC_OK;
 }
 
@@ -1591,9 +1597,8 @@ mc_status mc_create(mc_context** out, int device) {
   if (hipSetDevice(device) != hipSuccess || hipStreamCreate(&ctx->stream) != hipSuccess ||
       hipEventCreate(&ctx->ev0) != hipSuccess || hipEventCreate(&ctx->ev1) != hipSuccess ||
       scratch_address(device, &ctx->scratch) != hipSuccess ||
-      hipHostMalloc((void**)&ctx->clock, kClockStamps * sizeof(uint64_t), hipHostMallocDefault) !=
-          hipSuccess ||
-      get_pinned(ctx, 1) != MC_OK) {
+      hipHostMalloc((void**)&ctx->clock, kClockStamps * sizeof(uint64_t) + kPinnedMin * sizeof(double),
+                    hipHostMallocDefault) != hipSuccess) {
     mc_destroy(ctx);
     return MC_ERR_DEVICE;
   }
@@ -1604,6 +1609,8 @@ mc_status mc_create(mc_context** out, int device) {
   }
   ctx->clock_khz = (double)khz;
   std::memset(ctx->clock, 0, kClockStamps * sizeof(uint64_t));
+  ctx->pinned = (double*)(ctx->clock + kClockStamps);
+  ctx->pinned_count = kPinnedMin;
   *out = ctx;
   return MC_OK;
 }
@@ -1614,7 +1621,7 @@ mc_status mc_destroy(mc_context* ctx) {
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->mlmc_buf) (void)hipFree(ctx->mlmc_buf);
   if (ctx->qmc_buf) (void)hipFree(ctx->qmc_buf);
-  if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->grown) (void)hipHostFree(ctx->grown);
   if (ctx->clock) (void)hipHostFree(ctx->clock);
   if (ctx->dev_L) (void)hipFree(ctx->dev_L);
   if (ctx->split_buf) (void)hipFree(ctx->split_buf);
