@@ -15,8 +15,8 @@ namespace {
 // vectors t, t + NT, ... in order (about a shift, no division), then the
 // block reduction of the path kernels. A launch of its own: done by the last
 // workgroup of the path kernel, whose loads must then pass the dies' caches, it
-// was 1 us faster for 32 vectors (32.0 -> 31.0 us a call), level for 800 to
-// 2000 and 4 us slower for 1024 of three channels (56.6 -> 60.5).
+// was 1 us faster for 32 vectors (32.0 -> 31.0 us a call) and 4 us slower for
+// 1024 of three channels (56.6 -> 60.5).
 template <int C>
 constexpr int merge_threads() { return 256; }
 
