@@ -10,7 +10,7 @@
  * through Box-Muller; every step of the computation runs in hand-written
  * HIP kernels on one GPU.
  *
- * Random-number layout (shared contract with any independent checker):
+ * Random-number layout (shared contract with any independent implementation):
  *   normal k of path p in stream `tag` is slot (k mod 4) of the Philox block
  *   with counter (floor(k/4), p mod 2^32, p >> 32, tag) and key
  *   (seed mod 2^32, seed >> 32); a block's words (w0,w1,w2,w3) give

@@ -443,3 +443,31 @@ def test_split_basket_tiles(ctx, d, N):
                     opts=mc.Options(path_values=True))["pnl"]
     k = min(N, whole)
     assert np.array_equal(pa[:k], pb[:k])
+
+
+def test_results_past_the_contexts_first_pinned_block():
+    # 64 exercise dates return more results than the block of mc_create holds;
+    # the context then goes on with a larger one, a second context with its own.
+    model = mc.Model(kind=mc.MC_GBM, S0=100.0, r=0.05, T=3.0, sigma=0.2)
+    spec = mc.LsmSpec(payoff=PUT, K=100.0, dividend=0.02, n_dates=64, degree=2,
+                      n_paths_oos=5001)
+    asian = mc.Payoff(mc.MC_ASIAN_ARITH_CALL, K=100.0)
+    a, b = mc.mc_create(0), mc.mc_create(0)
+    try:
+        before = mc.mc_price(a, gbm(), asian, 5001, 13, SEED)
+        first = mc.mc_price_lsm(a, model, spec, 20011, SEED)
+        after = mc.mc_price(a, gbm(), asian, 5001, 13, SEED)
+        again = mc.mc_price_lsm(a, model, spec, 20011, SEED)
+        other = mc.mc_price_lsm(b, model, spec, 20011, SEED)
+    finally:
+        a.close()
+        b.close()
+    for k in ("price", "std_err"):
+        assert before[k] == after[k], k
+    for k in ("price", "std_err", "price_oos", "european"):
+        assert first[k] == again[k] == other[k], k
+    assert np.array_equal(first["beta"], other["beta"], equal_nan=True)
+    o = oracle.lsm(np.array([100.0]), np.array([0.2]), np.eye(1), 0.05, 0.02, 3.0, PUT, 100.0, 64,
+                   1, 2, 20011, SEED)
+    # FP32 states move decisions on the exercise boundary only.
+    assert abs(first["price"] - o["price"]) < 0.05 * first["std_err"]
