@@ -2214,11 +2214,13 @@ mc_status mc_risk(mc_context* ctx, const mc_model* m, const mc_portfolio* pf, ui
   if (pr.n_nonfinite != 0) return fail(ctx, MC_ERR_DEVICE, "non-finite P&L on %llu paths",
                                        (unsigned long long)pr.n_nonfinite);
   hipStream_t s = stream_of(ctx, o0);
-  if (!sel->done) HIP_TRY(ctx, launch_select_rest(x, n_paths, state, list, partials, sel, s));
+  // Read once: the launches below write the flag again while they run.
+  const bool rest = sel->done == 0;
+  if (rest) HIP_TRY(ctx, launch_select_rest(x, n_paths, state, list, partials, sel, s));
   if (o0.path_values)
     HIP_TRY(ctx, hipMemcpyAsync(o0.path_values, x, n_paths * sizeof(double),
                                 hipMemcpyDeviceToHost, s));
-  if (!sel->done || o0.path_values) HIP_TRY(ctx, hipStreamSynchronize(s));
+  if (rest || o0.path_values) HIP_TRY(ctx, hipStreamSynchronize(s));
   mc_risk_result r{};
   r.quantile_pnl = select_key_to_value(sel->key);
   r.var = -r.quantile_pnl;
