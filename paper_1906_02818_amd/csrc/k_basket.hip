@@ -308,9 +308,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   // QMC: the sums over a path's lanes in FP64 (see qmc_tile_kernel).
   typedef typename std::conditional<QMC, double, float>::type Sum;
   __shared__ Sum s_part[C][SETS][kTile];
-  // Sums of the first wave's paths over the workgroup's tiles (in LDS: as
-  // registers they would be held by every wave).
-  __shared__ ThreadSums<C> s_acc[kTile];
+  // The first wave's paths over the workgroup's tiles (in LDS: as registers
+  // they would be held by every wave). About a shift: a lane takes 2^18 paths
+  // of the longest runs, and a portfolio's values can be equal.
+  __shared__ PartSums<C> s_acc[kTile];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // Block blk of nblk of the launch, or of its replicate when replicates
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   }
   PartSums<C> part;
   part.zero();
-  if (wave == 0u) part = s_acc[lane].part();
+  if (wave == 0u) part = s_acc[lane];
   block_reduce<C, 64 * W>(part, partials, blk);
 }
 
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(64 * kQmcWaves, 4) void qmc_tile_kernel(const Baske
   const uint64_t first = P.path_offset, last = first + P.n_paths;   // last <= 2^32
   const uint64_t base0 = first & ~63ull, tiles = (last - base0 + 63u) >> 6;
   uint32_t at = 0;
-  ThreadSums<C> acc;
+  PartSums<C> acc;
   acc.zero();
   for (uint64_t tile = (uint64_t)blk * kQmcWaves + wave; tile < tiles;
        tile += (uint64_t)nblk * kQmcWaves) {
@@ -602,8 +603,7 @@ __global__ __launch_bounds__(64 * kQmcWaves, 4) void qmc_tile_kernel(const Baske
       acc.push(y, finite, !finite);
     }
   }
-  PartSums<C> part = acc.part();
-  block_reduce<C, 64 * kQmcWaves>(part, P.partials + (size_t)rep * n_moments(C) * nblk, blk);
+  block_reduce<C, 64 * kQmcWaves>(acc, P.partials + (size_t)rep * n_moments(C) * nblk, blk);
 }
 
 template <int PREC>

@@ -471,3 +471,35 @@ def test_results_past_the_contexts_first_pinned_block():
                    1, 2, 20011, SEED)
     # FP32 states move decisions on the exercise boundary only.
     assert abs(first["price"] - o["price"]) < 0.05 * first["std_err"]
+
+
+@pytest.mark.parametrize("prec", [mc.MC_FP32, mc.MC_BF16_GEMM])
+@pytest.mark.parametrize("d,N", [(16, 200003), (16, 1 << 20), (112, 300007)])
+def test_equal_paths_have_no_variance(ctx, prec, d, N):
+    """Several tiles per workgroup: paths of one value have a variance of
+    exactly 0 (their deviations about any one of them are 0), and a spread far
+    below the mean keeps its digits (reference: the values about the first)."""
+    def market(sigma):
+        return mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.03, T=1.0,
+                        sigma=np.full(d, sigma), corr=np.eye(d))
+    f = mc.Payoff(mc.MC_BASKET_CALL, 90.0)
+    r = mc.mc_price(ctx, market(0.0), f, N, 1, SEED, mc.Options(prec=prec, greeks=1))
+    assert r["std_err"] == 0.0 and r["delta_se"] == 0.0 and r["n_paths"] == N
+    r = mc.mc_risk(ctx, market(0.2), [50.0], [3.0], 0.9, N, 1, SEED, opts=mc.Options(prec=prec))
+    assert r["pnl_std_err"] == 0.0 and r["pnl_mean"] == -r["premium"]
+    r = mc.mc_price(ctx, market(1e-6), f, N, 1, SEED, mc.Options(prec=prec, path_values=True))
+    y = r["path_values"][:, 0]
+    se = (y - y[0]).std(ddof=1) / math.sqrt(N)
+    assert se > 0.0 and r["std_err"] == pytest.approx(se, rel=1e-9)
+
+
+@pytest.mark.parametrize("reps,N,n", [(64, 64 * 64 * 13, 1), (64, 64 * 2048, 5)])
+def test_equal_points_have_their_value_as_mean(ctx, reps, N, n):
+    # Thirteen and 64 tiles per lane, in the tile kernel and the general one.
+    m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(16, 100.0), r=0.03, T=1.0, sigma=np.zeros(16),
+                 corr=np.eye(16))
+    f = mc.Payoff(mc.MC_BASKET_CALL, 90.0)
+    one = mc.mc_price_qmc(ctx, m, f, 64, n, SEED, 1, mc.Options(path_values=True))["path_values"]
+    r = mc.mc_price_qmc(ctx, m, f, N, n, SEED, reps)
+    assert (one == one[0]).all()
+    assert set(r["replicate_price"]) == {one[0, 0]} and set(r["replicate_geo"]) == {one[0, 1]}
