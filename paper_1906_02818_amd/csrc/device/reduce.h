@@ -181,11 +181,12 @@ struct PartSums {
   }
 };
 
-// Per-thread sums of a persistent kernel's paths, y and y y^T about zero:
-// a thread prices at most a few hundred paths, whose rounding errors are
-// unbiased and average out across threads; the thread's part enters the
-// reduction about its own mean (part()), and everything above the thread
-// combines about shifts.
+// Per-thread sums of a persistent kernel's paths, y and y y^T about zero, on
+// grids of 2^21 threads: a few paths each (eight of 2^24, 2^15 of the longest
+// run's 2^36), whose rounding errors average out across threads; the thread's
+// part enters the reduction about its own mean (part()), and everything above
+// the thread combines about shifts. The rounding is of the size of y^2: of
+// equal values it can leave a negative sum of squares, which part() takes as 0.
 template <int C>
 struct ThreadSums {
   static constexpr int NC = C * (C + 1) / 2;
@@ -228,7 +229,10 @@ struct ThreadSums {
 #pragma unroll
     for (int a = 0; a < C; ++a)
 #pragma unroll
-      for (int b = a; b < C; ++b, ++k) p.s2[k] = n > 0.0 ? ss[k] - s[a] * s[b] * r : 0.0;
+      for (int b = a; b < C; ++b, ++k) {
+        const double m = ss[k] - s[a] * s[b] * r;
+        p.s2[k] = n == 0.0 || (a == b && m < 0.0) ? 0.0 : m;   // a NaN stays
+      }
     return p;
   }
 };
