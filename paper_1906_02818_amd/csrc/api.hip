@@ -1777,7 +1777,9 @@ mc_status mc_price_noalloc(mc_context* ctx, const mc_model* m, const mc_payoff* 
                            uint64_t n_paths, uint32_t n_steps, uint64_t seed,
                            const mc_options* opts, mc_result* out) {
   if (!ctx) return MC_ERR_INVALID_ARG;
-  const mc_options o = opts ? *opts : defaults();
+  mc_options o = opts ? *opts : defaults();
+  o.workspace = nullptr;                   // ignored, so not held to any size
+  o.workspace_bytes = 0;
   mc_status st = validate_all(ctx, m, f, n_paths, n_steps, o);
   if (st != MC_OK) return st;
   if (!out) return fail(ctx, MC_ERR_INVALID_ARG, "out must not be NULL");

@@ -59,3 +59,24 @@ ctx = mc.mc_create(0)
 r = mc.mc_risk(ctx, basket, [1.0], [1.0], 0.9, 1000, 1, 1)
 assert (r["quantile_pnl"], r["n_tail"], r["cvar"]) == (-12.5, 7, 14.0), r
 """)
+
+
+def test_noalloc_ignores_the_callers_workspace(run):
+    # Whatever workspace the options carry, also one too small for the run.
+    run("""
+ctx = mc.mc_create(0)
+gbm = mc.Model(kind=mc.MC_GBM, S0=100.0, r=0.03, T=1.0, sigma=0.2)
+hes = mc.Model(kind=mc.MC_HESTON, S0=100.0, r=0.03, T=1.0, v0=0.04, kappa=2.0, theta=0.04, xi=0.5,
+               rho=-0.7)
+calls = [(gbm, mc.Payoff(mc.MC_EURO_CALL, 100.0), dict()),
+         (gbm, mc.Payoff(mc.MC_UO_BARRIER_CALL, 100.0, B=120.0), dict(prec=mc.MC_FP64)),
+         (hes, mc.Payoff(mc.MC_EURO_CALL, 100.0), dict()),
+         (hes, mc.Payoff(mc.MC_ASIAN_ARITH_CALL, 100.0), dict(greeks=3))]
+for m, f, kw in calls:
+    call, res = mc._Marshal(m, f, mc.Options(**kw), 5000), _abi.McResult()
+    small = (C.c_char * 16)()
+    call.co.workspace, call.co.workspace_bytes = C.addressof(small), 16
+    st = _abi.load().mc_price_noalloc(ctx.handle, C.byref(call.cm), C.byref(call.cp), 5000, 8, 1,
+                                      C.byref(call.co), C.byref(res))
+    assert st == mc.MC_OK, (m, f, kw, mc.mc_last_error(ctx))
+""")
