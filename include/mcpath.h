@@ -153,7 +153,7 @@ typedef struct {
     uint64_t path_offset;      /* first global path index (sharding, resumption) */
     uint32_t stream_tag;       /* Philox stream tag, default 0 */
     void *hip_stream;          /* hipStream_t to run on; NULL = the context stream */
-    void *workspace;           /* device scratch; NULL = context-owned */
+    void *workspace;           /* device scratch (mc_workspace_bytes); NULL = context-owned */
     size_t workspace_bytes;
     const float *cv_weights;   /* [MC_MLP_NPARAM] host, for MC_CV_LEARNED */
     uint32_t cv_hedge_every;   /* learned hedge rebalanced every m steps (>= 1) */
@@ -200,7 +200,14 @@ void mc_options_default(mc_options *opts);
 mc_status mc_validate(mc_context *ctx, const mc_model *model, const mc_payoff *payoff,
                       uint64_t n_paths, uint32_t n_steps, const mc_options *opts);
 
-/* Bytes of device workspace one mc_price call needs (0 on bad arguments). */
+/* Bytes a caller's device workspace must have for one mc_price call (0 on bad
+ * arguments); a smaller one is refused. It serves the whole call, except that
+ * a basket call also uses memory of the context, kept for later calls: the
+ * factor of the last correlation matrix (8 dim^2 bytes), sums of tiles split
+ * over workgroups (below 16 MB, for counts of paths that fill the chip
+ * unevenly), and, where its moment vectors and operands are larger than this
+ * size allows for, those (below 1 MB; the per-path values stay in the
+ * workspace). */
 size_t mc_workspace_bytes(const mc_model *model, const mc_payoff *payoff,
                           uint64_t n_paths, uint32_t n_steps, const mc_options *opts);
 

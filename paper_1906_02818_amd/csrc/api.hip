@@ -424,13 +424,14 @@ void merge_moment_vec(double* acc, const double* b, int C) {
 
 // Launch wrapper: runs `launch` (which enqueues the path kernel), then the
 // final reduction and what `queued` adds behind it, and brings the moments to
-// the host.
+// the host. rows: device memory of the per-path values, where they do not
+// follow the moments in the workspace.
 template <typename F>
 mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, int C,
                       double* host_path_values, F&& launch, Moments* out, double* kernel_ms,
                       uint32_t paths_per_block = kBlock, uint32_t max_blocks = UINT32_MAX,
                       const std::function<hipError_t(hipStream_t)>& queued = nullptr,
-                      int ws_channels = 0) {
+                      int ws_channels = 0, double* rows = nullptr) {
   if (C < 1 || C > kMaxChannels) return fail(ctx, MC_ERR_DEVICE, "channel count %d", C);
   // A run of fewer channels than its rows would have asks a caller's workspace
   // for the rows' layout (mc_workspace_bytes).
@@ -441,8 +442,8 @@ mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, in
       return fail(ctx, MC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", o.workspace_bytes,
                   asked);
   }
-  const RunLayout L =
-      layout_for(n_paths, C, host_path_values != nullptr, paths_per_block, max_blocks);
+  const RunLayout L = layout_for(n_paths, C, host_path_values != nullptr && !rows,
+                                 paths_per_block, max_blocks);
   char* base = nullptr;
   mc_status st = get_ws(ctx, o, L.bytes, &base);
   if (st != MC_OK) return st;
@@ -455,8 +456,8 @@ mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, in
   double* hmom = ctx->pinned;
   hipStream_t s = stream_of(ctx, o);
   double* partials = (double*)base;
-  double* path_out =
-      ctx->sink ? ctx->sink : (host_path_values ? (double*)(base + L.off_path) : nullptr);
+  if (!rows && host_path_values) rows = (double*)(base + L.off_path);
+  double* path_out = ctx->sink ? ctx->sink : rows;
   uint32_t nb = 0;
   HIP_TRY(ctx, launch(partials, path_out, s, &nb));
   if (nb == 0 || nb > L.n_blocks) return fail(ctx, MC_ERR_DEVICE, "block count mismatch");
@@ -1074,8 +1075,10 @@ size_t basket_run_bytes(size_t layout_bytes, uint32_t d, mc_precision prec) {
 }
 
 // What a caller's workspace must hold, a contract of its own: a moment vector
-// per 256 paths, L' in 32 x 32 blocks and the per-asset table. A run that
-// needs more than a workspace of this size takes the context's.
+// per 256 paths, L' in 32 x 32 blocks and the per-asset table. Where a run
+// needs more (vectors of up to 4096 workgroups, three 16-bit terms of an FP32
+// L': 590 KB at most) and the workspace has only this, the per-path values
+// stay in the workspace and the rest goes to the context's memory.
 size_t basket_ws_bytes(uint64_t n_paths, bool want_path, uint32_t d, mc_precision prec) {
   const uint32_t nd = d <= 32 ? 1 : d <= 64 ? 2 : d <= 128 ? 4 : 8;
   const size_t blk = align256((size_t)nd * (nd + 1) * 512 * (prec == MC_FP32 ? 4 : 2));
@@ -1117,9 +1120,11 @@ mc_status get_split_buf(mc_context* ctx, size_t bytes, char** base) {
 // constants into the workspace (after the moment area of run_moments), and
 // the kernel parameters. *o_run is o0 with the workspace narrowed to the
 // moment area. The constants pass through the context's pinned memory, behind
-// the moments of any run, and nothing here waits for the device: the checks
-// twice, L' packed on the host, two copies and a wait took 120 us of a risk
-// call at d = 112 and 260 us of a basket at d = 256.
+// the moments of any run. With the matrix of the last call nothing here waits
+// for the device (the checks twice, L' packed on the host, two copies and a
+// wait took 120 us of a risk call at d = 112 and 260 us of a basket at d =
+// 256); a new matrix is factorised by the caller's thread and its factor
+// copied with a wait.
 constexpr size_t kBasketStage = 1024;                 // doubles: after the moments
 mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint64_t n_paths,
                        uint32_t n_steps, uint64_t seed, const mc_options& o0,
@@ -1131,18 +1136,23 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   if (ctx->chol_L.size() != dd) return fail(ctx, MC_ERR_DEVICE, "no factor for this basket");
   const double dt = m->T / n_steps, inv_ln2 = 1.0 / std::log(2.0);
   const int prec = basket_prec(o0.prec);
-  const RunLayout Lay = basket_layout(n_paths, 3, o0.path_values != nullptr);
-  const size_t off_blk = align256(Lay.bytes);
-  const size_t off_asset = off_blk + align256(basket_frag_bytes(d, o0.prec));
-  const size_t asked = basket_ws_bytes(n_paths, o0.path_values != nullptr, d, o0.prec);
-  const size_t needed = basket_run_bytes(Lay.bytes, d, o0.prec);
+  const bool want_rows = o0.path_values != nullptr;
+  const size_t asked = basket_ws_bytes(n_paths, want_rows, d, o0.prec);
   if (o0.workspace && o0.workspace_bytes < asked)
     return fail(ctx, MC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", o0.workspace_bytes,
                 asked);
+  RunLayout Lay = basket_layout(n_paths, 3, want_rows);
   mc_options ow = o0;
-  if (ow.workspace_bytes < needed) ow.workspace = nullptr;
+  double* rows = nullptr;
+  if (o0.workspace && o0.workspace_bytes < basket_run_bytes(Lay.bytes, d, o0.prec)) {
+    ow.workspace = nullptr;
+    if (want_rows) rows = (double*)o0.workspace;
+    Lay = basket_layout(n_paths, 3, false);
+  }
+  const size_t off_blk = align256(Lay.bytes);
+  const size_t off_asset = off_blk + align256(basket_frag_bytes(d, o0.prec));
   char* base = nullptr;
-  mc_status st = get_ws(ctx, ow, needed, &base);
+  mc_status st = get_ws(ctx, ow, basket_run_bytes(Lay.bytes, d, o0.prec), &base);
   if (st != MC_OK) return st;
   hipStream_t s = stream_of(ctx, o0);
   if (!ctx->dev_L_valid) {
@@ -1229,17 +1239,20 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   }
   p.qV = qmc ? qmc->V : nullptr;
   p.qshift = qmc ? qmc->shift : nullptr;
+  p.path_out = rows;
   *p_out = p;
   *prec_out = prec;
   *o_run = o;
   return MC_OK;
 }
 
-// Runs what basket_setup has prepared (o: its narrowed options).
+// Runs what basket_setup has prepared (o: its narrowed options; p.path_out:
+// the per-path values' memory, or nullptr behind the moments).
 mc_status basket_run(mc_context* ctx, BasketParams& p, int prec, const mc_options& o,
                      mc_result* out, double* geo_mean = nullptr,
                      const std::function<hipError_t(hipStream_t)>& queued = nullptr) {
   const bool port = p.n_strikes != 0;
+  double* const rows = p.path_out;
   Moments mom;
   double kms = 0.0;
   mc_status st = run_moments(ctx, o, p.n_paths, port ? 1 : 3, o.path_values,
@@ -1249,7 +1262,7 @@ mc_status basket_run(mc_context* ctx, BasketParams& p, int prec, const mc_option
                      p.clock = ctx->clock;
                      return launch_basket(p, prec, ss, nb);
                    },
-                   &mom, &kms, kBasketTile, kBasketMaxBlocks, queued);
+                   &mom, &kms, kBasketTile, kBasketMaxBlocks, queued, 0, rows);
   if (st != MC_OK) return st;
   mc_result r{};
   double v;

@@ -132,14 +132,18 @@ int hipGetSymbolAddress(void **p, const void *symbol) {
     *p = scratch;
     return 0;
 }
-int hipMalloc(void **p, size_t n) { return (*p = calloc(n, 1)) ? 0 : 2; }
+uint64_t stub_malloc_bytes;                /* device memory allocated so far */
+int hipMalloc(void **p, size_t n) {
+    stub_malloc_bytes += n;
+    return (*p = calloc(n, 1)) ? 0 : 2;
+}
 int hipFree(void *p) {
     free(p);
     return 0;
 }
 int hipHostMalloc(void **p, size_t n, unsigned flags) {
     (void)flags;
-    return hipMalloc(p, n);
+    return (*p = calloc(n, 1)) ? 0 : 2;
 }
 int hipHostFree(void *p) { return hipFree(p); }
 int hipMemcpyAsync(void *to, const void *from, size_t n, int kind, void *stream) {

@@ -80,3 +80,37 @@ for m, f, kw in calls:
                                       C.byref(call.co), C.byref(res))
     assert st == mc.MC_OK, (m, f, kw, mc.mc_last_error(ctx))
 """)
+
+
+def test_basket_rows_stay_in_the_callers_workspace(run):
+    # A workspace of the size asked for holds the rows of per-path values,
+    # all that grows with the paths; the context adds its factor (8 d^2 bytes)
+    # and one block of at most 1 MB. No kernel runs: the rows come back as the
+    # workspace held them.
+    run("""
+for d in (16, 112, 256):
+    m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.03, T=1.0, sigma=np.full(d, 0.2),
+                 corr=np.eye(d))
+    for prec in (mc.MC_FP32, mc.MC_BF16_GEMM, mc.MC_BF16X2_GEMM):
+        for N in (3000, 64 * 4096, 1 << 20):         # no split tiles
+            f = mc.Payoff(mc.MC_BASKET_CALL, 100.0)
+            call, res = mc._Marshal(m, f, mc.Options(prec=prec), N), _abi.McResult()
+            call.want_path_values(N, 3)
+            need = _abi.load().mc_workspace_bytes(C.byref(call.cm), C.byref(call.cp), N, 100,
+                                                  C.byref(call.co))
+            for size in (need, need + (1 << 20)):
+                ws = np.full(size // 8 + 1, 7.0)
+                call.path_buf[:] = 0.0
+                call.co.workspace, call.co.workspace_bytes = ws.ctypes.data, size
+                ctx = mc.mc_create(0)
+                before = cell("stub_malloc_bytes", C.c_uint64).value
+                st = _abi.load().mc_price(ctx.handle, C.byref(call.cm), C.byref(call.cp), N, 100, 1,
+                                          C.byref(call.co), C.byref(res))
+                more = cell("stub_malloc_bytes", C.c_uint64).value - before
+                ctx.close()
+                assert st == mc.MC_OK
+                split = d > 16 and N == 3000
+                assert more <= 8 * d * d + (1 << 20) + (47 * d * 256 + 4096 if split else 0), \
+                    (d, prec, N, more)
+                assert (call.path_buf == 7.0).all(), (d, prec, N)
+""")
