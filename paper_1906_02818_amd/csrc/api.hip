@@ -1173,6 +1173,16 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   if (st != MC_OK) return st;
   double* sigma = ctx->pinned + kBasketStage;
   float* asset = (float*)(sigma + 256);
+  // A value that the assets share (one price, one weight) would be off for every
+  // path once rounded to FP32. The table's prices are taken over a ratio near 1
+  // that makes the largest entry exact; the basket's strike, discount factor
+  // and constants are scaled to match, the portfolio's kernel multiplies.
+  double top = 0.0;
+  for (uint32_t a = 0; a < d; ++a)
+    top = std::fmax(top, std::fabs((port || !f->weights ? 1.0 : f->weights[a]) * m->S0[a]));
+  if (!port && !f->weights) top *= 1.0 / d;
+  double ratio = top / (double)(float)top;
+  if (!std::isfinite(ratio) || ratio == 0.0) ratio = 1.0;
   double geo0 = 0.0;
   for (uint32_t a = 0; a < d; ++a) {
     const double w = f->weights ? f->weights[a] : 1.0 / d;
@@ -1180,9 +1190,9 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     const double mu = (drift - 0.5 * m->sigma[a] * m->sigma[a]) * dt * inv_ln2;
     sigma[a] = m->sigma[a];
     asset[a] = (float)(n_steps * mu);
-    asset[256 + a] = (float)(w * m->S0[a]);
+    asset[256 + a] = (float)(w * m->S0[a] / ratio);
     asset[512 + a] = (float)(w * std::log(2.0));
-    asset[768 + a] = (float)m->S0[a];
+    asset[768 + a] = (float)(m->S0[a] / ratio);
     geo0 += w * std::log(m->S0[a]);
   }
   BasketPack k{};
@@ -1228,10 +1238,11 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
       p.x_scale *= 2.0f;
     }
   p.asset = (const float*)(base + off_asset);
-  p.disc = std::exp(-m->r * m->T);
-  p.K = f->K;
-  p.geo0 = geo0;
-  p.w0 = f->weights ? f->weights[0] : 1.0 / d;
+  p.disc = std::exp(-m->r * m->T) * ratio;
+  p.K = f->K / ratio;
+  p.geo0 = geo0 - std::log(ratio);
+  p.w0 = (f->weights ? f->weights[0] : 1.0 / d) / ratio;
+  p.ratio = ratio;
   p.n_strikes = port ? port->n_strikes : 0u;
   for (uint32_t k = 0; k < p.n_strikes; ++k) {
     p.pm[k] = (float)port->strike_mult[k];

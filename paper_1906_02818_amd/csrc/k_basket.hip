@@ -274,7 +274,7 @@ template <bool PORT, int C, typename R>
 __device__ __forceinline__ void channels(const BasketParams& P, const R (&v)[C],
                                          double (&y)[C]) {
   if constexpr (PORT) {
-    y[0] = (double)v[0] - P.premium;
+    y[0] = (double)v[0] * P.ratio - P.premium;
   } else {
     const double disc = P.disc, K = P.K;
     const double basket = (double)v[0];

@@ -165,7 +165,10 @@ struct BasketParams {
   // factor sqrt(2 ln 2) of the normals; half precision takes the sums times a
   // power of two (|sum| < 5.8 n_steps stays below 2^15) and the product over it.
   float z_scale, x_scale;
-  const float* asset;     // device [4][256]: n*mu_a (log2), w_a*S0_a, w_a*ln 2, S0_a
+  // Device [4][256]: n*mu_a (log2), w_a*S0_a / ratio, w_a*ln 2, S0_a / ratio; the
+  // prices' ratio (near 1, see basket_setup) also divides K and w0, multiplies
+  // disc, and its logarithm is taken off geo0.
+  const float* asset;
   double disc, K, geo0, w0;
   // Call portfolio (risk mode): q_k calls of strike m_k S0_a on every asset;
   // the per-path value is sum_a S0_a sum_k q_k (S_a/S0_a - m_k)^+ - premium.
@@ -188,6 +191,7 @@ struct BasketParams {
   double* partials;
   double* path_out;       // [n_paths][3] (basket) or [n_paths] (portfolio), or nullptr
   uint64_t* clock;        // start stamp, or nullptr
+  double ratio;           // the prices', for the portfolio's value
 };
 constexpr int kMaxStrikes = 8;
 // Words a run's set-up launch clears for later kernels of the call (n <= 2^20).

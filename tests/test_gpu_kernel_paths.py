@@ -524,3 +524,23 @@ def test_equal_paths_of_persistent_grids(ctx, prec):
         # A delta's two payoffs are of the size of the price, their difference
         # of its two-thousandth part.
         assert 0.0 <= r["delta_se"] < 1e-11 * abs(r["delta"]), K
+
+
+@pytest.mark.parametrize("d", [16, 128])
+@pytest.mark.parametrize("S", [101.7, 95.03])
+def test_basket_of_one_asset_has_its_price(ctx, d, S):
+    """The largest price of the asset table is not rounded to FP32: at sigma =
+    r = 0 a basket of that asset alone is worth it to FP64 rounding, and so is
+    a portfolio of shares whose other prices are 2^-30 (lost in the FP32 sums:
+    below 1e-9 of it)."""
+    S0, w = np.full(d, 2.0 ** -30), np.zeros(d)
+    S0[0], w[0] = S, 1.0
+    m = mc.Model(kind=mc.MC_GBM_BASKET, S0=S0, r=0.0, T=1.0, sigma=np.zeros(d), corr=np.eye(d))
+    for K in (0.0, 90.1):
+        for prec in (mc.MC_FP32, mc.MC_BF16_GEMM):
+            r = mc.mc_price(ctx, m, mc.Payoff(mc.MC_BASKET_CALL, K, weights=w), 64, 1, SEED,
+                            mc.Options(prec=prec, greeks=1))
+            assert r["price"] == pytest.approx(S - K, rel=1e-12)
+            assert r["delta"] == pytest.approx(1.0, rel=1e-12)
+    r = mc.mc_risk(ctx, m, [0.0], [1.0], 0.9, 64, 1, SEED)
+    assert r["pnl_mean"] + r["premium"] == pytest.approx(S, rel=1e-9)
