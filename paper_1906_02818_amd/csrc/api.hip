@@ -1199,8 +1199,8 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   k.L = ctx->dev_L;
   k.sigma = sigma;
   k.asset = asset;
-  k.sdt = std::sqrt(dt);
-  k.inv_ln2 = inv_ln2;
+  k.step = std::sqrt(dt) * inv_ln2;
+  if (prec == BK_FP32) k.step *= std::sqrt(2.0 * std::log(2.0));
   k.d = d;
   k.frag = (uint16_t*)(base + off_blk);
   k.asset_out = (float*)(base + off_asset);
@@ -1231,7 +1231,6 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   p.split_sums = split.parts > 1 ? (float*)ctx->split_buf : nullptr;
   p.split_arrivals = k.zero[1].words;
   p.z_scale = p.x_scale = 1.0f;
-  if (prec == BK_FP32) p.z_scale = (float)std::sqrt(2.0 * std::log(2.0));
   if (prec == BK_FP16)
     while (5.8 * (double)n_steps * p.z_scale > 32768.0) {
       p.z_scale *= 0.5f;

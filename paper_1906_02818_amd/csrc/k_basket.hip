@@ -88,7 +88,7 @@ __device__ __forceinline__ void mma(f32x4& acc, const f16x8& a, const f16x8& b) 
 
 // s += the normals of one or two steps (blocks a, b; two: b holds a step),
 // rounded as PREC's operands are. FP32 sums the normals over sqrt(2 ln 2), the
-// factor of every radius (P.z_scale restores it): one fma per normal.
+// factor of every radius, which L' carries: one fma per normal.
 template <int PREC>
 __device__ __forceinline__ void add_steps(float (&s)[4], const Words4& a, const Words4& b,
                                           bool two) {
@@ -160,8 +160,7 @@ __device__ __forceinline__ Words4 sobol_words(const uint32_t* __restrict__ V,
 }
 
 // Term t of v in the 16-bit type: bfloat16 terms are each the rounding of what
-// the earlier ones leave of the double (split BF16) or of its float (the
-// float's 24 bits as three); half has one.
+// the earlier ones leave of the double (three: 26 bits); half has one.
 __device__ __forceinline__ uint16_t to_bf16(float f) {
   const uint32_t u = __float_as_uint(f);
   return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
@@ -172,7 +171,7 @@ __device__ __forceinline__ void split_terms(double v, uint16_t (&h)[Form<PREC>::
     const _Float16 x = (_Float16)(float)v;
     __builtin_memcpy(&h[0], &x, 2);
   } else {
-    double rest = PREC == BK_BF16X2 ? v : (double)(float)v;
+    double rest = v;
 #pragma unroll
     for (int t = 0; t < Form<PREC>::NL; ++t) {
       h[t] = to_bf16((float)rest);
@@ -181,6 +180,10 @@ __device__ __forceinline__ void split_terms(double v, uint16_t (&h)[Form<PREC>::
   }
 }
 
+// L' carries, in FP64, what is common to all sums: a constant applied to them
+// in FP32 instead (sqrt(2 ln 2) of the FP32 form, 1.4e-8 off) shows in every
+// standard deviation, where the roundings of single paths average out.
+//
 // One workgroup per four fragments of L' (a lane writes its eight entries of
 // each term), one for the asset table, and the words to clear. Latency of a
 // launch and of reads over PCIe; 4 us.
@@ -202,7 +205,7 @@ __global__ __launch_bounds__(256) void basket_pack_kernel(const BasketPack K) {
   while (basket_pairs(rb + 1u) <= pair) ++rb;
   const uint32_t kb = pair - basket_pairs(rb);
   const uint32_t a = 16u * rb + (lane & 15u), b0 = 32u * kb + 8u * (lane >> 4);
-  const double scale = K.sigma[a] * K.sdt * K.inv_ln2;
+  const double scale = K.sigma[a] * K.step;
   uint16_t h[8][NL];
 #pragma unroll
   for (uint32_t e = 0; e < 8u; ++e) {

@@ -161,9 +161,9 @@ struct BasketParams {
   uint32_t n_steps, tag, k0, k1;
   uint32_t d;             // assets, multiple of 16, <= 256
   const void* Lfrag;      // [terms][basket_pairs(d / 16)][64][8] (device)
-  // Scale of the sums as operands, and of the product: FP32 restores the
-  // factor sqrt(2 ln 2) of the normals; half precision takes the sums times a
-  // power of two (|sum| < 5.8 n_steps stays below 2^15) and the product over it.
+  // Scale of the sums as operands, and of the product: half precision takes the
+  // sums times a power of two (|sum| < 5.8 n_steps stays below 2^15) and the
+  // product over it; 1 in the other forms.
   float z_scale, x_scale;
   // Device [4][256]: n*mu_a (log2), w_a*S0_a / ratio, w_a*ln 2, S0_a / ratio; the
   // prices' ratio (near 1, see basket_setup) also divides K and w0, multiplies
@@ -199,13 +199,14 @@ struct BasketZero {
   uint32_t* words = nullptr;
   uint32_t n = 0;
 };
-// Packs L' = diag(sigma_a sdt inv_ln2) L into Lfrag form and copies the asset
-// table from pinned memory.
+// Packs L' = diag(sigma_a step) L into Lfrag form and copies the asset table
+// from pinned memory. step: sqrt(dt) / ln 2, in FP32 times the factor
+// sqrt(2 ln 2) that its sums of normals leave out.
 struct BasketPack {
   const double* L;        // [d][d] lower factor (device)
   const double* sigma;    // [d] (pinned)
   const float* asset;     // [4][256] (pinned)
-  double sdt, inv_ln2;
+  double step;
   uint32_t d;
   uint16_t* frag;
   float* asset_out;

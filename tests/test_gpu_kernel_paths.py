@@ -544,3 +544,25 @@ def test_basket_of_one_asset_has_its_price(ctx, d, S):
             assert r["delta"] == pytest.approx(1.0, rel=1e-12)
     r = mc.mc_risk(ctx, m, [0.0], [1.0], 0.9, 64, 1, SEED)
     assert r["pnl_mean"] + r["premium"] == pytest.approx(S, rel=1e-9)
+
+
+def test_basket_sums_carry_no_common_error(ctx):
+    """FP32 log-returns of the geometric basket against L' times the sums of
+    the device's own normals, both in 64 bits: the roundings of single paths
+    average out (1e-7 of a return over the sqrt of 2^14 paths: 1e-9), what is
+    common to all stays as a slope. Allowed: 1.4e-9 of the FP32 constant in
+    the normals, 2e-9 of L' in three terms, three times the noise. L' is exact
+    in few bits here, so that no rounding of its entries hides an error."""
+    d, n, N = 16, 8, 1 << 14
+    step = math.sqrt(1.0 / n) / math.log(2.0)
+    L = np.arange(3, 3 + d) / 64.0
+    S = np.array([mc.mc_normals(ctx, SEED, 0, p, 0, n * d).reshape(n, d).sum(0) for p in range(N)])
+    sigma = L / step
+    m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.ones(d), r=0.0, T=1.0, sigma=sigma, corr=np.eye(d))
+    got = mc.mc_price(ctx, m, mc.Payoff(mc.MC_BASKET_CALL, 0.0), N, n, SEED,
+                      mc.Options(path_values=True))["path_values"][:, 1]
+    w = float(np.float32(math.log(2.0) / d))              # the asset table holds it in FP32
+    drift = np.float32(-0.5 * sigma * sigma / math.log(2.0)).astype(np.float64)
+    want = w * (S @ L)
+    slope = ((np.log(got) - w * drift.sum()) * want).sum() / (want * want).sum()
+    assert abs(slope - 1.0) < 1.4e-9 + 2e-9 + 3e-9
