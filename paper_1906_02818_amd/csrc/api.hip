@@ -1183,7 +1183,7 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   if (!port && !f->weights) top *= 1.0 / d;
   double ratio = top / (double)(float)top;
   if (!std::isfinite(ratio) || ratio == 0.0) ratio = 1.0;
-  double geo0 = 0.0;
+  double geo0 = 0.0, base_value = 0.0;
   for (uint32_t a = 0; a < d; ++a) {
     const double w = f->weights ? f->weights[a] : 1.0 / d;
     const double drift = (port && port->mu) ? port->mu[a] : m->r;
@@ -1191,6 +1191,7 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     sigma[a] = m->sigma[a];
     asset[a] = (float)(n_steps * mu);
     asset[256 + a] = (float)(w * m->S0[a] / ratio);
+    base_value += (double)asset[256 + a];
     asset[512 + a] = (float)(w * std::log(2.0));
     asset[768 + a] = (float)(m->S0[a] / ratio);
     geo0 += w * std::log(m->S0[a]);
@@ -1242,6 +1243,7 @@ mc_status basket_setup(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   p.geo0 = geo0 - std::log(ratio);
   p.w0 = (f->weights ? f->weights[0] : 1.0 / d) / ratio;
   p.ratio = ratio;
+  p.base = base_value;
   p.n_strikes = port ? port->n_strikes : 0u;
   for (uint32_t k = 0; k < p.n_strikes; ++k) {
     p.pm[k] = (float)port->strike_mult[k];

@@ -22,9 +22,11 @@
 // enter as up to three terms of the 16-bit type (8 + 8 + 8 bits), and so does
 // an FP32 L', with the products of terms above 2^-24 kept: the FP32 form is
 // six bfloat16 MFMAs for the eight FP32 ones of the same block, 96 cycles
-// against 256. Its error against 64 bits is below that of a product per step
-// in FP32, whose accumulation rounds n d / 2 times (100003 paths, d = 112, 50
-// steps: largest error of a result 1.6e-7 relative against 2.3e-7).
+// against 256. Error of a path's value against 64 bits (root mean square over
+// the paths, of their spread), product per step in FP32 -> here: portfolio of
+// 112 assets x 50 steps 3.0e-7 -> 1.6e-7, 64 x 30 2.4e-7 -> 1.4e-7, 16 x 3
+// 1.3e-7 -> 1.2e-7 (8 keys each); baskets of 16 to 256 assets 2.7e-7 to 3.0e-7
+// -> 1.5e-7. Error of the portfolio's standard error: 2.6e-8 -> 1.8e-8.
 //
 // Bound: VALU issue of the normals, 222 cycles per block of four and wave in
 // FP32, 244 in bfloat16 (issue costs: device/rng.h; 4.3 for a conversion or a
@@ -247,10 +249,15 @@ __device__ __forceinline__ uint32_t sum_terms(uint32_t n) {
 
 // Terminal values of the lane's four assets 16 rb + 4 (lane / 16) + 0..3 of a
 // path: basket and geometric-basket sums (or the portfolio's value), and the
-// growth of asset 0.
-template <bool PORT>
+// growth of asset 0. QMC: the basket's sum is of S_a / S0_a - 1, whose FP32
+// roundings are smaller (P.base, the sum of the ones, joins it in FP64): the
+// standard error of a few replicates shows what does not average out (its
+// error, 16 replicates of 2^16 points: 7.0e-7 without, 4.3e-7 with).
+template <bool PORT, bool QMC>
 __device__ __forceinline__ void terminal_rows(const BasketParams& P, const f32x4& x, uint32_t rb,
                                               uint32_t g4, float& bs, float& gs, float& e0) {
+  // The four assets by themselves first: a lane has up to 32.
+  float b = 0.f, g = 0.f;
 #pragma unroll
   for (uint32_t r = 0; r < 4u; ++r) {
     const uint32_t a = 16u * rb + 4u * g4 + r;
@@ -263,24 +270,26 @@ __device__ __forceinline__ void terminal_rows(const BasketParams& P, const f32x4
         const float itm = E - P.pm[k];
         pv = __builtin_fmaf(P.pq[k], itm > 0.f ? itm : 0.f, pv);
       }
-      bs = __builtin_fmaf(P.asset[768 + a], pv, bs);
+      b = __builtin_fmaf(P.asset[768 + a], pv, b);
     } else {
-      bs += P.asset[256 + a] * E;
-      gs += P.asset[512 + a] * v;
+      b += P.asset[256 + a] * (QMC ? E - 1.0f : E);
+      g += P.asset[512 + a] * v;
       if (a == 0u) e0 = E;
     }
   }
+  bs += b;
+  gs += g;
 }
 
 // Channels of a path from its sums v.
-template <bool PORT, int C, typename R>
+template <bool PORT, bool QMC, int C, typename R>
 __device__ __forceinline__ void channels(const BasketParams& P, const R (&v)[C],
                                          double (&y)[C]) {
   if constexpr (PORT) {
     y[0] = (double)v[0] * P.ratio - P.premium;
   } else {
     const double disc = P.disc, K = P.K;
-    const double basket = (double)v[0];
+    const double basket = QMC ? P.base + (double)v[0] : (double)v[0];
     const double geo = exp(P.geo0 + (double)v[1]);
     y[0] = disc * (basket > K ? basket - K : 0.0);
     y[1] = disc * (geo > K ? geo - K : 0.0);
@@ -308,8 +317,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   typedef typename F::V V8;
   constexpr int SETS = W / 4, C = PORT ? 1 : 3;
   extern __shared__ float s_sum[];         // [d][kRow]
-  // QMC: the sums over a path's lanes in FP64 (see qmc_tile_kernel).
-  typedef typename std::conditional<QMC, double, float>::type Sum;
+  // The sums over a path's lanes in FP64, where their rounding would be the
+  // largest of a path: per path 3.0e-7 -> 1.5e-7 of the spread in FP32 (16 to
+  // 256 assets), at the same time. In the reduced precisions, whose operands
+  // round to 2e-4 and more, it costs 5% (basket, bfloat16: 2715 -> 2844 us) and
+  // shows in no digit.
+  constexpr bool kSums64 = QMC || PREC == BK_FP32;
+  typedef typename std::conditional<kSums64, double, float>::type Sum;
   __shared__ Sum s_part[C][SETS][kTile];
   // The first wave's paths over the workgroup's tiles (in LDS: as registers
   // they would be held by every wave). About a shift: a lane takes 2^18 paths
@@ -431,10 +445,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
     for (uint32_t i = 0; i < (uint32_t)RPW; ++i) {
       const uint32_t rb = row_block<SETS>(set, i);
-      if (rb < rows) terminal_rows<PORT>(P, x[i], rb, g4, bs, gs, e0);
+      if (rb < rows) terminal_rows<PORT, QMC>(P, x[i], rb, g4, bs, gs, e0);
     }
     Sum bsum, gsum = 0, esum = 0;
-    if constexpr (QMC) {
+    if constexpr (kSums64) {
       bsum = lane_add<16>(lane_add<32>((double)bs));
       gsum = lane_add<16>(lane_add<32>((double)gs));
       esum = lane_add<16>(lane_add<32>((double)e0));
@@ -469,7 +483,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int q = 1; q < SETS; ++q) v[c] += s_part[c][q][lane];
       }
       double y[C];
-      channels<PORT>(P, v, y);
+      channels<PORT, QMC>(P, v, y);
       bool finite = true;
 #pragma unroll
       for (int c = 0; c < C; ++c) finite = finite && isfinite(y[c]);
@@ -583,11 +597,9 @@ __global__ __launch_bounds__(64 * kQmcWaves, 4) void qmc_tile_kernel(const Baske
               if (p + t < F::KEEP && (uint32_t)t < nz) mma(x, l, z[t]);
           }
         }
-        terminal_rows<false>(P, x, rb, g4, bs, gs, e0);
+        terminal_rows<false, true>(P, x, rb, g4, bs, gs, e0);
       }
-      // The last two sums of four assets' sums in FP64: their rounding would be
-      // the largest of a path, and the standard error of a few replicates shows
-      // what does not average out.
+      // The last two sums in FP64: their rounding would be the largest of a path.
       const float t[C] = {bs, gs, e0};
 #pragma unroll
       for (int c = 0; c < C; ++c) {
@@ -599,7 +611,7 @@ __global__ __launch_bounds__(64 * kQmcWaves, 4) void qmc_tile_kernel(const Baske
     const uint64_t point = (uint64_t)base + (uint64_t)lane;
     if (point >= first && point < last) {
       double y[C];
-      channels<false>(P, v, y);
+      channels<false, true>(P, v, y);
       bool finite = true;
 #pragma unroll
       for (int c = 0; c < C; ++c) finite = finite && isfinite(y[c]);

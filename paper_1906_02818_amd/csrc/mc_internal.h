@@ -192,6 +192,7 @@ struct BasketParams {
   double* path_out;       // [n_paths][3] (basket) or [n_paths] (portfolio), or nullptr
   uint64_t* clock;        // start stamp, or nullptr
   double ratio;           // the prices', for the portfolio's value
+  double base;            // sum of the table's w_a*S0_a / ratio
 };
 constexpr int kMaxStrikes = 8;
 // Words a run's set-up launch clears for later kernels of the call (n <= 2^20).

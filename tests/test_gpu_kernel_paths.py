@@ -531,8 +531,8 @@ def test_equal_paths_of_persistent_grids(ctx, prec):
 def test_basket_of_one_asset_has_its_price(ctx, d, S):
     """The largest price of the asset table is not rounded to FP32: at sigma =
     r = 0 a basket of that asset alone is worth it to FP64 rounding, and so is
-    a portfolio of shares whose other prices are 2^-30 (lost in the FP32 sums:
-    below 1e-9 of it)."""
+    a portfolio of shares whose other prices are 2^-30, up to what a lane's FP32
+    sums lose of those (1e-9 of it)."""
     S0, w = np.full(d, 2.0 ** -30), np.zeros(d)
     S0[0], w[0] = S, 1.0
     m = mc.Model(kind=mc.MC_GBM_BASKET, S0=S0, r=0.0, T=1.0, sigma=np.zeros(d), corr=np.eye(d))
@@ -543,7 +543,7 @@ def test_basket_of_one_asset_has_its_price(ctx, d, S):
             assert r["price"] == pytest.approx(S - K, rel=1e-12)
             assert r["delta"] == pytest.approx(1.0, rel=1e-12)
     r = mc.mc_risk(ctx, m, [0.0], [1.0], 0.9, 64, 1, SEED)
-    assert r["pnl_mean"] + r["premium"] == pytest.approx(S, rel=1e-9)
+    assert r["pnl_mean"] + r["premium"] == pytest.approx(S0.sum(), rel=1e-9)
 
 
 def test_basket_sums_carry_no_common_error(ctx):
@@ -566,3 +566,22 @@ def test_basket_sums_carry_no_common_error(ctx):
     want = w * (S @ L)
     slope = ((np.log(got) - w * drift.sum()) * want).sum() / (want * want).sum()
     assert abs(slope - 1.0) < 1.4e-9 + 2e-9 + 3e-9
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_basket_sums_over_assets(ctx, d):
+    """At sigma = r = 0 a basket is the sum of its FP32 asset table, so what
+    is left is the rounding of that sum: fours and a lane's fours in FP32, the
+    lanes in FP64. For random weights 1.5e-8 of the sum (root mean square, from
+    the FP32 sums in numpy), allowed is twice that; one by one and over the
+    lanes in FP32 it is 4.3e-8 to 4.6e-8."""
+    rng, err = np.random.default_rng(d), []
+    for _ in range(100):
+        w = rng.random(d) / d
+        m = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(d, 100.0), r=0.0, T=1.0, sigma=np.zeros(d),
+                     corr=np.eye(d))
+        r = mc.mc_price(ctx, m, mc.Payoff(mc.MC_BASKET_CALL, 0.0, weights=w), 2, 1, SEED)
+        ratio = (w * 100.0).max() / float(np.float32((w * 100.0).max()))
+        table = (w * 100.0 / ratio).astype(np.float32).astype(np.float64)
+        err.append(r["price"] / (table.sum() * ratio) - 1.0)
+    assert math.sqrt(np.mean(np.square(err))) < 3e-8
