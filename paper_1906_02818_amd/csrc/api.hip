@@ -364,6 +364,20 @@ hipStream_t stream_of(mc_context* ctx, const mc_options& o) {
   return o.hip_stream ? (hipStream_t)o.hip_stream : ctx->stream;
 }
 
+// Waits for the stream where a call ends early: what it has queued reads staged
+// inputs from, and writes results to, memory of the context that the next call
+// uses again. Disarmed by the call's own wait.
+struct QueueGuard {
+  hipStream_t s;
+  bool armed = true;
+  explicit QueueGuard(hipStream_t stream) : s(stream) {}
+  ~QueueGuard() {
+    if (armed) (void)hipStreamSynchronize(s);
+  }
+  QueueGuard(const QueueGuard&) = delete;
+  QueueGuard& operator=(const QueueGuard&) = delete;
+};
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Sizes of one moment run.
@@ -458,6 +472,7 @@ mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, in
   double* partials = (double*)base;
   if (!rows && host_path_values) rows = (double*)(base + L.off_path);
   double* path_out = ctx->sink ? ctx->sink : rows;
+  QueueGuard queue(s);
   uint32_t nb = 0;
   HIP_TRY(ctx, launch(partials, path_out, s, &nb));
   if (nb == 0 || nb > L.n_blocks) return fail(ctx, MC_ERR_DEVICE, "block count mismatch");
@@ -467,6 +482,7 @@ mc_status run_moments(mc_context* ctx, const mc_options& o, uint64_t n_paths, in
     HIP_TRY(ctx, hipMemcpyAsync(host_path_values, path_out, n_paths * C * sizeof(double),
                                 hipMemcpyDeviceToHost, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
+  queue.armed = false;
   if (kernel_ms) *kernel_ms += clock_ms(ctx, 0, 1);
   out->C = C;
   out->n = hmom[0];
@@ -1478,10 +1494,12 @@ mc_status fd_greek(mc_context* ctx, const mc_model* m, const mc_payoff* f, uint6
       if (st != MC_OK) return st;
       *kms += tmp.kernel_ms;
     }
+    QueueGuard queue(s);
     uint32_t nb = 0;
     HIP_TRY(ctx, launch_diff_moments(A, C, ch, B, C, ch, nc, partials, s, &nb));
     HIP_TRY(ctx, launch_final_merge(partials, nb, 3, 1, ctx->pinned, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
+    queue.armed = false;
     merge_moment_vec(acc, ctx->pinned, 3);
   }
   // acc: [n, nonfinite, mean d, mean a, mean b, M_dd, ...]
@@ -1562,16 +1580,14 @@ mc_status gbm_fd_price(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   p.partials = (double*)base;
   hipStream_t s = stream_of(ctx, o);
   double* mom = ctx->pinned + kFdMoments;
+  QueueGuard queue(s);
   uint32_t nb = 0;
   HIP_TRY(ctx, launch_gbm_fd(p, bit, want[0], want[1], s, &nb));
   mc_result r{};
-  const hipError_t merged = launch_final_merge(p.partials, nb, 1, n_greeks, mom, s, ctx->clock + 3);
-  if (merged == hipSuccess) st = mc_price_impl(ctx, m, f, n_paths, n_steps, seed, price_opts, &r);
-  if (merged != hipSuccess || st != MC_OK) {
-    HIP_TRY(ctx, hipStreamSynchronize(s));   // the queued kernels write to the context's memory
-    HIP_TRY(ctx, merged);
-    return st;
-  }
+  HIP_TRY(ctx, launch_final_merge(p.partials, nb, 1, n_greeks, mom, s, ctx->clock + 3));
+  st = mc_price_impl(ctx, m, f, n_paths, n_steps, seed, price_opts, &r);
+  if (st != MC_OK) return st;
+  queue.armed = false;                     // the price run has waited
   for (int g = 0; g < 2; ++g) {
     if (!want[g]) continue;
     const double n = mom[0];               // [n, non-finite, mean, sum of squares]
@@ -1989,12 +2005,14 @@ mc_status mc_price_mlmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, 
         if (st != MC_OK) return st;
         kms += tmp.kernel_ms;
       }
+      QueueGuard queue(s);
       uint32_t nb = 0;
       HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
       HIP_TRY(ctx, launch_diff_moments(A, Ca, ca, B, Cb, cb, nc, partials, s, &nb));
       HIP_TRY(ctx, launch_final_merge(partials, nb, 3, 1, ctx->pinned, s));
       HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
       HIP_TRY(ctx, hipStreamSynchronize(s));
+      queue.armed = false;
       float ms = 0.f;
       HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
       kms += ms;
@@ -2094,11 +2112,13 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
   if (o0.path_values) {
     // One replicate with per-path values: the plain basket run.
     BasketQmc q{ctx->qmc_buf, ctx->qmc_buf + (size_t)dims * 32, 0.0};
+    QueueGuard queue(s);
     HIP_TRY(ctx, launch_qmc_shifts((uint32_t)seed, (uint32_t)(seed >> 32), o0.stream_tag + 6u, 0,
                                    1, dims, (uint32_t*)q.shift, s));
     mc_result pr{};
     st = basket_price(ctx, m, f, n_points, n_steps, seed, o0, &pr, &q);
     if (st != MC_OK) return st;
+    queue.armed = false;
     r.replicate_price[0] = pr.price;
     r.replicate_geo[0] = q.geo_mean;
     r.kernel_ms = pr.kernel_ms;
@@ -2111,6 +2131,7 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     mc_options orun;
     st = basket_setup(ctx, m, f, n_points, n_steps, seed, o0, nullptr, &q0, {}, &p, &prec, &orun);
     if (st != MC_OK) return st;
+    QueueGuard queue(s);
     const RunLayout Lay = basket_layout(n_points, 3, false);
     const size_t b_shift = align256((size_t)n_replicates * dims * sizeof(uint32_t));
     const size_t b_part = align256((size_t)n_replicates * Lay.n_mom * Lay.n_blocks * sizeof(double));
@@ -2135,6 +2156,7 @@ mc_status mc_price_qmc(mc_context* ctx, const mc_model* m, const mc_payoff* f, u
     if (nb == 0 || nb > Lay.n_blocks) return fail(ctx, MC_ERR_DEVICE, "block count mismatch");
     HIP_TRY(ctx, launch_final_merge(parts, nb, 3, n_replicates, ctx->pinned, s, ctx->clock + 1));
     HIP_TRY(ctx, hipStreamSynchronize(s));
+    queue.armed = false;
     r.kernel_ms = clock_ms(ctx, 0, 1);
     for (uint32_t rep = 0; rep < n_replicates; ++rep) {
       // Moments: [n_valid, n_nonfinite, mean basket, mean geometric, ...].
@@ -2243,11 +2265,13 @@ mc_status mc_risk(mc_context* ctx, const mc_model* m, const mc_portfolio* pf, ui
   hipStream_t s = stream_of(ctx, o0);
   // Read once: the launches below write the flag again while they run.
   const bool rest = sel->done == 0;
+  QueueGuard queue(s);
   if (rest) HIP_TRY(ctx, launch_select_rest(x, n_paths, state, list, partials, sel, s));
   if (o0.path_values)
     HIP_TRY(ctx, hipMemcpyAsync(o0.path_values, x, n_paths * sizeof(double),
                                 hipMemcpyDeviceToHost, s));
   if (rest || o0.path_values) HIP_TRY(ctx, hipStreamSynchronize(s));
+  queue.armed = false;
   mc_risk_result r{};
   r.quantile_pnl = select_key_to_value(sel->key);
   r.var = -r.quantile_pnl;
@@ -2613,6 +2637,11 @@ mc_status mc_price_lsm(mc_context* ctx, const mc_model* m, const mc_lsm_spec* sp
     red.host = stage == (Noos ? M : M - 1) ? ctx->pinned : nullptr;
     return launch_lsm_reduce(p.partials, blocks, n_mom, nf, date, red, s);
   };
+  // Copies of per-path values land here: declared before the guard, which
+  // waits before they go.
+  std::vector<float> h_c;
+  std::vector<uint8_t> h_e, h_oe;
+  QueueGuard queue(s);
   uint32_t nb = 0;
   p.clock = clock + upd_clock(0);
   HIP_TRY(ctx, launch_lsm_sim(p, s, &nb));
@@ -2639,8 +2668,9 @@ mc_status mc_price_lsm(mc_context* ctx, const mc_model* m, const mc_lsm_spec* sp
     HIP_TRY(ctx, launch_lsm_oos(po, s, &nb));
     HIP_TRY(ctx, reduce(M, nb, 2, 0));
   }
-  std::vector<float> h_c(want_cf ? n_paths : 0);
-  std::vector<uint8_t> h_e(want_ex ? n_paths : 0), h_oe(want_oe ? Noos : 0);
+  h_c.resize(want_cf ? n_paths : 0);
+  h_e.resize(want_ex ? n_paths : 0);
+  h_oe.resize(want_oe ? Noos : 0);
   if (want_cf)
     HIP_TRY(ctx, hipMemcpyAsync(h_c.data(), p.C, n_paths * 4, hipMemcpyDeviceToHost, s));
   if (want_ex) HIP_TRY(ctx, hipMemcpyAsync(h_e.data(), p.ex, n_paths, hipMemcpyDeviceToHost, s));
@@ -2648,6 +2678,7 @@ mc_status mc_price_lsm(mc_context* ctx, const mc_model* m, const mc_lsm_spec* sp
     HIP_TRY(ctx, hipMemcpyAsync(diag->oos_value, oval, Noos * 8, hipMemcpyDeviceToHost, s));
   if (want_oe) HIP_TRY(ctx, hipMemcpyAsync(h_oe.data(), oex, Noos, hipMemcpyDeviceToHost, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
+  queue.armed = false;
   auto ms = [&](size_t from, size_t to) {
     return (double)(h_clock[to] - h_clock[from]) / ctx->clock_khz;
   };

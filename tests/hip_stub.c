@@ -2,7 +2,7 @@
  * and a launch runs no kernel but leaves what the host code reads of its
  * results. Loaded before libmcpath.so, whose calls then resolve here, it lets
  * the CPU tests observe the library's queueing: which results it reads before
- * it has waited for them. */
+ * it has waited for them, and what it leaves in the queue when a call fails. */
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
@@ -31,10 +31,12 @@ int stub_select_misses;
 uint64_t stub_key;
 double stub_n_tail, stub_tail_sum;
 
-void stub_reset(void) {
-    n_late = 0;
-    stub_select_misses = 0;
-}
+/* Launches and copies queued since the last wait. */
+int stub_pending;
+/* The stub_fail_at-th call (from 1) that can fail does; 0: none. Counts down. */
+int stub_fail_at;
+static int last_error;
+static int fails(void) { return stub_fail_at > 0 && --stub_fail_at == 0; }
 
 static void later(void *to, const void *value) {
     late[n_late].to = (uint64_t *)to;
@@ -100,6 +102,8 @@ int __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, void **strea
 }
 int hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
     (void)block, (void)lds, (void)stream;
+    if (fails()) return last_error = 719;  /* hipErrorLaunchFailure */
+    ++stub_pending;
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].fn == fn) {
             ran(kernels[i].name, grid, args);
@@ -110,11 +114,15 @@ int hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t l
 int hipStreamSynchronize(void *stream) {
     (void)stream;
     for (int i = 0; i < n_late; ++i) *late[i].to = late[i].value;
-    n_late = 0;
+    n_late = stub_pending = 0;
     return 0;
 }
 
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void) {
+    const int e = last_error;
+    last_error = 0;
+    return e;
+}
 const char *hipGetErrorString(int e) { return e ? "error" : "no error"; }
 int hipGetDeviceCount(int *n) {
     *n = 1;
@@ -134,6 +142,7 @@ int hipGetSymbolAddress(void **p, const void *symbol) {
 }
 uint64_t stub_malloc_bytes;                /* device memory allocated so far */
 int hipMalloc(void **p, size_t n) {
+    if (fails()) return 2;                 /* hipErrorOutOfMemory */
     stub_malloc_bytes += n;
     return (*p = calloc(n, 1)) ? 0 : 2;
 }
@@ -143,11 +152,14 @@ int hipFree(void *p) {
 }
 int hipHostMalloc(void **p, size_t n, unsigned flags) {
     (void)flags;
+    if (fails()) return 2;
     return (*p = calloc(n, 1)) ? 0 : 2;
 }
 int hipHostFree(void *p) { return hipFree(p); }
 int hipMemcpyAsync(void *to, const void *from, size_t n, int kind, void *stream) {
     (void)kind, (void)stream;
+    if (fails()) return 719;
+    ++stub_pending;
     memcpy(to, from, n);
     return 0;
 }
@@ -169,7 +181,7 @@ int hipEventCreate(void **e) { return hipStreamCreate(e); }
 int hipEventDestroy(void *e) { return hipStreamDestroy(e); }
 int hipEventRecord(void *e, void *s) {
     (void)e, (void)s;
-    return 0;
+    return fails() ? 719 : 0;
 }
 int hipEventElapsedTime(float *ms, void *a, void *b) {
     (void)a, (void)b;
@@ -178,5 +190,5 @@ int hipEventElapsedTime(float *ms, void *a, void *b) {
 }
 int hipFuncSetAttribute(const void *f, int a, int v) {
     (void)f, (void)a, (void)v;
-    return 0;
+    return fails() ? 719 : 0;
 }

@@ -114,3 +114,55 @@ for d in (16, 112, 256):
                     (d, prec, N, more)
                 assert (call.path_buf == 7.0).all(), (d, prec, N)
 """)
+
+
+def test_failed_calls_leave_nothing_queued(run):
+    # Kernels read staged inputs from, and write results to, memory of the
+    # context that its next call uses again: wherever a call fails, it has
+    # waited for what it had queued, and the same call then succeeds.
+    run("""
+gbm = mc.Model(kind=mc.MC_GBM, S0=100.0, r=0.03, T=1.0, sigma=0.2)
+hes = mc.Model(kind=mc.MC_HESTON, S0=100.0, r=0.03, T=1.0, v0=0.04, kappa=2.0, theta=0.04, xi=0.5,
+               rho=-0.7)
+wide = mc.Model(kind=mc.MC_GBM_BASKET, S0=np.full(256, 100.0), r=0.03, T=1.0,
+                sigma=np.full(256, 0.2), corr=np.eye(256))
+pay, asian, call = (mc.Payoff(mc.MC_BASKET_CALL, 100.0), mc.Payoff(mc.MC_ASIAN_ARITH_CALL, 100.0),
+                    mc.Payoff(mc.MC_EURO_CALL, 100.0))
+fd = dict(greeks=3, greeks_method=mc.MC_GREEKS_FD_CRN)
+spec = mc.LsmSpec(payoff=mc.MC_LSM_BASKET_PUT, K=100.0, dividend=0.0, n_dates=64, degree=2, n_paths_oos=500)
+levels = [mc.Level(4, mc.MC_FP32, 1000), mc.Level(8, mc.MC_FP32, 500)]
+O = mc.Options
+calls = [
+    lambda c: mc.mc_price(c, gbm, mc.Payoff(mc.MC_ASIAN_ARITH_CALL, 100.0, cv=mc.MC_CV_GEO_ASIAN), 1000, 8, 1),
+    lambda c: mc.mc_price(c, gbm, asian, 1000, 8, 1, O(path_values=True)),
+    lambda c: mc.mc_price(c, gbm, call, 1000, 8, 1, O(**fd)),
+    lambda c: mc.mc_price(c, hes, call, 1000, 8, 1, O(**fd)),
+    lambda c: mc.mc_price(c, hes, asian, 1000, 300, 1, O(greeks=3)),
+    lambda c: mc.mc_price(c, wide, pay, 3000, 8, 1, O(path_values=True)),
+    lambda c: mc.mc_price_qmc(c, basket, pay, 1000, 2, 1, 4),
+    lambda c: mc.mc_price_qmc(c, wide, pay, 1000, 2, 1, 4),
+    lambda c: mc.mc_price_qmc(c, basket, pay, 1000, 2, 1, 1, O(path_values=True)),
+    lambda c: mc.mc_risk(c, basket, [1.0], [1.0], 0.9, 1000, 1, 1, opts=O(path_values=True)),
+    lambda c: mc.mc_price_lsm(c, gbm, spec, 1000, 1, want_paths=True),
+    lambda c: mc.mc_price_mlmc(c, gbm, call, levels, 1),
+]
+for n, f in enumerate(calls):
+    for k in range(1, 1000):
+        ctx = mc.mc_create(0)
+        cell("stub_pending", C.c_int).value = 0
+        cell("stub_select_misses", C.c_int).value = 1
+        cell("stub_fail_at", C.c_int).value = k
+        try:
+            f(ctx)
+            done = cell("stub_fail_at", C.c_int).value > 0
+            assert done, (n, k, "failure not reported")
+        except mc.McError:
+            done = False
+        assert cell("stub_pending", C.c_int).value == 0, (n, k, mc.mc_last_error(ctx))
+        cell("stub_fail_at", C.c_int).value = 0
+        f(ctx)
+        ctx.close()
+        if done:
+            break
+    assert k > 2
+""")
