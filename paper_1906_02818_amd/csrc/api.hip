@@ -1643,12 +1643,13 @@ mc_status mc_create(mc_context** out, int device) {
     mc_destroy(ctx);
     return MC_ERR_DEVICE;
   }
+  // Kernel times only: where the rate is not reported, that of gfx950.
   int khz = 0;
-  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0) {
-    mc_destroy(ctx);
-    return MC_ERR_DEVICE;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess) {
+    khz = 0;
+    (void)hipGetLastError();               // or the next launch would report it
   }
-  ctx->clock_khz = (double)khz;
+  ctx->clock_khz = khz > 0 ? (double)khz : 100000.0;
   std::memset(ctx->clock, 0, kClockStamps * sizeof(uint64_t));
   ctx->pinned = (double*)(ctx->clock + kClockStamps);
   ctx->pinned_count = kPinnedMin;

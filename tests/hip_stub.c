@@ -129,10 +129,11 @@ int hipGetDeviceCount(int *n) {
     return 0;
 }
 int hipSetDevice(int d) { return d == 0 ? 0 : 101; }
+int stub_clock_khz = 100000;               /* 0: not reported */
 int hipDeviceGetAttribute(int *value, int attribute, int d) {
     (void)attribute, (void)d;
-    *value = 100000;                       /* kHz */
-    return 0;
+    *value = stub_clock_khz;
+    return stub_clock_khz ? 0 : (last_error = 1);   /* hipErrorInvalidValue */
 }
 int hipGetSymbolAddress(void **p, const void *symbol) {
     static char scratch[4 << 20];

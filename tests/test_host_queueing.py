@@ -166,3 +166,14 @@ for n, f in enumerate(calls):
             break
     assert k > 2
 """)
+
+
+def test_create_needs_no_reported_clock_rate(run):
+    # The rate of the device's constant clock serves the kernel times alone.
+    run("""
+cell("stub_clock_khz", C.c_int).value = 0
+ctx = mc.mc_create(0)
+r = mc.mc_price(ctx, mc.Model(kind=mc.MC_GBM, S0=100.0, r=0.03, T=1.0, sigma=0.2),
+                mc.Payoff(mc.MC_EURO_CALL, 100.0), 1000, 8, 1)
+assert r["price"] == 1.0 and r["kernel_ms"] == 0.0
+""")
