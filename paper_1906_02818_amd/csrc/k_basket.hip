@@ -519,7 +519,8 @@ __global__ __launch_bounds__(64 * kQmcWaves, 4) void qmc_tile_kernel(const Baske
   typedef Form<PREC> F;
   typedef typename F::V V8;
   constexpr int C = 3;
-  extern __shared__ uint32_t s_words[];    // [dims / 4][64][4], [32][dims], then the sums
+  // [dims / 4][64][4], read 16 bytes at a time, [32][dims], then the sums.
+  extern __shared__ __attribute__((aligned(16))) uint32_t s_words[];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t d = P.d, n = P.n_steps, nq = d >> 2, rows = d >> 4, dims = n * d;
