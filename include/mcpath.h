@@ -201,7 +201,9 @@ mc_status mc_validate(mc_context *ctx, const mc_model *model, const mc_payoff *p
                       uint64_t n_paths, uint32_t n_steps, const mc_options *opts);
 
 /* Bytes a caller's device workspace must have for one mc_price call (0 on bad
- * arguments); a smaller one is refused. It serves the whole call, except that
+ * arguments); a smaller one is refused. For Heston pathwise greeks above 256
+ * steps it has room for the checkpoints of mc_greeks_adjoint, so that one
+ * workspace serves both. It serves the whole call, except that
  * a basket call also uses memory of the context, kept for later calls: the
  * factor of the last correlation matrix (8 dim^2 bytes), sums of tiles split
  * over workgroups (below 16 MB, for counts of paths that fill the chip
@@ -229,7 +231,8 @@ mc_status mc_price(mc_context *ctx, const mc_model *model, const mc_payoff *payo
  * to what fits a fixed device scratch: models MC_GBM and MC_HESTON, payoffs
  * without the learned control variate (the geometric-Asian control variate
  * and its pilot are allowed), pathwise greeks only (GBM tangents; Heston
- * forward tangents, or its MC_GREEKS_PATHWISE greeks up to n_steps = 256),
+ * forward tangents, or its MC_GREEKS_PATHWISE greeks, offered here up to
+ * n_steps = 256),
  * no path_values; opts->workspace is ignored. The call
  * performs no device or pinned-host allocation and no free: the block
  * moments live in a static device array of MC_NOALLOC_SCRATCH_BYTES, one per

@@ -1746,7 +1746,7 @@ size_t mc_workspace_bytes(const mc_model* m, const mc_payoff* f, uint64_t n_path
   const uint32_t C = mc_path_channels(m, f, &o);
   if (C == 0) return 0;
   // Persistent grids: GBM, and the Heston price and tangent kernels (the
-  // adjoint and the learned CV take one path per thread).
+  // pathwise kernel, the adjoint and the learned CV take one path per thread).
   const bool heston_persistent = m->kind == MC_HESTON && f->cv != MC_CV_LEARNED &&
                                  !(o.greeks && o.greeks_method != MC_GREEKS_TANGENT);
   const uint32_t cap = m->kind == MC_GBM ? kGbmMaxBlocks
@@ -1755,6 +1755,9 @@ size_t mc_workspace_bytes(const mc_model* m, const mc_payoff* f, uint64_t n_path
   if (m->kind == MC_GBM_BASKET)
     return basket_ws_bytes(n_paths, o.path_values != nullptr, m->dim, o.prec);
   size_t bytes = layout_for(n_paths, (int)C, o.path_values != nullptr, kBlock, cap).bytes;
+  // A contract of its own: above 256 steps a workspace for pathwise greeks has
+  // room for the checkpoints of mc_greeks_adjoint, so that one size serves both
+  // calls. heston_pathwise_kernel keeps none and uses the moment area.
   if (m->kind == MC_HESTON && o.greeks && o.greeks_method == MC_GREEKS_PATHWISE &&
       (n_steps + mcp::kCkpt - 1) / mcp::kCkpt > (uint32_t)mcp::kLdsCkpt)
     bytes = align256(bytes) + align256(mc_adjoint_ckpt_bytes(n_paths, n_steps, mcp::kCkpt));
@@ -1836,9 +1839,8 @@ mc_status mc_price_noalloc(mc_context* ctx, const mc_model* m, const mc_payoff* 
   if (m->kind == MC_HESTON && o.greeks && o.greeks_method != MC_GREEKS_TANGENT &&
       (n_steps + mcp::kCkpt - 1) / mcp::kCkpt > (uint32_t)mcp::kLdsCkpt)
     return fail(ctx, MC_ERR_UNSUPPORTED,
-                "mc_price_noalloc: the Heston adjoint keeps more than %d checkpoints in device "
-                "memory above %d steps; use MC_GREEKS_TANGENT", mcp::kLdsCkpt,
-                mcp::kLdsCkpt * mcp::kCkpt);
+                "mc_price_noalloc: Heston pathwise greeks are offered up to %d steps; use "
+                "MC_GREEKS_TANGENT above", mcp::kLdsCkpt * mcp::kCkpt);
   if (!ctx->scratch)
     return fail(ctx, MC_ERR_UNSUPPORTED, "no static scratch on device %d", ctx->device);
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, MC_ERR_DEVICE, "hipSetDevice");
