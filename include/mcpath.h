@@ -177,7 +177,13 @@ typedef struct {
     double plain_price, plain_std_err; /* same paths without the control variate */
     double cv_beta;                    /* coefficient used (static CV) */
     double vrf;                        /* variance-reduction factor plain/CV */
-    uint64_t n_paths, n_nonfinite;
+    uint64_t n_paths, n_nonfinite;     /* paths in the estimate, and paths left out: those
+                                  with a non-finite value among the ones the run computes.
+                                  With path_values these are all channels of the row;
+                                  without, the payoff's own, what its greeks and control
+                                  variate take, and at most channels computed along with
+                                  them. The two kinds of run can differ where values
+                                  overflow */
     double kernel_ms;                  /* device time of the path kernel(s) */
     int cv_fallback;                   /* 1 when the learned CV lost to plain MC on the pilot */
     int greeks_method;                 /* mc_greeks_method that produced delta and vega */

@@ -585,3 +585,19 @@ def test_basket_sums_over_assets(ctx, d):
         table = (w * 100.0 / ratio).astype(np.float32).astype(np.float64)
         err.append(r["price"] / (table.sum() * ratio) - 1.0)
     assert math.sqrt(np.mean(np.square(err))) < 3e-8
+
+
+def test_paths_left_out_depend_on_the_channels_computed(ctx):
+    """S_T overflows FP32 on some paths: alone, the barrier payoff is 0 there
+    and every path counts; with rows, whose average payoff is infinite there,
+    those paths are left out."""
+    N = 5000
+    m = mc.Model(kind=mc.MC_GBM, S0=100.0, r=84.1, T=1.0, sigma=0.25)   # S0 e^84.1 = 3.4e38
+    f = mc.Payoff(mc.MC_UO_BARRIER_CALL, 100.0, B=125.0)
+    alone = mc.mc_price(ctx, m, f, N, 4, SEED)
+    assert (alone["n_paths"], alone["n_nonfinite"], alone["price"]) == (N, 0, 0.0)
+    rows = mc.mc_price(ctx, m, f, N, 4, SEED, mc.Options(path_values=True))
+    out = ~np.isfinite(rows["path_values"]).all(1)
+    assert 0 < out.sum() < N
+    assert (rows["n_paths"], rows["n_nonfinite"]) == (N - out.sum(), out.sum())
+    assert rows["price"] == 0.0
