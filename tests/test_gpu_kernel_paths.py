@@ -601,3 +601,55 @@ def test_paths_left_out_depend_on_the_channels_computed(ctx):
     assert 0 < out.sum() < N
     assert (rows["n_paths"], rows["n_nonfinite"]) == (N - out.sum(), out.sum())
     assert rows["price"] == 0.0
+
+
+@pytest.mark.parametrize("d,degree,M,spd,n_oos,offset", [
+    (2, 2, 3, 1, 5, 0), (2, 2, 3, 1, 1000, (1 << 32) - 500), (1, 3, 5, 2, 257, (1 << 32) - 3),
+    (4, 1, 2, 1, 300, 9), (3, 2, 4, 1, 4099, (1 << 33) - 70)])
+def test_lsm_fresh_paths(ctx, d, degree, M, spd, n_oos, offset):
+    """Out of sample, the fitted rule on fresh paths, the last waves partial
+    and some across a multiple of 2^32: each value the oracle's under the same
+    coefficients, except where FP32 states decide otherwise at the exercise
+    boundary (at most one path), and their mean the price."""
+    S0, sigma, K, N = np.full(d, 100.0), 0.2 + 0.03 * np.arange(d), 100.0, 20011
+    kind = PUT if d == 1 else MAXC
+    corr = np.full((d, d), 0.3) + 0.7 * np.eye(d)
+    model = mc.Model(kind=mc.MC_GBM if d == 1 else mc.MC_GBM_BASKET, S0=S0, r=0.05, T=1.0,
+                     sigma=sigma, corr=corr if d > 1 else None)
+    spec = mc.LsmSpec(payoff=kind, K=K, dividend=0.1, n_dates=M, steps_per_date=spd, degree=degree,
+                      n_paths_oos=n_oos)
+    g = mc.mc_price_lsm(ctx, model, spec, N, SEED, mc.Options(path_offset=offset), want_paths=True)
+    assert np.asarray(g["beta_valid"])[:M - 1].all()
+    nf = g["n_features"]
+    o = oracle.lsm_oos(S0, sigma, np.linalg.cholesky(corr), 0.05, 0.1, 1.0, kind, K, M, spd, degree,
+                       np.asarray(g["beta"])[:M, :nf], n_oos, SEED, tag=7, path0=offset)
+    same = g["oos_exercise_date"] == o["ex"]
+    assert (~same).sum() <= 1
+    np.testing.assert_allclose(g["oos_value"][same], o["Y"][same], rtol=1e-5, atol=3e-5 * K)
+    assert g["price_oos"] == pytest.approx(g["oos_value"].mean(), rel=1e-12)
+    assert g["std_err_oos"] == pytest.approx(g["oos_value"].std(ddof=1) / math.sqrt(n_oos), rel=1e-9)
+
+
+@pytest.mark.parametrize("prec", [mc.MC_BF16_GEMM, mc.MC_FP16_GEMM, mc.MC_BF16X2_GEMM])
+@pytest.mark.parametrize("d,N,n", [(16, 130, 1), (32, 67, 2), (96, 67, 1), (256, 65, 2)])
+def test_reduced_forms_path_by_path(ctx, prec, d, N, n):
+    """Every path but those with a normal on the other side of a rounding
+    boundary (one normal in 2^14 within FP32 error of one, counted twice;
+    the count's mean plus four of its standard deviations plus one, which is
+    below N) has the value of the 64-bit model of its form."""
+    sigma, corr, _ = synth.basket_market(d)
+    S0, w, K, r_, T = np.full(d, 100.0), np.full(d, 1.0 / d), 40.0, 0.05, 1.0
+    r = mc.mc_price(ctx, mc.Model(kind=mc.MC_GBM_BASKET, S0=S0, r=r_, T=T, sigma=sigma, corr=corr),
+                    mc.Payoff(mc.MC_BASKET_CALL, K, weights=w), N, n, SEED,
+                    mc.Options(prec=prec, path_values=True))
+    L = np.linalg.cholesky(corr) * (sigma * np.sqrt(T / n) / np.log(2.0))[:, None]
+    Lr = _rounded(L, prec)
+    if prec == mc.MC_BF16X2_GEMM:
+        Lr = Lr + _bf16(L - Lr)
+    x = np.array([Lr @ _rounded(oracle.normals(SEED, 0, p, 0, n * d).reshape(n, d), prec).sum(0)
+                  for p in range(N)])
+    E = 2.0 ** (x + (r_ - 0.5 * sigma * sigma) * T / np.log(2.0))
+    ref = np.exp(-r_ * T) * np.maximum((E * S0 * w).sum(1) - K, 0.0)
+    moved = int((np.abs(r["path_values"][:, 0] - ref) > 4e-6 * 100.0).sum())
+    mean = N * 2.0 * n * d * 2.0 ** -14
+    assert moved <= mean + 4.0 * math.sqrt(mean) + 1.0 < N
