@@ -71,7 +71,10 @@ typedef enum { MC_LOG_EULER = 0, MC_EULER_S = 1 } mc_scheme;
  * increment Z L^T is a matrix product on the matrix cores: MC_FP32 uses
  * FP32 inputs, MC_BF16_GEMM / MC_FP16_GEMM round Z and L to bfloat16 /
  * half with FP32 accumulation, MC_BF16X2_GEMM splits L into two bfloat16
- * terms (hi + lo) to remove the systematic rounding of L. */
+ * terms (hi + lo) to remove the systematic rounding of L. The product is taken
+ * once per path, not per step, so the reduced precisions save no time on this
+ * GPU: MC_FP32 is the fastest form as well as the most exact, the others are
+ * there for what their rounding does. */
 typedef enum {
     MC_FP64 = 0, MC_FP32 = 1, MC_BF16_GEMM = 2, MC_FP16_GEMM = 3, MC_BF16X2_GEMM = 4
 } mc_precision;
@@ -209,13 +212,14 @@ mc_status mc_validate(mc_context *ctx, const mc_model *model, const mc_payoff *p
 /* Bytes a caller's device workspace must have for one mc_price call (0 on bad
  * arguments); a smaller one is refused. For Heston pathwise greeks above 256
  * steps it has room for the checkpoints of mc_greeks_adjoint, so that one
- * workspace serves both. It serves the whole call, except that
- * a basket call also uses memory of the context, kept for later calls: the
- * factor of the last correlation matrix (8 dim^2 bytes), sums of tiles split
- * over workgroups (below 16 MB, for counts of paths that fill the chip
- * unevenly), and, where its moment vectors and operands are larger than this
- * size allows for, those (below 1 MB; the per-path values stay in the
- * workspace). */
+ * workspace serves both. It serves the whole call, with two exceptions, which
+ * use memory of the context and keep it for later calls. Finite differences
+ * keep the moments (GBM) or per-path values (Heston, basket; at most 2^20 paths
+ * at a time) of their bumped runs there; a basket call keeps the factor of the
+ * last correlation matrix (8 dim^2 bytes), sums of tiles split over workgroups
+ * (below 16 MB, for counts of paths that fill the chip unevenly), and, where
+ * its moment vectors and operands are larger than this size allows for, those
+ * (below 1 MB; the per-path values stay in the workspace). */
 size_t mc_workspace_bytes(const mc_model *model, const mc_payoff *payoff,
                           uint64_t n_paths, uint32_t n_steps, const mc_options *opts);
 

@@ -2,6 +2,10 @@
 // arguments the paths have: Box-Muller from two 23-bit uniforms, and exp of
 // a log-price. A library log / sincos / exp / sqrt accepts every double, and
 // its argument reduction and special cases were most of an FP64 path's time.
+// log and exp are table-driven after P. T. P. Tang (ACM Transactions on
+// Mathematical Software 15 (1989) 144 for exp, 16 (1990) 378 for log): the
+// argument is reduced by the nearest of a table's points, a short polynomial
+// takes the rest.
 //
 //  - log u: u = m 2^-24 with an odd m below 2^24. z = m scaled to [1, 2)
 //    falls in one of 128 intervals with a centre c; 1/c is held to 24 bits,
